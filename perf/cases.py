@@ -99,7 +99,8 @@ def _lengths(B, T, gen):
     return n.to(torch.int32)
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """The tensors of a case, made from the seed."""
     c = dict(case)
     host = torch.Generator().manual_seed(seed)
     dev = torch.Generator(device="cuda").manual_seed(seed)
@@ -110,31 +111,29 @@ def prepare(case, seed):
     B, T, d, V, d_h, K = (c[k] for k in ("B", "T", "d", "V", "d_h", "K"))
     store = torch.bfloat16 if c["dtype"] == "bf16" else torch.float32
     width = 2048.0 / max(K, 1)
-    centers = (torch.arange(K, device="cuda", dtype=torch.float32) + 0.5) * width if K > 1 else None
+    s = {"centers": (torch.arange(K, device="cuda", dtype=torch.float32) + 0.5) * width if K > 1 else None}
 
     if c["op"] == "train":
-        x = normal(B, d)
-        y = torch.exp(5.5 + 0.8 * (x @ normal(d, std=1.0 / math.sqrt(d))) + 0.3 * normal(B)).clamp_(1.0, 2047.0)
-        bins = (y / width).to(torch.int32).clamp_(0, K - 1)
-        trainer = egtp.HeadTrainer(normal(d_h, d, std=1.0 / math.sqrt(d)), normal(d_h, std=0.1),
-                                   normal(K, d_h, std=1.0 / math.sqrt(d_h)), normal(K, std=0.1), centers)
+        s["x"] = x = normal(B, d)
+        s["y"] = y = torch.exp(5.5 + 0.8 * (x @ normal(d, std=1.0 / math.sqrt(d))) + 0.3 * normal(B)).clamp_(1.0, 2047.0)
+        s["bins"] = (y / width).to(torch.int32).clamp_(0, K - 1)
+        s["params"] = dict(w1=normal(d_h, d, std=1.0 / math.sqrt(d)), b1=normal(d_h, std=0.1),
+                           w2=normal(K, d_h, std=1.0 / math.sqrt(d_h)), b2=normal(K, std=0.1))
         # samples are decode steps of sequences: every sample knows how many its sequence has
-        n_seqs = max(1, B // 16)
+        s["n_seqs"] = n_seqs = max(1, B // 16)
         owner = torch.cat([torch.arange(n_seqs), torch.randint(0, n_seqs, (B - n_seqs,), generator=host)])
-        steps = torch.bincount(owner, minlength=n_seqs)[owner].to(torch.int32).cuda()
-        return {"case": c, "trainer": trainer, "x": x, "bins": bins, "y": y, "steps": steps, "n_seqs": n_seqs}
+        s["steps"] = torch.bincount(owner, minlength=n_seqs)[owner].to(torch.int32).cuda()
+        return s
 
     hidden = normal(T, d)
     hidden.mul_(torch.rand(T, 1, generator=dev, device="cuda").mul_(1.5).add_(0.5))
-    hidden = hidden.to(store)
-    w_lm = normal(V, d, std=1.0 / math.sqrt(d)).to(store)
+    s["hidden"] = hidden.to(store)
+    s["w_lm"] = normal(V, d, std=1.0 / math.sqrt(d)).to(store)
     # a scalar head is stored like the model, a K-bin head as training leaves it (fp32, with biases)
     head_store = store if K == 1 else torch.float32
-    w1 = normal(d_h, d, std=1.0 / math.sqrt(d)).to(head_store)
-    w2 = normal(K, d_h, std=1.0 / math.sqrt(d_h)).to(head_store)
-    biases = (normal(d_h, std=0.1), normal(K, std=0.1)) if K > 1 else (None, None)
-    scorer = egtp.Scorer(w_lm, egtp.make_head(w1, w2, *biases, bin_centers=centers))
-    s = {"case": c, "scorer": scorer, "hidden": hidden}
+    s["w1"] = normal(d_h, d, std=1.0 / math.sqrt(d)).to(head_store)
+    s["w2"] = normal(K, d_h, std=1.0 / math.sqrt(d_h)).to(head_store)
+    s["b1"], s["b2"] = (normal(d_h, std=0.1), normal(K, std=0.1)) if K > 1 else (None, None)
     if c["op"] != "step":
         s["lengths"] = _lengths(B, T, host).cuda()
     if c["op"] in ("step", "fold"):
@@ -143,10 +142,20 @@ def prepare(case, seed):
         s["pooled"] = normal(n, d, std=0.1)
         s["lse"] = torch.rand(n, generator=dev, device="cuda").mul_(3.0).add_(math.log(V) + 4.0)
         s["slot"] = torch.randperm(n, generator=host)[:B].to(torch.int32).cuda() if c["slots"] else None
-        if c["op"] == "fold":
-            s["offsets"] = scorer.build_offsets(s["lengths"], T)
-    if c["op"] == "pool":
-        s["offsets"] = scorer.build_offsets(s["lengths"], T)
+    return s
+
+
+def prepare(case, seed):
+    c, s = dict(case), _inputs(case, seed)
+    s["case"] = c
+    B, T, d, K = (c[k] for k in ("B", "T", "d", "K"))
+    if c["op"] == "train":
+        p = s["params"]
+        s["trainer"] = egtp.HeadTrainer(p["w1"], p["b1"], p["w2"], p["b2"], s["centers"])
+        return s
+    s["scorer"] = egtp.Scorer(s["w_lm"], egtp.make_head(s["w1"], s["w2"], s["b1"], s["b2"], bin_centers=s["centers"]))
+    if c["op"] in ("fold", "pool"):
+        s["offsets"] = s["scorer"].build_offsets(s["lengths"], T)
     if c["op"] == "score" and K > 1:
         s["out"] = [torch.empty(n, device="cuda", dtype=torch.float32) for n in (T, (B, d), B, B, (B, K))]
     return s
@@ -210,3 +219,90 @@ def tolerance(case):
         # a scalar prediction can come out near zero, and a few of them do not make up a norm
         return {"rel": 1e-4, "max": 1e-4}
     return {"rel": 6e-6, "max": 2.5e-5}
+
+
+def _entropy64(hidden, w_lm):
+    """Eq. 2 in fp64, a block of tokens at a time."""
+    w = w_lm.double()
+    H = torch.empty(hidden.shape[0], device="cuda", dtype=torch.float64)
+    rows = max(1, (1 << 28) // w.shape[0])
+    for t in range(0, H.numel(), rows):
+        z = hidden[t:t + rows].double() @ w.T
+        z -= z.max(dim=1, keepdim=True).values
+        e = torch.exp(z)
+        S = e.sum(dim=1)
+        H[t:t + rows] = torch.log(S) - e.mul_(z).sum(dim=1) / S
+    return H
+
+
+def _head64(s, pooled):
+    """(prediction, distribution over the bins or None)"""
+    b1, b2 = (0.0 if s[k] is None else s[k].double() for k in ("b1", "b2"))
+    out = torch.relu(pooled @ s["w1"].double().T + b1) @ s["w2"].double().T + b2
+    if s["centers"] is None:
+        return out[:, 0], None
+    p = torch.softmax(out, dim=1)
+    return p @ s["centers"].double(), p
+
+
+def _train64(s, c):
+    """Eq. 5, 7, 9 and the first AdamW step, at the trainer's default hyper-parameters."""
+    lam, lr, beta1, beta2, eps, wd = 0.95, 2e-5, 0.9, 0.999, 1e-8, 0.01
+    old = {k: p.double() for k, p in s["params"].items()}
+    x, y, centers = s["x"].double(), s["y"].double(), s["centers"].double()
+    pre = x @ old["w1"].T + old["b1"]
+    act = torch.relu(pre)
+    z = act @ old["w2"].T + old["b2"]
+    p, logp = torch.softmax(z, dim=1), torch.log_softmax(z, dim=1)
+    q = torch.softmax(-(torch.arange(c["K"], device="cuda")[None, :] - s["bins"][:, None]).abs().double(), dim=1)
+    yhat = p @ centers
+    wb = 1.0 / (s["n_seqs"] * s["steps"].double())
+    ce, mse = -(wb * (q * logp).sum(dim=1)).sum(), (wb * (yhat - y) ** 2).sum()
+    dz = wb[:, None] * (lam * (p - q) + (1 - lam) * 2 * (yhat - y)[:, None] * p * (centers[None, :] - yhat[:, None]))
+    da = (dz @ old["w2"]) * (pre > 0)
+    g = dict(w1=da.T @ x, b1=da.sum(dim=0), w2=dz.T @ act, b2=dz.sum(dim=0))
+    m, v = {k: (1 - beta1) * t for k, t in g.items()}, {k: (1 - beta2) * t * t for k, t in g.items()}
+    params = {k: t - lr * wd * t - lr * (m[k] / (1 - beta1)) / ((v[k] / (1 - beta2)).sqrt() + eps) for k, t in old.items()}
+    # A pre-activation this close to zero may count as active or not in fp32, and a row of the gradient hangs on it.
+    if bool((pre.abs() < 1e-6).any()):
+        for t in (params, m, v):
+            t["w1"] = t["b1"] = None
+    return {"loss": torch.stack([lam * ce + (1 - lam) * mse, ce, mse]), "params": params, "m": m, "v": v}
+
+
+def exact(case, seed):
+    c, s = dict(case), _inputs(case, seed)
+    B, T, d, K = (c[k] for k in ("B", "T", "d", "K"))
+    if c["op"] == "train":
+        return _train64(s, c)
+    lengths = s["lengths"].long() if "lengths" in s else torch.ones(B, device="cuda", dtype=torch.int64)
+    seq = torch.repeat_interleave(torch.arange(B, device="cuda"), lengths)
+    hidden = s["hidden"].double()
+    if c["op"] == "pool":
+        if c["kind"] == "last":
+            pooled = hidden[torch.cumsum(lengths, 0) - 1]
+        else:
+            how = "mean" if c["kind"] == "average" else "amax"
+            pooled = torch.zeros(B, d, device="cuda", dtype=torch.float64).index_reduce_(0, seq, hidden, how, include_self=False)
+        return pooled, _head64(s, pooled)[0]
+    H = _entropy64(s["hidden"], s["w_lm"])
+    # Eq. 3 and 4, joined with the running state of Eq. 8 where there is one
+    row = torch.arange(B, device="cuda")
+    none = torch.full((B,), -math.inf, device="cuda", dtype=torch.float64)
+    lse_old, pooled_old = none, torch.zeros(B, d, device="cuda", dtype=torch.float64)
+    if c["op"] != "score":
+        row = row if s["slot"] is None else s["slot"].long()
+        lse_old, pooled_old = s["lse"].double()[row], s["pooled"].double()[row]
+    top = torch.maximum(none.index_reduce(0, seq, H, "amax"), lse_old)
+    lse = top + torch.log(torch.exp(lse_old - top).index_add(0, seq, torch.exp(H - top[seq])))
+    pooled = pooled_old * torch.exp(lse_old - lse)[:, None]
+    pooled.index_add_(0, seq, hidden.mul_(torch.exp(H - lse[seq])[:, None]))
+    pred, p_hat = _head64(s, pooled)
+    if c["op"] == "score":
+        zero = torch.zeros(1, device="cuda", dtype=torch.int64)
+        out = {"offsets": torch.cat([zero, torch.cumsum(lengths, 0)]).to(torch.int32), "entropy": H, "pooled": pooled,
+               "lse": lse, "pred": pred}
+        return out if K == 1 else {**out, "p_hat": p_hat}
+    all_pooled, all_lse = s["pooled"].double(), s["lse"].double()
+    all_pooled[row], all_lse[row] = pooled, lse
+    return {"remaining": pred, "pooled": all_pooled, "lse": all_lse}
