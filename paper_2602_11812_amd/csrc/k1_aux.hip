@@ -95,12 +95,13 @@ __global__ __launch_bounds__(256) void k1_merge_wide_kernel(const float *__restr
     }
 }
 
-// Packs rows of a row-major bf16 matrix src[R x d] into blocks of 256 rows x 32 K-elements in
+// Packs rows of a row-major bf16 matrix src[R x d] into blocks of tile_rows (256, or fewer for the narrow
+// kernel's hidden states) rows x 32 K-elements in
 // LDS-image order; rows >= R and K >= d are zero.  One workgroup packs 8 consecutive K steps
 // of `rows_per_wg` rows (a multiple of 8; blockIdx.z picks the row group) of one row tile: a wave
 // reads 512 contiguous bytes of each of two rows at a time.
 __global__ __launch_bounds__(256) void pack_rows_bf16_kernel(const unsigned char *__restrict__ src, long R,
-                                                             int d, int KT, int rows_per_wg,
+                                                             int d, int KT, int tile_rows, int rows_per_wg,
                                                              unsigned char *__restrict__ dst)
 {
     const long tile = blockIdx.x;
@@ -112,10 +113,10 @@ __global__ __launch_bounds__(256) void pack_rows_bf16_kernel(const unsigned char
     const long k_elem = (long)ks * BK + chunk * 8;
     if (ks >= KT)
         return;
-    unsigned char *blk = dst + (tile * KT + ks) * (long)TILE_BYTES;
+    unsigned char *blk = dst + (tile * KT + ks) * (long)(tile_rows * ROW_BYTES);
     const int r0 = blockIdx.z * rows_per_wg;
     for (int r = r0 + rsub; r < r0 + rows_per_wg; r += 8) {
-        const long row = tile * 256 + r;
+        const long row = tile * tile_rows + r;
         uint4 v = make_uint4(0, 0, 0, 0);
         if (row < R && k_elem < d)
             v = *(const uint4 *)(src + (row * d + k_elem) * 2);
@@ -137,7 +138,7 @@ __device__ constexpr int SPLIT_H[K1_SPLIT_TERMS] = {0, 1, 2, 0, 1, 0};
 // its 8 values once, splits them, and stores the piece each segment asks for.
 template <bool HIDDEN_SIDE>
 __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *__restrict__ src, long R, int d,
-                                                                  int kseg, int rows_per_wg,
+                                                                  int kseg, int tile_rows, int rows_per_wg,
                                                                   unsigned char *__restrict__ dst)
 {
     const long tile = blockIdx.x;
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *_
     const long KT = (long)K1_SPLIT_TERMS * kseg;
     const int r0 = blockIdx.z * rows_per_wg;
     for (int r = r0 + rsub; r < r0 + rows_per_wg; r += 8) {
-        const long row = tile * 256 + r;
+        const long row = tile * tile_rows + r;
         float4 lo4 = make_float4(0.f, 0.f, 0.f, 0.f), hi4 = lo4;
         if (row < R) {  // d % 4 == 0: a group of four lies wholly inside a row or wholly past its end
             if (k_elem < d)
@@ -173,29 +174,32 @@ __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *_
 #pragma unroll
         for (int s = 0; s < K1_SPLIT_TERMS; ++s) {
             const int piece = HIDDEN_SIDE ? SPLIT_H[s] : SPLIT_W[s];
-            *(uint4 *)(dst + (tile * KT + (long)s * kseg + kk) * (long)TILE_BYTES + in_block) = q[piece];
+            *(uint4 *)(dst + (tile * KT + (long)s * kseg + kk) * (long)(tile_rows * ROW_BYTES) + in_block) = q[piece];
         }
     }
 }
 
 }  // namespace
 
-hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, void *dst, hipStream_t st)
+hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, int tile_rows, void *dst,
+                                  hipStream_t st)
 {
     if (rows <= 0)
         return hipSuccess;
-    const long tiles = (rows + 255) / 256;
+    if (tile_rows < 64 || tile_rows > 256 || tile_rows % 64 != 0)
+        return hipErrorInvalidValue;
+    const long tiles = (rows + tile_rows - 1) / tile_rows;
     const int kseg = k1_split_segment(d) / BK;
     if (tiles > 0x7fffffffL || k_steps((int)k1_contraction_len(DT_F32, d)) != K1_SPLIT_TERMS * kseg)
         return hipErrorInvalidValue;
-    const int rows_per_wg = tiles * ((kseg + 7) / 8) >= 1024 ? 256 : 32;
-    const dim3 grid((unsigned)tiles, (kseg + 7) / 8, 256 / rows_per_wg);
+    const int rows_per_wg = tiles * ((kseg + 7) / 8) >= 1024 ? tile_rows : 32;
+    const dim3 grid((unsigned)tiles, (kseg + 7) / 8, tile_rows / rows_per_wg);
     if (hidden_side)
         hipLaunchKernelGGL(pack_rows_f32_split_kernel<true>, grid, dim3(256), 0, st, (const float *)src, (long)rows,
-                           d, kseg, rows_per_wg, (unsigned char *)dst);
+                           d, kseg, tile_rows, rows_per_wg, (unsigned char *)dst);
     else
         hipLaunchKernelGGL(pack_rows_f32_split_kernel<false>, grid, dim3(256), 0, st, (const float *)src, (long)rows,
-                           d, kseg, rows_per_wg, (unsigned char *)dst);
+                           d, kseg, tile_rows, rows_per_wg, (unsigned char *)dst);
     return hipGetLastError();
 }
 
@@ -206,19 +210,21 @@ size_t k1_packed_bytes(int64_t rows, int K)
     return (size_t)(tiles * kt) * TILE_BYTES;
 }
 
-hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, void *dst, hipStream_t st)
+hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, hipStream_t st)
 {
     if (rows <= 0)
         return hipSuccess;
-    const long tiles = (rows + 255) / 256;
+    if (tile_rows < 64 || tile_rows > 256 || tile_rows % 64 != 0)
+        return hipErrorInvalidValue;
+    const long tiles = (rows + tile_rows - 1) / tile_rows;
     const int kt = k_steps(d);
     if (tiles > 0x7fffffffL)
         return hipErrorInvalidValue;
     // whole tiles per workgroup when there are many of them, 32-row groups when a small batch
     // would otherwise leave most of the chip idle
-    const int rows_per_wg = tiles * ((kt + 7) / 8) >= 1024 ? 256 : 32;
-    hipLaunchKernelGGL(pack_rows_bf16_kernel, dim3((unsigned)tiles, (kt + 7) / 8, 256 / rows_per_wg), dim3(256), 0,
-                       st, (const unsigned char *)src, (long)rows, d, kt, rows_per_wg, (unsigned char *)dst);
+    const int rows_per_wg = tiles * ((kt + 7) / 8) >= 1024 ? tile_rows : 32;
+    hipLaunchKernelGGL(pack_rows_bf16_kernel, dim3((unsigned)tiles, (kt + 7) / 8, tile_rows / rows_per_wg), dim3(256), 0,
+                       st, (const unsigned char *)src, (long)rows, d, kt, tile_rows, rows_per_wg, (unsigned char *)dst);
     return hipGetLastError();
 }
 

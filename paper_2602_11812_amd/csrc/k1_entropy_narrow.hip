@@ -1,0 +1,280 @@
+// Fused LM-head contraction + streaming entropy (Eq. 2) for batches of few tokens: one query, a decode step with a
+// few live sequences, a small model's batch.  Same formulation, packed W_lm and partial triples as the 256 x 256
+// kernel; what differs is the tile and what bounds it.
+//
+// A few tokens make the sweep a stream over W_lm, and a 256-token tile pays for its empty columns in matrix-core
+// time and in power.  Here a token block is 32 NI tokens (NI = 2, 4, 6, 8), a vocabulary tile 128 rows (half a
+// packed block: 8 contiguous KiB per K step), so that a step's MFMAs (8 NI per wave) hide under the step's share
+// of the memory stream and the vocabulary divides more evenly over the compute units.  The LDS ring is as deep as
+// the LDS allows: what it holds in flight per compute unit sets the rate of the stream.
+//
+// Workgroup = 4 waves (2 along vocabulary x 2 along tokens), wave tile 64 x 16 NI = 4 x NI MFMA 16x16x32 tiles.
+// One barrier per step: behind it every wave's loads of the next step have landed and every wave's fragment reads
+// of the current step have returned, so its stage can be loaded again; fragments are read one step ahead of
+// their MFMAs into two register sets that swap roles (the loop is unrolled by two, K is an even number of steps).
+//
+// Measured: 64 tokens against V = 151936, d = 4096: 199 us = 6.3 TB/s of W_lm (the 256 x 256 tile: 286 us on 198 of the
+// 256 compute units); 128 tokens 225, 192 tokens 261 (LDS: fill plus fragment reads of 20 KiB steps), 256 tokens 320,
+// where the wide tile's 280 is better.  309 fp32 tokens against V = 4096, d = 256: 15.4 us, 37.1 before.
+#include "k1_stream.h"
+
+namespace egtp {
+namespace {
+
+constexpr int NM = K1_NARROW_TILE_V;           // vocabulary rows per tile
+constexpr int W_STEP_BYTES = NM * ROW_BYTES;   // 8 KiB
+constexpr int TB_GROUP = 8;                    // token blocks that sweep the same vocabulary range together
+static_assert(NM == 128 && TILE_BYTES == 2 * W_STEP_BYTES, "a vocabulary tile is half a packed block");
+
+template <int NI>
+struct Ring {
+    static constexpr int H_STEP_BYTES = 32 * NI * ROW_BYTES;
+    static constexpr int STAGE_BYTES = W_STEP_BYTES + H_STEP_BYTES;
+    static constexpr int LOADS = STAGE_BYTES / 4096;             // 16-byte loads per lane and step
+    static constexpr int STAGES = 144 * 1024 / STAGE_BYTES;      // 12, 9, 7, 6 stages for NI = 2, 4, 6, 8
+    static constexpr int BYTES = STAGES * STAGE_BYTES;
+    static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "ring depth");
+};
+
+template <int NI, bool STREAM_W>
+__global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigned char *__restrict__ Wp,
+                                                                   const unsigned char *__restrict__ Hp, long T, int KT,
+                                                                   int V, int ntb, int nsplit, int ntiles_v,
+                                                                   float *__restrict__ part)
+{
+    using R = Ring<NI>;
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1;  // vocabulary half of the tile
+    const int wn = wave & 1;   // token half
+
+    // Workgroup i runs on XCD i % 8: each XCD gets a contiguous range of logical units, token blocks varying
+    // fastest, so that the blocks that read the same rows of W_lm share its L2.
+    int tb, sp;
+    {
+        const int units = gridDim.x;
+        const int q = units >> 3, r = units & 7;
+        const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+        const int logical = x * q + (x < r ? x : r) + j;
+        const int per_group = TB_GROUP * nsplit;
+        const int g = logical / per_group;
+        const int rem = logical - g * per_group;
+        const int gsize = min(TB_GROUP, ntb - g * TB_GROUP);
+        sp = __builtin_amdgcn_readfirstlane(rem / gsize);
+        tb = __builtin_amdgcn_readfirstlane(g * TB_GROUP + (rem - sp * gsize));
+    }
+    // the first ntiles_v % nsplit ranges hold one tile more than the others
+    const int per_range = __builtin_amdgcn_readfirstlane(ntiles_v / nsplit);
+    const int longer = ntiles_v - per_range * nsplit;
+    const int vt_begin = sp * per_range + min(sp, longer);
+    const int vt_end = vt_begin + per_range + (sp < longer ? 1 : 0);
+    const long tok0 = (long)tb * (32 * NI);
+    const int total = (vt_end - vt_begin) * KT;
+
+    // ---- global -> LDS: a block is copied linearly, 1 KiB per wave-wide load
+    const int lane_off = wave * 1024 + lane * 16;
+    const int w_tile_bytes = KT * TILE_BYTES;  // (the launcher checks the range)
+    const int h_tile_bytes = KT * R::H_STEP_BYTES;
+    const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
+    unsigned char *lds_wave = smem + wave * 1024;
+    // The load stream runs ahead of the MFMAs by the ring.  Past the end it keeps re-reading the last step (into
+    // stages nobody reads any more), so every step issues the same number of loads and one wait constant serves.
+    int lvt = vt_begin, lkt = 0, lstep = 0;
+    auto issue_loads = [&](int stage) {
+        lvt = __builtin_amdgcn_readfirstlane(lvt);  // a descriptor must be uniform, and known to be
+        const __amdgpu_buffer_rsrc_t rW = raw_buffer(Wp + (long)(lvt >> 1) * w_tile_bytes, w_tile_bytes);
+        const int woff = lkt * TILE_BYTES + (lvt & 1) * W_STEP_BYTES;
+        const int hoff = lkt * R::H_STEP_BYTES;
+        unsigned char *dst = lds_wave + stage * R::STAGE_BYTES;
+#pragma unroll
+        for (int p = 0; p < W_STEP_BYTES / 4096; ++p)
+            load16_to_lds<STREAM_W>(rW, lane_off, woff + p * 4096, dst + p * 4096);
+#pragma unroll
+        for (int p = 0; p < R::H_STEP_BYTES / 4096; ++p)
+            load16_to_lds(rH, lane_off, hoff + p * 4096, dst + W_STEP_BYTES + p * 4096);
+        const int adv = lstep + 1 < total ? 1 : 0;
+        lstep += adv;
+        const int nk = lkt + adv;
+        const int wrap = nk == KT ? 1 : 0;
+        lkt = wrap ? 0 : nk;
+        lvt += wrap;
+    };
+
+    // ---- fragment reads: row r, chunk c of a block sits at r * 64 + ((c ^ swizzle_key(r)) * 16)
+    const int l15 = lane & 15;
+    const int kq = lane >> 4;
+    const unsigned swz = (unsigned)((kq ^ swizzle_key(l15)) << 4);
+    const unsigned fragA = (unsigned)(wm * 64 + l15) * ROW_BYTES + swz;
+    const unsigned fragB = (unsigned)W_STEP_BYTES + (unsigned)(wn * 16 * NI + l15) * ROW_BYTES + swz;
+    constexpr int FRAG_STRIDE = 16 * ROW_BYTES;
+    struct Frags {
+        bf16x8 a[4], b[NI];
+    };
+    auto read_frags = [&](Frags &f, int stage) {
+        const unsigned char *s = smem + stage * R::STAGE_BYTES;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            f.a[i] = *(const bf16x8 *)(s + fragA + i * FRAG_STRIDE);
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            f.b[i] = *(const bf16x8 *)(s + fragB + i * FRAG_STRIDE);
+    };
+
+    Stats st[NI];
+    f32x4 acc[4][NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        st[ni].m = NEG_BIG;
+        st[ni].S = 0.f;
+        st[ni].U = 0.f;
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+            acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+#pragma unroll
+    for (int s = 0; s < R::STAGES; ++s)
+        issue_loads(s);
+    wait_vmcnt<(R::STAGES - 1) * R::LOADS>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    Frags f0, f1;
+    read_frags(f0, 0);
+    int cstage = 0;  // stage of the step whose MFMAs are next
+
+    // One step: `cur` holds its fragments.  Wait for the next step's loads (the newest STAGES - 2 steps may still be
+    // in flight) and for this wave's own fragment reads, meet the other waves, refill the stage just freed, read the
+    // next fragments, multiply.  A bare barrier: a fence would drain the ring.
+    auto step = [&](const Frags &cur, Frags &next) {
+        wait_vmcnt<(R::STAGES - 2) * R::LOADS>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const int nstage = cstage + 1 == R::STAGES ? 0 : cstage + 1;
+        read_frags(next, nstage);
+        issue_loads(cstage);
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a[mi], cur.b[ni], acc[mi][ni], 0, 0, 0);
+        cstage = nstage;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    for (int vt = vt_begin; vt < vt_end; ++vt) {
+        for (int kt = 0; kt < KT; kt += 2) {
+            step(f0, f1);
+            step(f1, f0);
+        }
+        // a tile of logits is in registers: fold it into the statistics and forget it
+        const int row_base = vt * NM + wm * 64 + 4 * kq;
+        const bool masked = vt * NM + NM > V;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            float z[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    z[4 * q + i] = acc[q][ni][i];
+                    acc[q][ni][i] = 0.f;
+                }
+            if (masked)
+                fold16<true>(z, st[ni], row_base, V);
+            else
+                fold16<false>(z, st[ni], row_base, V);
+        }
+    }
+    wait_vmcnt<0>();
+    __syncthreads();
+
+    // ---- combine the four lanes, then the two waves, that hold the same token
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            Stats o;
+            o.m = __shfl_xor(st[ni].m, off);
+            o.S = __shfl_xor(st[ni].S, off);
+            o.U = __shfl_xor(st[ni].U, off);
+            st[ni] = merge(st[ni], o);
+        }
+    }
+    float *red = (float *)smem;  // [wn][ni][16][3]
+    if (wm == 1 && lane < 16) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            float *r = red + ((wn * NI + ni) * 16 + lane) * 3;
+            r[0] = st[ni].m;
+            r[1] = st[ni].S;
+            r[2] = st[ni].U;
+        }
+    }
+    __syncthreads();
+    if (wm == 0 && lane < 16) {
+        const long plane = (long)nsplit * T;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            const float *r = red + ((wn * NI + ni) * 16 + lane) * 3;
+            Stats o;
+            o.m = r[0];
+            o.S = r[1];
+            o.U = r[2];
+            const Stats f = merge(st[ni], o);
+            const long tok = tok0 + (wn * NI + ni) * 16 + lane;
+            if (tok < T) {
+                const long idx = (long)sp * T + tok;
+                part[idx] = f.m;
+                part[plane + idx] = f.S;
+                part[2 * plane + idx] = f.U;
+            }
+        }
+    }
+}
+
+template <int NI, bool STREAM_W>
+hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p,
+                  float *part, hipStream_t st)
+{
+    static DeviceMask lds_limit_raised{0};
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<NI, STREAM_W>, Ring<NI>::BYTES,
+                                                 lds_limit_raised);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL((k1_entropy_narrow_kernel<NI, STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), Ring<NI>::BYTES,
+                       st, (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
+                       p.nsplit, p.ntiles_v, part);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+                             const K1Plan &p, float *part, hipStream_t st)
+{
+    const int kt = k_steps(K);
+    if (T <= 0 || p.tile_v != NM || p.nsplit < 1 || p.nsplit > p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
+        (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + NM - 1) / NM || (long)kt * TILE_BYTES > 0x7fffffffL)
+        return hipErrorInvalidValue;
+    // One token block reads W_lm once.  If the 256 MiB Infinity Cache cannot hold it until the next call either, its
+    // loads carry the non-temporal hint: 64 tokens, d = 4096, V = 151936 (1.24 GB) 225 -> 199 us = 6.3 TB/s; V = 65536
+    // and d = 2560 (336 MB) 60.5 -> 55.7; but V = 65536 and d = 2048 (268 MB) 44 -> 46 and V = 32000 (131 MB) 25 -> 26.
+    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * kt * W_STEP_BYTES > ((int64_t)256 << 20);
+#define EGTP_NARROW(NI)                                                                   \
+    (stream ? launch<NI, true>(hidden_packed, w_packed, T, kt, V, p, part, st)            \
+            : launch<NI, false>(hidden_packed, w_packed, T, kt, V, p, part, st))
+    switch (p.tb_tokens) {
+    case 64: return EGTP_NARROW(2);
+    case 128: return EGTP_NARROW(4);
+    case 192: return EGTP_NARROW(6);
+    case 256: return EGTP_NARROW(8);
+    }
+#undef EGTP_NARROW
+    return hipErrorInvalidValue;
+}
+
+}  // namespace egtp

@@ -11,6 +11,57 @@ static constexpr int TB = 256, TV = 256, TARGET_UNITS = 8192;
 static constexpr int NUM_CUS = 256;
 static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number of ranges may go
 
+// ---- the kernel for few tokens -----------------------------------------------------------
+// Both kernels are priced in ns from what a K step of one workgroup was measured to take (d = 4096, V = 151936 and
+// d = 2048, V = 32000, every block size at T = 24 ... 1000, one workgroup per compute unit): 745 for the 256 x 256
+// tile, 115 + 48 NI for the 128-row tile over 32 NI tokens (its LDS fill and fragment reads, not its MFMAs), about
+// 3000 for a workgroup to fill its ring and to merge and store at the end -- and no sweep is faster than one read of
+// W_lm (5.7 TB/s).  The model picks the fastest measured variant at each of those sizes: T = 24, d = 4096,
+// V = 151936 takes 199 us on 64-token blocks, 225 on 128, 286 on the wide tile; T = 173 262 on 192 against 279;
+// T = 300 424 on the wide tile against 459 on 192; T = 309, V = 4096, d = 256 in fp32 15.4 on 64 against 37.1.
+static constexpr double WIDE_STEP_NS = 745.0, NARROW_STEP_NS = 115.0, NARROW_STEP_NS_PER_NI = 48.0;
+static constexpr double WORKGROUP_NS = 3000.0, W_STREAM_BYTES_PER_NS = 5700.0;
+
+static double sweep_ns(const K1Plan &p, long steps, double step_ns)
+{
+    const long rounds = ((long)p.ntb * p.nsplit + NUM_CUS - 1) / NUM_CUS;
+    const double busy = (double)rounds * ((double)p.tiles_per_split * (double)steps * step_ns + WORKGROUP_NS);
+    const double stream = (double)p.ntiles_v * p.tile_v * (double)steps * 64.0 / W_STREAM_BYTES_PER_NS;
+    return (busy > stream ? busy : stream) + 0.1 * busy;  // of two that only wait for the stream, the lighter one
+}
+
+// a narrow plan where that is cheaper than the wide plan p
+static K1Plan narrower(const K1Plan &p, int64_t T, int V, long steps)
+{
+    if (V <= TV || T <= 0)
+        return p;  // a vocabulary inside one tile: there is nothing to divide
+    K1Plan best = p;
+    double best_ns = 0.97 * sweep_ns(p, steps, WIDE_STEP_NS);  // (a gain within the model's error is none)
+    for (int ni = 2; ni <= 8; ni += 2) {
+        K1Plan q;
+        q.tb_tokens = 32 * ni;
+        q.tile_v = K1_NARROW_TILE_V;
+        const int64_t ntb = (T + q.tb_tokens - 1) / q.tb_tokens;
+        if (ntb * q.tb_tokens > (int64_t)p.ntb * TB)
+            continue;  // more padding than the wide blocks (whose packed copy the workspace is sized for)
+        q.ntb = (int)ntb;
+        q.ntiles_v = (V + q.tile_v - 1) / q.tile_v;
+        for (int rounds = 1; rounds <= 3; ++rounds) {
+            const int64_t slots = (int64_t)rounds * NUM_CUS / ntb;
+            if (slots < 1)
+                continue;
+            q.tiles_per_split = (int)((q.ntiles_v + slots - 1) / slots);
+            q.nsplit = (q.ntiles_v + q.tiles_per_split - 1) / q.tiles_per_split;
+            const double ns = sweep_ns(q, steps, NARROW_STEP_NS + NARROW_STEP_NS_PER_NI * ni);
+            if (ns < best_ns) {
+                best_ns = ns;
+                best = q;
+            }
+        }
+    }
+    return best;
+}
+
 K1Plan k1_plan(int dtype, int64_t T, int d, int V)
 {
     K1Plan p;
@@ -45,7 +96,7 @@ K1Plan k1_plan(int dtype, int64_t T, int d, int V)
                 p.tiles_per_split = tps;
             }
         }
-        return p;
+        return narrower(p, T, V, 2 * ((dk + 63) / 64));
     }
     // One workgroup per (token block, vocabulary range), one workgroup per compute unit at a
     // time, all of about the same length: among the next few range counts take the one whose
@@ -76,6 +127,7 @@ size_t k1_partial_floats_bound(int64_t T)
 {
     // nsplit(T') <= target / ntb(T') + 1 + NSPLIT_SLACK, so
     // nsplit(T') * T' <= (target + (1 + NSPLIT_SLACK) * ntb(T')) * tb_tokens for every T' <= T
+    // (narrow plans have at most three rounds of workgroups: far less)
     const int64_t tbk = TB;
     const int64_t target = TARGET_UNITS;
     const int64_t ntb = (T + tbk - 1) / tbk;

@@ -32,6 +32,9 @@ constexpr long K1_MAX_CONTRACTION = 4194240;
 // the vocabulary into `nsplit` ranges of `tiles_per_split` tiles of `tile_v` rows; each
 // (token block, vocabulary range) pair is one workgroup and leaves one partial (m, S, U)
 // triple per token.
+// vocabulary rows per tile of the kernel for few tokens (the other kernel's tiles have 256)
+constexpr int K1_NARROW_TILE_V = 128;
+
 struct K1Plan {
     int tb_tokens;        // tokens per block
     int tile_v;           // vocabulary rows per tile
@@ -56,6 +59,9 @@ size_t k1_pace_ints_bound(int64_t T);
 constexpr int K1_PACE_TILES = 4;
 // Pacing serves the token blocks that share vocabulary tiles in an XCD's L2 (groups of eight): a batch of
 // fewer blocks streams W_lm once from HBM whatever the workgroups' relative progress.
-inline bool k1_plan_paces(const K1Plan &p) { return p.tiles_per_split > K1_PACE_TILES && p.ntb >= 8; }
+inline bool k1_plan_paces(const K1Plan &p)
+{
+    return p.tile_v != K1_NARROW_TILE_V && p.tiles_per_split > K1_PACE_TILES && p.ntb >= 8;
+}
 
 }  // namespace egtp

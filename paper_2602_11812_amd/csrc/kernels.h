@@ -45,11 +45,14 @@ inline hipError_t raise_dynamic_lds_limit(const void *kernel, int bytes, DeviceM
 // to whole blocks.  K is the contraction length the kernel sees: d for bf16 operands,
 // k1_contraction_len(DT_F32, d) for fp32 operands split into bf16 pieces.
 constexpr int K1_PACK_K = 32;
-constexpr int K1_PACK_BLOCK_BYTES = 256 * K1_PACK_K * 2;
+constexpr int K1_PACK_ROWS = 256;
+constexpr int K1_PACK_BLOCK_BYTES = K1_PACK_ROWS * K1_PACK_K * 2;
+// Hidden states for the narrow kernel use row tiles of the plan's tb_tokens instead of 256 rows (`tile_rows`, a
+// multiple of 64 up to 256); everything else is the same.
 size_t k1_packed_bytes(int64_t rows, int K);
-hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, void *dst, hipStream_t st);
+hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, hipStream_t st);
 // fp32 rows (d % 4 == 0) into the six K segments of the W_lm side or of the hidden-state side
-hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, void *dst,
+hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, int tile_rows, void *dst,
                                   hipStream_t st);
 
 // Eq. 2, fused: partial (m = max z log2 e, sum e^{z-m}, sum e^{z-m}(z-m) log2 e) per token and vocabulary range.
@@ -57,6 +60,9 @@ hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hid
 // (contents do not matter on entry), or NULL to run without pacing.
 hipError_t k1_entropy_bf16(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
                            const K1Plan &p, float *part, int *pace, hipStream_t st);
+// the same for a narrow plan (p.tile_v == K1_NARROW_TILE_V)
+hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+                             const K1Plan &p, float *part, hipStream_t st);
 // merges the nsplit partial triples of each token in a fixed order; entropy[t] = ln S - U/S
 hipError_t k1_merge(const float *part, int nsplit, int64_t T, float *entropy, hipStream_t st);
 
