@@ -2,8 +2,8 @@
 // either the scalar itself (n_out == 1) or the expected value over K bins of Eq. 6.
 //
 // Layer 1 is a small [B x d] . [d x d_h] contraction kept entirely in fp32 (the pooled
-// vector is never re-rounded); the plain kernel is LDS-tiled, 64 x 64 outputs per workgroup, 4 x 4
-// per thread.  The contraction is split along d so that about a thousand workgroups exist even for one
+// vector is never re-rounded), on the fp32 matrix instructions where the weights are fp32 and the batch is more
+// than a handful.  The contraction is split along d so that several hundred workgroups exist even for one
 // small batch; the splits leave partial pre-activations that layer 2 adds in split order
 // (fixed order, bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode are one
 // workgroup per sequence.
@@ -27,10 +27,10 @@ constexpr int TN = 64;  // sequences per tile
 constexpr int TK = 16;
 constexpr int PAD = 4;
 
-template <bool WBF16>
+// Layer 1, bf16 weights whose rows are not 16-byte aligned (d a multiple of 4 only): fp32 FMAs.
 __global__ __launch_bounds__(256) void head_layer1_kernel(const float *__restrict__ x,
                                                           const int32_t *__restrict__ slot, int B, int d,
-                                                          int d_h, const void *__restrict__ w1, int kchunk,
+                                                          int d_h, const unsigned short *__restrict__ w1, int kchunk,
                                                           float *__restrict__ act_part)
 {
     __shared__ float As[TK][TM + PAD];  // As[k][j]
@@ -61,15 +61,11 @@ __global__ __launch_bounds__(256) void head_layer1_kernel(const float *__restric
     for (int k0 = kbeg; k0 < kend; k0 += TK) {
         float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
         if (k0 + lk < kend) {
-            if (WBF16) {
-                const uint2 q = *(const uint2 *)((const unsigned short *)w1 + (long)jrow * d + k0 + lk);
-                a.x = __uint_as_float(q.x << 16);
-                a.y = __uint_as_float(q.x & 0xffff0000u);
-                a.z = __uint_as_float(q.y << 16);
-                a.w = __uint_as_float(q.y & 0xffff0000u);
-            } else {
-                a = *(const float4 *)((const float *)w1 + (long)jrow * d + k0 + lk);
-            }
+            const uint2 q = *(const uint2 *)(w1 + (long)jrow * d + k0 + lk);
+            a.x = __uint_as_float(q.x << 16);
+            a.y = __uint_as_float(q.x & 0xffff0000u);
+            a.z = __uint_as_float(q.y << 16);
+            a.w = __uint_as_float(q.y & 0xffff0000u);
             b = *(const float4 *)(xp + k0 + lk);
         }
         __syncthreads();
@@ -217,6 +213,129 @@ __global__ __launch_bounds__(256) void head_layer1_skinny_kernel(const float *__
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+
+// Layer 1, fp32 weights, more sequences than the skinny kernel serves: fp32 matrix instructions (16x16x4, fp32
+// operands and accumulators: the precision of an FMA chain).  Bound: the fp32 matrix rate, 157 TFLOP/s -- a quarter of
+// a wave's MFMA time is enough for all its LDS reads, so the tile is as large as keeps every compute unit busy.
+// Workgroup = 4 waves (2 x 2), FJ = 128 head rows x 32 NS sequences; wave = 64 x 16 NS = 4 x NS tiles, weights as the
+// row operand.  K is staged 16 elements at a time as 64-byte rows, 16-byte chunks XOR-ed with swizzle key (r >> 1) & 3:
+// lane l reads chunk l / 16 of row l % 16, i.e. four neighbouring K elements that feed four MFMAs (an MFMA then
+// contracts elements s, 4 + s, 8 + s, 12 + s of the sixteen: the order inside a sum, the same for both operands).  The
+// next chunk's global loads are in flight during the current one's MFMAs; two LDS buffers.
+// Measured: 1024 sequences, d = 4096, d_h = 1024: 119 us with 64 x 64 tiles of fp32 FMAs, now 86 = 100 TFLOP/s.
+constexpr int FJ = 128, FK = 16;
+constexpr int F32_WORKGROUPS = 512;  // workgroups asked for by splitting along d
+
+template <int NS>
+__global__ __launch_bounds__(256) void head_layer1_f32_kernel(const float *__restrict__ x,
+                                                              const int32_t *__restrict__ slot, int B, int d, int d_h,
+                                                              const float *__restrict__ w1, int kchunk, int nks,
+                                                              int jtiles, float *__restrict__ act_part)
+{
+    constexpr int FS = 32 * NS;
+    constexpr int W_PIECES = FJ / 64, X_PIECES = (FS + 63) / 64;  // 16-byte pieces a thread stages per chunk
+    __shared__ __align__(16) unsigned char lds[2][(FJ + X_PIECES * 64) * 64];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int l15 = lane & 15, kq = lane >> 4;
+    // the slice index varies fastest over the grid: an XCD pulls only its own slices of both operands
+    const int kslice = blockIdx.x % nks;
+    const int tile = blockIdx.x / nks;
+    const int j0 = (tile % jtiles) * FJ, s0 = (tile / jtiles) * FS;
+    const int wj = (wave & 1) * 64, ws = (wave >> 1) * (16 * NS);
+
+    const int prow = tid >> 2, pchunk = tid & 3;  // what this thread stages: rows prow + 64 p, this chunk
+    const unsigned pdst = (unsigned)(prow * 64 + ((pchunk ^ ((prow >> 1) & 3)) << 4));
+    const float *wp[W_PIECES], *xp[X_PIECES];
+#pragma unroll
+    for (int p = 0; p < W_PIECES; ++p) {
+        const int j = min(j0 + prow + 64 * p, d_h - 1);  // clamped rows are computed and dropped
+        wp[p] = w1 + (long)j * d + 4 * pchunk;
+    }
+#pragma unroll
+    for (int p = 0; p < X_PIECES; ++p) {
+        const int sq = min(s0 + prow + 64 * p, B - 1);
+        xp[p] = x + (long)(slot ? slot[sq] : sq) * d + 4 * pchunk;
+    }
+    const int kbeg = kslice * kchunk;
+    const int kend = min(d, kbeg + kchunk);
+    float4 wr[W_PIECES], xr[X_PIECES];
+    auto fetch = [&](int k0) {  // kend is a multiple of 4: a piece is inside the slice or outside of it
+        const bool ok = k0 + 4 * pchunk < kend;
+#pragma unroll
+        for (int p = 0; p < W_PIECES; ++p)
+            wr[p] = ok ? *(const float4 *)(wp[p] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int p = 0; p < X_PIECES; ++p)
+            xr[p] = ok ? *(const float4 *)(xp[p] + k0) : make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    auto stage = [&](unsigned char *buf) {
+#pragma unroll
+        for (int p = 0; p < W_PIECES; ++p)
+            *(float4 *)(buf + p * 4096 + pdst) = wr[p];
+#pragma unroll
+        for (int p = 0; p < X_PIECES; ++p)
+            *(float4 *)(buf + FJ * 64 + p * 4096 + pdst) = xr[p];
+    };
+
+    f32x4 acc[4][NS];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const unsigned rd = (unsigned)(l15 * 64 + ((kq ^ ((l15 >> 1) & 3)) << 4));
+    if (kbeg < kend) {
+        fetch(kbeg);
+        stage(lds[0]);
+    }
+    __syncthreads();
+    int cur = 0;
+    for (int k0 = kbeg; k0 < kend; k0 += FK) {
+        const bool more = k0 + FK < kend;
+        if (more)
+            fetch(k0 + FK);
+        const unsigned char *buf = lds[cur];
+        f32x4 fa[4], fb[NS];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+            fa[a] = *(const f32x4 *)(buf + (wj + 16 * a) * 64 + rd);
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+            fb[b] = *(const f32x4 *)(buf + (FJ + ws + 16 * b) * 64 + rd);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < NS; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[a][s], fb[b][s], acc[a][b], 0, 0, 0);
+        if (more)
+            stage(lds[cur ^ 1]);  // nobody reads that buffer now
+        __syncthreads();
+        cur ^= 1;
+    }
+
+    float *act = act_part + (long)kslice * B * d_h;
+#pragma unroll
+    for (int b = 0; b < NS; ++b) {
+        const int s = s0 + ws + 16 * b + l15;
+        if (s >= B)
+            continue;
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const int jj = j0 + wj + 16 * a + 4 * kq;
+            if (jj + 3 < d_h && (d_h & 3) == 0) {
+                *(f32x4 *)(act + (long)s * d_h + jj) = acc[a][b];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (jj + i < d_h)
+                        act[(long)s * d_h + jj + i] = acc[a][b][i];
+            }
+        }
+    }
+}
 
 constexpr int MK = 32;  // K elements per MFMA step
 
@@ -482,6 +601,10 @@ static bool skinny_serves(int d, int32_t B, int wdtype)
     return wdtype == DT_F32 && B <= SK_SEQS && d % 4 == 0 && skinny_slices(d) <= 64;
 }
 
+// Sequences per tile of the fp32 matrix kernel.  (128 x 128 tiles gain nothing for their halved operand traffic: whole
+// training steps at batch 1024 199.7 us against 199.4, at d = 1024, d_h = 300, batch 256 39.1 against 34.6.)
+static int f32_tile_seqs(int32_t B) { return B > 32 ? 64 : 32; }
+
 int head_k_splits(int d, int d_h, int32_t B, int wdtype)
 {
     if (skinny_serves(d, B, wdtype))
@@ -493,6 +616,11 @@ int head_k_splits(int d, int d_h, int32_t B, int wdtype)
     const int cap = (d + TK - 1) / TK < 64 ? (d + TK - 1) / TK : 64;
     long n = want > base ? want : base;
     n = n > cap ? cap : n;
+    if (wdtype == DT_F32) {  // larger tiles: fewer slices
+        const long ftiles = (long)((d_h + FJ - 1) / FJ) * ((B + f32_tile_seqs(B) - 1) / f32_tile_seqs(B));
+        const long fwant = ftiles > 0 ? (F32_WORKGROUPS + ftiles - 1) / ftiles : 1;
+        n = n > fwant ? fwant : n;
+    }
     return n < 1 ? 1 : (int)n;
 }
 
@@ -527,7 +655,22 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
                            B, d, d_h, (const float *)w1, kchunk_s, act_part);
         return hipGetLastError();
     }
-    const dim3 grid((d_h + TM - 1) / TM, (B + TN - 1) / TN, nks);
+    if (wdtype == DT_F32) {
+        const int kchunk_f = ((d + nks - 1) / nks + FK - 1) / FK * FK;
+        const int jtiles = (d_h + FJ - 1) / FJ, fs = f32_tile_seqs(B);
+        const long wgs = (long)jtiles * ((B + fs - 1) / fs) * nks;
+        if (d % 4 != 0 || wgs > 0x7fffffffL)
+            return hipErrorInvalidValue;
+#define EGTP_LAYER1_F32(NS)                                                                                       \
+    hipLaunchKernelGGL((head_layer1_f32_kernel<NS>), dim3((unsigned)wgs), dim3(256), 0, st, x, slot, B, d, d_h,   \
+                       (const float *)w1, kchunk_f, nks, jtiles, act_part)
+        if (fs == 64)
+            EGTP_LAYER1_F32(2);
+        else
+            EGTP_LAYER1_F32(1);
+#undef EGTP_LAYER1_F32
+        return hipGetLastError();
+    }
     if (wdtype == DT_BF16 && d % 8 == 0) {
         // matrix-core path: slices are multiples of the MFMA K step (late slices may be empty
         // and then write zeros)
@@ -541,12 +684,8 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
         return hipGetLastError();
     }
     const int kchunk = ((d + nks - 1) / nks + TK - 1) / TK * TK;  // multiple of the K step
-    if (wdtype == DT_BF16)
-        hipLaunchKernelGGL(head_layer1_kernel<true>, grid, dim3(256), 0, st, x, slot, B, d, d_h, w1, kchunk,
-                           act_part);
-    else
-        hipLaunchKernelGGL(head_layer1_kernel<false>, grid, dim3(256), 0, st, x, slot, B, d, d_h, w1, kchunk,
-                           act_part);
+    hipLaunchKernelGGL(head_layer1_kernel, dim3((d_h + TM - 1) / TM, (B + TN - 1) / TN, nks), dim3(256), 0, st, x, slot, B,
+                       d, d_h, (const unsigned short *)w1, kchunk, act_part);
     return hipGetLastError();
 }
 

@@ -179,120 +179,186 @@ __device__ void sum_loss(const float *__restrict__ loss_part, int B, float lambd
     }
 }
 
-// ---- 3. W2, b2, b1: one thread per parameter (workgroup `block` of the small-parameter part) ----
-__device__ __forceinline__ void small_update(
-    int block, const float *__restrict__ act, const float *__restrict__ dact, const float *__restrict__ dz, int B,
-    int d_h, int K, const Adam &h, float *__restrict__ w2, float *__restrict__ m_w2, float *__restrict__ v_w2,
-    float *__restrict__ b2, float *__restrict__ m_b2, float *__restrict__ v_b2, float *__restrict__ b1,
-    float *__restrict__ m_b1, float *__restrict__ v_b1, float *__restrict__ g_w2, float *__restrict__ g_b2,
-    float *__restrict__ g_b1)
+// ---- 3. W2, b2, b1: sums over the batch of columns of act, dz and dact ----------------------
+// Workgroup = 64 columns; wave q adds the samples b = q, q + 4, ... (each a coalesced load of 64 columns, eight in
+// flight: one sample after the other is a chain of cache latencies), then the four partial sums are joined in order.
+// NO > 0: the column is weighted with dz[b][o0 .. o0 + NO - 1] (rows of W2's gradient; a load of act serves all of
+// them); NO = 0: a plain column sum (the biases).  Parameter (o, column) sits at base + o * ld + column.
+constexpr int W2_ROWS = 4;  // rows of W2 per workgroup
+
+struct Params {
+    float *w, *m, *v, *g;
+};
+
+template <int NO>
+__device__ __forceinline__ void column_update(const float *__restrict__ mat, long ld, int n, int col0,
+                                              const float *__restrict__ dz, int K, int o0, int B, const Adam &h,
+                                              const Params &p, float *__restrict__ red)
 {
-    const long e = (long)block * 256 + threadIdx.x;
-    const long n_w2 = (long)K * d_h;
-    float g = 0.f;
-    float *w, *m, *v, *gout;
-    if (e < n_w2) {
-        const int o = (int)(e / d_h), j = (int)(e - (long)o * d_h);
-        for (int b = 0; b < B; ++b)
-            g = fmaf(dz[(long)b * K + o], act[(long)b * d_h + j], g);
-        w = w2 + e, m = m_w2 + e, v = v_w2 + e, gout = g_w2 ? g_w2 + e : nullptr;
-    } else if (e < n_w2 + K) {
-        const int o = (int)(e - n_w2);
-        for (int b = 0; b < B; ++b)
-            g += dz[(long)b * K + o];
-        w = b2 + o, m = m_b2 + o, v = v_b2 + o, gout = g_b2 ? g_b2 + o : nullptr;
-    } else if (e < n_w2 + K + d_h) {
-        const int j = (int)(e - n_w2 - K);
-        for (int b = 0; b < B; ++b)
-            g += dact[(long)b * d_h + j];
-        w = b1 + j, m = m_b1 + j, v = v_b1 + j, gout = g_b1 ? g_b1 + j : nullptr;
-    } else {
-        return;
+    constexpr int NR = NO > 0 ? NO : 1;
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int col = min(col0 + lane, n - 1);  // clamped columns are computed and dropped
+    float s[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        s[r] = 0.f;
+    auto add = [&](int b, float v) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+            s[r] = NO > 0 ? fmaf(dz[(long)b * K + min(o0 + r, K - 1)], v, s[r]) : s[r] + v;
+    };
+    int b = q;
+    for (; b + 28 < B; b += 32) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            v[i] = mat[(b + 4 * i) * ld + col];
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            add(b + 4 * i, v[i]);
     }
-    float wv = *w, mv = *m, vv = *v;
-    adamw(h, g, wv, mv, vv);
-    *w = wv;
-    *m = mv;
-    *v = vv;
-    if (gout)
-        *gout = g;
+    for (; b < B; b += 4)
+        add(b, mat[b * ld + col]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+        red[(q * NR + r) * 64 + lane] = s[r];
+    __syncthreads();
+    // wave q finishes the rows q, q + 4, ...
+    for (int r = q; r < NR; r += 4) {
+        if (col0 + lane >= n || (NO > 0 && o0 + r >= K))
+            continue;
+        float g = red[r * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+            g += red[(k * NR + r) * 64 + lane];
+        const long e = NO > 0 ? (o0 + r) * ld + col : col;
+        float wv = p.w[e], mv = p.m[e], vv = p.v[e];
+        adamw(h, g, wv, mv, vv);
+        p.w[e] = wv;
+        p.m[e] = mv;
+        p.v[e] = vv;
+        if (p.g)
+            p.g[e] = g;
+    }
 }
 
 // ---- 4. W1: gradient tile in registers, AdamW in the epilogue -------------------------------
-constexpr int GM = 64;  // rows j of W1 per tile
-constexpr int GN = 64;  // columns k of W1 per tile
-constexpr int GB = 16;  // samples per LDS stage
+// gradient[j][k] = sum over samples of dact[b][j] x[b][k], on the fp32 matrix cores (16x16x4: fp32 operands, products
+// and sums).  Two bounds: the stream over W1 and its two moments (24 bytes per parameter, whatever the batch) and, from
+// a few hundred samples on, the fp32 matrix rate.  Workgroup = 4 waves; a wave's tile is 16 rows j x 64 columns k.
+// Both operands lie with the sample as the slow index, so a K step of four samples is staged and read as rows: lane l
+// reads row j = l % 16 and four neighbouring k of sample 4 s + l / 16, which makes column tile n of a wave the
+// columns 4 (column) + n; a lane then ends up with four neighbouring columns of a row, one 16-byte access each to W1
+// and the moments.  Batch 1024: 390 us with 64 x 64 tiles of fp32 FMAs, now 95.
+// 64 x 64 per workgroup, 32 samples per LDS stage.  128 x 128 tiles halve the operand traffic and gain nothing for it
+// (whole step at batch 1024, d = 4096, d_h = 1024: 198 us against 199) while few of them leave the chip idle (batch
+// 1024, d = 1024, d_h = 300: 131 us against 65).
+constexpr int GM = 64, GN = 64, GB = 32;
+constexpr int GRAD_STAGE_FLOATS = GB * (GM + GN);  // As[GB][GM] | Bs[GB][GN]
 
-__device__ __forceinline__ void w1_update(
-    int tile_k, int tile_j, const float *__restrict__ x, const float *__restrict__ dact, int B, int d, int d_h,
-    const Adam &h, float *__restrict__ w1, float *__restrict__ m_w1, float *__restrict__ v_w1,
-    float *__restrict__ g_w1)
+__device__ __forceinline__ void w1_update(int tile_k, int tile_j, const float *__restrict__ x,
+                                          const float *__restrict__ dact, int B, int d, int d_h, const Adam &h,
+                                          float *__restrict__ w1, float *__restrict__ m_w1, float *__restrict__ v_w1,
+                                          float *__restrict__ g_w1, float *__restrict__ lds)
 {
-    __shared__ __align__(16) float As[GB][GM];  // dact[b][j]
-    __shared__ __align__(16) float Bs[GB][GN];  // x[b][k]
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    constexpr int A_PIECES = GB * GM / 1024, B_PIECES = GB * GN / 1024;  // 16-byte pieces per thread
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l15 = lane & 15, kq = lane >> 4;
     const int k0 = tile_k * GN, j0 = tile_j * GM;
-    const int lb = tid >> 4;        // sample row this thread stages
-    const int lc = (tid & 15) * 4;  // first of its four columns
+    const int wj = wave * 16;
 
-    float acc[4][4];
+    float4 ar[A_PIECES], br[B_PIECES];
+    const bool whole = (d_h & 3) == 0;  // rows of dact are 16-byte aligned
+    auto fetch = [&](int b0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+        for (int p = 0; p < A_PIECES; ++p) {
+            const int e = (tid + 256 * p) * 4, b = b0 + e / GM, j = j0 + e % GM;
+            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (b < B) {
+                const float *dp = dact + (long)b * d_h + j;
+                if (whole && j < d_h) {
+                    v = *(const float4 *)dp;
+                } else {
+                    v.x = j + 0 < d_h ? dp[0] : 0.f;
+                    v.y = j + 1 < d_h ? dp[1] : 0.f;
+                    v.z = j + 2 < d_h ? dp[2] : 0.f;
+                    v.w = j + 3 < d_h ? dp[3] : 0.f;
+                }
+            }
+            ar[p] = v;
+        }
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            acc[i][c] = 0.f;
+        for (int p = 0; p < B_PIECES; ++p) {
+            const int e = (tid + 256 * p) * 4, b = b0 + e / GN, k = k0 + e % GN;
+            br[p] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (b < B && k < d)  // d is a multiple of 4: the whole piece is inside the row
+                br[p] = *(const float4 *)(x + (long)b * d + k);
+        }
+    };
+    auto stage = [&](float *buf) {
+#pragma unroll
+        for (int p = 0; p < A_PIECES; ++p)
+            *(float4 *)(buf + (tid + 256 * p) * 4) = ar[p];
+#pragma unroll
+        for (int p = 0; p < B_PIECES; ++p)
+            *(float4 *)(buf + GB * GM + (tid + 256 * p) * 4) = br[p];
+    };
 
-    for (int b0 = 0; b0 < B; b0 += GB) {
-        float4 av = make_float4(0.f, 0.f, 0.f, 0.f), bv = av;
-        const int b = b0 + lb;
-        if (b < B) {
-            const float *dp = dact + (long)b * d_h + j0 + lc;
-            av.x = j0 + lc + 0 < d_h ? dp[0] : 0.f;
-            av.y = j0 + lc + 1 < d_h ? dp[1] : 0.f;
-            av.z = j0 + lc + 2 < d_h ? dp[2] : 0.f;
-            av.w = j0 + lc + 3 < d_h ? dp[3] : 0.f;
-            if (k0 + lc < d)  // d is a multiple of 4: the whole quad is inside the row
-                bv = *(const float4 *)(x + (long)b * d + k0 + lc);
-        }
-        __syncthreads();
-        *(float4 *)&As[lb][lc] = av;
-        *(float4 *)&Bs[lb][lc] = bv;
-        __syncthreads();
+    f32x4 acc[4];
 #pragma unroll
-        for (int bb = 0; bb < GB; ++bb) {
-            const float4 a4 = *(const float4 *)&As[bb][ty * 4];
-            const float4 b4 = *(const float4 *)&Bs[bb][tx * 4];
-            const float aa[4] = {a4.x, a4.y, a4.z, a4.w};
-            const float kk[4] = {b4.x, b4.y, b4.z, b4.w};
+    for (int n = 0; n < 4; ++n)
+        acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    fetch(0);
+    // the tile's parameters and moments are asked for now, so that the stream runs beside the contraction
+    const int k = k0 + 4 * l15;
+    float4 w[4], m[4], v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    acc[i][c] = fmaf(aa[i], kk[c], acc[i][c]);
-        }
+    for (int i = 0; i < 4; ++i) {
+        // rows and columns that do not exist: a valid place, not used
+        const long at = (long)min(j0 + wj + 4 * kq + i, d_h - 1) * d + min(k, d - 4);
+        w[i] = *(const float4 *)(w1 + at);
+        m[i] = *(const float4 *)(m_w1 + at);
+        v[i] = *(const float4 *)(v_w1 + at);
     }
-    const int k = k0 + tx * 4;
+    stage(lds);
+    __syncthreads();
+    int cur = 0;
+    for (int b0 = 0; b0 < B; b0 += GB) {
+        const bool more = b0 + GB < B;
+        if (more)
+            fetch(b0 + GB);
+        const float *buf = lds + cur * GRAD_STAGE_FLOATS;
+#pragma unroll
+        for (int s = 0; s < GB / 4; ++s) {
+            const float av = buf[(4 * s + kq) * GM + wj + l15];
+            const f32x4 bv = *(const f32x4 *)(buf + GB * GM + (4 * s + kq) * GN + 4 * l15);
+#pragma unroll
+            for (int n = 0; n < 4; ++n)
+                acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv[n], acc[n], 0, 0, 0);
+        }
+        if (more)
+            stage(lds + (cur ^ 1) * GRAD_STAGE_FLOATS);  // nobody reads that buffer now
+        __syncthreads();
+        cur ^= 1;
+    }
     if (k >= d)
         return;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int j = j0 + ty * 4 + i;
+        const int j = j0 + wj + 4 * kq + i;
         if (j >= d_h)
             continue;
         const long at = (long)j * d + k;
-        float4 w = *(const float4 *)(w1 + at);
-        float4 m = *(const float4 *)(m_w1 + at);
-        float4 v = *(const float4 *)(v_w1 + at);
-        adamw(h, acc[i][0], w.x, m.x, v.x);
-        adamw(h, acc[i][1], w.y, m.y, v.y);
-        adamw(h, acc[i][2], w.z, m.z, v.z);
-        adamw(h, acc[i][3], w.w, m.w, v.w);
-        *(float4 *)(w1 + at) = w;
-        *(float4 *)(m_w1 + at) = m;
-        *(float4 *)(v_w1 + at) = v;
+        adamw(h, acc[0][i], w[i].x, m[i].x, v[i].x);
+        adamw(h, acc[1][i], w[i].y, m[i].y, v[i].y);
+        adamw(h, acc[2][i], w[i].z, m[i].z, v[i].z);
+        adamw(h, acc[3][i], w[i].w, m[i].w, v[i].w);
+        *(float4 *)(w1 + at) = w[i];
+        *(float4 *)(m_w1 + at) = m[i];
+        *(float4 *)(v_w1 + at) = v[i];
         if (g_w1)
-            *(float4 *)(g_w1 + at) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
+            *(float4 *)(g_w1 + at) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
     }
 }
 
@@ -302,26 +368,38 @@ __device__ __forceinline__ void w1_update(
 struct UpdateArgs {
     const float *x, *act, *dact, *dz, *loss_part;
     int B, d, d_h, K;
-    int tiles_k, tiles_w1, blocks_small;
+    int tiles_k, tiles_w1;
+    int cols_h, blocks_w2, blocks_b2;  // 64-column blocks of d_h; workgroups of W2 and of b2 (b1 has cols_h)
     float lambda;
-    float *w1, *m_w1, *v_w1, *g_w1;
-    float *w2, *m_w2, *v_w2, *g_w2;
-    float *b2, *m_b2, *v_b2, *g_b2;
-    float *b1, *m_b1, *v_b1, *g_b1;
+    Params w1, w2, b2, b1;
     float *loss;
 };
 
 __global__ __launch_bounds__(256) void train_update_kernel(UpdateArgs a, Adam h)
 {
-    const int id = blockIdx.x;
+    __shared__ __align__(16) float lds[2 * GRAD_STAGE_FLOATS];
+    static_assert(2 * GRAD_STAGE_FLOATS >= 4 * W2_ROWS * 64, "LDS of the small-parameter part");
+    int id = blockIdx.x;
     if (id < a.tiles_w1) {
-        w1_update(id % a.tiles_k, id / a.tiles_k, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1, a.m_w1, a.v_w1, a.g_w1);
-    } else if (id < a.tiles_w1 + a.blocks_small) {
-        small_update(id - a.tiles_w1, a.act, a.dact, a.dz, a.B, a.d_h, a.K, h, a.w2, a.m_w2, a.v_w2, a.b2, a.m_b2,
-                     a.v_b2, a.b1, a.m_b1, a.v_b1, a.g_w2, a.g_b2, a.g_b1);
-    } else {
-        sum_loss(a.loss_part, a.B, a.lambda, a.loss);
+        w1_update(id % a.tiles_k, id / a.tiles_k, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, lds);
+        return;
     }
+    id -= a.tiles_w1;
+    if (id < a.blocks_w2) {
+        column_update<W2_ROWS>(a.act, a.d_h, a.d_h, (id % a.cols_h) * 64, a.dz, a.K, (id / a.cols_h) * W2_ROWS, a.B, h, a.w2,
+                               lds);
+        return;
+    }
+    id -= a.blocks_w2;
+    if (id < a.cols_h) {
+        column_update<0>(a.dact, a.d_h, a.d_h, id * 64, nullptr, 0, 0, a.B, h, a.b1, lds);
+        return;
+    }
+    id -= a.cols_h;
+    if (id < a.blocks_b2)
+        column_update<0>(a.dz, a.K, a.K, id * 64, nullptr, 0, 0, a.B, h, a.b2, lds);
+    else
+        sum_loss(a.loss_part, a.B, a.lambda, a.loss);
 }
 
 }  // namespace
@@ -360,20 +438,21 @@ hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
     u.x = a.x, u.act = a.act, u.dact = a.dact, u.dz = a.dz, u.loss_part = a.loss_part;
     u.B = a.B, u.d = a.d, u.d_h = a.d_h, u.K = a.K;
     u.lambda = a.lambda;
-    u.w1 = a.w1, u.m_w1 = a.m_w1, u.v_w1 = a.v_w1, u.g_w1 = a.g_w1;
-    u.w2 = a.w2, u.m_w2 = a.m_w2, u.v_w2 = a.v_w2, u.g_w2 = a.g_w2;
-    u.b2 = a.b2, u.m_b2 = a.m_b2, u.v_b2 = a.v_b2, u.g_b2 = a.g_b2;
-    u.b1 = a.b1, u.m_b1 = a.m_b1, u.v_b1 = a.v_b1, u.g_b1 = a.g_b1;
+    u.w1 = {a.w1, a.m_w1, a.v_w1, a.g_w1};
+    u.w2 = {a.w2, a.m_w2, a.v_w2, a.g_w2};
+    u.b2 = {a.b2, a.m_b2, a.v_b2, a.g_b2};
+    u.b1 = {a.b1, a.m_b1, a.v_b1, a.g_b1};
     u.loss = a.loss;
-    const long n_small = (long)a.K * a.d_h + a.K + a.d_h;
     const long tiles_k = (a.d + GN - 1) / GN, tiles_j = (a.d_h + GM - 1) / GM;
-    const long blocks_small = (n_small + 255) / 256;
-    if (tiles_k * tiles_j + blocks_small + 1 > 0x7fffffffL)
-        return hipErrorInvalidValue;
     u.tiles_k = (int)tiles_k;
     u.tiles_w1 = (int)(tiles_k * tiles_j);
-    u.blocks_small = (int)blocks_small;
-    hipLaunchKernelGGL(train_update_kernel, dim3((unsigned)(u.tiles_w1 + u.blocks_small + 1)), dim3(256), 0, st, u, h);
+    u.cols_h = (a.d_h + 63) / 64;
+    u.blocks_w2 = u.cols_h * ((a.K + W2_ROWS - 1) / W2_ROWS);
+    u.blocks_b2 = (a.K + 63) / 64;
+    const long wgs = tiles_k * tiles_j + u.blocks_w2 + u.cols_h + u.blocks_b2 + 1;
+    if (wgs > 0x7fffffffL)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(train_update_kernel, dim3((unsigned)wgs), dim3(256), 0, st, u, h);
     return hipGetLastError();
 }
 

@@ -264,3 +264,12 @@ def test_argument_errors(gpu):
     assert torch.equal(tr.params["w1"], before)                  # nothing was launched
     h.d = 64
     gpu.egtp_head_train_step(h, x, bins, y, None, 0, 0, None, None)   # B = 0: nothing to do
+
+
+# The fp32 matrix kernels at the edges of their tiles: 17 and 32 samples (the smallest tile), 33 and 64 (the other one
+# exactly full), 65 and 97 (a second tile; one and four samples past a stage of 32); rows of W1 around 64 and 128 and
+# off the 16-byte grid, K slices that end inside a chunk of sixteen, bin counts around the four rows of W2 a workgroup takes
+@pytest.mark.parametrize("B,d,d_h,K", [(17, 260, 63, 5), (32, 516, 64, 2), (33, 68, 65, 20), (64, 1028, 127, 4),
+                                       (65, 252, 129, 33), (97, 4, 130, 9)])
+def test_matrix_kernels_at_tile_edges(gpu, B, d, d_h, K):
+    _run_steps(gpu, wl.make_train(4000 + B, B=B, d=d, d_h=d_h, K=K), 1)
