@@ -51,12 +51,12 @@ struct Carver {
 
 struct Workspace {
     float *entropy;      // [T]
-    float *k1_part;      // partial triples
+    float *k1_part;      // partial triples of the fused kernel; later, in the same memory, of the pooling:
+    float *pool_part;    //   partial rows of its units ...
+    float *pool_stats;   //   ... and two statistics each
+    int pool_unit;       // tokens per unit
+    float *lse_old;      // [B]
     int *k1_pace;        // pacing counters of the fused kernel
-    int32_t *unit_start; // [B+1]
-    float *lse_new;      // [B]
-    float *state_scale;  // [B]
-    float *pool_part;    // [units_bound x d]
     float *act;          // [k splits x B x d_h_max]
     unsigned char *hidden_packed;  // packed copy of this call's hidden states
     unsigned char *w_packed;       // when no persistent packed W_lm was given
@@ -73,12 +73,15 @@ Workspace carve(const egtp_ctx *ctx, void *base, int64_t T, int32_t B)
     const size_t act_len = head_act_floats_bound(c.d, c.head_len.d_h, B, c.head_len.wdtype);
     const size_t act_rem = head_act_floats_bound(c.d, c.head_rem.d_h, B, c.head_rem.wdtype);
     w.entropy = cv.take<float>((size_t)T);
-    w.k1_part = cv.take<float>(k1_partial_floats_bound(T));
+    // the pooling runs when the partial triples have been merged: its units take their place
+    const size_t triples = k1_partial_floats_bound(T), units = pool_unit_floats(c.d, T, B, POOL_UNIT);
+    const size_t shared_floats = triples > units ? triples : units;
+    w.k1_part = cv.take<float>(shared_floats);
     w.k1_pace = cv.take<int>(k1_pace_ints_bound(T));
-    w.unit_start = cv.take<int32_t>((size_t)B + 1);
-    w.lse_new = cv.take<float>((size_t)B);
-    w.state_scale = cv.take<float>((size_t)B);
-    w.pool_part = cv.take<float>((size_t)pool_units_bound(T, B) * (size_t)c.d);
+    w.pool_unit = pool_unit(c.dtype, c.d, T, B, shared_floats);
+    w.pool_part = w.k1_part;
+    w.pool_stats = w.k1_part ? w.k1_part + (size_t)pool_units_bound(T, B, w.pool_unit) * (size_t)c.d : nullptr;
+    w.lse_old = cv.take<float>((size_t)B);
     w.act = cv.take<float>(act_len > act_rem ? act_len : act_rem);
     const int K = (int)k1_contraction_len(c.dtype, c.d);
     w.hidden_packed = cv.take<unsigned char>(k1_packed_bytes(T, K));
@@ -541,10 +544,10 @@ egtp_status score_impl(egtp_ctx *ctx, const void *hidden, const int32_t *offsets
     a.state_pooled = nullptr;
     a.out_pooled = pooled_out;
     a.out_lse = lse_out;
-    a.unit_start = w.unit_start;
-    a.lse_new = w.lse_new;
-    a.state_scale = w.state_scale;
+    a.unit = w.pool_unit;
     a.partial = w.pool_part;
+    a.unit_stats = w.pool_stats;
+    a.lse_old = w.lse_old;
     EGTP_HIP(pool_entropy_weighted(a, st));
     return run_head(ctx, c.head_len, pooled_out, nullptr, B, w, pred_out, p_hat_out, st);
 }
@@ -600,10 +603,10 @@ egtp_status step_impl(egtp_ctx *ctx, const void *hidden_new, const int32_t *offs
     a.state_pooled = pooled_state;
     a.out_pooled = pooled_state;
     a.out_lse = lse_state;
-    a.unit_start = w.unit_start;
-    a.lse_new = w.lse_new;
-    a.state_scale = w.state_scale;
+    a.unit = w.pool_unit;
     a.partial = w.pool_part;
+    a.unit_stats = w.pool_stats;
+    a.lse_old = w.lse_old;
     EGTP_HIP(pool_entropy_weighted(a, st));
     return run_head(ctx, c.head_rem, pooled_state, slot_dev, B, w, rem_pred_out, p_hat_out, st);
 }
@@ -688,7 +691,7 @@ egtp_status egtp_pool_ablation(egtp_ctx *ctx, const void *hidden, const int32_t 
     hipStream_t st = (hipStream_t)stream;
     const egtp_config &c = ctx->cfg;
     const Workspace w = carve(ctx, workspace, T, B);
-    EGTP_HIP(pool_plain(hidden, c.dtype, c.d, offsets_dev, B, T, (int)kind, w.unit_start, w.pool_part, pooled_out,
+    EGTP_HIP(pool_plain(hidden, c.dtype, c.d, offsets_dev, B, T, (int)kind, w.pool_unit, w.pool_part, pooled_out,
                         st));
     if (pred_out)
         return run_head(ctx, c.head_len, pooled_out, nullptr, B, w, pred_out, nullptr, st);

@@ -2,10 +2,15 @@
 // streaming PLP fold of Eq. 8, the ablation poolers of Table 3, and the ragged plumbing.
 //
 // Pooling is HBM-bound: every hidden state is read once more (16 bytes per lane, a wave
-// reads 1 KiB of one token row at a time).  A sequence is cut into units of at most
-// POOL_UNIT tokens so that long and short sequences load the chip evenly; each unit leaves a
-// partial weighted sum (already normalised with the sequence's final log-sum-exp), and a
-// finalize kernel adds a sequence's partials in unit order.  No atomics: bit-reproducible.
+// reads 1 KiB of one token row at a time).  A sequence is cut into units of at most 256 tokens
+// (fewer in a small batch) so that long and short sequences load the chip evenly; each unit leaves a
+// partial weighted sum relative to its own largest entropy, with that reference and the sum of its weights, and a
+// finalize kernel joins a sequence's units in order.  No atomics: bit-reproducible.
+//
+// Units need no table: sequence b owns the unit numbers from offsets[b] / unit + b on.  Consecutive sequences
+// never meet, because ceil((y - x) / unit) <= floor(y / unit) - floor(x / unit) + 1; of the
+// floor(T / unit) + B numbers some stay unused.  (A scan kernel made a table, and another one the
+// log-sum-exps, before: two launches more.)
 #include "k1_common.h"
 #include "stream_load.h"
 #include "wave_reduce.h"
@@ -15,30 +20,9 @@ namespace {
 
 constexpr float NEG_INF = -__builtin_inff();
 
-// ---- block reductions (256 threads), fixed tree => deterministic ---------------------
-__device__ float block_max(float v, float *sh)
-{
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-        sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(sh[0], sh[1]), fmaxf(sh[2], sh[3]));
-}
-__device__ float block_sum(float v, float *sh)
-{
-    v = wave_sum(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0)
-        sh[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return (sh[0] + sh[1]) + (sh[2] + sh[3]);
-}
-
 // ---- ragged plumbing ---------------------------------------------------------------------
-// offsets[0..B] = exclusive scan of f(lengths[b]); one workgroup walks the array in chunks
-// of 256 with a running carry.  UNITS: scan ceil(n_b / POOL_UNIT) of n_b = in[b+1]-in[b].
-template <bool UNITS>
+// offsets[0..B] = exclusive scan of lengths[b]; one workgroup walks the array in chunks
+// of 256 with a running carry.
 __global__ __launch_bounds__(256) void scan_kernel(const int32_t *__restrict__ in, int32_t B,
                                                    int32_t *__restrict__ out)
 {
@@ -52,16 +36,7 @@ __global__ __launch_bounds__(256) void scan_kernel(const int32_t *__restrict__ i
     __syncthreads();
     for (int base = 0; base < B; base += 256) {
         const int b = base + tid;
-        int v = 0;
-        if (b < B) {
-            if (UNITS) {
-                const int n = in[b + 1] - in[b];
-                v = n > 0 ? (n + POOL_UNIT - 1) / POOL_UNIT : 0;
-            } else {
-                v = in[b];
-            }
-        }
-        sh[tid] = v;
+        sh[tid] = b < B ? in[b] : 0;
         __syncthreads();
         for (int o = 1; o < 256; o <<= 1) {  // inclusive Hillis-Steele scan
             int add = tid >= o ? sh[tid - o] : 0;
@@ -105,43 +80,9 @@ __global__ __launch_bounds__(256) void seg_ids_kernel(const int32_t *__restrict_
 // index leaves the partial buffer (a malformed table gives wrong numbers, not wild accesses).
 __device__ __forceinline__ long clamp_token(long t, long T) { return t < 0 ? 0 : (t > T ? T : t); }
 
-// ---- Eq. 3: per-sequence log-sum-exp of H/alpha, joined with the old state's lse ---------
-__global__ __launch_bounds__(256) void pool_lse_kernel(const float *__restrict__ entropy,
-                                                       const int32_t *__restrict__ offsets, long T,
-                                                       const int32_t *__restrict__ slot, float inv_alpha,
-                                                       const float *__restrict__ state_lse,
-                                                       float *__restrict__ lse_new,
-                                                       float *__restrict__ state_scale)
-{
-    __shared__ float sh[4];
-    const int b = blockIdx.x;
-    const int lo = (int)clamp_token(offsets[b], T), hi = (int)clamp_token(offsets[b + 1], T);
-    const int s = slot ? slot[b] : b;
-    const float L_old = state_lse ? state_lse[s] : NEG_INF;
-    float mx = NEG_INF;
-    for (int i = lo + threadIdx.x; i < hi; i += 256)
-        mx = fmaxf(mx, entropy[i] * inv_alpha);
-    mx = fmaxf(block_max(mx, sh), L_old);
-    float sum = 0.f;
-    if (mx > NEG_INF)
-        for (int i = lo + threadIdx.x; i < hi; i += 256)
-            sum += __expf(entropy[i] * inv_alpha - mx);
-    sum = block_sum(sum, sh);
-    if (threadIdx.x == 0) {
-        float L = NEG_INF, sc = 0.f;
-        if (mx > NEG_INF) {
-            const float old = L_old > NEG_INF ? __expf(L_old - mx) : 0.f;
-            L = mx + __logf(sum + old);
-            sc = L_old > NEG_INF ? __expf(L_old - L) : 0.f;
-        }
-        lse_new[b] = L;
-        state_scale[b] = sc;
-    }
-}
-
 // ---- Eq. 4: partial weighted sums per unit --------------------------------------------------
-// MODE 0: weights e^{H/alpha - lse} (Eq. 3-4); MODE 1: plain sums (average pooling, divided by the
-// length when the units are joined); MODE 2: element-wise maxima.
+// MODE 0: weights e^{H/alpha - m} (Eq. 3-4), m the unit's largest H/alpha; MODE 1: plain sums (average pooling,
+// divided by the length when the units are joined); MODE 2: element-wise maxima.
 enum : int { POOL_WEIGHTED = 0, POOL_SUM = 1, POOL_MAXIMUM = 2 };
 
 template <bool BF16, typename Q>
@@ -162,27 +103,77 @@ __device__ __forceinline__ void widen16(const Q &q, float (&h)[BF16 ? 8 : 4])
     }
 }
 
+// first unit number of a sequence that starts at token `begin`
+__device__ __forceinline__ long unit_base(int begin, int b, int unit_log2) { return (long)(max(begin, 0) >> unit_log2) + b; }
+
+// the sequence that unit number u belongs to.  Every workgroup starts with this: up to UNIT_SCAN sequences are
+// looked through by all threads at once (one memory latency), more of them by bisection.
+constexpr int UNIT_SCAN = 2048;
+__device__ int unit_sequence(const int32_t *__restrict__ offsets, int B, long u, int unit_log2, int *sh)
+{
+    if (B > UNIT_SCAN) {
+        int lo = 0, hi = B;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (unit_base(offsets[mid], mid, unit_log2) <= u)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        return lo;
+    }
+    if (threadIdx.x == 0)
+        *sh = 0;
+    __syncthreads();
+    for (int b = threadIdx.x; b < B; b += 256)
+        if (unit_base(offsets[b], b, unit_log2) <= u && u < unit_base(offsets[b + 1], b + 1, unit_log2))
+            *sh = b;
+    __syncthreads();
+    return *sh;
+}
+
 template <bool BF16, int MODE>
 __global__ __launch_bounds__(256) void pool_partial_kernel(
     const void *__restrict__ hidden, int d, const float *__restrict__ entropy,
-    const int32_t *__restrict__ offsets, int32_t B, long T, float inv_alpha, const float *__restrict__ lse_new,
-    const int32_t *__restrict__ unit_start, int ysplit, float *__restrict__ partial)
+    const int32_t *__restrict__ offsets, int32_t B, long T, float inv_alpha, int unit_log2, int ysplit,
+    const int32_t *__restrict__ slot, const float *state_lse, float *__restrict__ lse_old,
+    float *__restrict__ partial, float2 *__restrict__ unit_stats)
 {
-    __shared__ float w[POOL_UNIT];
+    __shared__ float w[256];
+    __shared__ float red[2][4];
+    __shared__ int seq;
     // Workgroup = (unit, feature slice), the slice varying fastest so that the slices of a unit -- pieces of
-    // the same token rows -- are read at about the same time.  The grid holds pool_units_bound(T, B) units:
+    // the same token rows -- are read at about the same time.  The grid holds pool_units_bound(T, B, unit) units:
     // u indexes inside the partial buffer.
     const int u = blockIdx.x / ysplit;
     const int yslice = blockIdx.x - u * ysplit;
-    if (u >= unit_start[B])
-        return;
-    const int b = find_segment(unit_start, B, u);
-    const long t0 = clamp_token((long)offsets[b] + (long)(u - unit_start[b]) * POOL_UNIT, T);
-    const int n = (int)max(0L, min((long)POOL_UNIT, clamp_token(offsets[b + 1], T) - t0));
+    // the states' log-sum-exps, for the join (whose workgroups replace them in place): one workgroup each, there
+    // are at least B
+    if (MODE == POOL_WEIGHTED && state_lse != nullptr && (int64_t)blockIdx.x < B && threadIdx.x == 0)
+        lse_old[blockIdx.x] = state_lse[slot ? slot[blockIdx.x] : blockIdx.x];
+    const int b = unit_sequence(offsets, B, u, unit_log2, &seq);
+    const int begin = offsets[b];
+    const long t0 = clamp_token(begin + ((u - unit_base(begin, b, unit_log2)) << unit_log2), T);
+    const int n = (int)max(0L, min(1L << unit_log2, clamp_token(offsets[b + 1], T) - t0));
+    if (n == 0)
+        return;  // an unused number
     if (MODE == POOL_WEIGHTED) {
-        if (threadIdx.x < POOL_UNIT)
-            w[threadIdx.x] = threadIdx.x < n ? __expf(entropy[t0 + threadIdx.x] * inv_alpha - lse_new[b]) : 0.f;
+        const int tid = threadIdx.x, wave = tid >> 6;
+        static_assert(POOL_UNIT <= 256, "a token per thread");
+        const float a = tid < n ? entropy[t0 + tid] * inv_alpha : NEG_INF;
+        const float wm = wave_max(a);
+        if ((tid & 63) == 0)
+            red[0][wave] = wm;
         __syncthreads();
+        const float m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
+        const float e = tid < n ? __expf(a - m) : 0.f;
+        w[tid] = e;
+        const float ws = wave_sum(e);
+        if ((tid & 63) == 0)
+            red[1][wave] = ws;
+        __syncthreads();
+        if (tid == 0 && yslice == 0)
+            unit_stats[u] = make_float2(m, (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]));
     }
 
     constexpr int VEC = BF16 ? 8 : 4;  // elements per 16-byte load
@@ -225,54 +216,90 @@ __global__ __launch_bounds__(256) void pool_partial_kernel(
     }
 }
 
-// ---- joining a sequence's unit partials ----------------------------------------------------------
-// Thread = four consecutive features of one sequence; the partials are combined in unit order (a fixed
-// order: bit-reproducible), JOIN_AHEAD of them fetched before any is used -- a sequence of 8192 tokens
-// has 64 units, and one load at a time would make the join a chain of 64 memory latencies.
-constexpr int JOIN_AHEAD = 8;
+// ---- joining a sequence's units ----------------------------------------------------------------
+// Workgroup = JOIN_COLS features of one sequence, four consecutive ones per thread; wave q combines the units
+// q, q + 4, ... of the sequence in order, JOIN_AHEAD of them fetched before any is used (one load at a time
+// would make the join of a long sequence a chain of memory latencies), and the four waves' results are combined in
+// order: bit-reproducible.
+constexpr int JOIN_AHEAD = 8, JOIN_FACTORS = 1024, JOIN_COLS = 256;
 
 template <int MODE>
-__device__ __forceinline__ float4 join_units(const float *__restrict__ partial, int u0, int u1, int d, int k,
-                                             float init)
+__device__ __forceinline__ void join(float4 &r, const float4 &v, float f)
 {
-    float4 r = make_float4(init, init, init, init);
-    auto add = [&](const float4 &v) {
-        if (MODE == POOL_MAXIMUM) {
-            r.x = fmaxf(r.x, v.x), r.y = fmaxf(r.y, v.y), r.z = fmaxf(r.z, v.z), r.w = fmaxf(r.w, v.w);
-        } else {
-            r.x += v.x, r.y += v.y, r.z += v.z, r.w += v.w;
-        }
-    };
-    int u = u0;
-    for (; u + JOIN_AHEAD <= u1; u += JOIN_AHEAD) {
+    if (MODE == POOL_MAXIMUM)
+        r.x = fmaxf(r.x, v.x), r.y = fmaxf(r.y, v.y), r.z = fmaxf(r.z, v.z), r.w = fmaxf(r.w, v.w);
+    else if (MODE == POOL_SUM)
+        r.x += v.x, r.y += v.y, r.z += v.z, r.w += v.w;
+    else
+        r.x = fmaf(f, v.x, r.x), r.y = fmaf(f, v.y, r.y), r.z = fmaf(f, v.z, r.z), r.w = fmaf(f, v.w, r.w);
+}
+
+// r joined with this wave's share of the units [u0, u1); POOL_WEIGHTED: unit u counts scale[u - u0] times
+template <int MODE>
+__device__ __forceinline__ float4 join_units(const float *__restrict__ partial, long u0, long u1, int d, int k,
+                                             float4 r, const float *scale)
+{
+    auto factor = [&](long u) { return MODE == POOL_WEIGHTED ? scale[u - u0] : 1.f; };
+    long u = u0 + (threadIdx.x >> 6);
+    for (; u + 4 * (JOIN_AHEAD - 1) < u1; u += 4 * JOIN_AHEAD) {
         float4 v[JOIN_AHEAD];
 #pragma unroll
         for (int i = 0; i < JOIN_AHEAD; ++i)
-            v[i] = *(const float4 *)(partial + (long)(u + i) * d + k);
+            v[i] = *(const float4 *)(partial + (u + 4 * i) * d + k);
 #pragma unroll
         for (int i = 0; i < JOIN_AHEAD; ++i)
-            add(v[i]);
+            join<MODE>(r, v[i], factor(u + 4 * i));
     }
-    for (; u < u1; ++u)
-        add(*(const float4 *)(partial + (long)u * d + k));
+    for (; u < u1; u += 4)
+        join<MODE>(r, *(const float4 *)(partial + u * d + k), factor(u));
     return r;
+}
+
+// the four waves' results, in wave 0
+template <int MODE>
+__device__ __forceinline__ float4 join_waves(float4 r, float4 (&sh)[3][64])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (wave > 0)
+        sh[wave - 1][lane] = r;
+    __syncthreads();
+    if (wave == 0)
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+            join<MODE == POOL_MAXIMUM ? POOL_MAXIMUM : POOL_SUM>(r, sh[q][lane], 1.f);
+    return r;
+}
+
+// the unit numbers [u0, u1) of sequence b, inside the partial buffer whatever the offsets hold
+__device__ __forceinline__ void sequence_units(const int32_t *__restrict__ offsets, int b, int unit_log2, long units_cap,
+                                               long &u0, long &u1)
+{
+    const int begin = offsets[b];
+    const long len = (long)offsets[b + 1] - begin;
+    u0 = min(unit_base(begin, b, unit_log2), units_cap);
+    u1 = min(u0 + (len > 0 ? (len + (1 << unit_log2) - 1) >> unit_log2 : 0), units_cap);
 }
 
 // Table 3 alternatives: sum / length, or maximum
 template <int MODE>
 __global__ __launch_bounds__(256) void pool_finalize_plain_kernel(const float *__restrict__ partial,
-                                                                  const int32_t *__restrict__ unit_start,
                                                                   const int32_t *__restrict__ offsets, int d,
-                                                                  int units_cap, float *__restrict__ out_pooled)
+                                                                  int unit_log2, long units_cap,
+                                                                  float *__restrict__ out_pooled)
 {
+    __shared__ float4 waves[3][64];
     const int b = blockIdx.x;
-    const int k = (blockIdx.y * 256 + threadIdx.x) * 4;
-    if (k >= d)
-        return;
-    const int u0 = unit_start[b], u1 = min(unit_start[b + 1], units_cap);
+    const int k = blockIdx.y * JOIN_COLS + (threadIdx.x & 63) * 4;
+    long u0, u1;
+    sequence_units(offsets, b, unit_log2, units_cap, u0, u1);
     const int len = offsets[b + 1] - offsets[b];
-    // an empty sequence pools to zero
-    float4 r = join_units<MODE>(partial, u0, u1, d, k, (MODE == POOL_MAXIMUM && len > 0) ? NEG_INF : 0.f);
+    const float init = (MODE == POOL_MAXIMUM && len > 0) ? NEG_INF : 0.f;  // an empty sequence pools to zero
+    float4 r = make_float4(init, init, init, init);
+    if (k < d)
+        r = join_units<MODE>(partial, u0, u1, d, k, r, nullptr);
+    r = join_waves<MODE>(r, waves);
+    if (threadIdx.x >= 64 || k >= d)
+        return;
     if (MODE == POOL_SUM && len > 0) {
         const float inv = 1.0f / (float)len;
         r.x *= inv, r.y *= inv, r.z *= inv, r.w *= inv;
@@ -280,29 +307,70 @@ __global__ __launch_bounds__(256) void pool_finalize_plain_kernel(const float *_
     *(float4 *)(out_pooled + (long)b * d + k) = r;
 }
 
-// Eq. 4 / Eq. 8: the sum of a sequence's partials plus the rescaled old state
+// Eq. 3, 4 and 8: the log-sum-exp of the units and the old state, the sum of the units' partials brought to it, plus
+// the rescaled old state.  Every workgroup of a sequence finds the log-sum-exp for itself.
 __global__ __launch_bounds__(256) void pool_finalize_kernel(
-    const float *__restrict__ partial, const int32_t *__restrict__ unit_start,
-    const int32_t *__restrict__ slot, int d, int units_cap, const float *state_pooled,
-    const float *__restrict__ state_scale, const float *__restrict__ lse_new, float *out_pooled,
-    float *out_lse)
+    const float *__restrict__ partial, const float2 *__restrict__ unit_stats, const int32_t *__restrict__ offsets,
+    const int32_t *__restrict__ slot, int d, int unit_log2, long units_cap, const float *state_pooled,
+    const float *__restrict__ lse_old, float *out_pooled, float *out_lse)
 {
+    __shared__ float factor[JOIN_FACTORS];
+    __shared__ float4 waves[3][64];
+    __shared__ float red[2][4];
     const int b = blockIdx.x;
-    const int k = (blockIdx.y * 256 + threadIdx.x) * 4;
+    const int k = blockIdx.y * JOIN_COLS + (threadIdx.x & 63) * 4;
+    const int tid = threadIdx.x, wave = tid >> 6;
     const int s = slot ? slot[b] : b;
-    if (k < d) {
-        const int u0 = unit_start[b], u1 = min(unit_start[b + 1], units_cap);
-        float4 sum = join_units<POOL_SUM>(partial, u0, u1, d, k, 0.f);
-        const float sc = state_scale[b];
+    const float L_old = lse_old ? lse_old[b] : NEG_INF;
+    long u0, u1;
+    sequence_units(offsets, b, unit_log2, units_cap, u0, u1);
+    float mx = NEG_INF;
+    for (long u = u0 + tid; u < u1; u += 256)
+        mx = fmaxf(mx, unit_stats[u].x);
+    mx = wave_max(mx);
+    if ((tid & 63) == 0)
+        red[0][wave] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3])), L_old);
+    float sum = 0.f;
+    if (mx > NEG_INF)
+        for (long u = u0 + tid; u < u1; u += 256) {
+            const float2 q = unit_stats[u];
+            sum = fmaf(q.y, __expf(q.x - mx), sum);
+        }
+    sum = wave_sum(sum);
+    if ((tid & 63) == 0)
+        red[1][wave] = sum;
+    __syncthreads();
+    sum = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
+    float L = NEG_INF, sc = 0.f;
+    if (mx > NEG_INF) {
+        const float old = L_old > NEG_INF ? __expf(L_old - mx) : 0.f;
+        L = mx + __logf(sum + old);
+        sc = L_old > NEG_INF ? __expf(L_old - L) : 0.f;
+    }
+    if (blockIdx.y == 0 && tid == 0)
+        out_lse[s] = L;
+
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (long c0 = u0; c0 < u1; c0 += JOIN_FACTORS) {
+        const long c1 = min(c0 + JOIN_FACTORS, u1);
+        __syncthreads();
+        for (long u = c0 + tid; u < c1; u += 256)
+            factor[u - c0] = __expf(unit_stats[u].x - L);
+        __syncthreads();
+        if (k < d)
+            r = join_units<POOL_WEIGHTED>(partial, c0, c1, d, k, r, factor);
+    }
+    r = join_waves<POOL_WEIGHTED>(r, waves);
+    if (threadIdx.x < 64 && k < d) {
         if (state_pooled && sc != 0.f) {
             const float4 old = *(const float4 *)(state_pooled + (long)s * d + k);
-            sum.x = fmaf(old.x, sc, sum.x), sum.y = fmaf(old.y, sc, sum.y);
-            sum.z = fmaf(old.z, sc, sum.z), sum.w = fmaf(old.w, sc, sum.w);
+            r.x = fmaf(old.x, sc, r.x), r.y = fmaf(old.y, sc, r.y);
+            r.z = fmaf(old.z, sc, r.z), r.w = fmaf(old.w, sc, r.w);
         }
-        *(float4 *)(out_pooled + (long)s * d + k) = sum;
+        *(float4 *)(out_pooled + (long)s * d + k) = r;
     }
-    if (blockIdx.y == 0 && threadIdx.x == 0)
-        out_lse[s] = lse_new[b];
 }
 
 // ---- Eq. 8 fast path: exactly one new token per sequence ------------------------------------
@@ -427,6 +495,13 @@ __global__ __launch_bounds__(256) void pool_last_kernel(const void *__restrict__
 
 }  // namespace
 
+// Tokens per unit: 256, halved while a batch makes fewer than POOL_WORKGROUPS workgroups and the smaller units'
+// partials fit `cap_floats`.  A workgroup walks its unit's rows eight at a time, one memory latency each: 173 tokens,
+// d = 4096 in units of 128 are 6 workgroups of 16 latencies (14 us), in units of 16 25 of two (7 us).  Large units
+// leave fewer partials to write and join: average pooling of 137720 tokens takes 219 us with 256, 222 with 128, 233
+// with 64; of 10689 tokens, d = 2048, 30.3 us where 256 workgroups are asked for, 32.6 with 512 or 1024.
+constexpr int POOL_UNIT_MIN = 16, POOL_WORKGROUPS = 256;
+
 // workgroups a unit's features are spread over: one 16-byte chunk per thread
 static unsigned pool_feature_split(int d, bool bf16)
 {
@@ -435,9 +510,19 @@ static unsigned pool_feature_split(int d, bool bf16)
     return (unsigned)(n < 1 ? 1 : (n > 64 ? 64 : n));
 }
 
+int pool_unit(int dtype, int d, int64_t T, int32_t B, size_t cap_floats)
+{
+    int unit = POOL_UNIT;
+    const int64_t ysplit = pool_feature_split(d, dtype == DT_BF16);
+    while (unit > POOL_UNIT_MIN && (T / unit) * ysplit < POOL_WORKGROUPS &&
+           pool_unit_floats(d, T, B, unit / 2) <= cap_floats)
+        unit /= 2;
+    return unit;
+}
+
 hipError_t scan_lengths(const int32_t *lengths, int32_t B, int32_t *offsets, hipStream_t st)
 {
-    hipLaunchKernelGGL(scan_kernel<false>, dim3(1), dim3(256), 0, st, lengths, B, offsets);
+    hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(256), 0, st, lengths, B, offsets);
     return hipGetLastError();
 }
 
@@ -464,29 +549,28 @@ hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st)
                                a.k1_part, a.k1_nsplit, (long)a.T, a.slot, a.inv_alpha, a.out_pooled, a.out_lse);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(256), 0, st, a.offsets, a.B, a.unit_start);
-    hipLaunchKernelGGL(pool_lse_kernel, dim3(a.B), dim3(256), 0, st, a.entropy, a.offsets, (long)a.T, a.slot,
-                       a.inv_alpha, a.state_lse, a.lse_new, a.state_scale);
-    const long units = pool_units_bound(a.T, a.B);
-    if (units > 0x7fffffffL)
-        return hipErrorInvalidValue;
+    const long units = pool_units_bound(a.T, a.B, a.unit);
     const unsigned ysplit = pool_feature_split(a.d, bf16);
     if (units * ysplit > 0x7fffffffL)
         return hipErrorInvalidValue;
+    float2 *stats = (float2 *)a.unit_stats;
+    const int unit_log2 = __builtin_ctz(a.unit);
     if (bf16)
         hipLaunchKernelGGL((pool_partial_kernel<true, POOL_WEIGHTED>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, a.hidden,
-                           a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, a.lse_new, a.unit_start, (int)ysplit, a.partial);
+                           a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
+                           a.lse_old, a.partial, stats);
     else
         hipLaunchKernelGGL((pool_partial_kernel<false, POOL_WEIGHTED>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, a.hidden,
-                           a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, a.lse_new, a.unit_start, (int)ysplit, a.partial);
-    hipLaunchKernelGGL(pool_finalize_kernel, dim3(a.B, (a.d + 1023) / 1024), dim3(256), 0, st, a.partial,
-                       a.unit_start, a.slot, a.d, (int)units, a.state_pooled, a.state_scale, a.lse_new, a.out_pooled,
+                           a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
+                           a.lse_old, a.partial, stats);
+    hipLaunchKernelGGL(pool_finalize_kernel, dim3(a.B, (a.d + JOIN_COLS - 1) / JOIN_COLS), dim3(256), 0, st, a.partial, stats, a.offsets,
+                       a.slot, a.d, unit_log2, units, a.state_pooled, a.state_lse ? a.lse_old : nullptr, a.out_pooled,
                        a.out_lse);
     return hipGetLastError();
 }
 
 hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offsets, int32_t B, int64_t T,
-                      int kind, int32_t *unit_start, float *partial, float *out_pooled, hipStream_t st)
+                      int kind, int unit, float *partial, float *out_pooled, hipStream_t st)
 {
     if (B <= 0)
         return hipSuccess;
@@ -502,21 +586,20 @@ hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offse
                                out_pooled);
         return hipGetLastError();
     }
-    // average and maximum stream every token once: same units of <= POOL_UNIT tokens as Eq. 4
-    const long units = pool_units_bound(T, B);
-    if (units > 0x7fffffffL)
-        return hipErrorInvalidValue;
+    // average and maximum stream every token once: same units as Eq. 4
+    const long units = pool_units_bound(T, B, unit);
+    const int unit_log2 = __builtin_ctz(unit);
+    const dim3 fgrid(B, (d + JOIN_COLS - 1) / JOIN_COLS);
     const unsigned ysplit = pool_feature_split(d, bf16);
     if (units * ysplit > 0x7fffffffL)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(256), 0, st, offsets, B, unit_start);
-    const dim3 fgrid(B, (d + 1023) / 1024);
 #define EGTP_POOL_PLAIN(BF, MODE)                                                                          \
     do {                                                                                                   \
         hipLaunchKernelGGL((pool_partial_kernel<BF, MODE>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, hidden, \
-                           d, nullptr, offsets, B, (long)T, 0.f, nullptr, unit_start, (int)ysplit, partial); \
-        hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, unit_start, \
-                           offsets, d, (int)units, out_pooled);                                            \
+                           d, nullptr, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
+                           partial, nullptr);                                                              \
+        hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, offsets, d,  \
+                           unit_log2, units, out_pooled);                                                  \
     } while (0)
     if (kind == 0) {
         if (bf16)

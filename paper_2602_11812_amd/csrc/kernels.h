@@ -70,10 +70,17 @@ hipError_t k1_merge(const float *part, int nsplit, int64_t T, float *entropy, hi
 hipError_t scan_lengths(const int32_t *lengths, int32_t B, int32_t *offsets, hipStream_t st);
 hipError_t segment_ids(const int32_t *offsets, int32_t B, int64_t T, int32_t *seg, hipStream_t st);
 
-// Eq. 3 / Eq. 4 / Eq. 8 over ragged offsets.  A sequence is cut into units of at most
-// POOL_UNIT tokens; unit_start[B+1] is the exclusive scan of units per sequence.
-constexpr int POOL_UNIT = 128;
-inline int64_t pool_units_bound(int64_t T, int32_t B) { return (T + POOL_UNIT - 1) / POOL_UNIT + B; }
+// Eq. 3 / Eq. 4 / Eq. 8 over ragged offsets.  A sequence is cut into units of at most `unit` tokens
+// (POOL_UNIT, or less in a small batch); sequence b's units are numbered from offsets[b] / unit + b on.
+constexpr int POOL_UNIT = 256;
+inline int64_t pool_units_bound(int64_t T, int32_t B, int unit) { return T / unit + B; }
+// floats a pooling call keeps per unit: a partial row and two statistics
+inline size_t pool_unit_floats(int d, int64_t T, int32_t B, int unit)
+{
+    return (size_t)pool_units_bound(T, B, unit) * ((size_t)d + 2);
+}
+// the unit for a batch; units below POOL_UNIT are only chosen if pool_unit_floats of them is at most cap_floats
+int pool_unit(int dtype, int d, int64_t T, int32_t B, size_t cap_floats);
 
 struct PoolArgs {
     const void *hidden;       // [T x d]
@@ -92,17 +99,17 @@ struct PoolArgs {
     float *out_pooled;        // [S x d] (may alias state_pooled)
     float *out_lse;           // [S]     (may alias state_lse)
     // workspace
-    int32_t *unit_start;      // [B+1]
-    float *lse_new;           // [B]
-    float *state_scale;       // [B]
+    int unit;                 // tokens per unit, a power of two (ragged offsets only)
     float *partial;           // [units_bound x d]
+    float *unit_stats;        // [units_bound x 2], 8-byte aligned
+    float *lse_old;           // [B], with a state: its log-sum-exps as they were
 };
 hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st);
 
-// Table 3 alternatives: kind 0 average, 1 max, 2 last token.  Average and max use the unit table
-// (unit_start[B+1]) and the unit partials ([pool_units_bound(T, B) x d]) of the weighted pooling.
+// Table 3 alternatives: kind 0 average, 1 max, 2 last token.  Average and max use units and partials
+// ([pool_units_bound(T, B, unit) x d]) like the weighted pooling.
 hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offsets, int32_t B, int64_t T,
-                      int kind, int32_t *unit_start, float *partial, float *out_pooled, hipStream_t st);
+                      int kind, int unit, float *partial, float *out_pooled, hipStream_t st);
 
 // Prediction head.
 struct HeadArgs {

@@ -1,0 +1,84 @@
+"""Ragged pooling cuts sequences into units of 16 to 256 tokens whose numbers follow from the offsets alone: lengths
+around every unit size, empty sequences at both ends and in rows, more sequences than are looked through at once,
+with and without an old state read and replaced through slots.  References in fp64 from the library's own entropies
+(which other tests hold to the oracle): pooled 1e-5 relative L2, fp32 sums of at most a thousand terms with weights
+accurate to a few 2^-24; lse 1e-5 absolute at |lse| < 20."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2602_11812_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+RAGGED = {
+    "one": (1,),
+    "unit edges": (15, 16, 17, 0, 31, 32, 33, 63, 64, 65),
+    "large unit edges": (127, 128, 129, 0, 0, 255, 256, 257, 1, 511, 513),
+    "long": (9000, 3),
+    "empty ends": (0, 0, 5, 0, 200, 0),
+    "many": tuple([1, 0, 2] * 700),
+    "very many": tuple([0, 1, 3, 0] * 600),
+}
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 2056), ("bf16", 64), ("f32", 1028)])
+@pytest.mark.parametrize("name", list(RAGGED))
+def test_units_of_ragged_batches(name, dtype, d):
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    lens = RAGGED[name]
+    B, T = len(lens), sum(lens)
+    w = wl.make(wl.scaled(wl.SPECS["mid" if dtype == "bf16" else "tiny"], seed=9000 + B, B=B, d=d, V=40, d_h=8, lengths=lens))
+    td = gpu.to_device
+    sc = gpu.Scorer(td(w.w_lm), gpu.make_head(td(w.w1), td(w.w2)))
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    off_dev = td(off.astype(np.int32))
+    hidden = td(w.hidden)
+    h = hidden.cpu().double().numpy()
+    ws = sc.workspace(T, B)
+
+    ws.fill_(255)
+    out = {k: v.cpu().numpy().astype(np.float64) for k, v in sc.score(hidden, off_dev).items()}
+    H = out["entropy"]
+    rng = np.random.default_rng(B)
+    S = B + 5
+    slot = rng.permutation(S)[:B].astype(np.int32)
+    old_p, old_l = rng.standard_normal((S, d)).astype(np.float32), rng.uniform(1.0, 6.0, S).astype(np.float32)
+    old_l[slot[::3]] = -math.inf                                  # some states are empty
+    new_p, new_l = td(old_p.copy()), td(old_l.copy())
+    ws.fill_(255)
+    sc.step(hidden, new_p, new_l, offsets_new_dev=off_dev, slot_dev=td(slot))
+    new_p, new_l = new_p.cpu().numpy().astype(np.float64), new_l.cpu().numpy().astype(np.float64)
+
+    def fold(b, p_old, l_old):
+        a = H[off[b]:off[b + 1]]
+        terms = np.append(a, l_old)
+        if not np.isfinite(terms.max()):
+            return np.zeros(d), -math.inf
+        m = terms.max()
+        lse = m + math.log(np.exp(terms - m).sum())
+        return np.exp(a - lse) @ h[off[b]:off[b + 1]] + (np.exp(l_old - lse) * p_old if l_old > -math.inf else 0.0), lse
+
+    for b in range(B):
+        for got_p, got_l, (p, l) in ((out["pooled"][b], out["lse"][b], fold(b, 0.0, -math.inf)),
+                                     (new_p[slot[b]], new_l[slot[b]], fold(b, old_p[slot[b]].astype(np.float64),
+                                                                           float(old_l[slot[b]])))):
+            if l == -math.inf:
+                assert got_l == -math.inf and not got_p.any()
+            else:
+                assert abs(got_l - l) <= 1e-5 and np.linalg.norm(got_p - p) <= 1e-5 * np.linalg.norm(p), (name, b)
+    rest = np.setdiff1d(np.arange(S), slot)
+    assert np.array_equal(new_p[rest], old_p[rest].astype(np.float64)) and np.array_equal(new_l[rest], old_l[rest])
+
+    for kind, want in ((gpu.EGTP_POOL_AVERAGE, lambda x: x.mean(axis=0)), (gpu.EGTP_POOL_MAX, lambda x: x.max(axis=0)),
+                       (gpu.EGTP_POOL_LAST, lambda x: x[-1])):
+        ws.fill_(255)
+        got = sc.pool_ablation(hidden, off_dev, kind)[0].cpu().numpy().astype(np.float64)
+        for b in range(B):
+            x = h[off[b]:off[b + 1]]
+            p = want(x) if len(x) else np.zeros(d)
+            tol = 1e-5 * np.sqrt(np.mean(x * x)) if kind == gpu.EGTP_POOL_AVERAGE and len(x) else 0.0
+            assert np.abs(got[b] - p).max() <= tol, (name, b, kind)
+    sc.close()
