@@ -155,6 +155,8 @@ egtp_status run_entropy(egtp_ctx *ctx, const void *hidden, int64_t T, const Work
     const int K = (int)k1_contraction_len(c.dtype, c.d);
     if (p.tile_v == K1_NARROW_TILE_V)
         EGTP_HIP(k1_entropy_narrow(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, st));
+    else if (p.tile_v == K1_STREAM_TILE_V)
+        EGTP_HIP(k1_entropy_stream(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
     else
         EGTP_HIP(k1_entropy_bf16(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
     if (timed) {

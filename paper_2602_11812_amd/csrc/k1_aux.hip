@@ -179,7 +179,22 @@ __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *_
     }
 }
 
+__global__ void k1_pace_zero_kernel(int *__restrict__ pace, int n)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n)
+        pace[i] = 0;
+}
+
 }  // namespace
+
+// pacing counters, cleared by a kernel (a caller may be capturing a graph)
+hipError_t k1_clear_pace(int *pace, long count, hipStream_t st)
+{
+    const int n = (int)count;
+    hipLaunchKernelGGL(k1_pace_zero_kernel, dim3((n + 255) / 256), dim3(256), 0, st, pace, n);
+    return hipGetLastError();
+}
 
 hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, int tile_rows, void *dst,
                                   hipStream_t st)

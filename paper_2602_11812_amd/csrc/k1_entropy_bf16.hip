@@ -51,20 +51,9 @@ constexpr int STAGE_BYTES = 2 * TILE_BYTES;  // W block + hidden block
 constexpr int NPASS = TILE_BYTES / 4096;     // 16-byte loads per lane and operand block (4)
 constexpr int LOADS_PER_STEP = 2 * NPASS;
 constexpr int TB_GROUP = 8;    // token blocks that sweep the same vocabulary range together
-constexpr int XCDS = 8;            // workgroup i is placed on XCD i % 8
-constexpr int COHORT = 32;         // workgroups one XCD runs at a time (its compute units)
 constexpr int PACE_TILES = K1_PACE_TILES;  // vocabulary tiles between two pacing points
-constexpr int PACE_SPINS = 24;     // bound of one wait: polls of the counter ...
-constexpr int PACE_SLEEP = 4;      // ... each followed by a sleep of 64 * PACE_SLEEP cycles
 // scheduling-group masks of the AMDGPU backend
 constexpr int SG_MFMA = 0x008, SG_VMEM_READ = 0x020, SG_DS_READ = 0x100;
-
-__global__ void k1_pace_zero_kernel(int *__restrict__ pace, int n)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n)
-        pace[i] = 0;
-}
 
 template <int NSTAGE>
 __global__ __launch_bounds__(256, 1) void k1_entropy_bf16_kernel(
@@ -395,13 +384,10 @@ hipError_t k1_entropy_bf16(const void *hidden_packed, const void *w_packed, int6
     const int kt = k_steps(K);
     if ((long)kt * TILE_BYTES > 0x7fffffffL)
         return hipErrorInvalidValue;  // a row tile over all of K is addressed with 32-bit byte offsets
-    // pacing counters: one per cohort, cleared by a kernel (a caller may be capturing a graph)
     if (!k1_plan_paces(p))
         pace = nullptr;  // no pacing point inside a range
-    if (pace != nullptr) {
-        const int n = XCDS * k1_pace_cohorts(units);
-        hipLaunchKernelGGL(k1_pace_zero_kernel, dim3((n + 255) / 256), dim3(256), 0, st, pace, n);
-    }
+    if (pace != nullptr && (ea = k1_clear_pace(pace, 8 * k1_pace_cohorts(units), st)) != hipSuccess)
+        return ea;
     hipLaunchKernelGGL((k1_entropy_bf16_kernel<NSTAGE>), dim3((unsigned)units), dim3(256), LDS_BYTES, st,
                        (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V,
                        p.ntb, p.nsplit, p.tiles_per_split, p.ntiles_v, part, pace);

@@ -3,7 +3,7 @@
 // kernel; what differs is the tile and what bounds it.
 //
 // A few tokens make the sweep a stream over W_lm, and a 256-token tile pays for its empty columns in matrix-core
-// time and in power.  Here a token block is 32 NI tokens (NI = 2, 4, 6, 8), a vocabulary tile 128 rows (half a
+// time and in power.  Here a token block is 32 NI tokens (NI = 2 or 6), a vocabulary tile 128 rows (half a
 // packed block: 8 contiguous KiB per K step), so that a step's MFMAs (8 NI per wave) hide under the step's share
 // of the memory stream and the vocabulary divides more evenly over the compute units.  The LDS ring is as deep as
 // the LDS allows: what it holds in flight per compute unit sets the rate of the stream.
@@ -14,8 +14,8 @@
 // their MFMAs into two register sets that swap roles (the loop is unrolled by two, K is an even number of steps).
 //
 // Measured: 64 tokens against V = 151936, d = 4096: 199 us = 6.3 TB/s of W_lm (the 256 x 256 tile: 286 us on 198 of the
-// 256 compute units); 128 tokens 225, 192 tokens 261 (LDS: fill plus fragment reads of 20 KiB steps), 256 tokens 320,
-// where the wide tile's 280 is better.  309 fp32 tokens against V = 4096, d = 256: 15.4 us, 37.1 before.
+// 256 compute units); 192 tokens 261 (LDS: fill plus fragment reads of 20 KiB steps) against 280; 309 fp32 tokens
+// against V = 4096, d = 256: 15.4 us, 37.1 before.  Two K steps per barrier gain nothing at NI = 2 and cost 20 % at 6.
 #include "k1_stream.h"
 
 namespace egtp {
@@ -31,7 +31,7 @@ struct Ring {
     static constexpr int H_STEP_BYTES = 32 * NI * ROW_BYTES;
     static constexpr int STAGE_BYTES = W_STEP_BYTES + H_STEP_BYTES;
     static constexpr int LOADS = STAGE_BYTES / 4096;             // 16-byte loads per lane and step
-    static constexpr int STAGES = 144 * 1024 / STAGE_BYTES;      // 12, 9, 7, 6 stages for NI = 2, 4, 6, 8
+    static constexpr int STAGES = 144 * 1024 / STAGE_BYTES;      // 12 and 7 stages for NI = 2 and 6
     static constexpr int BYTES = STAGES * STAGE_BYTES;
     static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "ring depth");
 };
@@ -269,9 +269,7 @@ hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, in
             : launch<NI, false>(hidden_packed, w_packed, T, kt, V, p, part, st))
     switch (p.tb_tokens) {
     case 64: return EGTP_NARROW(2);
-    case 128: return EGTP_NARROW(4);
     case 192: return EGTP_NARROW(6);
-    case 256: return EGTP_NARROW(8);
     }
 #undef EGTP_NARROW
     return hipErrorInvalidValue;

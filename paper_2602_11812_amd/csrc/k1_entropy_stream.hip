@@ -1,0 +1,376 @@
+// Fused LM-head contraction + streaming entropy (Eq. 2), W_lm loaded straight into registers: for the largest batches
+// and for those between the other two kernels.  Same formulation, packed W_lm and partial triples as theirs; what
+// differs is the way of W_lm to the matrix cores.
+//
+// A token block is 128 tokens and a wave works alone on its rows of W_lm: a 16-row fragment of a packed block is one
+// contiguous KiB in exactly the order the MFMA wants, so the wave loads it straight into registers (two K steps
+// ahead) and it never passes through the LDS.  Only the hidden states do, 8 KiB per K step shared by the four
+// waves -- per product less than half the LDS traffic of a tile that stages both operands.  Rows are dealt
+// to waves in single fragments: a wave sweeps eight of them at a time (8 x 8 MFMA 16x16x32 tiles, 128 rows x 128
+// tokens) and the remainder in a shorter sweep of two, four or six, so the vocabulary divides
+// evenly over the compute units whatever its size.
+//
+// Bound: bf16 MFMA at the package power limit for large batches, the read of W_lm for one token block.  Measured
+// against the 256 x 256 tile, same box: 137720 tokens, d = 4096, V = 151936 118.6 -> 114.7 ms = 1.49 PFLOP/s; 65088
+// tokens, d = 5120 70.5 -> 64.7 = 1.56 PFLOP/s; 4000 tokens 3.57 -> 3.37; 384 tokens 447 -> 378 us; 128 tokens 280 ->
+// 199 us.  No faster: the barrier in the middle of a step (3 % slower), other spacings of the loads, four or eight ring
+// stages, a pacing point every sweep or every fourth.
+//
+// Pacing is that of the 256 x 256 kernel: cohorts of 32 workgroups that share blocks in an XCD's L2 count themselves in
+// every second sweep and wait, bounded, for the rest; a hint that no result depends on.
+#include <type_traits>
+
+#include "k1_stream.h"
+
+namespace egtp {
+namespace {
+
+constexpr int BN = K1_STREAM_TOKENS;            // tokens per block
+constexpr int H_STEP_BYTES = BN * ROW_BYTES;    // 8 KiB
+constexpr int FRAG_BYTES = 16 * ROW_BYTES;      // 16 rows of one K step
+
+constexpr int H_LOADS = H_STEP_BYTES / 4096;    // 16-byte loads per lane and step
+constexpr int NI = BN / 16;                     // token fragments
+constexpr int MAX_MI = 8;                       // vocabulary fragments of a wave's longest sweep
+constexpr int H_STAGES = 6;
+constexpr int PACE_SWEEPS = K1_STREAM_PACE_TILES / MAX_MI;  // sweeps between two pacing points
+static_assert(K1_STREAM_TILE_V == 64, "a tile is one fragment for each of the four waves");
+
+template <bool STREAM_W>
+__device__ __forceinline__ bf16x8 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int lane_byte_offset, int scalar_byte_offset)
+{
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_byte_offset, scalar_byte_offset,
+                                                                           STREAM_W ? 2 : 0));
+}
+
+template <bool STREAM_W>
+__global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigned char *__restrict__ Wp,
+                                                                   const unsigned char *__restrict__ Hp, long T, int KT,
+                                                                   int V, int ntb, int nsplit, int tps, int ntiles_v, int group, bool whole_cohorts,
+                                                                   float *__restrict__ part, int *__restrict__ pace)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // Which (token block, vocabulary range) this workgroup owns.  Workgroup i runs on XCD i % 8, 32 of an XCD's at a
+    // time (a cohort).
+    int tb, sp;
+    int *pace_cnt = nullptr;  // this workgroup's cohort counter (thread 0 only)
+    int pace_members = 0;
+    {
+        const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
+        if (whole_cohorts) {
+            // A cohort is `group` token blocks x 32 / group ranges, so that its blocks of both operands are shared
+            // in the XCD's L2; an XCD gets whole cohorts, and a place without a unit is left empty.  (Cut
+            // anywhere, cohorts of half the blocks of one group and half of the next read a third more.)
+            const int ranges = COHORT / group;
+            const int per_group = (nsplit + ranges - 1) / ranges;
+            const int cohorts = (ntb + group - 1) / group * per_group;
+            const int c = (int)((long)x * cohorts / 8) + j / COHORT;
+            const int g = c / per_group, r = j % COHORT;
+            tb = g * group + r % group;
+            sp = (c - g * per_group) * ranges + r / group;
+            if (c >= (int)((long)(x + 1) * cohorts / 8) || tb >= ntb || sp >= nsplit)
+                return;
+            if (pace != nullptr && tid == 0) {
+                pace_cnt = pace + c;
+                pace_members = min(group, ntb - g * group) * min(ranges, nsplit - (c - g * per_group) * ranges);
+            }
+        } else {
+            // each XCD gets a contiguous range of units, token blocks varying fastest
+            const int units = ntb * nsplit;
+            const int q = units >> 3, r = units & 7;
+            if (pace != nullptr && tid == 0) {
+                const int cohort = j / COHORT;
+                pace_cnt = pace + x * k1_pace_cohorts(units) + cohort;
+                pace_members = min(COHORT, q + (x < r ? 1 : 0) - cohort * COHORT);
+            }
+            const int logical = x * q + (x < r ? x : r) + j;
+            const int per_group = group * nsplit;
+            const int g = logical / per_group;
+            const int rem = logical - g * per_group;
+            const int gsize = min(group, ntb - g * group);
+            sp = rem / gsize;
+            tb = g * group + (rem - sp * gsize);
+        }
+        sp = __builtin_amdgcn_readfirstlane(sp);
+        tb = __builtin_amdgcn_readfirstlane(tb);
+    }
+    // this range's tiles = so many fragments for each wave
+    const int vt_begin = sp * tps;
+    const int count = min(tps, ntiles_v - vt_begin);
+    const int f_begin = 4 * vt_begin + wave * count, f_end = f_begin + count;
+    const long tok0 = (long)tb * BN;
+    const int row_end = min(V, f_end * 16);
+
+    // ---- W_lm: the fragments of a sweep, by scalar offsets from the packed block its first one lies in
+    const int l15 = lane & 15;
+    const int kq = lane >> 4;
+    const int lane_w = l15 * ROW_BYTES + ((kq ^ swizzle_key(l15)) << 4);
+    const int w_tile_bytes = KT * TILE_BYTES;  // (the launcher checks that two of them can be addressed)
+    __amdgpu_buffer_rsrc_t rW;
+    int frag_off[MAX_MI];
+    auto set_rows = [&](int f0) {  // past the end: the last fragment, loaded and not used
+        const int first = min(f0, f_end - 1);
+        const int blk = __builtin_amdgcn_readfirstlane(first >> 4);
+        const int blocks = __builtin_amdgcn_readfirstlane(((f_end - 1) >> 4) - blk > 0 ? 2 : 1);
+        rW = raw_buffer(Wp + (long)blk * w_tile_bytes, blocks * w_tile_bytes);
+#pragma unroll
+        for (int m = 0; m < MAX_MI; ++m) {
+            const int f = min(f0 + m, f_end - 1);
+            frag_off[m] = __builtin_amdgcn_readfirstlane(((f >> 4) - blk) * w_tile_bytes + (f & 15) * FRAG_BYTES);
+        }
+    };
+    bf16x8 wr[2][MAX_MI];  // even and odd K steps, two steps ahead
+
+    // ---- hidden states: memory -> LDS ring, copied linearly, 1 KiB per wave-wide load; the same block sweep after sweep
+    const int lane_h = wave * 1024 + lane * 16;
+    const int h_tile_bytes = KT * H_STEP_BYTES;
+    const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
+    int hkt = 0;
+    auto load_h = [&](int stage) {
+        unsigned char *dst = smem + stage * H_STEP_BYTES + wave * 1024;
+#pragma unroll
+        for (int p = 0; p < H_LOADS; ++p)
+            load16_to_lds(rH, lane_h, hkt * H_STEP_BYTES + p * 4096, dst + p * 4096);
+        hkt = hkt + 1 == KT ? 0 : hkt + 1;
+    };
+    const unsigned frag_h = (unsigned)lane_w;
+    bf16x8 fb[2][NI];
+
+    Stats st[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        st[ni].m = NEG_BIG;
+        st[ni].S = 0.f;
+        st[ni].U = 0.f;
+    }
+
+    set_rows(f_begin);
+#pragma unroll
+    for (int s = 0; s < H_STAGES; ++s)
+        load_h(s);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int m = 0; m < MAX_MI; ++m)
+            wr[s][m] = load_fragment<STREAM_W>(rW, lane_w, s * TILE_BYTES + frag_off[m]);
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+        fb[0][ni] = *(const bf16x8 *)(smem + frag_h + ni * FRAG_BYTES);
+    int cstage = 0;  // stage of the step whose MFMAs are next
+
+    // All K steps of MI fragments from f0 on, then the fold of their logits.  Before its last two steps the loads
+    // move on to the fragments of the next sweep.
+    auto sweep = [&](auto mi_const, int f0, bool masked) {
+        constexpr int MI = decltype(mi_const)::value;
+        f32x4 acc[MI][NI];
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+                acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+        // One step of parity P.  The barrier: every wave's loads of the next step's hidden states have landed (the
+        // newest H_STAGES - 2 steps' loads may be in flight; a step issues at least H_LOADS + MI of them) and every wave's
+        // fragment reads of the current step have returned, so its stage can be loaded again.
+        auto step = [&](auto p_const, int kt_load) {
+            constexpr int P = decltype(p_const)::value;
+            wait_vmcnt<(H_STAGES - 2) * (H_LOADS + MI)>();
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            const int nstage = cstage + 1 == H_STAGES ? 0 : cstage + 1;
+            const unsigned char *s = smem + nstage * H_STEP_BYTES + frag_h;
+            // The order is pinned row by row: the fragment reads behind the first row's MFMAs, then in every row the
+            // load of the row before it (whose registers are free by then), the hidden states' loads in rows 0 and 1.
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) {
+                if (mi == 0) {
+#pragma unroll
+                    for (int ni = 0; ni < NI; ++ni)
+                        fb[P ^ 1][ni] = *(const bf16x8 *)(s + ni * FRAG_BYTES);
+                } else {
+                    wr[P][mi - 1] = load_fragment<STREAM_W>(rW, lane_w, kt_load * TILE_BYTES + frag_off[mi - 1]);
+                }
+                if (mi == 1)
+                    load_h(cstage);
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[P][mi], fb[P][ni], acc[mi][ni], 0, 0, 0);
+                if (mi == 0) {
+#pragma unroll
+                    for (int j = 0; j < NI; ++j) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < (mi == 1 ? 1 + H_LOADS : 1); ++j) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x008, NI, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            wr[P][MI - 1] = load_fragment<STREAM_W>(rW, lane_w, kt_load * TILE_BYTES + frag_off[MI - 1]);
+            cstage = nstage;
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const std::integral_constant<int, 0> even{};
+        const std::integral_constant<int, 1> odd{};
+        for (int kt = 2; kt < KT; kt += 2) {
+            step(even, kt);
+            step(odd, kt + 1);
+        }
+        set_rows(f0 + MI);
+        step(even, 0);
+        step(odd, 1);
+
+        const int row0 = f0 * 16 + 4 * kq;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+            for (int h = 0; h < MI; h += 4) {
+                constexpr int N = 16;
+                float z[N];
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        z[4 * q + i] = h + q < MI ? acc[h + q < MI ? h + q : 0][ni][i] : NEG_BIG;
+                if (masked || MI % 4 != 0)
+                    fold16<true>(z, st[ni], row0 + h * 16, h + 4 > MI ? min(row_end, (f0 + MI) * 16) : row_end);
+                else
+                    fold16<false>(z, st[ni], row0 + h * 16, V);
+            }
+        }
+    };
+    const int max_sweeps = (tps + MAX_MI - 1) / MAX_MI;
+    int sweeps = 0;
+    for (int f = f_begin; f < f_end;) {
+        const int rest = f_end - f;
+        // pacing point: the other waves wait for this thread at the next step's barrier
+        const bool pace_now = pace_cnt != nullptr && sweeps != 0 && sweeps % PACE_SWEEPS == 0;
+        if (pace_now) {
+            const int want = pace_members * (sweeps / PACE_SWEEPS);
+            __hip_atomic_fetch_add(pace_cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            bool met = false;
+            for (int spin = 0; spin < PACE_SPINS && !met; ++spin) {
+                met = __hip_atomic_load(pace_cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= want;
+                if (!met)
+                    __builtin_amdgcn_s_sleep(PACE_SLEEP);
+            }
+            if (!met) {
+                // the cohort is not running together: count in for every later point and stop
+                const int later = (max_sweeps - 1) / PACE_SWEEPS - sweeps / PACE_SWEEPS;
+                if (later > 0)
+                    __hip_atomic_fetch_add(pace_cnt, later, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                pace_cnt = nullptr;
+            }
+        }
+        ++sweeps;
+        if (rest > 4) {
+            sweep(std::integral_constant<int, 8>{}, f, rest < 8 || (f + 8) * 16 > V);
+            f += 8;
+        } else if (rest > 2) {
+            sweep(std::integral_constant<int, 4>{}, f, rest < 4 || (f + 4) * 16 > V);
+            f += 4;
+        } else {
+            sweep(std::integral_constant<int, 2>{}, f, true);
+            f += 2;
+        }
+    }
+    if (pace_cnt != nullptr) {
+        // a range with fewer sweeps than the others leaves early: count in for the points it skips
+        const int skipped = (max_sweeps - 1) / PACE_SWEEPS - (sweeps - 1) / PACE_SWEEPS;
+        if (skipped > 0)
+            __hip_atomic_fetch_add(pace_cnt, skipped, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    wait_vmcnt<0>();
+    __syncthreads();
+
+    // ---- combine the four lanes, then the four waves, that hold the same token
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            Stats o;
+            o.m = __shfl_xor(st[ni].m, off);
+            o.S = __shfl_xor(st[ni].S, off);
+            o.U = __shfl_xor(st[ni].U, off);
+            st[ni] = merge(st[ni], o);
+        }
+    }
+    float *red = (float *)smem;  // [wave][token][3]
+    if (lane < 16) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            float *r = red + (wave * BN + ni * 16 + lane) * 3;
+            r[0] = st[ni].m;
+            r[1] = st[ni].S;
+            r[2] = st[ni].U;
+        }
+    }
+    __syncthreads();
+    if (tid < BN && tok0 + tid < T) {
+        Stats a;
+        a.m = red[tid * 3], a.S = red[tid * 3 + 1], a.U = red[tid * 3 + 2];
+#pragma unroll
+        for (int k = 1; k < 4; ++k) {
+            const float *r = red + (k * BN + tid) * 3;
+            Stats o;
+            o.m = r[0], o.S = r[1], o.U = r[2];
+            a = merge(a, o);
+        }
+        const long plane = (long)nsplit * T, idx = (long)sp * T + tok0 + tid;
+        part[idx] = a.m;
+        part[plane + idx] = a.S;
+        part[2 * plane + idx] = a.U;
+    }
+}
+
+}  // namespace
+
+hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V, const K1Plan &p,
+                             float *part, int *pace, hipStream_t st)
+{
+    constexpr int LDS_BYTES = H_STAGES * H_STEP_BYTES;
+    static_assert(4 * BN * 3 * sizeof(float) <= LDS_BYTES && LDS_BYTES <= 64 * 1024, "LDS");
+    const int kt = k_steps(K);
+    if (T <= 0 || p.tb_tokens != BN || p.tile_v != K1_STREAM_TILE_V || p.nsplit < 1 || p.tiles_per_split < 1 ||
+        (long)p.nsplit * p.tiles_per_split < p.ntiles_v || (long)(p.nsplit - 1) * p.tiles_per_split >= p.ntiles_v ||
+        (long)p.ntb * p.nsplit > 0x7fffffffL || (int64_t)p.ntb * BN < T ||
+        p.ntiles_v != (V + K1_STREAM_TILE_V - 1) / K1_STREAM_TILE_V || 2L * kt * TILE_BYTES > 0x7fffffffL)
+        return hipErrorInvalidValue;
+    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * kt * 4 * FRAG_BYTES > ((int64_t)256 << 20);
+    const int group = k1_stream_group(p.nsplit);
+    const long units = (long)p.ntb * p.nsplit, cohorts = k1_stream_cohorts(p.ntb, p.nsplit);
+    const long wgs = p.whole_cohorts ? 8 * ((cohorts + 7) / 8) * COHORT : units;
+    if (wgs > 0x7fffffffL)
+        return hipErrorInvalidValue;
+    if (!k1_plan_paces(p))
+        pace = nullptr;
+    if (pace != nullptr) {
+        const hipError_t e = k1_clear_pace(pace, p.whole_cohorts ? cohorts : 8 * k1_pace_cohorts(units), st);
+        if (e != hipSuccess)
+            return e;
+    }
+    const dim3 grid((unsigned)wgs);
+    if (stream)
+        hipLaunchKernelGGL(k1_entropy_stream_kernel<true>, grid, dim3(256), LDS_BYTES, st,
+                           (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
+                           p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
+    else
+        hipLaunchKernelGGL(k1_entropy_stream_kernel<false>, grid, dim3(256), LDS_BYTES, st,
+                           (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
+                           p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
+    return hipGetLastError();
+}
+
+}  // namespace egtp

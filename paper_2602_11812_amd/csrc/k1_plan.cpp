@@ -2,6 +2,8 @@
 // vocabulary of V rows is cut into (token block, vocabulary range) workgroups.  Host code only.
 #include "k1_plan.h"
 
+#include <math.h>
+
 namespace egtp {
 
 // ---- geometry of the fused entropy kernel ------------------------------------------------
@@ -11,53 +13,123 @@ static constexpr int TB = 256, TV = 256, TARGET_UNITS = 8192;
 static constexpr int NUM_CUS = 256;
 static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number of ranges may go
 
-// ---- the kernel for few tokens -----------------------------------------------------------
-// Both kernels are priced in ns from what a K step of one workgroup was measured to take (d = 4096, V = 151936 and
-// d = 2048, V = 32000, every block size at T = 24 ... 1000, one workgroup per compute unit): 745 for the 256 x 256
-// tile, 115 + 48 NI for the 128-row tile over 32 NI tokens (its LDS fill and fragment reads, not its MFMAs), about
-// 3000 for a workgroup to fill its ring and to merge and store at the end -- and no sweep is faster than one read of
-// W_lm (5.7 TB/s).  The model picks the fastest measured variant at each of those sizes: T = 24, d = 4096,
-// V = 151936 takes 199 us on 64-token blocks, 225 on 128, 286 on the wide tile; T = 173 262 on 192 against 279;
-// T = 300 424 on the wide tile against 459 on 192; T = 309, V = 4096, d = 256 in fp32 15.4 on 64 against 37.1.
-static constexpr double WIDE_STEP_NS = 745.0, NARROW_STEP_NS = 115.0, NARROW_STEP_NS_PER_NI = 48.0;
+// ---- the other two kernels --------------------------------------------------------------
+// The three kernels are priced in ns from what one workgroup on its compute unit was measured to take, over T = 24 to
+// 137720 at d = 64 to 5120 and V = 4096 to 151936: per K step, per fold of a sweep's logits, and per workgroup (filling
+// the load ring, final merge and stores) -- and no plan is faster than one read of W_lm (5.7 TB/s).
+//   wide     256 rows x 256 tokens        625 a step for a W_lm of 48 MB, 18.5 more per doubling up to 712 for 1.2 GB;
+//            5000 a tile
+//   narrow   128 rows x 32 NI tokens      115 + 45.6 NI a step, 312 NI a tile
+//   stream   512 rows x 128 tokens        642 a step (+ 400 / token blocks: fewer of them share a read of W_lm), 6200
+//            a sweep; remainders of 4 and 2 fragments a wave 406 and 288, 3100 and 1550
+// The model picks the fastest measured plan or one within 2 % of it.  At d = 4096, V = 151936, in us:
+//   tokens   24   100   173   300   512   800  1217  4000  20000   45000
+//   wide    286   280   280   425   475   860  1088  3525  18170   40950
+//   narrow  199   223   253   491
+//   stream  198   199   289   367   495   793  1123  3320  17450   38900
+// (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964; at d = 256 the
+// folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
+static constexpr double WIDE_STEP_NS = 625.0, WIDE_STEP_NS_PER_DOUBLING = 18.5, WIDE_W_BYTES = 48e6, WIDE_FOLD_NS = 5000.0;
+static constexpr double NARROW_STEP_NS = 115.0, NARROW_STEP_NS_PER_NI = 45.6, NARROW_FOLD_NS_PER_NI = 312.0;
+static constexpr double STREAM_STEP_NS = 642.0, STREAM_ALONE_NS = 400.0, STREAM_FOLD_NS = 6200.0;
+static constexpr double STREAM_STEP4_NS = 406.0, STREAM_STEP2_NS = 288.0;
 static constexpr double WORKGROUP_NS = 3000.0, W_STREAM_BYTES_PER_NS = 5700.0;
+static constexpr long STREAM_MIN_STEPS = 8;  // below, folds are most of the work and the wide tile folds faster
+static constexpr double WORTH_IT = 0.955;  // another kernel than the wide one is worth this much of its price
+// Several rounds of the stream kernel, relative to one round or to whole cohorts of 16 token blocks x 2 ranges: cohorts
+// cut anywhere (65088 tokens, d = 5120, in 4 ranges 70.3 ms against 66.1; 137720, d = 4096, 122.7 against 116); whole
+// ones, per doubling of the ranges (64.6, 66.1, 67.1 ms in 2, 4, 8 ranges); all in one range (131072 tokens, d = 4096:
+// 119.0 ms against 109.3 in two).
+static constexpr double CUT_COHORTS = 1.05, MORE_RANGES = 0.017, ONE_RANGE = 1.09;
 
-static double sweep_ns(const K1Plan &p, long steps, double step_ns)
+// what a plan takes if a range of its takes range_ns
+static double plan_ns(const K1Plan &p, long steps, double range_ns)
 {
-    const long rounds = ((long)p.ntb * p.nsplit + NUM_CUS - 1) / NUM_CUS;
-    const double busy = (double)rounds * ((double)p.tiles_per_split * (double)steps * step_ns + WORKGROUP_NS);
-    const double stream = (double)p.ntiles_v * p.tile_v * (double)steps * 64.0 / W_STREAM_BYTES_PER_NS;
-    return (busy > stream ? busy : stream) + 0.1 * busy;  // of two that only wait for the stream, the lighter one
+    const long units = (long)p.ntb * p.nsplit;
+    const long rounds = p.whole_cohorts ? (k1_stream_cohorts(p.ntb, p.nsplit) + 7) / 8 : (units + NUM_CUS - 1) / NUM_CUS;
+    double busy = (double)rounds * (range_ns + WORKGROUP_NS);
+    if (p.tile_v == K1_STREAM_TILE_V) {
+        if (!p.whole_cohorts)
+            busy *= rounds > 1 ? CUT_COHORTS : 1.0;
+        else if (p.nsplit == 1)
+            busy *= ONE_RANGE;
+        else
+            for (int n = 4; n <= p.nsplit; n *= 2)
+                busy *= 1.0 + MORE_RANGES;
+    }
+    const double read = (double)p.ntiles_v * p.tile_v * (double)steps * 64.0 / W_STREAM_BYTES_PER_NS;
+    return (busy > read ? busy : read) + 0.1 * busy;  // of two that only wait for W_lm, the lighter one
 }
 
-// a narrow plan where that is cheaper than the wide plan p
-static K1Plan narrower(const K1Plan &p, int64_t T, int V, long steps)
+static double stream_range_ns(const K1Plan &p, long steps)
+{
+    const int full = p.tiles_per_split / 8, rest = p.tiles_per_split % 8;
+    const double step = STREAM_STEP_NS + STREAM_ALONE_NS / p.ntb;
+    double ns = (double)(full + (rest > 4 ? 1 : 0)) * ((double)steps * step + STREAM_FOLD_NS);
+    if (rest > 2 && rest <= 4)
+        ns += (double)steps * STREAM_STEP4_NS + STREAM_FOLD_NS / 2;
+    else if (rest > 0 && rest <= 2)
+        ns += (double)steps * STREAM_STEP2_NS + STREAM_FOLD_NS / 4;
+    return ns;
+}
+
+// the plan of another kernel where that is cheaper than the wide plan p
+static K1Plan cheaper(const K1Plan &p, int64_t T, int V, long steps)
 {
     if (V <= TV || T <= 0)
         return p;  // a vocabulary inside one tile: there is nothing to divide
     K1Plan best = p;
-    double best_ns = 0.97 * sweep_ns(p, steps, WIDE_STEP_NS);  // (a gain within the model's error is none)
-    for (int ni = 2; ni <= 8; ni += 2) {
-        K1Plan q;
-        q.tb_tokens = 32 * ni;
-        q.tile_v = K1_NARROW_TILE_V;
-        const int64_t ntb = (T + q.tb_tokens - 1) / q.tb_tokens;
-        if (ntb * q.tb_tokens > (int64_t)p.ntb * TB)
-            continue;  // more padding than the wide blocks (whose packed copy the workspace is sized for)
-        q.ntb = (int)ntb;
-        q.ntiles_v = (V + q.tile_v - 1) / q.tile_v;
+    const double w_bytes = (double)p.ntiles_v * TV * (double)steps * 64.0;
+    const double doublings = w_bytes > WIDE_W_BYTES ? log2(w_bytes / WIDE_W_BYTES) : 0.0;
+    const double wide_step = WIDE_STEP_NS + WIDE_STEP_NS_PER_DOUBLING * (doublings < 5.0 ? doublings : 5.0);
+    double best_ns = WORTH_IT * plan_ns(p, steps, p.tiles_per_split * ((double)steps * wide_step + WIDE_FOLD_NS));
+    // Workspace is sized for what wide plans need at most: packed hidden states, partial triples, pacing counters.
+    auto fits = [&](const K1Plan &q) {
+        return (int64_t)q.ntb * q.tb_tokens <= (int64_t)p.ntb * TB &&
+               (int64_t)q.nsplit * T <= ((int64_t)TARGET_UNITS + (1 + NSPLIT_SLACK) * (int64_t)p.ntb) * TB &&
+               (int64_t)q.nsplit * q.ntb <= (int64_t)TARGET_UNITS + (1 + NSPLIT_SLACK) * (int64_t)p.ntb &&
+               (!q.whole_cohorts || k1_stream_cohorts(q.ntb, q.nsplit) <= (long)k1_pace_ints_bound(T));
+    };
+    auto cut = [&](K1Plan &q, int tb_tokens, int tile_v, int64_t ranges) {
+        q.tb_tokens = tb_tokens;
+        q.tile_v = tile_v;
+        q.ntb = (int)((T + tb_tokens - 1) / tb_tokens);
+        q.ntiles_v = (V + tile_v - 1) / tile_v;
+        q.tiles_per_split = (int)((q.ntiles_v + ranges - 1) / ranges);
+        q.nsplit = (q.ntiles_v + q.tiles_per_split - 1) / q.tiles_per_split;
+    };
+    K1Plan q;
+    const int64_t blocks64 = (T + 63) / 64;
+    for (int ni = 2; ni <= 6 && blocks64 <= 32; ni += 4)
         for (int rounds = 1; rounds <= 3; ++rounds) {
-            const int64_t slots = (int64_t)rounds * NUM_CUS / ntb;
-            if (slots < 1)
+            const int64_t ranges = (int64_t)rounds * NUM_CUS * 32 * ni / (blocks64 * 64);
+            if (ranges < 1)
                 continue;
-            q.tiles_per_split = (int)((q.ntiles_v + slots - 1) / slots);
-            q.nsplit = (q.ntiles_v + q.tiles_per_split - 1) / q.tiles_per_split;
-            const double ns = sweep_ns(q, steps, NARROW_STEP_NS + NARROW_STEP_NS_PER_NI * ni);
-            if (ns < best_ns) {
+            cut(q, 32 * ni, K1_NARROW_TILE_V, ranges);
+            const double tile = (double)steps * (NARROW_STEP_NS + NARROW_STEP_NS_PER_NI * ni) + NARROW_FOLD_NS_PER_NI * ni;
+            const double ns = plan_ns(q, steps, q.tiles_per_split * tile);
+            if (ns < best_ns && fits(q)) {
                 best_ns = ns;
                 best = q;
             }
         }
+    // 1, 2, 3, ... long ranges and as many as make one to four rounds of workgroups; paced plans in whole cohorts, too
+    for (int i = 1; i <= 20 && steps >= STREAM_MIN_STEPS; ++i) {
+        const int64_t ntb = (T + K1_STREAM_TOKENS - 1) / K1_STREAM_TOKENS;
+        const int64_t ranges = i <= 16 ? i : (int64_t)(i - 16) * NUM_CUS / ntb;
+        if (ranges < 1 || (i > 16 && ranges <= 16))
+            continue;
+        cut(q, K1_STREAM_TOKENS, K1_STREAM_TILE_V, ranges);
+        for (int whole = 0; whole <= (k1_plan_paces(q) ? 1 : 0); ++whole) {
+            q.whole_cohorts = whole != 0;
+            const double ns = plan_ns(q, steps, stream_range_ns(q, steps));
+            // (among plans of this kernel, fewer rounds of workgroups unless more are clearly cheaper)
+            if (ns < (best.tile_v == K1_STREAM_TILE_V ? 0.99 : 1.0) * best_ns && fits(q)) {
+                best_ns = ns;
+                best = q;
+            }
+        }
+        q.whole_cohorts = false;
     }
     return best;
 }
@@ -96,7 +168,7 @@ K1Plan k1_plan(int dtype, int64_t T, int d, int V)
                 p.tiles_per_split = tps;
             }
         }
-        return narrower(p, T, V, 2 * ((dk + 63) / 64));
+        return cheaper(p, T, V, 2 * ((dk + 63) / 64));
     }
     // One workgroup per (token block, vocabulary range), one workgroup per compute unit at a
     // time, all of about the same length: among the next few range counts take the one whose
@@ -118,7 +190,7 @@ K1Plan k1_plan(int dtype, int64_t T, int d, int V)
         if (nsc == p.ntiles_v)
             break;
     }
-    return p;
+    return cheaper(p, T, V, 2 * ((dk + 63) / 64));
 }
 
 size_t k1_partial_floats(const K1Plan &p, int64_t T) { return (size_t)3 * (size_t)p.nsplit * (size_t)T; }
@@ -127,7 +199,7 @@ size_t k1_partial_floats_bound(int64_t T)
 {
     // nsplit(T') <= target / ntb(T') + 1 + NSPLIT_SLACK, so
     // nsplit(T') * T' <= (target + (1 + NSPLIT_SLACK) * ntb(T')) * tb_tokens for every T' <= T
-    // (narrow plans have at most three rounds of workgroups: far less)
+    // (plans of the other kernels are only taken if they fit this)
     const int64_t tbk = TB;
     const int64_t target = TARGET_UNITS;
     const int64_t ntb = (T + tbk - 1) / tbk;

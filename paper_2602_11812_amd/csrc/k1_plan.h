@@ -34,6 +34,9 @@ constexpr long K1_MAX_CONTRACTION = 4194240;
 // triple per token.
 // vocabulary rows per tile of the kernel for few tokens (the other kernel's tiles have 256)
 constexpr int K1_NARROW_TILE_V = 128;
+// ... and tokens per block and rows per tile of the kernel between the two
+constexpr int K1_STREAM_TOKENS = 128, K1_STREAM_TILE_V = 64;
+constexpr int K1_STREAM_PACE_TILES = 16;  // its pacing points, in tiles
 
 struct K1Plan {
     int tb_tokens;        // tokens per block
@@ -42,6 +45,7 @@ struct K1Plan {
     int ntiles_v;         // vocabulary tiles in total
     int nsplit;           // vocabulary ranges
     int tiles_per_split;  // tiles per range (last range may hold fewer)
+    bool whole_cohorts = false;  // stream kernel, paced: each XCD gets whole cohorts (k1_stream_cohorts)
 };
 
 K1Plan k1_plan(int dtype, int64_t T, int d, int V);
@@ -54,6 +58,15 @@ size_t k1_partial_floats_bound(int64_t T);
 EGTP_HOST_DEVICE inline int k1_pace_cohorts(long units) { return (int)(((units + 7) / 8 + 31) / 32); }
 size_t k1_pace_ints_bound(int64_t T);
 
+// The stream kernel: token blocks that sweep the same ranges together, such that a cohort of 32 workgroups holds
+// 32 / group ranges, and how many cohorts that makes.
+inline int k1_stream_group(int nsplit) { return nsplit >= 4 ? 8 : (nsplit >= 2 ? 16 : 32); }
+inline long k1_stream_cohorts(int ntb, int nsplit)
+{
+    const int group = k1_stream_group(nsplit), ranges = 32 / group;
+    return (long)((ntb + group - 1) / group) * ((nsplit + ranges - 1) / ranges);
+}
+
 // A range has a pacing point after every K1_PACE_TILES vocabulary tiles, so only
 // ranges longer than that pace at all.
 constexpr int K1_PACE_TILES = 4;
@@ -61,6 +74,8 @@ constexpr int K1_PACE_TILES = 4;
 // fewer blocks streams W_lm once from HBM whatever the workgroups' relative progress.
 inline bool k1_plan_paces(const K1Plan &p)
 {
+    if (p.tile_v == K1_STREAM_TILE_V)
+        return p.tiles_per_split > K1_STREAM_PACE_TILES && p.ntb >= 16;
     return p.tile_v != K1_NARROW_TILE_V && p.tiles_per_split > K1_PACE_TILES && p.ntb >= 8;
 }
 

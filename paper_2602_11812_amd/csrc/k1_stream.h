@@ -10,6 +10,11 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 namespace {
 
+// Pacing: workgroup i is placed on XCD i % 8; a cohort are the workgroups one XCD runs at a time (its compute units)
+constexpr int COHORT = 32;
+constexpr int PACE_SPINS = 24;     // bound of one wait: polls of the counter ...
+constexpr int PACE_SLEEP = 4;      // ... each followed by a sleep of 64 * PACE_SLEEP cycles
+
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding: vmcnt in bits
 // [3:0] and [15:14], export and LDS/scalar counters left at their maxima)
 template <int N>

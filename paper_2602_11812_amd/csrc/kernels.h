@@ -63,6 +63,11 @@ hipError_t k1_entropy_bf16(const void *hidden_packed, const void *w_packed, int6
 // the same for a narrow plan (p.tile_v == K1_NARROW_TILE_V)
 hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, hipStream_t st);
+// clears `count` pacing counters
+hipError_t k1_clear_pace(int *pace, long count, hipStream_t st);
+// ... and for a plan with p.tile_v == K1_STREAM_TILE_V
+hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+                             const K1Plan &p, float *part, int *pace, hipStream_t st);
 // merges the nsplit partial triples of each token in a fixed order; entropy[t] = ln S - U/S
 hipError_t k1_merge(const float *part, int nsplit, int64_t T, float *entropy, hipStream_t st);
 
