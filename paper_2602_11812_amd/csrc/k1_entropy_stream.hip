@@ -35,6 +35,7 @@ constexpr int MAX_MI = 8;                       // vocabulary fragments of a wav
 constexpr int H_STAGES = 6;
 constexpr int PACE_SWEEPS = K1_STREAM_PACE_TILES / MAX_MI;  // sweeps between two pacing points
 static_assert(K1_STREAM_TILE_V == 64, "a tile is one fragment for each of the four waves");
+static_assert(2L * K1_STREAM_MAX_STEPS * TILE_BYTES <= 0x7fffffffL, "two packed tiles under one offset");
 
 template <bool STREAM_W>
 __device__ __forceinline__ bf16x8 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int lane_byte_offset, int scalar_byte_offset)
@@ -346,7 +347,7 @@ hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, in
     if (T <= 0 || p.tb_tokens != BN || p.tile_v != K1_STREAM_TILE_V || p.nsplit < 1 || p.tiles_per_split < 1 ||
         (long)p.nsplit * p.tiles_per_split < p.ntiles_v || (long)(p.nsplit - 1) * p.tiles_per_split >= p.ntiles_v ||
         (long)p.ntb * p.nsplit > 0x7fffffffL || (int64_t)p.ntb * BN < T ||
-        p.ntiles_v != (V + K1_STREAM_TILE_V - 1) / K1_STREAM_TILE_V || 2L * kt * TILE_BYTES > 0x7fffffffL)
+        p.ntiles_v != (V + K1_STREAM_TILE_V - 1) / K1_STREAM_TILE_V || kt > K1_STREAM_MAX_STEPS)
         return hipErrorInvalidValue;
     const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * kt * 4 * FRAG_BYTES > ((int64_t)256 << 20);
     const int group = k1_stream_group(p.nsplit);

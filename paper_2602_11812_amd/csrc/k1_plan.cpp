@@ -114,7 +114,7 @@ static K1Plan cheaper(const K1Plan &p, int64_t T, int V, long steps)
             }
         }
     // 1, 2, 3, ... long ranges and as many as make one to four rounds of workgroups; paced plans in whole cohorts, too
-    for (int i = 1; i <= 20 && steps >= STREAM_MIN_STEPS; ++i) {
+    for (int i = 1; i <= 20 && steps >= STREAM_MIN_STEPS && steps <= K1_STREAM_MAX_STEPS; ++i) {
         const int64_t ntb = (T + K1_STREAM_TOKENS - 1) / K1_STREAM_TOKENS;
         const int64_t ranges = i <= 16 ? i : (int64_t)(i - 16) * NUM_CUS / ntb;
         if (ranges < 1 || (i > 16 && ranges <= 16))

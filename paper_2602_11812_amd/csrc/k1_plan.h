@@ -37,6 +37,9 @@ constexpr int K1_NARROW_TILE_V = 128;
 // ... and tokens per block and rows per tile of the kernel between the two
 constexpr int K1_STREAM_TOKENS = 128, K1_STREAM_TILE_V = 64;
 constexpr int K1_STREAM_PACE_TILES = 16;  // its pacing points, in tiles
+// A sweep of its may straddle two packed 256-row tiles of W_lm, 16 KiB per K step each, under one 32-bit byte offset:
+// half of what the other kernels address.
+constexpr long K1_STREAM_MAX_STEPS = 0x7fffffffL / (2 * 16384);
 
 struct K1Plan {
     int tb_tokens;        // tokens per block
