@@ -273,3 +273,10 @@ def test_argument_errors(gpu):
                                        (65, 252, 129, 33), (97, 4, 130, 9)])
 def test_matrix_kernels_at_tile_edges(gpu, B, d, d_h, K):
     _run_steps(gpu, wl.make_train(4000 + B, B=B, d=d, d_h=d_h, K=K), 1)
+
+
+# W2, b2 and b1: 32 samples of each of four waves at a time -- one chunk less a sample, full, one sample over, two chunks
+# and a part; rows of W2 around the four a workgroup takes, columns around 64
+@pytest.mark.parametrize("B,d_h,K", [(127, 65, 4), (128, 64, 5), (129, 63, 7), (300, 128, 3)])
+def test_small_parameters_at_chunk_edges(gpu, B, d_h, K):
+    _run_steps(gpu, wl.make_train(6000 + B, B=B, d=64, d_h=d_h, K=K), 1)
