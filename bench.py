@@ -23,8 +23,9 @@ FP32_MFMA_PEAK_TFLOPS = 157.3    # MI355X dense fp32 matrix-core peak (what fp32
 HBM_PEAK_GBPS = 8000.0            # MI355X HBM3E peak
 
 
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k1_entropy_bf16_serving_hbm_traffic.txt")
-K1_SOURCES = [os.path.join(ROOT, "paper_2602_11812_amd", "csrc", f) for f in ("k1_entropy_bf16.hip", "k1_common.h", "k1_plan.cpp")]
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k1_entropy_serving_hbm_traffic.txt")
+K1_SOURCES = [os.path.join(ROOT, "paper_2602_11812_amd", "csrc", f) for f in
+              ("k1_entropy_bf16.hip", "k1_entropy_stream.hip", "k1_stream.h", "k1_common.h", "k1_plan.h", "k1_plan.cpp")]
 
 
 def recorded_traffic():
@@ -108,7 +109,7 @@ def bench_plp(args, gpu, wl, np, torch) -> int:
         "config": {"workload": f"plp_decode: {B} live sequences x 1 new token per step, d={spec.d}, V={spec.V}, "
                                f"remaining-length head {spec.d}->{spec.d_h}->1, seed {spec.seed}", "B": B,
                    "launch": "hip graph of 16 steps" if args.graph else "eager"},
-        "roofline": {"kernel": "k1_entropy_bf16 (fused LM-head + entropy)", "bound": "mfma", "achieved": achieved,
+        "roofline": {"kernel": "k1_entropy (fused LM-head + entropy)", "bound": "mfma", "achieved": achieved,
                      "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / BF16_MFMA_PEAK_TFLOPS,
                      "traffic": None, "avg_launch_ms": k1_s * 1e3, "launches": int(k1_ms.size),
                      "w_lm_stream_TBps": spec.V * spec.d * 2 / k1_s / 1e12},
@@ -160,7 +161,7 @@ def bench_rl(args, gpu, wl, np, torch) -> int:
         "config": {"workload": f"rl: {spec.B} prompts x {S_PER} samples, {live.size} live at decode step 64, {T} new "
                                f"tokens per call, d={spec.d}, V={spec.V}, head {spec.d}->{spec.d_h}->1, seed {spec.seed}",
                    "B": int(live.size), "T": T},
-        "roofline": {"kernel": "k1_entropy_bf16 (fused LM-head + entropy)", "bound": "mfma", "achieved": achieved,
+        "roofline": {"kernel": "k1_entropy (fused LM-head + entropy)", "bound": "mfma", "achieved": achieved,
                      "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": achieved / BF16_MFMA_PEAK_TFLOPS,
                      "traffic": None, "avg_launch_ms": k1_s * 1e3},
         "cpu_baseline": None}), flush=True)
@@ -398,11 +399,11 @@ def main() -> int:
                    "B": B, "T": T, "d": spec.d, "V": spec.V, "d_h": spec.d_h},
         ("pct_fp32_mfma_peak_whole_step" if f32 else "pct_bf16_mfma_peak_whole_step"):
             100.0 * flops_per_launch / (ms_per_step * 1e-3) / 1e12 / peak,
-        "roofline": {"kernel": "k1_entropy_bf16 (fused LM-head + entropy)", "bound": "mfma", "achieved": achieved,
+        "roofline": {"kernel": "k1_entropy (fused LM-head + entropy)", "bound": "mfma", "achieved": achieved,
                      "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
                      "executed_bf16_tflops": executed, "executed_frac_of_bf16_peak": executed / BF16_MFMA_PEAK_TFLOPS,
                      "traffic": traffic if args.workload == "serving" and not f32 else None,
-                     "traffic_source": ("profiles/k1_entropy_bf16_serving_hbm_traffic.txt (rocprofv3 FETCH_SIZE + "
+                     "traffic_source": ("profiles/k1_entropy_serving_hbm_traffic.txt (rocprofv3 FETCH_SIZE + "
                                         "WRITE_SIZE passes of an earlier run of this kernel; replayed while the kernel "
                                         "and launch-plan sources hash to the recorded value, not measured in this run)")
                      if traffic is not None and args.workload == "serving" and not f32 else None,
