@@ -41,10 +41,13 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const unsigned char
     return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000);
 }
 
-// Fold 16 logits of one token: zin[4*q+i] is vocabulary row row0 + 16*q + i.
+// Fold 16 logits of one token: zin[4*q+i] is vocabulary row row0 + 16*q + i.  MASK: rows from V on do not exist.
+// Whether a lane has any row at all follows from the row numbers: its maximum cannot tell, fmaxf passes over NaN.
 template <bool MASK>
 __device__ __forceinline__ void fold16(const float (&zin)[16], Stats &st, int row0, int V)
 {
+    if (MASK && row0 >= V)
+        return;  // nothing to add (and perhaps no reference maximum yet)
     float z[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -57,8 +60,6 @@ __device__ __forceinline__ void fold16(const float (&zin)[16], Stats &st, int ro
 #pragma unroll
     for (int i = 1; i < 16; ++i)
         mx = fmaxf(mx, z[i]);
-    if (MASK && !(mx > NEG_BIG))
-        return;  // every row of this lane is masked: nothing to add (and no reference maximum yet)
     // The reference lives in log2 units, r = fl(max z * log2 e): every exponent is then ONE fused
     // multiply-add z * log2 e - r (exact product, one rounding of a small result) and re-referencing is an
     // exact difference of two r, so the precision does not degrade with the magnitude of the logits.

@@ -61,3 +61,51 @@ def test_every_tile_shape_against_the_oracle(dtype, d, V, T, block, rows, per_ra
     assert_egtp_close(runs[0], want)
     assert np.abs(runs[0]["entropy"] - want.entropy).max() <= 2e-5
     sc.close()
+
+
+def _rows_of_one_lane(rows, per_range, V):
+    """Row groups of a tile shape of which a lane folds four fragments' worth at once, or the part of four that is
+    left over: what a mask has to tell from rows that do not exist.  64-row tiles: the waves of the first range (16
+    per_range rows each); otherwise the last group of the vocabulary."""
+    if rows != 64:
+        return [((V - 1) // 64 * 64, V)]
+    return [(16 * f, 16 * min(f + 4, (wave + 1) * per_range))
+            for wave in (0, 3) for f in range(wave * per_range, (wave + 1) * per_range, 4)]
+
+
+# 64-row tiles with every kind of sweep that masks (1, 2, 3, 7 and 8 + 1, 8 + 7 fragments a wave), and the last,
+# partly filled tile of the other two kernels
+@pytest.mark.parametrize("dtype,d,V,T,rows,per_range", [
+    ("bf16", 216, 5422, 338, 64, 1), ("bf16", 224, 16511, 65, 64, 2), ("bf16", 208, 33136, 66, 64, 3),
+    ("f32", 36, 33791, 261, 64, 7), ("bf16", 208, 33664, 415, 64, 9), ("bf16", 216, 33834, 773, 64, 15),
+    ("bf16", 512, 4223, 65, 128, 1), ("bf16", 232, 31206, 389, 256, 1)])
+def test_nan_reaches_the_entropy(dtype, d, V, T, rows, per_range):
+    """Rows of W_lm that are all NaN make every token's entropy NaN, also where they fill all that a lane folds; a NaN
+    hidden state makes its own token NaN and leaves the other tokens' bits alone."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    plan = gpu.egtp_launch_plan_query(gpu.EGTP_BF16 if dtype == "bf16" else gpu.EGTP_F32, d, V, T)
+    assert (plan.rows_per_tile, plan.tiles_per_range) == (rows, per_range)
+    base = wl.SPECS["tiny" if dtype == "f32" else "mid"]
+    w = wl.make(wl.scaled(base, seed=7500 + T, B=1, d=d, V=V, d_h=16, lengths=(T,)))
+    td = gpu.to_device
+    hidden, off = td(w.hidden), torch.tensor([0, T], dtype=torch.int32).cuda()
+
+    def entropies(w_lm, hidden):
+        sc = gpu.Scorer(w_lm, gpu.make_head(td(w.w1), td(w.w2)))
+        out = sc.score(hidden, off)["entropy"].cpu().numpy()
+        sc.close()
+        return out
+
+    clean = entropies(td(w.w_lm), hidden)
+    assert np.isfinite(clean).all()
+    for lo, hi in _rows_of_one_lane(rows, per_range, V):
+        broken = td(w.w_lm)
+        broken[lo:hi] = float("nan")
+        assert np.isnan(entropies(broken, hidden)).all(), (lo, hi)
+    for t in (0, T // 2, T - 1):
+        broken = hidden.clone()
+        broken[t] = float("nan")
+        got = entropies(td(w.w_lm), broken)
+        assert np.isnan(got[t])
+        assert np.array_equal(np.delete(got, t), np.delete(clean, t)), t
