@@ -81,8 +81,10 @@ __global__ __launch_bounds__(256) void seg_ids_kernel(const int32_t *__restrict_
 __device__ __forceinline__ long clamp_token(long t, long T) { return t < 0 ? 0 : (t > T ? T : t); }
 
 // ---- Eq. 4: partial weighted sums per unit --------------------------------------------------
-// MODE 0: weights e^{H/alpha - m} (Eq. 3-4), m the unit's largest H/alpha; MODE 1: plain sums (average pooling,
+// MODE 0: weights e^{H/alpha - m} / unit (Eq. 3-4), m the unit's largest H/alpha; MODE 1: plain sums (average pooling,
 // divided by the length when the units are joined); MODE 2: element-wise maxima.
+// The division by the unit, a power of two, changes no bit of a result: it keeps the sum of a unit's weights at or below
+// one, so that a partial is no larger than the largest hidden state and cannot overflow where the pooled vector does not.
 enum : int { POOL_WEIGHTED = 0, POOL_SUM = 1, POOL_MAXIMUM = 2 };
 
 template <bool BF16, typename Q>
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(256) void pool_partial_kernel(
         __syncthreads();
         const float m = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
         const float e = tid < n ? __expf(a - m) : 0.f;
-        w[tid] = e;
+        w[tid] = ldexpf(e, -unit_log2);
         const float ws = wave_sum(e);
         if ((tid & 63) == 0)
             red[1][wave] = ws;
@@ -361,7 +363,7 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
         const long c1 = min(c0 + JOIN_FACTORS, u1);
         __syncthreads();
         for (long u = c0 + tid; u < c1; u += 256)
-            factor[u - c0] = __expf(unit_stats[u].x - mx) * inv;
+            factor[u - c0] = ldexpf(__expf(unit_stats[u].x - mx) * inv, unit_log2);  // (partials are divided by the unit)
         __syncthreads();
         if (k < d)
             r = join_units<POOL_WEIGHTED>(partial, c0, c1, d, k, r, factor);

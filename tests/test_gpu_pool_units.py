@@ -82,3 +82,28 @@ def test_units_of_ragged_batches(name, dtype, d):
             tol = 1e-5 * np.sqrt(np.mean(x * x)) if kind == gpu.EGTP_POOL_AVERAGE and len(x) else 0.0
             assert np.abs(got[b] - p).max() <= tol, (name, b, kind)
     sc.close()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_hidden_states_near_the_largest_number(dtype):
+    """A pooled vector lies between the smallest and the largest hidden state of its sequence, so it is finite whatever
+    they are: 3e38 in every token, the same entropy everywhere (W_lm of zeros), on their own and onto an old state.
+    Weights are accurate to a few 2^-24 and their sum is one to the same, hence 1e-5 relative."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    d, V, lens = 136, 40, (1000, 1, 37, 256)
+    T, B = sum(lens), len(lens)
+    store = torch.bfloat16 if dtype == "bf16" else torch.float32
+    sign = torch.where(torch.arange(d) % 3 == 0, -1.0, 1.0)
+    row = (3e38 * sign).to(store)
+    hidden = row.expand(T, d).contiguous().cuda()
+    zeros = lambda *s: torch.zeros(*s, dtype=store, device="cuda")
+    sc = gpu.Scorer(zeros(V, d), gpu.make_head(zeros(8, d), zeros(1, 8)))
+    off = sc.build_offsets(torch.tensor(lens, dtype=torch.int32).cuda(), T)
+    want = row.double().expand(B, d).numpy()
+    got = sc.score(hidden, off)["pooled"].cpu().numpy().astype(np.float64)
+    assert np.abs(got / want - 1.0).max() <= 1e-5
+    state, lse = row.float().expand(B, d).contiguous().cuda(), torch.full((B,), 5.0, device="cuda")
+    sc.step(hidden, state, lse, offsets_new_dev=off)
+    assert np.abs(state.cpu().numpy().astype(np.float64) / want - 1.0).max() <= 1e-5
+    sc.close()
