@@ -272,12 +272,13 @@ __device__ __forceinline__ float4 join_waves(float4 r, float4 (&sh)[3][64])
     return r;
 }
 
-// the unit numbers [u0, u1) of sequence b, inside the partial buffer whatever the offsets hold
-__device__ __forceinline__ void sequence_units(const int32_t *__restrict__ offsets, int b, int unit_log2, long units_cap,
-                                               long &u0, long &u1)
+// the unit numbers [u0, u1) of sequence b, inside the partial buffer whatever the offsets hold; only units that hold
+// tokens, since the others' partials are not written
+__device__ __forceinline__ void sequence_units(const int32_t *__restrict__ offsets, int b, long T, int unit_log2,
+                                               long units_cap, long &u0, long &u1)
 {
     const int begin = offsets[b];
-    const long len = (long)offsets[b + 1] - begin;
+    const long len = clamp_token(offsets[b + 1], T) - begin;
     u0 = min(unit_base(begin, b, unit_log2), units_cap);
     u1 = min(u0 + (len > 0 ? (len + (1 << unit_log2) - 1) >> unit_log2 : 0), units_cap);
 }
@@ -285,17 +286,17 @@ __device__ __forceinline__ void sequence_units(const int32_t *__restrict__ offse
 // Table 3 alternatives: sum / length, or maximum
 template <int MODE>
 __global__ __launch_bounds__(256) void pool_finalize_plain_kernel(const float *__restrict__ partial,
-                                                                  const int32_t *__restrict__ offsets, int d,
-                                                                  int unit_log2, long units_cap,
+                                                                  const int32_t *__restrict__ offsets, long T,
+                                                                  int d, int unit_log2, long units_cap,
                                                                   float *__restrict__ out_pooled)
 {
     __shared__ float4 waves[3][64];
     const int b = blockIdx.x;
     const int k = blockIdx.y * JOIN_COLS + (threadIdx.x & 63) * 4;
     long u0, u1;
-    sequence_units(offsets, b, unit_log2, units_cap, u0, u1);
+    sequence_units(offsets, b, T, unit_log2, units_cap, u0, u1);
     const int len = offsets[b + 1] - offsets[b];
-    const float init = (MODE == POOL_MAXIMUM && len > 0) ? NEG_INF : 0.f;  // an empty sequence pools to zero
+    const float init = (MODE == POOL_MAXIMUM && u1 > u0) ? NEG_INF : 0.f;  // an empty sequence pools to zero
     float4 r = make_float4(init, init, init, init);
     if (k < d)
         r = join_units<MODE>(partial, u0, u1, d, k, r, nullptr);
@@ -313,7 +314,7 @@ __global__ __launch_bounds__(256) void pool_finalize_plain_kernel(const float *_
 // the rescaled old state.  Every workgroup of a sequence finds the log-sum-exp for itself.
 __global__ __launch_bounds__(256) void pool_finalize_kernel(
     const float *__restrict__ partial, const float2 *__restrict__ unit_stats, const int32_t *__restrict__ offsets,
-    const int32_t *__restrict__ slot, int d, int unit_log2, long units_cap, const float *state_pooled,
+    const int32_t *__restrict__ slot, long T, int d, int unit_log2, long units_cap, const float *state_pooled,
     const float *__restrict__ lse_old, float *out_pooled, float *out_lse)
 {
     __shared__ float factor[JOIN_FACTORS];
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
     const int s = slot ? slot[b] : b;
     const float L_old = lse_old ? lse_old[b] : NEG_INF;
     long u0, u1;
-    sequence_units(offsets, b, unit_log2, units_cap, u0, u1);
+    sequence_units(offsets, b, T, unit_log2, units_cap, u0, u1);
     float mx = NEG_INF;
     for (long u = u0 + tid; u < u1; u += 256)
         mx = fmaxf(mx, unit_stats[u].x);
@@ -570,7 +571,7 @@ hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st)
                            a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
                            a.lse_old, a.partial, stats);
     hipLaunchKernelGGL(pool_finalize_kernel, dim3(a.B, (a.d + JOIN_COLS - 1) / JOIN_COLS), dim3(256), 0, st, a.partial, stats, a.offsets,
-                       a.slot, a.d, unit_log2, units, a.state_pooled, a.state_lse ? a.lse_old : nullptr, a.out_pooled,
+                       a.slot, (long)a.T, a.d, unit_log2, units, a.state_pooled, a.state_lse ? a.lse_old : nullptr, a.out_pooled,
                        a.out_lse);
     return hipGetLastError();
 }
@@ -604,7 +605,7 @@ hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offse
         hipLaunchKernelGGL((pool_partial_kernel<BF, MODE>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, hidden, \
                            d, nullptr, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
                            partial, nullptr);                                                              \
-        hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, offsets, d,  \
+        hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, offsets, (long)T, d, \
                            unit_log2, units, out_pooled);                                                  \
     } while (0)
     if (kind == 0) {

@@ -107,3 +107,30 @@ def test_hidden_states_near_the_largest_number(dtype):
     sc.step(hidden, state, lse, offsets_new_dev=off)
     assert np.abs(state.cpu().numpy().astype(np.float64) / want - 1.0).max() <= 1e-5
     sc.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 2056), ("f32", 36)])
+def test_offsets_past_the_batch_pool_the_tokens_there_are(dtype, d):
+    """Device offsets are the caller's word: where a table runs past T, a sequence has the tokens up to T (bit for bit as
+    if the table said so), and nothing that the workspace held before gets into a result."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    lens = (40, 200, 3, 57)
+    w = wl.make(wl.scaled(wl.SPECS["mid" if dtype == "bf16" else "tiny"], seed=9300, B=4, d=d, V=40, d_h=8, lengths=lens))
+    td = gpu.to_device
+    sc = gpu.Scorer(td(w.w_lm), gpu.make_head(td(w.w1), td(w.w2)))
+    hidden, T = td(w.hidden), sum(lens)
+    i32 = lambda *v: torch.tensor(v, dtype=torch.int32).cuda()
+
+    def results(off):
+        out = []
+        for call in (lambda: sc.score(hidden, off), lambda: sc.pool_ablation(hidden, off, gpu.EGTP_POOL_MAX)[0]):
+            sc.workspace(T, 4).fill_(255)
+            r = call()
+            out += [v.cpu().numpy() for k, v in r.items() if k != "entropy"] if isinstance(r, dict) else [r.cpu().numpy()]
+        return out
+
+    for past, cut in (((0, 40, 240, 243, T + 500), (0, 40, 240, 243, T)), ((0, 40, 240, T + 90, T + 700), (0, 40, 240, T, T))):
+        for a, b in zip(results(i32(*past)), results(i32(*cut))):
+            assert np.array_equal(a, b), past
+    sc.close()
