@@ -1,6 +1,8 @@
 """The fused entropy kernels for small and for very large batches: 128-row vocabulary tiles over 64 or 192 tokens, and
 64-row tiles (a fragment per wave) over 128.  Every kind at the edges of its tiles against the fp64 oracle.  Entropies
 to fp32 grade (2e-5 nat, the bar of the fp32 tests: logits are fp32 sums of d exact products)."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -12,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 # (dtype, d, V, T, tokens per block, rows per tile, tiles per range): one token, a block exactly full, one token over,
 # several blocks with a ragged last one, more than eight blocks; a last vocabulary tile of 1, 127 and 128 rows in either
-# half of a packed block; a last range that is shorter; K of a single pair of steps and K longer than the ring.  With
-# 64-row tiles every remainder of a range modulo eight fragments a wave (1 to 8, 9, 13, 35), ranges that straddle packed
+# half of a packed block; a last range that is shorter; K of a single pair of steps and K longer than the ring; ranges of
+# several tiles, so that the ring runs from one tile into the next, with some ranges a tile shorter.  With 64-row tiles every remainder of a range modulo eight fragments a wave (1 to 8, 9, 13, 35), ranges that straddle packed
 # blocks, a vocabulary that ends inside a fragment
 CASES = [
     ("bf16", 64, 257, 1, 64, 128, 1),
@@ -23,6 +25,10 @@ CASES = [
     ("bf16", 1024, 1025, 579, 64, 128, 1),
     ("bf16", 2048, 32000, 173, 192, 128, 1),
     ("f32", 256, 4096, 309, 64, 128, 1),
+    ("bf16", 104, 20138, 291, 64, 128, 4),
+    ("bf16", 8, 35546, 554, 64, 128, 10),
+    ("bf16", 64, 48959, 341, 192, 128, 3),
+    ("bf16", 48, 52583, 565, 192, 128, 5),
     ("bf16", 216, 5422, 338, 128, 64, 1),
     ("bf16", 224, 16511, 65, 128, 64, 2),
     ("bf16", 2048, 32000, 128, 128, 64, 2),
@@ -37,12 +43,26 @@ CASES = [
 ]
 
 
+class _Plan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("tb_tokens", "tile_v", "ntb", "ntiles_v", "nsplit", "tiles_per_split")]
+    _fields_ += [("whole_cohorts", ctypes.c_bool)]
+
+
+def _whole_cohorts(dtype, d, V, T):
+    """What the queried plan does not say: whether each XCD gets whole cohorts of workgroups."""
+    from paper_2602_11812_amd import binding as gpu
+    plan = gpu.load_library()._ZN4egtp7k1_planEilii
+    plan.restype, plan.argtypes = _Plan, [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    return plan(gpu.EGTP_BF16 if dtype == "bf16" else gpu.EGTP_F32, T, d, V).whole_cohorts
+
+
 @pytest.mark.parametrize("dtype,d,V,T,block,rows,per_range", CASES)
 def test_every_tile_shape_against_the_oracle(dtype, d, V, T, block, rows, per_range):
     import torch
     from paper_2602_11812_amd import binding as gpu
     plan = gpu.egtp_launch_plan_query(gpu.EGTP_BF16 if dtype == "bf16" else gpu.EGTP_F32, d, V, T)
     assert (plan.tokens_per_block, plan.rows_per_tile, plan.tiles_per_range) == (block, rows, per_range)
+    assert plan.paced == (per_range == 17) and _whole_cohorts(dtype, d, V, T) == (per_range == 17 and T > 10000)
     lens = (T,) if T < 3 else (T // 3, 0, T - T // 3)
     base = wl.SPECS["tiny" if dtype == "f32" else "mid"]
     w = wl.make(wl.scaled(base, seed=7000 + T, B=len(lens), d=d, V=V, d_h=16, lengths=lens))
@@ -60,6 +80,35 @@ def test_every_tile_shape_against_the_oracle(dtype, d, V, T, block, rows, per_ra
     want = oracle.egtp(w.hidden, off, w.w_lm, oracle.Head(w.w1, w.w2))
     assert_egtp_close(runs[0], want)
     assert np.abs(runs[0]["entropy"] - want.entropy).max() <= 2e-5
+    sc.close()
+
+
+def test_one_token_block_against_a_large_vocabulary():
+    """One token block against a W_lm that the 256 MiB Infinity Cache cannot hold (1.24 GB): the instantiations that read
+    it with the non-temporal hint, in the plans of decode steps with few sequences and of single prompts -- 64 and 192
+    tokens a block against ranges of 5 tiles of 128 rows, 128 against ranges of 10 of 64.  Every token against the oracle
+    and the same bits whatever the workspace held."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    d, V, most = 4096, 151936, 173
+    w = wl.make(wl.scaled(wl.SPECS["serving"], seed=7900, B=1, d=d, V=V, d_h=16, lengths=(most,)))
+    want = oracle.entropy(w.hidden, w.w_lm)
+    td = gpu.to_device
+    sc = gpu.Scorer(td(w.w_lm), gpu.make_head(td(w.w1), td(w.w2)))
+    hidden = td(w.hidden)
+    ws = sc.workspace(most, 1)
+    for T, tile in ((1, (64, 128, 5)), (24, (64, 128, 5)), (64, (64, 128, 5)), (100, (128, 64, 10)), (128, (128, 64, 10)),
+                    (173, (192, 128, 5))):
+        plan = gpu.egtp_launch_plan_query(gpu.EGTP_BF16, d, V, T)
+        assert (plan.tokens_per_block, plan.rows_per_tile, plan.tiles_per_range, plan.token_blocks) == (*tile, 1)
+        off = torch.tensor([0, T], dtype=torch.int32).cuda()
+        runs = []
+        for fill in (0, 255):
+            ws.fill_(fill)
+            runs.append({k: v.cpu().numpy() for k, v in sc.score(hidden[:T], off).items()})
+        for k in runs[0]:
+            assert np.array_equal(runs[0][k], runs[1][k]), (T, k)
+        assert np.abs(runs[0]["entropy"] - want[:T]).max() <= 2e-5, T
     sc.close()
 
 

@@ -1,8 +1,10 @@
-"""Ragged pooling cuts sequences into units of 16 to 256 tokens whose numbers follow from the offsets alone: lengths
-around every unit size, empty sequences at both ends and in rows, more sequences than are looked through at once,
-with and without an old state read and replaced through slots.  References in fp64 from the library's own entropies
-(which other tests hold to the oracle): pooled 1e-5 relative L2, fp32 sums of at most a thousand terms with weights
-accurate to a few 2^-24; lse 1e-5 absolute at |lse| < 20."""
+"""Ragged pooling cuts sequences into units of 16 to 256 tokens whose numbers follow from the offsets alone: small
+batches of many kinds, in units of 16 to 64 (empty sequences at both ends and in rows, more sequences than are looked
+through at once), lengths around the unit in every unit size, and a sequence of more units than the join keeps factors
+for at a time; with and without an old state read and replaced through slots.  References in fp64 from the library's
+own entropies (which other tests hold to the oracle): pooled 1e-5 relative L2, fp32 sums of at most 300 terms in a row
+(a unit's tokens, then a quarter of the units) with weights accurate to a few 2^-24; lse 1e-5 absolute at |lse| < 20."""
+import ctypes
 import math
 
 import numpy as np
@@ -26,9 +28,43 @@ RAGGED = {
 @pytest.mark.parametrize("dtype,d", [("bf16", 2056), ("bf16", 64), ("f32", 1028)])
 @pytest.mark.parametrize("name", list(RAGGED))
 def test_units_of_ragged_batches(name, dtype, d):
+    _check_units(name, RAGGED[name], dtype, d)
+
+
+def _unit(dtype, d, T, B):
+    """Tokens per unit, from the library's own rule.  It may use as many floats of partials as the larger of the merged
+    triples' and those of units of 256."""
+    from paper_2602_11812_amd import binding as gpu
+    lib = gpu.load_library()
+    triples, unit = lib._ZN4egtp23k1_partial_floats_boundEl, lib._ZN4egtp9pool_unitEiilim
+    triples.restype, triples.argtypes = ctypes.c_size_t, [ctypes.c_int64]
+    unit.restype, unit.argtypes = ctypes.c_int, [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_int32, ctypes.c_size_t]
+    cap = max(triples(T), (T // 256 + B) * (d + 2))
+    return unit(gpu.EGTP_BF16 if dtype == "bf16" else gpu.EGTP_F32, d, T, B, cap)
+
+
+# A long sequence in the middle makes the batch large enough for the unit; around it lengths one below, at and one above
+# one and two units, starting at multiples of the unit and off them
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 36)])
+@pytest.mark.parametrize("unit,long", [(16, 0), (32, 8200), (64, 17001), (128, 34001), (256, 66001)])
+def test_lengths_around_every_unit(unit, long, dtype, d):
+    edges = [k * unit + e for k in (1, 2) for e in (-1, 0, 1)]
+    lens = (*edges, 0, 0, long, *edges[::-1], 1)
+    assert _unit(dtype, d, sum(lens), len(lens)) == unit
+    _check_units(f"units of {unit}", lens, dtype, d)
+
+
+# 270 000 tokens are 1055 units of 256; the join keeps the factors of 1024
+@pytest.mark.parametrize("dtype,d", [("bf16", 8), ("f32", 4)])
+def test_more_units_in_a_sequence_than_factors_are_kept(dtype, d):
+    lens = (300, 270000, 5)
+    assert _unit(dtype, d, sum(lens), len(lens)) == 256
+    _check_units("chunked join", lens, dtype, d)
+
+
+def _check_units(name, lens, dtype, d):
     import torch
     from paper_2602_11812_amd import binding as gpu
-    lens = RAGGED[name]
     B, T = len(lens), sum(lens)
     w = wl.make(wl.scaled(wl.SPECS["mid" if dtype == "bf16" else "tiny"], seed=9000 + B, B=B, d=d, V=40, d_h=8, lengths=lens))
     td = gpu.to_device
