@@ -241,7 +241,7 @@ def bench_train(args, gpu, wl, np, torch) -> int:
         "ms_per_step": dt / steps * 1e3, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": f"train: batch {B}, d={d}, d_h={d_h}, K={K}, lambda 0.95, AdamW lr 2e-5", "B": B},
-        "roofline": {"kernel": "whole step (dominated by train_w1_update: W1 + two moments streamed once)",
+        "roofline": {"kernel": "whole step (dominated by train_update_kernel: W1 + two moments streamed once)",
                      "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBPS, "traffic": None},
         "cpu_baseline": None}), flush=True)

@@ -204,7 +204,9 @@ egtp_status plp_step_static(egtp_ctx *ctx, const void *hidden_new, const int32_t
 
 /* Average / max / last-token pooling over the same ragged layout (Table 3's alternatives),
  * followed by head_len.  pooled_out [B x d] fp32, pred_out [B] fp32 (optional).  An empty
- * sequence pools to zeros. */
+ * sequence pools to zeros.  The same call gives the same bits every time; the sums of an average
+ * are grouped by the size of the whole batch (T, B and d), so that one sequence's average may
+ * differ in the last bits beside other sequences.  The entropy-weighted pooling does the same. */
 egtp_status egtp_pool_ablation(egtp_ctx *ctx, const void *hidden, const int32_t *offsets_dev,
                                const int32_t *offsets_host, int32_t B, int64_t T,
                                egtp_pool_kind kind, void *workspace, size_t workspace_bytes,

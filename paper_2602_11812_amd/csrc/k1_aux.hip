@@ -95,8 +95,8 @@ __global__ __launch_bounds__(256) void k1_merge_wide_kernel(const float *__restr
     }
 }
 
-// Packs rows of a row-major bf16 matrix src[R x d] into blocks of tile_rows (256, or fewer for the narrow
-// kernel's hidden states) rows x 32 K-elements in
+// Packs rows of a row-major bf16 matrix src[R x d] into blocks of tile_rows (256, or fewer for the hidden states of the
+// narrow and the stream kernel) rows x 32 K-elements in
 // LDS-image order; rows >= R and K >= d are zero.  One workgroup packs 8 consecutive K steps
 // of `rows_per_wg` rows (a multiple of 8; blockIdx.z picks the row group) of one row tile: a wave
 // reads 512 contiguous bytes of each of two rows at a time.

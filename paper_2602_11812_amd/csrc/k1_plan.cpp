@@ -22,13 +22,14 @@ static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number 
 //   narrow   128 rows x 32 NI tokens      115 + 45.6 NI a step, 312 NI a tile
 //   stream   512 rows x 128 tokens        642 a step (+ 400 / token blocks: fewer of them share a read of W_lm), 6200
 //            a sweep; remainders of 4 and 2 fragments a wave 406 and 288, 3100 and 1550
-// The model picks the fastest measured plan or one within 2 % of it.  At d = 4096, V = 151936, in us:
+// The model picks the fastest measured plan or one within 2.5 % of it.  At d = 4096, V = 151936, in us (nothing was
+// measured from 193 to 256 tokens, where the wide tile runs on 198 of the compute units):
 //   tokens   24   100   173   300   512   800  1217  4000  20000   45000
 //   wide    286   280   280   425   475   860  1088  3525  18170   40950
 //   narrow  199   223   253   491
 //   stream  198   199   289   367   495   793  1123  3320  17450   38900
-// (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964; at d = 256 the
-// folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
+// (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964, where WORTH_IT
+// keeps the wide tile -- the 2.5 %; at d = 256 the folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
 static constexpr double WIDE_STEP_NS = 625.0, WIDE_STEP_NS_PER_DOUBLING = 18.5, WIDE_W_BYTES = 48e6, WIDE_FOLD_NS = 5000.0;
 static constexpr double NARROW_STEP_NS = 115.0, NARROW_STEP_NS_PER_NI = 45.6, NARROW_FOLD_NS_PER_NI = 312.0;
 static constexpr double STREAM_STEP_NS = 642.0, STREAM_ALONE_NS = 400.0, STREAM_FOLD_NS = 6200.0;
@@ -39,7 +40,7 @@ static constexpr double WORTH_IT = 0.955;  // another kernel than the wide one i
 // Several rounds of the stream kernel, relative to one round or to whole cohorts of 16 token blocks x 2 ranges: cohorts
 // cut anywhere (65088 tokens, d = 5120, in 4 ranges 70.3 ms against 66.1; 137720, d = 4096, 122.7 against 116); whole
 // ones, per doubling of the ranges (64.6, 66.1, 67.1 ms in 2, 4, 8 ranges); all in one range (131072 tokens, d = 4096:
-// 119.0 ms against 109.3 in two).
+// 119.0 ms against 109.3 in two).  The three factors rest on these eight launches of three batches, all against V = 151936.
 static constexpr double CUT_COHORTS = 1.05, MORE_RANGES = 0.017, ONE_RANGE = 1.09;
 
 // what a plan takes if a range of its takes range_ns

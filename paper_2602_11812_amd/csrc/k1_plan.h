@@ -32,9 +32,10 @@ constexpr long K1_MAX_CONTRACTION = 4194240;
 // the vocabulary into `nsplit` ranges of `tiles_per_split` tiles of `tile_v` rows; each
 // (token block, vocabulary range) pair is one workgroup and leaves one partial (m, S, U)
 // triple per token.
-// vocabulary rows per tile of the kernel for few tokens (the other kernel's tiles have 256)
+// vocabulary rows per tile of the narrow kernel, for few tokens (the wide kernel's tiles have 256)
 constexpr int K1_NARROW_TILE_V = 128;
-// ... and tokens per block and rows per tile of the kernel between the two
+// ... and tokens per block and rows per tile of the stream kernel, for the largest batches and for those between the
+// other two
 constexpr int K1_STREAM_TOKENS = 128, K1_STREAM_TILE_V = 64;
 constexpr int K1_STREAM_PACE_TILES = 16;  // its pacing points, in tiles
 // A sweep of its may straddle two packed 256-row tiles of W_lm, 16 KiB per K step each, under one 32-bit byte offset:

@@ -1,4 +1,4 @@
-// Pieces shared by the two fused entropy kernels (Eq. 2): loads from memory straight into the LDS ring, the
+// Pieces shared by the three fused entropy kernels (Eq. 2): loads from memory straight into the LDS ring, the
 // matching wait, and the fold of a tile's logits into a token's streaming statistics.  Device-side header.
 #pragma once
 #include "k1_common.h"

@@ -5,7 +5,8 @@
 // reads 1 KiB of one token row at a time).  A sequence is cut into units of at most 256 tokens
 // (fewer in a small batch) so that long and short sequences load the chip evenly; each unit leaves a
 // partial weighted sum relative to its own largest entropy, with that reference and the sum of its weights, and a
-// finalize kernel joins a sequence's units in order.  No atomics: bit-reproducible.
+// finalize kernel joins a sequence's units in order.  No atomics: a call is bit-reproducible.  The unit follows the
+// batch, so a sequence's sums are grouped differently beside other sequences.
 //
 // Units need no table: sequence b owns the unit numbers from offsets[b] / unit + b on.  Consecutive sequences
 // never meet, because ceil((y - x) / unit) <= floor(y / unit) - floor(x / unit) + 1; of the

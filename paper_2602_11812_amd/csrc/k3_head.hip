@@ -222,7 +222,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 // lane l reads chunk l / 16 of row l % 16, i.e. four neighbouring K elements that feed four MFMAs (an MFMA then
 // contracts elements s, 4 + s, 8 + s, 12 + s of the sixteen: the order inside a sum, the same for both operands).  The
 // next chunk's global loads are in flight during the current one's MFMAs; two LDS buffers.
-// Measured: 1024 sequences, d = 4096, d_h = 1024: 119 us with 64 x 64 tiles of fp32 FMAs, now 86 = 100 TFLOP/s.
+// Measured: 1024 sequences, d = 4096, d_h = 1024: 119 us with 64 x 64 tiles of fp32 FMAs, now 86 to 90 = 95 to 100 TFLOP/s.
 constexpr int FJ = 128, FK = 16;
 constexpr int F32_WORKGROUPS = 512;  // workgroups asked for by splitting along d
 

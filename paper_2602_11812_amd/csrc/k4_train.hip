@@ -12,8 +12,8 @@
 //                          is never written unless the caller asks for a copy.  With the
 //                          paper's batch of 16 this part is a pure stream over W1 and its two
 //                          moments (read and written once each).
-//      small parameters    gradient of W2, b2 and b1 reduced over the batch in a fixed order,
-//                          AdamW applied in the same thread
+//      small parameters    gradient of W2, b2 and b1, 64 columns a workgroup, reduced over the batch in a fixed
+//                          order and consumed by AdamW on the spot
 //      loss                fixed-order sum of the per-sample terms (the last workgroup)
 // No floating-point atomics anywhere: results are bit-reproducible.
 #include "kernels.h"
@@ -259,7 +259,7 @@ __device__ __forceinline__ void column_update(const float *__restrict__ mat, lon
 // Both operands lie with the sample as the slow index, so a K step of four samples is staged and read as rows: lane l
 // reads row j = l % 16 and four neighbouring k of sample 4 s + l / 16, which makes column tile n of a wave the
 // columns 4 (column) + n; a lane then ends up with four neighbouring columns of a row, one 16-byte access each to W1
-// and the moments.  Batch 1024: 390 us with 64 x 64 tiles of fp32 FMAs, now 95.
+// and the moments.  Batch 1024, the launch with its small parameters: 390 us with 64 x 64 tiles of fp32 FMAs, now 117 to 120.
 // 64 x 64 per workgroup, 32 samples per LDS stage.  128 x 128 tiles halve the operand traffic and gain nothing for it
 // (whole step at batch 1024, d = 4096, d_h = 1024: 198 us against 199) while few of them leave the chip idle (batch
 // 1024, d = 1024, d_h = 300: 131 us against 65).

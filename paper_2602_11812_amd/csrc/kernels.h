@@ -47,8 +47,8 @@ inline hipError_t raise_dynamic_lds_limit(const void *kernel, int bytes, DeviceM
 constexpr int K1_PACK_K = 32;
 constexpr int K1_PACK_ROWS = 256;
 constexpr int K1_PACK_BLOCK_BYTES = K1_PACK_ROWS * K1_PACK_K * 2;
-// Hidden states for the narrow kernel use row tiles of the plan's tb_tokens instead of 256 rows (`tile_rows`, a
-// multiple of 64 up to 256); everything else is the same.
+// Hidden states for the narrow and the stream kernel use row tiles of the plan's tb_tokens instead of 256 rows
+// (`tile_rows`, a multiple of 64 up to 256); everything else is the same.
 size_t k1_packed_bytes(int64_t rows, int K);
 hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, hipStream_t st);
 // fp32 rows (d % 4 == 0) into the six K segments of the W_lm side or of the hidden-state side
@@ -129,9 +129,10 @@ struct HeadArgs {
     float *pred;              // [B]
     float *p_hat;             // [B x n_out] softmax over the bins (Eq. 6), or NULL; n_out > 1 only
 };
-// Number of partial pre-activation planes layer 1 leaves: it is split along d so that about a
-// thousand workgroups exist whatever the batch (a small batch gets many thin slices); a small batch on fp32
-// weights is served by a kernel of its own that leaves one plane per 512 elements of d.
+// Number of partial pre-activation planes layer 1 leaves: it is split along d so that the chip is filled whatever the
+// batch (a small batch gets many thin slices): into about a thousand 64 x 64 tiles' worth with bf16 weights, 512
+// workgroups of larger tiles with fp32 weights.  At most sixteen sequences on fp32 weights are served by a kernel of
+// its own that leaves one plane per 512 elements of d.
 int head_k_splits(int d, int d_h, int32_t B, int wdtype);
 // floats of partial planes sufficient for every batch of at most B sequences
 size_t head_act_floats_bound(int d, int d_h, int32_t B, int wdtype);
