@@ -298,17 +298,24 @@ void plan_checks()
     using namespace egtp;
     const int vocabs[] = {1, 255, 256, 257, 1000, 4096, 32000, 128037, 151936, 1 << 20};
     const int64_t big[] = {65536, 137720, 1000000, 16777216, 0x7fffffffLL};
+    const int widths[] = {8, 208, 1024, 4096};  // the choice between the kernels depends on the contraction
+    int kinds = 0, whole = 0;
     for (int dtype = 0; dtype < 2; ++dtype)
-        for (int V : vocabs) {
+        for (int i = 0; i < 40; ++i) {
+            const int V = vocabs[i % 10], d = widths[i / 10];
             size_t worst_part = 0, worst_pace = 0;
             auto one = [&](int64_t T) {
-                const K1Plan p = k1_plan(dtype, T, 4096, V);
+                const K1Plan p = k1_plan(dtype, T, d, V);
+                kinds |= p.tile_v;
+                whole += p.whole_cohorts;
                 CHECK(p.ntb == (T + p.tb_tokens - 1) / p.tb_tokens && p.ntiles_v == (V + p.tile_v - 1) / p.tile_v);
                 CHECK(p.nsplit >= 1 && p.tiles_per_split >= 1);
                 CHECK((int64_t)p.nsplit * p.tiles_per_split >= p.ntiles_v);           // the ranges cover the vocabulary
                 CHECK((int64_t)(p.nsplit - 1) * p.tiles_per_split < p.ntiles_v);      // and none of them is empty
                 const size_t part = k1_partial_floats(p, T);
-                const size_t pace = (size_t)8 * (size_t)k1_pace_cohorts((long)p.ntb * p.nsplit);
+                const size_t pace = p.whole_cohorts ? (size_t)k1_stream_cohorts(p.ntb, p.nsplit)
+                                                    : (size_t)8 * (size_t)k1_pace_cohorts((long)p.ntb * p.nsplit);
+                CHECK((int64_t)p.ntb * p.tb_tokens <= (T + 255) / 256 * 256);         // packed hidden states: whole 256-row tiles
                 worst_part = part > worst_part ? part : worst_part;
                 worst_pace = pace > worst_pace ? pace : worst_pace;
                 // a workspace sized for T serves every smaller batch: the bounds cover the worst seen so far
@@ -321,6 +328,7 @@ void plan_checks()
                 for (int64_t dT = -2; dT <= 0; ++dT)
                     one(T + dT);
         }
+    CHECK(kinds == (256 | K1_NARROW_TILE_V | K1_STREAM_TILE_V) && whole > 0);         // every kernel's plans were among them
     // the paced configuration is the one with more than K1_PACE_TILES tiles per range
     const K1Plan serving = k1_plan(DT_BF16, 137720, 4096, 151936);
     CHECK(serving.tiles_per_split > K1_PACE_TILES && k1_plan_paces(serving));
