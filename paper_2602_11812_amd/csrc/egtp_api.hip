@@ -153,9 +153,9 @@ egtp_status run_entropy(egtp_ctx *ctx, const void *hidden, int64_t T, const Work
     if (timed)
         EGTP_HIP(hipEventRecord(ctx->prof_events[2 * ctx->prof_count], st));
     const int K = (int)k1_contraction_len(c.dtype, c.d);
-    if (p.tile_v == K1_NARROW_TILE_V)
+    if (p.tile_v == K1_NARROW_TILE_V && p.tb_tokens == K1_NARROW_TOKENS)
         EGTP_HIP(k1_entropy_narrow(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, st));
-    else if (p.tile_v == K1_STREAM_TILE_V)
+    else if (p.tile_v != K1_WIDE_TILE_V)
         EGTP_HIP(k1_entropy_stream(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
     else
         EGTP_HIP(k1_entropy_bf16(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));

@@ -282,9 +282,9 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_bf16_kernel(
                         acc[4 * h + q][ni][i] = 0.f;
                     }
                 if (masked)
-                    fold16<true>(z, st[ni], row_base + h * 64, V);
+                    fold<true>(z, st[ni], row_base + h * 64, V);
                 else
-                    fold16<false>(z, st[ni], row_base + h * 64, V);
+                    fold<false>(z, st[ni], row_base + h * 64, V);
             }
         }
         if (pace_now) {

@@ -3,19 +3,19 @@
 // kernel; what differs is the tile and what bounds it.
 //
 // A few tokens make the sweep a stream over W_lm, and a 256-token tile pays for its empty columns in matrix-core
-// time and in power.  Here a token block is 32 NI tokens (NI = 2 or 6), a vocabulary tile 128 rows (half a
-// packed block: 8 contiguous KiB per K step), so that a step's MFMAs (8 NI per wave) hide under the step's share
+// time and in power.  Here a token block is 64 tokens, a vocabulary tile 128 rows (half a
+// packed block: 8 contiguous KiB per K step), so that a step's MFMAs (8 per wave) hide under the step's share
 // of the memory stream and the vocabulary divides more evenly over the compute units.  The LDS ring is as deep as
 // the LDS allows: what it holds in flight per compute unit sets the rate of the stream.
 //
-// Workgroup = 4 waves (2 along vocabulary x 2 along tokens), wave tile 64 x 16 NI = 4 x NI MFMA 16x16x32 tiles.
+// Workgroup = 4 waves (2 along vocabulary x 2 along tokens), wave tile 64 x 32 = 4 x 2 MFMA 16x16x32 tiles.
 // One barrier per step: behind it every wave's loads of the next step have landed and every wave's fragment reads
 // of the current step have returned, so its stage can be loaded again; fragments are read one step ahead of
 // their MFMAs into two register sets that swap roles (the loop is unrolled by two, K is an even number of steps).
 //
 // Measured: 64 tokens against V = 151936, d = 4096: 199 us = 6.3 TB/s of W_lm (the 256 x 256 tile: 286 us on 198 of the
-// 256 compute units); 192 tokens 261 (LDS: fill plus fragment reads of 20 KiB steps) against 280; 309 fp32 tokens
-// against V = 4096, d = 256: 15.4 us, 37.1 before.  Two K steps per barrier gain nothing at NI = 2 and cost 20 % at 6.
+// 256 compute units); 309 fp32 tokens against V = 4096, d = 256: 15.4 us, 37.1 before.  Two K steps per barrier gain
+// nothing.  (Blocks of 192 tokens, which ran on this kernel as well, are the stream kernel's now.)
 #include "k1_stream.h"
 
 namespace egtp {
@@ -26,23 +26,20 @@ constexpr int W_STEP_BYTES = NM * ROW_BYTES;   // 8 KiB
 constexpr int TB_GROUP = 8;                    // token blocks that sweep the same vocabulary range together
 static_assert(NM == 128 && TILE_BYTES == 2 * W_STEP_BYTES, "a vocabulary tile is half a packed block");
 
-template <int NI>
-struct Ring {
-    static constexpr int H_STEP_BYTES = 32 * NI * ROW_BYTES;
-    static constexpr int STAGE_BYTES = W_STEP_BYTES + H_STEP_BYTES;
-    static constexpr int LOADS = STAGE_BYTES / 4096;             // 16-byte loads per lane and step
-    static constexpr int STAGES = 144 * 1024 / STAGE_BYTES;      // 12 and 7 stages for NI = 2 and 6
-    static constexpr int BYTES = STAGES * STAGE_BYTES;
-    static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "ring depth");
-};
+constexpr int NI = K1_NARROW_TOKENS / 32;            // token fragments of a wave
+constexpr int H_STEP_BYTES = K1_NARROW_TOKENS * ROW_BYTES;
+constexpr int STAGE_BYTES = W_STEP_BYTES + H_STEP_BYTES;
+constexpr int LOADS = STAGE_BYTES / 4096;           // 16-byte loads per lane and step
+constexpr int STAGES = 144 * 1024 / STAGE_BYTES;    // 12
+constexpr int RING_BYTES = STAGES * STAGE_BYTES;
+static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "ring depth");
 
-template <int NI, bool STREAM_W>
+template <bool STREAM_W>
 __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigned char *__restrict__ Wp,
                                                                    const unsigned char *__restrict__ Hp, long T, int KT,
                                                                    int V, int ntb, int nsplit, int ntiles_v,
                                                                    float *__restrict__ part)
 {
-    using R = Ring<NI>;
     extern __shared__ __align__(16) unsigned char smem[];
 
     const int tid = threadIdx.x;
@@ -77,7 +74,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     // ---- global -> LDS: a block is copied linearly, 1 KiB per wave-wide load
     const int lane_off = wave * 1024 + lane * 16;
     const int w_tile_bytes = KT * TILE_BYTES;  // (the launcher checks the range)
-    const int h_tile_bytes = KT * R::H_STEP_BYTES;
+    const int h_tile_bytes = KT * H_STEP_BYTES;
     const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
     unsigned char *lds_wave = smem + wave * 1024;
     // The load stream runs ahead of the MFMAs by the ring.  Past the end it keeps re-reading the last step (into
@@ -87,13 +84,13 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
         lvt = __builtin_amdgcn_readfirstlane(lvt);  // a descriptor must be uniform, and known to be
         const __amdgpu_buffer_rsrc_t rW = raw_buffer(Wp + (long)(lvt >> 1) * w_tile_bytes, w_tile_bytes);
         const int woff = lkt * TILE_BYTES + (lvt & 1) * W_STEP_BYTES;
-        const int hoff = lkt * R::H_STEP_BYTES;
-        unsigned char *dst = lds_wave + stage * R::STAGE_BYTES;
+        const int hoff = lkt * H_STEP_BYTES;
+        unsigned char *dst = lds_wave + stage * STAGE_BYTES;
 #pragma unroll
         for (int p = 0; p < W_STEP_BYTES / 4096; ++p)
             load16_to_lds<STREAM_W>(rW, lane_off, woff + p * 4096, dst + p * 4096);
 #pragma unroll
-        for (int p = 0; p < R::H_STEP_BYTES / 4096; ++p)
+        for (int p = 0; p < H_STEP_BYTES / 4096; ++p)
             load16_to_lds(rH, lane_off, hoff + p * 4096, dst + W_STEP_BYTES + p * 4096);
         const int adv = lstep + 1 < total ? 1 : 0;
         lstep += adv;
@@ -114,7 +111,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
         bf16x8 a[4], b[NI];
     };
     auto read_frags = [&](Frags &f, int stage) {
-        const unsigned char *s = smem + stage * R::STAGE_BYTES;
+        const unsigned char *s = smem + stage * STAGE_BYTES;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             f.a[i] = *(const bf16x8 *)(s + fragA + i * FRAG_STRIDE);
@@ -136,9 +133,9 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     }
 
 #pragma unroll
-    for (int s = 0; s < R::STAGES; ++s)
+    for (int s = 0; s < STAGES; ++s)
         issue_loads(s);
-    wait_vmcnt<(R::STAGES - 1) * R::LOADS>();
+    wait_vmcnt<(STAGES - 1) * LOADS>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     Frags f0, f1;
@@ -149,11 +146,11 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     // in flight) and for this wave's own fragment reads, meet the other waves, refill the stage just freed, read the
     // next fragments, multiply.  A bare barrier: a fence would drain the ring.
     auto step = [&](const Frags &cur, Frags &next) {
-        wait_vmcnt<(R::STAGES - 2) * R::LOADS>();
+        wait_vmcnt<(STAGES - 2) * LOADS>();
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        const int nstage = cstage + 1 == R::STAGES ? 0 : cstage + 1;
+        const int nstage = cstage + 1 == STAGES ? 0 : cstage + 1;
         read_frags(next, nstage);
         issue_loads(cstage);
 #pragma unroll
@@ -184,9 +181,9 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
                     acc[q][ni][i] = 0.f;
                 }
             if (masked)
-                fold16<true>(z, st[ni], row_base, V);
+                fold<true>(z, st[ni], row_base, V);
             else
-                fold16<false>(z, st[ni], row_base, V);
+                fold<false>(z, st[ni], row_base, V);
         }
     }
     wait_vmcnt<0>();
@@ -236,16 +233,16 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     }
 }
 
-template <int NI, bool STREAM_W>
+template <bool STREAM_W>
 hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p,
                   float *part, hipStream_t st)
 {
     static DeviceMask lds_limit_raised{0};
-    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<NI, STREAM_W>, Ring<NI>::BYTES,
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<STREAM_W>, RING_BYTES,
                                                  lds_limit_raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((k1_entropy_narrow_kernel<NI, STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), Ring<NI>::BYTES,
+    hipLaunchKernelGGL((k1_entropy_narrow_kernel<STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), RING_BYTES,
                        st, (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
                        p.nsplit, p.ntiles_v, part);
     return hipGetLastError();
@@ -257,22 +254,15 @@ hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, in
                              const K1Plan &p, float *part, hipStream_t st)
 {
     const int kt = k_steps(K);
-    if (T <= 0 || p.tile_v != NM || p.nsplit < 1 || p.nsplit > p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
+    if (T <= 0 || p.tb_tokens != K1_NARROW_TOKENS || p.tile_v != NM || p.nsplit < 1 || p.nsplit > p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
         (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + NM - 1) / NM || (long)kt * TILE_BYTES > 0x7fffffffL)
         return hipErrorInvalidValue;
     // One token block reads W_lm once.  If the 256 MiB Infinity Cache cannot hold it until the next call either, its
     // loads carry the non-temporal hint: 64 tokens, d = 4096, V = 151936 (1.24 GB) 225 -> 199 us = 6.3 TB/s; V = 65536
     // and d = 2560 (336 MB) 60.5 -> 55.7; but V = 65536 and d = 2048 (268 MB) 44 -> 46 and V = 32000 (131 MB) 25 -> 26.
     const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * kt * W_STEP_BYTES > ((int64_t)256 << 20);
-#define EGTP_NARROW(NI)                                                                   \
-    (stream ? launch<NI, true>(hidden_packed, w_packed, T, kt, V, p, part, st)            \
-            : launch<NI, false>(hidden_packed, w_packed, T, kt, V, p, part, st))
-    switch (p.tb_tokens) {
-    case 64: return EGTP_NARROW(2);
-    case 192: return EGTP_NARROW(6);
-    }
-#undef EGTP_NARROW
-    return hipErrorInvalidValue;
+    return stream ? launch<true>(hidden_packed, w_packed, T, kt, V, p, part, st)
+                  : launch<false>(hidden_packed, w_packed, T, kt, V, p, part, st);
 }
 
 }  // namespace egtp

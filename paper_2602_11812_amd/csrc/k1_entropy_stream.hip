@@ -2,19 +2,28 @@
 // and for those between the other two kernels.  Same formulation, packed W_lm and partial triples as theirs; what
 // differs is the way of W_lm to the matrix cores.
 //
-// A token block is 128 tokens and a wave works alone on its rows of W_lm: a 16-row fragment of a packed block is one
-// contiguous KiB in exactly the order the MFMA wants, so the wave loads it straight into registers (two K steps
-// ahead) and it never passes through the LDS.  Only the hidden states do, 8 KiB per K step shared by the four
+// A token block is 128 or 192 tokens and a wave works alone on its rows of W_lm: a 16-row fragment of a packed block is
+// one contiguous KiB in exactly the order the MFMA wants, so the wave loads it straight into registers (D K steps
+// ahead) and it never passes through the LDS.  Only the hidden states do, 8 or 12 KiB per K step shared by the four
 // waves -- per product less than half the LDS traffic of a tile that stages both operands.  Rows are dealt
-// to waves in single fragments: a wave sweeps eight of them at a time (8 x 8 MFMA 16x16x32 tiles, 128 rows x 128
-// tokens) and the remainder in a shorter sweep of two, four or six, so the vocabulary divides
-// evenly over the compute units whatever its size.
+// to waves in single fragments, so the vocabulary divides evenly over the compute units whatever its size:
+//   128 tokens  a wave sweeps eight fragments at a time (8 x 8 MFMA 16x16x32 tiles, 128 rows x 128 tokens) and the
+//               remainder in a shorter sweep of two, four or six;
+//   192 tokens  four fragments at a time (4 x 12 tiles), the remainder in a sweep of two; two fragments to a vocabulary
+//               tile.  Half as many rows in flight per step, hence four steps ahead where K is a multiple of four
+//               steps (two sets of registers would hold 32 KiB of W_lm per compute unit in flight, four hold 64).
 //
 // Bound: bf16 MFMA at the package power limit for large batches, the read of W_lm for one token block.  Measured
 // against the 256 x 256 tile, same box: 137720 tokens, d = 4096, V = 151936 118.6 -> 114.7 ms = 1.49 PFLOP/s; 65088
 // tokens, d = 5120 70.5 -> 64.7 = 1.56 PFLOP/s; 4000 tokens 3.57 -> 3.37; 384 tokens 447 -> 378 us; 128 tokens 280 ->
 // 199 us.  No faster: the barrier in the middle of a step (3 % slower), other spacings of the loads, four or eight ring
 // stages, a pacing point every sweep or every fourth.
+// 192 tokens: what limits a sweep beside the stream is the way from the L2 into the compute unit, about 42 bytes/ns
+// whatever the kernel: per 256 rows and K step 28 KiB here, 40 with both operands through the LDS (the narrow kernel's
+// tile, which served these batches before): 173 tokens against V = 151936 285 to 325 -> 236 to 257 us by box, V = 70812,
+// d = 1800 77 -> 64.  No faster: two waves side by side on the same rows, 96 tokens each (less LDS traffic, but every
+// fragment of W_lm loaded twice: 316 us), five fragments at a time (registers spill: 315).  For 256 tokens the pair of
+// waves gives the 256 x 256 tile's times within 2 %, and a wave of its own on 64 rows x 256 tokens spills: not built.
 //
 // Pacing is that of the 256 x 256 kernel: cohorts of 32 workgroups that share blocks in an XCD's L2 count themselves in
 // every second sweep and wait, bounded, for the rest; a hint that no result depends on.
@@ -25,16 +34,24 @@
 namespace egtp {
 namespace {
 
-constexpr int BN = K1_STREAM_TOKENS;            // tokens per block
-constexpr int H_STEP_BYTES = BN * ROW_BYTES;    // 8 KiB
-constexpr int FRAG_BYTES = 16 * ROW_BYTES;      // 16 rows of one K step
+constexpr int FRAG_BYTES = 16 * ROW_BYTES;  // 16 rows of one K step
 
-constexpr int H_LOADS = H_STEP_BYTES / 4096;    // 16-byte loads per lane and step
-constexpr int NI = BN / 16;                     // token fragments
-constexpr int MAX_MI = 8;                       // vocabulary fragments of a wave's longest sweep
-constexpr int H_STAGES = 6;
-constexpr int PACE_SWEEPS = K1_STREAM_PACE_TILES / MAX_MI;  // sweeps between two pacing points
-static_assert(K1_STREAM_TILE_V == 64, "a tile is one fragment for each of the four waves");
+// The two shapes: a token block is 16 NI tokens, a wave's longest sweep MAX_MI fragments of 16 rows (together they fill the
+// accumulators), a tile of the plan FPW fragments for each of the four waves, and the ring holds STAGES K steps of hidden states.
+template <int NI>
+struct Shape {
+    static constexpr int TOKENS = 16 * NI;
+    static constexpr int MAX_MI = NI == 8 ? 8 : 4;
+    static constexpr int FPW = NI == 8 ? 1 : 2;
+    static constexpr int STAGES = NI == 8 ? 6 : 8;
+    static constexpr int H_STEP_BYTES = TOKENS * ROW_BYTES;
+    static constexpr int H_LOADS = H_STEP_BYTES / 4096;  // 16-byte loads per lane and step
+    static constexpr int LDS_BYTES = STAGES * H_STEP_BYTES;
+    static_assert((STAGES - 2) * (H_LOADS + MAX_MI) < 64, "one wait covers the ring");
+};
+static_assert(Shape<8>::TOKENS == K1_STREAM_TOKENS && Shape<8>::FPW * 64 == K1_STREAM_TILE_V, "plan");
+static_assert(Shape<12>::TOKENS == K1_STREAM_WIDE_TOKENS && Shape<12>::FPW * 64 == K1_NARROW_TILE_V, "plan");
+constexpr int PACE_SWEEPS = K1_STREAM_PACE_TILES / Shape<8>::MAX_MI;  // sweeps between two pacing points
 static_assert(2L * K1_STREAM_MAX_STEPS * TILE_BYTES <= 0x7fffffffL, "two packed tiles under one offset");
 
 template <bool STREAM_W>
@@ -44,12 +61,15 @@ __device__ __forceinline__ bf16x8 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int
                                                                            STREAM_W ? 2 : 0));
 }
 
-template <bool STREAM_W>
+template <int NI, int D, bool STREAM_W>
 __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigned char *__restrict__ Wp,
                                                                    const unsigned char *__restrict__ Hp, long T, int KT,
                                                                    int V, int ntb, int nsplit, int tps, int ntiles_v, int group, bool whole_cohorts,
                                                                    float *__restrict__ part, int *__restrict__ pace)
 {
+    using S = Shape<NI>;
+    constexpr int MAX_MI = S::MAX_MI, FPW = S::FPW, H_STAGES = S::STAGES;
+    constexpr int H_STEP_BYTES = S::H_STEP_BYTES, H_LOADS = S::H_LOADS;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -100,10 +120,17 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
         tb = __builtin_amdgcn_readfirstlane(tb);
     }
     // this range's tiles = so many fragments for each wave
-    const int vt_begin = sp * tps;
-    const int count = min(tps, ntiles_v - vt_begin);
-    const int f_begin = 4 * vt_begin + wave * count, f_end = f_begin + count;
-    const long tok0 = (long)tb * BN;
+    int vt_begin, count;
+    if (FPW == 2) {  // the first ntiles_v % nsplit ranges hold one tile more than the others
+        const int per_range = ntiles_v / nsplit, longer = ntiles_v - per_range * nsplit;
+        vt_begin = sp * per_range + min(sp, longer);
+        count = per_range + (sp < longer ? 1 : 0);
+    } else {
+        vt_begin = sp * tps;
+        count = min(tps, ntiles_v - vt_begin);
+    }
+    const int f_begin = FPW * (4 * vt_begin + wave * count), f_end = f_begin + FPW * count;
+    const long tok0 = (long)tb * S::TOKENS;
     const int row_end = min(V, f_end * 16);
 
     // ---- W_lm: the fragments of a sweep, by scalar offsets from the packed block its first one lies in
@@ -124,7 +151,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
             frag_off[m] = __builtin_amdgcn_readfirstlane(((f >> 4) - blk) * w_tile_bytes + (f & 15) * FRAG_BYTES);
         }
     };
-    bf16x8 wr[2][MAX_MI];  // even and odd K steps, two steps ahead
+    bf16x8 wr[D][MAX_MI];
 
     // ---- hidden states: memory -> LDS ring, copied linearly, 1 KiB per wave-wide load; the same block sweep after sweep
     const int lane_h = wave * 1024 + lane * 16;
@@ -154,7 +181,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     for (int s = 0; s < H_STAGES; ++s)
         load_h(s);
 #pragma unroll
-    for (int s = 0; s < 2; ++s)
+    for (int s = 0; s < D; ++s)
 #pragma unroll
         for (int m = 0; m < MAX_MI; ++m)
             wr[s][m] = load_fragment<STREAM_W>(rW, lane_w, s * TILE_BYTES + frag_off[m]);
@@ -166,7 +193,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
         fb[0][ni] = *(const bf16x8 *)(smem + frag_h + ni * FRAG_BYTES);
     int cstage = 0;  // stage of the step whose MFMAs are next
 
-    // All K steps of MI fragments from f0 on, then the fold of their logits.  Before its last two steps the loads
+    // All K steps of MI fragments from f0 on, then the fold of their logits.  Before its last D steps the loads
     // move on to the fragments of the next sweep.
     auto sweep = [&](auto mi_const, int f0, bool masked) {
         constexpr int MI = decltype(mi_const)::value;
@@ -180,7 +207,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
         // newest H_STAGES - 2 steps' loads may be in flight; a step issues at least H_LOADS + MI of them) and every wave's
         // fragment reads of the current step have returned, so its stage can be loaded again.
         auto step = [&](auto p_const, int kt_load) {
-            constexpr int P = decltype(p_const)::value;
+            constexpr int P = decltype(p_const)::value, Q = P & 1;
             wait_vmcnt<(H_STAGES - 2) * (H_LOADS + MI)>();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
             __builtin_amdgcn_s_barrier();
@@ -194,15 +221,15 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
                 if (mi == 0) {
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni)
-                        fb[P ^ 1][ni] = *(const bf16x8 *)(s + ni * FRAG_BYTES);
+                        fb[Q ^ 1][ni] = *(const bf16x8 *)(s + ni * FRAG_BYTES);
                 } else {
-                    wr[P][mi - 1] = load_fragment<STREAM_W>(rW, lane_w, kt_load * TILE_BYTES + frag_off[mi - 1]);
+                    wr[P][mi - 1] = load_fragment<STREAM_W>(rW, lane_w, (kt_load + P) * TILE_BYTES + frag_off[mi - 1]);
                 }
                 if (mi == 1)
                     load_h(cstage);
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[P][mi], fb[P][ni], acc[mi][ni], 0, 0, 0);
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[P][mi], fb[Q][ni], acc[mi][ni], 0, 0, 0);
                 if (mi == 0) {
 #pragma unroll
                     for (int j = 0; j < NI; ++j) {
@@ -219,40 +246,47 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            wr[P][MI - 1] = load_fragment<STREAM_W>(rW, lane_w, kt_load * TILE_BYTES + frag_off[MI - 1]);
+            wr[P][MI - 1] = load_fragment<STREAM_W>(rW, lane_w, (kt_load + P) * TILE_BYTES + frag_off[MI - 1]);
             cstage = nstage;
             __builtin_amdgcn_sched_barrier(0);
         };
-        const std::integral_constant<int, 0> even{};
-        const std::integral_constant<int, 1> odd{};
-        for (int kt = 2; kt < KT; kt += 2) {
-            step(even, kt);
-            step(odd, kt + 1);
-        }
+        auto steps = [&](int kt_load) {
+            step(std::integral_constant<int, 0>{}, kt_load);
+            step(std::integral_constant<int, 1>{}, kt_load);
+            if constexpr (D == 4) {
+                step(std::integral_constant<int, 2>{}, kt_load);
+                step(std::integral_constant<int, 3>{}, kt_load);
+            }
+        };
+        for (int kt = D; kt < KT; kt += D)
+            steps(kt);
         set_rows(f0 + MI);
-        step(even, 0);
-        step(odd, 1);
+        steps(0);
 
         const int row0 = f0 * 16 + 4 * kq;
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
 #pragma unroll
             for (int h = 0; h < MI; h += 4) {
-                constexpr int N = 16;
-                float z[N];
+                // fragments folded at once (128 tokens: a remainder of two is folded with two that do not exist;
+                // without them the compiler orders the loads of the long sweeps worse, 1 % of their time)
+                constexpr int N = NI > 8 && MI < 4 ? MI : 4;
+                float z[4 * N];
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < N; ++q)
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
                         z[4 * q + i] = h + q < MI ? acc[h + q < MI ? h + q : 0][ni][i] : NEG_BIG;
-                if (masked || MI % 4 != 0)
-                    fold16<true>(z, st[ni], row0 + h * 16, h + 4 > MI ? min(row_end, (f0 + MI) * 16) : row_end);
+                if (masked || MI % N != 0)
+                    fold<true>(z, st[ni], row0 + h * 16, h + 4 > MI ? min(row_end, (f0 + MI) * 16) : row_end);
                 else
-                    fold16<false>(z, st[ni], row0 + h * 16, V);
+                    fold<false>(z, st[ni], row0 + h * 16, row_end);
             }
+            if (NI > 8)
+                __builtin_amdgcn_sched_barrier(0);  // (one token at a time, for the registers)
         }
     };
-    const int max_sweeps = (tps + MAX_MI - 1) / MAX_MI;
+    const int max_sweeps = (tps * FPW + MAX_MI - 1) / MAX_MI;
     int sweeps = 0;
     for (int f = f_begin; f < f_end;) {
         const int rest = f_end - f;
@@ -276,14 +310,18 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
             }
         }
         ++sweeps;
-        if (rest > 4) {
-            sweep(std::integral_constant<int, 8>{}, f, rest < 8 || (f + 8) * 16 > V);
-            f += 8;
-        } else if (rest > 2) {
+        if constexpr (MAX_MI == 8) {
+            if (rest > 4) {
+                sweep(std::integral_constant<int, 8>{}, f, rest < 8 || (f + 8) * 16 > V);
+                f += 8;
+                continue;
+            }
+        }
+        if (rest > 2) {
             sweep(std::integral_constant<int, 4>{}, f, rest < 4 || (f + 4) * 16 > V);
             f += 4;
         } else {
-            sweep(std::integral_constant<int, 2>{}, f, true);
+            sweep(std::integral_constant<int, 2>{}, f, rest < 2 || (f + 2) * 16 > V);
             f += 2;
         }
     }
@@ -312,19 +350,19 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     if (lane < 16) {
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            float *r = red + (wave * BN + ni * 16 + lane) * 3;
+            float *r = red + (wave * S::TOKENS + ni * 16 + lane) * 3;
             r[0] = st[ni].m;
             r[1] = st[ni].S;
             r[2] = st[ni].U;
         }
     }
     __syncthreads();
-    if (tid < BN && tok0 + tid < T) {
+    if (tid < S::TOKENS && tok0 + tid < T) {
         Stats a;
         a.m = red[tid * 3], a.S = red[tid * 3 + 1], a.U = red[tid * 3 + 2];
 #pragma unroll
         for (int k = 1; k < 4; ++k) {
-            const float *r = red + (k * BN + tid) * 3;
+            const float *r = red + (k * S::TOKENS + tid) * 3;
             Stats o;
             o.m = r[0], o.S = r[1], o.U = r[2];
             a = merge(a, o);
@@ -336,21 +374,35 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     }
 }
 
+template <int NI, int D, bool STREAM_W>
+hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p, int group,
+                  long wgs, float *part, int *pace, hipStream_t st)
+{
+    using S = Shape<NI>;
+    static_assert(4 * S::TOKENS * 3 * sizeof(float) <= S::LDS_BYTES, "LDS");
+    static DeviceMask lds_limit_raised{0};
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_stream_kernel<NI, D, STREAM_W>, S::LDS_BYTES,
+                                                 lds_limit_raised);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL((k1_entropy_stream_kernel<NI, D, STREAM_W>), dim3((unsigned)wgs), dim3(256), S::LDS_BYTES, st,
+                       (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
+                       p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V, const K1Plan &p,
                              float *part, int *pace, hipStream_t st)
 {
-    constexpr int LDS_BYTES = H_STAGES * H_STEP_BYTES;
-    static_assert(4 * BN * 3 * sizeof(float) <= LDS_BYTES && LDS_BYTES <= 64 * 1024, "LDS");
     const int kt = k_steps(K);
-    if (T <= 0 || p.tb_tokens != BN || p.tile_v != K1_STREAM_TILE_V || p.nsplit < 1 || p.tiles_per_split < 1 ||
-        (long)p.nsplit * p.tiles_per_split < p.ntiles_v || (long)(p.nsplit - 1) * p.tiles_per_split >= p.ntiles_v ||
-        (long)p.ntb * p.nsplit > 0x7fffffffL || (int64_t)p.ntb * BN < T ||
-        p.ntiles_v != (V + K1_STREAM_TILE_V - 1) / K1_STREAM_TILE_V || kt > K1_STREAM_MAX_STEPS)
+    if (T <= 0 || p.nsplit < 1 || p.tiles_per_split < 1 || (long)p.nsplit * p.tiles_per_split < p.ntiles_v ||
+        (long)(p.nsplit - 1) * p.tiles_per_split >= p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
+        (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + p.tile_v - 1) / p.tile_v || kt > K1_STREAM_MAX_STEPS)
         return hipErrorInvalidValue;
-    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * kt * 4 * FRAG_BYTES > ((int64_t)256 << 20);
-    const int group = k1_stream_group(p.nsplit);
+    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * p.tile_v * kt * ROW_BYTES > ((int64_t)256 << 20);
+    const int group = p.tile_v == K1_STREAM_TILE_V ? k1_stream_group(p.nsplit) : 8;
     const long units = (long)p.ntb * p.nsplit, cohorts = k1_stream_cohorts(p.ntb, p.nsplit);
     const long wgs = p.whole_cohorts ? 8 * ((cohorts + 7) / 8) * COHORT : units;
     if (wgs > 0x7fffffffL)
@@ -362,16 +414,15 @@ hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, in
         if (e != hipSuccess)
             return e;
     }
-    const dim3 grid((unsigned)wgs);
-    if (stream)
-        hipLaunchKernelGGL(k1_entropy_stream_kernel<true>, grid, dim3(256), LDS_BYTES, st,
-                           (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
-                           p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
-    else
-        hipLaunchKernelGGL(k1_entropy_stream_kernel<false>, grid, dim3(256), LDS_BYTES, st,
-                           (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
-                           p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
-    return hipGetLastError();
+#define EGTP_STREAM(NI, D)                                                                                     \
+    (stream ? launch<NI, D, true>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st)             \
+            : launch<NI, D, false>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st))
+    if (p.tb_tokens == K1_STREAM_TOKENS && p.tile_v == K1_STREAM_TILE_V)
+        return EGTP_STREAM(8, 2);
+    if (p.tb_tokens == K1_STREAM_WIDE_TOKENS && p.tile_v == K1_NARROW_TILE_V)
+        return kt % 4 == 0 ? EGTP_STREAM(12, 4) : EGTP_STREAM(12, 2);
+#undef EGTP_STREAM
+    return hipErrorInvalidValue;
 }
 
 }  // namespace egtp

@@ -19,19 +19,22 @@ static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number 
 // the load ring, final merge and stores) -- and no plan is faster than one read of W_lm (5.7 TB/s).
 //   wide     256 rows x 256 tokens        625 a step for a W_lm of 48 MB, 18.5 more per doubling up to 712 for 1.2 GB;
 //            5000 a tile
-//   narrow   128 rows x 32 NI tokens      115 + 45.6 NI a step, 312 NI a tile
+//   narrow   128 rows x 64 tokens         206 a step, 624 a tile
 //   stream   512 rows x 128 tokens        642 a step (+ 400 / token blocks: fewer of them share a read of W_lm), 6200
 //            a sweep; remainders of 4 and 2 fragments a wave 406 and 288, 3100 and 1550
-// The model picks the fastest measured plan or one within 2.5 % of it.  At d = 4096, V = 151936, in us (nothing was
-// measured from 193 to 256 tokens, where the wide tile runs on 198 of the compute units):
-//   tokens   24   100   173   300   512   800  1217  4000  20000   45000
-//   wide    286   280   280   425   475   860  1088  3525  18170   40950
-//   narrow  199   223   253   491
-//   stream  198   199   289   367   495   793  1123  3320  17450   38900
+//            256 rows x 192 tokens        700 a step, 4000 a sweep; the remainder of 128 rows 410 and 2000
+// The model picks the fastest measured plan or one within 2.5 % of it.  At d = 4096, V = 151936, in us (from 193 to 256
+// tokens the wide tile runs on 198 of the compute units: 288 to 297 by box for 230):
+//   tokens          24   100   173   300   512   800  1217  4000  20000   45000
+//   wide           286   280   280   425   475   860  1088  3525  18170   40950
+//   narrow         199
+//   stream, 128    198   199   289   367   495   793  1123  3320  17450   38900
+//   stream, 192                236
 // (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964, where WORTH_IT
 // keeps the wide tile -- the 2.5 %; at d = 256 the folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
 static constexpr double WIDE_STEP_NS = 625.0, WIDE_STEP_NS_PER_DOUBLING = 18.5, WIDE_W_BYTES = 48e6, WIDE_FOLD_NS = 5000.0;
-static constexpr double NARROW_STEP_NS = 115.0, NARROW_STEP_NS_PER_NI = 45.6, NARROW_FOLD_NS_PER_NI = 312.0;
+static constexpr double NARROW_STEP_NS = 206.0, NARROW_FOLD_NS = 624.0;
+static constexpr double PAIR_STEP_NS = 700.0, SINGLE_STEP_NS = 410.0, PAIR_FOLD_NS = 4000.0;
 static constexpr double STREAM_STEP_NS = 642.0, STREAM_ALONE_NS = 400.0, STREAM_FOLD_NS = 6200.0;
 static constexpr double STREAM_STEP4_NS = 406.0, STREAM_STEP2_NS = 288.0;
 static constexpr double WORKGROUP_NS = 3000.0, W_STREAM_BYTES_PER_NS = 5700.0;
@@ -101,14 +104,18 @@ static K1Plan cheaper(const K1Plan &p, int64_t T, int V, long steps)
     };
     K1Plan q;
     const int64_t blocks64 = (T + 63) / 64;
-    for (int ni = 2; ni <= 6 && blocks64 <= 32; ni += 4)
-        for (int rounds = 1; rounds <= 3; ++rounds) {
-            const int64_t ranges = (int64_t)rounds * NUM_CUS * 32 * ni / (blocks64 * 64);
+    for (int tokens = K1_NARROW_TOKENS; tokens <= K1_STREAM_WIDE_TOKENS && blocks64 <= 32;
+         tokens += K1_STREAM_WIDE_TOKENS - K1_NARROW_TOKENS)
+        for (int rounds = 1; rounds <= 3 && (tokens == K1_NARROW_TOKENS || steps <= K1_STREAM_MAX_STEPS); ++rounds) {
+            const int64_t ranges = (int64_t)rounds * NUM_CUS * tokens / (blocks64 * 64);
             if (ranges < 1)
                 continue;
-            cut(q, 32 * ni, K1_NARROW_TILE_V, ranges);
-            const double tile = (double)steps * (NARROW_STEP_NS + NARROW_STEP_NS_PER_NI * ni) + NARROW_FOLD_NS_PER_NI * ni;
-            const double ns = plan_ns(q, steps, q.tiles_per_split * tile);
+            cut(q, tokens, K1_NARROW_TILE_V, ranges);
+            const double range = tokens == K1_NARROW_TOKENS
+                                     ? q.tiles_per_split * ((double)steps * NARROW_STEP_NS + NARROW_FOLD_NS)
+                                     : (q.tiles_per_split / 2) * ((double)steps * PAIR_STEP_NS + PAIR_FOLD_NS) +
+                                           (q.tiles_per_split % 2) * ((double)steps * SINGLE_STEP_NS + PAIR_FOLD_NS / 2);
+            const double ns = plan_ns(q, steps, range);
             if (ns < best_ns && fits(q)) {
                 best_ns = ns;
                 best = q;

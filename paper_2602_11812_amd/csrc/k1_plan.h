@@ -32,11 +32,14 @@ constexpr long K1_MAX_CONTRACTION = 4194240;
 // the vocabulary into `nsplit` ranges of `tiles_per_split` tiles of `tile_v` rows; each
 // (token block, vocabulary range) pair is one workgroup and leaves one partial (m, S, U)
 // triple per token.
-// vocabulary rows per tile of the narrow kernel, for few tokens (the wide kernel's tiles have 256)
-constexpr int K1_NARROW_TILE_V = 128;
-// ... and tokens per block and rows per tile of the stream kernel, for the largest batches and for those between the
-// other two
+// rows per tile of the wide kernel (256 tokens a block); tokens per block and rows per tile of the narrow kernel, for
+// few tokens
+constexpr int K1_WIDE_TILE_V = 256;
+constexpr int K1_NARROW_TOKENS = 64, K1_NARROW_TILE_V = 128;
+// ... and of the stream kernel, for the largest batches and for those between the other two: 128 tokens against tiles of
+// 64 rows, or 192 against the narrow kernel's
 constexpr int K1_STREAM_TOKENS = 128, K1_STREAM_TILE_V = 64;
+constexpr int K1_STREAM_WIDE_TOKENS = 192;
 constexpr int K1_STREAM_PACE_TILES = 16;  // its pacing points, in tiles
 // A sweep of its may straddle two packed 256-row tiles of W_lm, 16 KiB per K step each, under one 32-bit byte offset:
 // half of what the other kernels address.

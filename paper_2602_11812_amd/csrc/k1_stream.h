@@ -41,16 +41,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const unsigned char
     return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000);
 }
 
-// Fold 16 logits of one token: zin[4*q+i] is vocabulary row row0 + 16*q + i.  MASK: rows from V on do not exist.
+// Fold N logits of one token: zin[4*q+i] is vocabulary row row0 + 16*q + i.  MASK: rows from V on do not exist.
 // Whether a lane has any row at all follows from the row numbers: its maximum cannot tell, fmaxf passes over NaN.
-template <bool MASK>
-__device__ __forceinline__ void fold16(const float (&zin)[16], Stats &st, int row0, int V)
+template <bool MASK, int N>
+__device__ __forceinline__ void fold(const float (&zin)[N], Stats &st, int row0, int V)
 {
     if (MASK && row0 >= V)
         return;  // nothing to add (and perhaps no reference maximum yet)
-    float z[16];
+    float z[N];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
+    for (int i = 0; i < N; ++i) {
         float v = zin[i];
         if (MASK)
             v = (row0 + 16 * (i >> 2) + (i & 3)) < V ? v : NEG_BIG;
@@ -58,7 +58,7 @@ __device__ __forceinline__ void fold16(const float (&zin)[16], Stats &st, int ro
     }
     float mx = z[0];
 #pragma unroll
-    for (int i = 1; i < 16; ++i)
+    for (int i = 1; i < N; ++i)
         mx = fmaxf(mx, z[i]);
     // The reference lives in log2 units, r = fl(max z * log2 e): every exponent is then ONE fused
     // multiply-add z * log2 e - r (exact product, one rounding of a small result) and re-referencing is an
@@ -74,7 +74,7 @@ __device__ __forceinline__ void fold16(const float (&zin)[16], Stats &st, int ro
     const float mc = -st.m;
     float S0 = 0.f, S1 = 0.f, U0 = 0.f, U1 = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; i += 2) {
+    for (int i = 0; i < N; i += 2) {
         float t0 = fmaf(z[i], LOG2E, mc);
         float t1 = fmaf(z[i + 1], LOG2E, mc);
         float e0 = fast_exp2(t0);
