@@ -18,5 +18,42 @@ __device__ __forceinline__ void split3_bits(float f, unsigned &hi, unsigned &mid
     lo = __float_as_uint(r2) & 0xffff0000u;
 }
 
+typedef __attribute__((ext_vector_type(8))) __bf16 split_bf16x8;
+typedef __attribute__((ext_vector_type(4))) unsigned split_u32x4;
+
+// the upper halves of two neighbours in one register
+__device__ __forceinline__ unsigned pack_halves(unsigned even, unsigned odd)
+{
+    return __builtin_amdgcn_perm(odd, even, 0x07060302u);
+}
+
+// two neighbours, packed piece by piece
+__device__ __forceinline__ void split3_pair(bool may_be_inf, float even, float odd, unsigned &hi, unsigned &mid, unsigned &lo)
+{
+    const float e1 = even - __uint_as_float(__float_as_uint(even) & 0xffff0000u);
+    const float o1 = odd - __uint_as_float(__float_as_uint(odd) & 0xffff0000u);
+    // an infinite value: its lower pieces are zero, not NaN
+    const float e1z = may_be_inf && __builtin_isinf(even) ? 0.f : e1, o1z = may_be_inf && __builtin_isinf(odd) ? 0.f : o1;
+    hi = pack_halves(__float_as_uint(even), __float_as_uint(odd));
+    mid = pack_halves(__float_as_uint(e1z), __float_as_uint(o1z));
+    lo = pack_halves(__float_as_uint(e1z - __uint_as_float(__float_as_uint(e1z) & 0xffff0000u)),
+                     __float_as_uint(o1z - __uint_as_float(__float_as_uint(o1z) & 0xffff0000u)));
+}
+
+// 8 fp32 values -> three bf16 fragments whose sum is exactly the input
+__device__ __forceinline__ void split3(const float (&f)[8], split_bf16x8 &hi, split_bf16x8 &mid, split_bf16x8 &lo)
+{
+    split_u32x4 ph, pm, pl;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        unsigned h, m, l;
+        split3_pair(false, f[2 * i], f[2 * i + 1], h, m, l);
+        ph[i] = h, pm[i] = m, pl[i] = l;
+    }
+    hi = __builtin_bit_cast(split_bf16x8, ph);
+    mid = __builtin_bit_cast(split_bf16x8, pm);
+    lo = __builtin_bit_cast(split_bf16x8, pl);
+}
+
 }  // namespace
 }  // namespace egtp

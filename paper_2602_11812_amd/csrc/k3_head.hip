@@ -3,7 +3,7 @@
 //
 // Layer 1 is a small [B x d] . [d x d_h] contraction kept entirely in fp32 (the pooled
 // vector is never re-rounded), on the fp32 matrix instructions where the weights are fp32 and the batch is more
-// than a handful.  The contraction is split along d so that several hundred workgroups exist even for one
+// than a handful, and as products of bf16 pieces where it is more than 64.  The contraction is split along d so that several hundred workgroups exist even for one
 // small batch; the splits leave partial pre-activations that layer 2 adds in split order
 // (fixed order, bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode are one
 // workgroup per sequence.
@@ -14,13 +14,17 @@
 // fp32, so three MFMAs per weight fragment accumulate the same products an fp32 dot product
 // would, in fp32.  Fragments come straight from global memory: a lane's 8 K-elements are 16
 // contiguous bytes of a weight row and 32 contiguous bytes of a pooled row.
-#include "bf16_split.h"
 #include "kernels.h"
 #include "partial_planes.h"
+#include "split_mfma.h"
 #include "wave_reduce.h"
 
 namespace egtp {
 namespace {
+
+typedef split_bf16x8 bf16x8;
+typedef split_f32x4 f32x4;
+typedef split_u32x4 u32x4;
 
 constexpr int TM = 64;  // head rows j per tile
 constexpr int TN = 64;  // sequences per tile
@@ -210,21 +214,18 @@ __global__ __launch_bounds__(256) void head_layer1_skinny_kernel(const float *__
         act_part[((long)blockIdx.y * B + b) * d_h + j] = acc[0];
 }
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-
-// Layer 1, fp32 weights, more sequences than the skinny kernel serves: fp32 matrix instructions (16x16x4, fp32
-// operands and accumulators: the precision of an FMA chain).  Bound: the fp32 matrix rate, 157 TFLOP/s -- a quarter of
-// a wave's MFMA time is enough for all its LDS reads, so the tile is as large as keeps every compute unit busy.
+// Layer 1, fp32 weights, 17 to F32_MAX_SEQS sequences: fp32 matrix instructions (16x16x4, fp32 operands and accumulators: the
+// precision of an FMA chain).  Bound: latency of the few chunks that a slice has.
 // Workgroup = 4 waves (2 x 2), FJ = 128 head rows x 32 NS sequences; wave = 64 x 16 NS = 4 x NS tiles, weights as the
 // row operand.  K is staged 16 elements at a time as 64-byte rows, 16-byte chunks XOR-ed with swizzle key (r >> 1) & 3:
 // lane l reads chunk l / 16 of row l % 16, i.e. four neighbouring K elements that feed four MFMAs (an MFMA then
 // contracts elements s, 4 + s, 8 + s, 12 + s of the sixteen: the order inside a sum, the same for both operands).  The
 // next chunk's global loads are in flight during the current one's MFMAs; two LDS buffers.
-// Measured: 1024 sequences, d = 4096, d_h = 1024: 119 us with 64 x 64 tiles of fp32 FMAs, now 86 to 90 = 95 to 100 TFLOP/s.
+// (On bf16 pieces, below, whose pipeline takes longer to fill: whole training steps with 32 and 64 samples 38.3 -> 41.0 us and
+// 45.8 -> 47.0; 71 samples, d = 4040 52.6 -> 51.1.)
 constexpr int FJ = 128, FK = 16;
 constexpr int F32_WORKGROUPS = 512;  // workgroups asked for by splitting along d
+constexpr int F32_MAX_SEQS = 64;
 
 template <int NS>
 __global__ __launch_bounds__(256) void head_layer1_f32_kernel(const float *__restrict__ x,
@@ -337,27 +338,119 @@ __global__ __launch_bounds__(256) void head_layer1_f32_kernel(const float *__res
     }
 }
 
-constexpr int MK = 32;  // K elements per MFMA step
+// Layer 1, fp32 weights, more sequences: fp32 products as bf16 pieces (split_mfma.h), weights as the rows of the tile,
+// sequences as its columns.  Bound: six bf16 MFMAs per 32 K elements, 34 us at the rate that the matrix cores hold for
+// 1024 sequences, d = 4096, d_h = 1024, beside the splitting of both operands (208 vector instructions to 96 MFMAs).  That
+// batch took 86 to 90 us on the fp32 matrix instructions (95 to 100 TFLOP/s), now 50 to 54; the error against fp64
+// is 0.7 of what it was (fewer roundings: one per MFMA, of 32 products).  Tried: both operands split once per workgroup
+// and read from the LDS, 8 waves 55 us and 4 waves 60 against 52 in the same run; without a pinned order of instructions 65.
+// Columns of 64 instead of 128 fill the chip with two workgroups per compute unit (59 us) and hold the pipeline's start
+// down: taken where a slice has fewer than SPLIT_WIDE_STEPS steps (1024 sequences, d = 1024, d_h = 300: training step
+// 69.7 -> 64.1 us; 309, d = 2208, d_h = 700: 66.2 -> 62.8).
+constexpr int SPLIT_WIDE_STEPS = 8;
 
-// 8 fp32 values -> three bf16 fragments whose sum is exactly the input (truncating splits)
-__device__ __forceinline__ void split3(const float (&f)[8], bf16x8 &hi, bf16x8 &mid, bf16x8 &lo)
+template <class S>
+struct Layer1Source {
+    static constexpr int ROW_LOADS = 2 * S::FA, COL_LOADS = 2 * S::SHARE;
+    static constexpr bool COLS_MAY_BE_INF = true;
+    struct Rows {
+        float4 v[S::FA][2];
+    };
+    struct Cols {
+        float4 v[S::SHARE][2];
+    };
+    const float *w[S::FA], *x[S::SHARE];  // + 8 (lane / 16)
+    int kbeg, kend, kq, wave, lane;
+
+    // Past the end of the slice its last four elements are loaded again (no branch around a load: the loads in flight stay
+    // countable) and counted as zeros; kend is a multiple of 4, so four elements are inside the slice or outside.
+    __device__ __forceinline__ float4 four(const float *p, int i, int h) const
+    {
+        return *(const float4 *)(p + min(kbeg + i * S::STEP + 4 * h, kend - 4 - 8 * kq));
+    }
+    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const { r.v[l / 2][l % 2] = four(w[l / 2], i, l % 2); }
+    __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const { r.v[l / 2][l % 2] = four(x[l / 2], i, l % 2); }
+    template <int N>
+    __device__ __forceinline__ void clear(int i, float4 (&v)[N][2]) const
+    {
+        const int k0 = kbeg + i * S::STEP;
+        if (k0 + S::STEP <= kend)
+            return;
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (k0 + 8 * kq + 4 * h >= kend)
+                    v[n][h] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __device__ __forceinline__ void clear_rows(int i, Rows &r) const { clear(i, r.v); }
+    __device__ __forceinline__ void clear_cols(int i, Cols &r) const { clear(i, r.v); }
+    __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const { return (&r.v[a][e / 4].x)[e % 4]; }
+    __device__ __forceinline__ float col_value(const Cols &r, int p, int e) const { return (&r.v[p][e / 4].x)[e % 4]; }
+    __device__ __forceinline__ int place(int p) const { return ((wave + S::WAVES * p) * 64 + lane) * 16; }
+};
+
+template <class S>
+__global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_split_kernel(
+    const float *__restrict__ x, const int32_t *__restrict__ slot, int B, int d, int d_h, const float *__restrict__ w1,
+    int kchunk, int nks, int jtiles, float *__restrict__ act_part)
 {
-    unsigned h[8], m[8], l[8];
+    static_assert(S::ROWS == FJ, "tile");
+    constexpr int FA = S::FA, FB = S::FB;
+    __shared__ __align__(16) unsigned char lds[S::LDS_BYTES];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, kq = lane >> 4;
+    // the slice index varies fastest over the grid: an XCD pulls only its own slices of both operands
+    const int kslice = blockIdx.x % nks;
+    const int tile = blockIdx.x / nks;
+    const int j0 = (tile % jtiles) * S::ROWS, s0 = (tile / jtiles) * S::COLS;
+
+    Layer1Source<S> src;
+    src.kbeg = kslice * kchunk;
+    src.kend = min(d, src.kbeg + kchunk);
+    src.kq = kq, src.wave = wave, src.lane = lane;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        split3_bits(f[i], h[i], m[i], l[i]);
+    for (int a = 0; a < FA; ++a) {
+        const int j = min(j0 + 16 * (wave * FA + a) + l15, d_h - 1);  // clamped rows are computed and dropped
+        src.w[a] = w1 + (long)j * d + 8 * kq;
     }
-    u32x4 ph, pm, pl;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        ph[i] = (h[2 * i] >> 16) | h[2 * i + 1];
-        pm[i] = (m[2 * i] >> 16) | m[2 * i + 1];
-        pl[i] = (l[2 * i] >> 16) | l[2 * i + 1];
+    for (int p = 0; p < S::SHARE; ++p) {
+        const int sq = min(s0 + 16 * (wave + S::WAVES * p) + l15, B - 1);
+        src.x[p] = x + (long)(slot ? slot[sq] : sq) * d + 8 * kq;
     }
-    hi = __builtin_bit_cast(bf16x8, ph);
-    mid = __builtin_bit_cast(bf16x8, pm);
-    lo = __builtin_bit_cast(bf16x8, pl);
+    split_f32x4 acc[FA][FB];
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+            acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+    if (src.kbeg < src.kend)
+        split_contract<S>(lds, (src.kend - src.kbeg + S::STEP - 1) / S::STEP, lane, acc, src);
+
+    float *act = act_part + (long)kslice * B * d_h;
+#pragma unroll
+    for (int b = 0; b < FB; ++b) {
+        const int s = s0 + 16 * b + l15;
+        if (s >= B)
+            continue;
+#pragma unroll
+        for (int a = 0; a < FA; ++a) {
+            const int jj = j0 + 16 * (wave * FA + a) + 4 * kq;
+            if (jj + 3 < d_h && (d_h & 3) == 0) {
+                *(split_f32x4 *)(act + (long)s * d_h + jj) = acc[a][b];
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (jj + i < d_h)
+                        act[(long)s * d_h + jj + i] = acc[a][b][i];
+            }
+        }
+    }
 }
+
+constexpr int MK = 32;  // K elements per MFMA step
 
 // Layer 1 on the matrix cores, bf16 weights, d % 8 == 0.  Workgroup = 4 waves, MJ = 128 head rows x
 // TN = 64 sequences; wave = 64 x 32 = 4 x 2 MFMA 16x16x32 tiles, weights as the row operand (lane l:
@@ -639,6 +732,9 @@ int head_k_splits(int d, int d_h, int32_t B, int wdtype)
         const long ftiles = (long)((d_h + FJ - 1) / FJ) * ((B + f32_tile_seqs(B) - 1) / f32_tile_seqs(B));
         const long fwant = ftiles > 0 ? (F32_WORKGROUPS + ftiles - 1) / ftiles : 1;
         n = n > fwant ? fwant : n;
+        // a slice of at least two K steps of the kernel on bf16 pieces
+        if (B > F32_MAX_SEQS && n > (d + 63) / 64)
+            n = (d + 63) / 64;
     }
     return n < 1 ? 1 : (int)n;
 }
@@ -675,18 +771,25 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
         return hipGetLastError();
     }
     if (wdtype == DT_F32) {
-        const int kchunk_f = ((d + nks - 1) / nks + FK - 1) / FK * FK;
-        const int jtiles = (d_h + FJ - 1) / FJ, fs = f32_tile_seqs(B);
+        const bool small = B <= F32_MAX_SEQS;
+        const int kstep = small ? FK : SplitTile<2, 4>::STEP;
+        const int kchunk_f = ((d + nks - 1) / nks + kstep - 1) / kstep * kstep;
+        const bool wide = !small && kchunk_f >= SPLIT_WIDE_STEPS * kstep;
+        const int jtiles = (d_h + FJ - 1) / FJ, fs = small ? f32_tile_seqs(B) : (wide ? 128 : 64);
         const long wgs = (long)jtiles * ((B + fs - 1) / fs) * nks;
         if (d % 4 != 0 || wgs > 0x7fffffffL)
             return hipErrorInvalidValue;
-#define EGTP_LAYER1_F32(NS)                                                                                       \
-    hipLaunchKernelGGL((head_layer1_f32_kernel<NS>), dim3((unsigned)wgs), dim3(256), 0, st, x, slot, B, d, d_h,   \
-                       (const float *)w1, kchunk_f, nks, jtiles, act_part)
-        if (fs == 64)
-            EGTP_LAYER1_F32(2);
+#define EGTP_LAYER1_F32(KERNEL)                                                                                   \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)wgs), dim3(256), 0, st, x, slot, B, d, d_h, (const float *)w1, kchunk_f, \
+                       nks, jtiles, act_part)
+        if (wide)
+            EGTP_LAYER1_F32((head_layer1_split_kernel<SplitTile<2, 8>>));
+        else if (!small)
+            EGTP_LAYER1_F32((head_layer1_split_kernel<SplitTile<2, 4>>));
+        else if (fs == 64)
+            EGTP_LAYER1_F32(head_layer1_f32_kernel<2>);
         else
-            EGTP_LAYER1_F32(1);
+            EGTP_LAYER1_F32(head_layer1_f32_kernel<1>);
 #undef EGTP_LAYER1_F32
         return hipGetLastError();
     }

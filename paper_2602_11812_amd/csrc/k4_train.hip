@@ -8,8 +8,9 @@
 //                          terms, d loss / d logits and d loss / d pre-activation
 //   3. the updates, one grid of three kinds of workgroups that only need what 2. left behind:
 //      W1                  gradient tile [64 x 64] of  dact^T . x  accumulated over the batch in
-//                          registers and consumed by AdamW on the spot -- the d_h x d gradient
-//                          is never written unless the caller asks for a copy.  With the
+//                          registers and consumed by AdamW on the spot (128 x 64 for large
+//                          batches) -- the d_h x d gradient is never written unless the
+//                          caller asks for a copy.  With the
 //                          paper's batch of 16 this part is a pure stream over W1 and its two
 //                          moments (read and written once each).
 //      small parameters    gradient of W2, b2 and b1, 64 columns a workgroup, reduced over the batch in a fixed
@@ -18,6 +19,7 @@
 // No floating-point atomics anywhere: results are bit-reproducible.
 #include "kernels.h"
 #include "partial_planes.h"
+#include "split_mfma.h"
 #include "wave_reduce.h"
 
 namespace egtp {
@@ -372,6 +374,116 @@ __device__ __forceinline__ void w1_update(int tile_k, int tile_j, const float *_
     }
 }
 
+// The same for more samples: fp32 products as bf16 pieces (split_mfma.h).  Workgroup = 128 rows j x 64 columns k, a wave 32
+// rows of its own.  The contraction runs over the samples, the slow index of both operands, of which a fragment wants eight
+// in a lane: a lane loads two neighbouring j (or one k) of eight samples and deals them to two fragments (one), so that row
+// c of a wave's fragment a is j = 2 c + a and column c of fragment b is k = 4 c + b.  A lane ends up with four neighbouring
+// k of a row j, one 16-byte access each to W1 and the moments.
+// Two workgroups per compute unit; the workgroups of the small parameters, chains of cache latencies, start before the
+// tiles, which puts some tiles' parameter streams beside others' products (512 samples 92.7 -> 89.1 us a step).
+// Bound: the splitting beside the MFMAs, 49 us per 1024 samples at d = 4096, d_h = 1024, and about 30 us for the parameters.
+// 1024 samples: the launch 117 to 120 us on the fp32 matrix instructions, now 75 to 82.  128 x 128 tiles: 85.
+typedef SplitTile<2, 4> GradTile;
+// From this many samples and tiles on (whole steps, fp32 -> split: 128 samples, d = 4096, d_h = 1024 52.4 -> 56.6 us, 256
+// 67.5 -> 65.2; 309 samples against 210 tiles 62.8 -> 60.8, 1024 against 48 64.1 -> 65.6).
+constexpr int SPLIT_SAMPLES = 192, SPLIT_TILES = 128;
+
+struct GradSource {
+    static constexpr int ROW_LOADS = 8, COL_LOADS = 8;
+    static constexpr bool COLS_MAY_BE_INF = false;
+    struct Rows {
+        float2 v[8];
+    };
+    struct Cols {
+        float v[8];
+    };
+    const float *dact, *x;  // this lane's columns of the two operands
+    long d_h, d;
+    int B, kq, place0;
+
+    // Past the end of the batch the last sample is loaded again (no branch around a load: the loads in flight stay
+    // countable) and counted as zeros.
+    __device__ __forceinline__ int sample(int i, int l) const { return min(i * GradTile::STEP + 8 * kq + l, B - 1); }
+    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const { r.v[l] = *(const float2 *)(dact + sample(i, l) * d_h); }
+    __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const { r.v[l] = x[sample(i, l) * d]; }
+    template <class V>
+    __device__ __forceinline__ void clear(int i, V (&v)[8], V zero) const
+    {
+        if ((i + 1) * GradTile::STEP <= B)
+            return;
+#pragma unroll
+        for (int l = 0; l < 8; ++l)
+            if (i * GradTile::STEP + 8 * kq + l >= B)
+                v[l] = zero;
+    }
+    __device__ __forceinline__ void clear_rows(int i, Rows &r) const { clear(i, r.v, make_float2(0.f, 0.f)); }
+    __device__ __forceinline__ void clear_cols(int i, Cols &r) const { clear(i, r.v, 0.f); }
+    __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const { return a == 0 ? r.v[e].x : r.v[e].y; }
+    __device__ __forceinline__ float col_value(const Cols &r, int, int e) const { return r.v[e]; }
+    __device__ __forceinline__ int place(int) const { return place0; }
+};
+
+__device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const float *__restrict__ x,
+                                                const float *__restrict__ dact, int B, int d, int d_h, const Adam &h,
+                                                float *__restrict__ w1, float *__restrict__ m_w1, float *__restrict__ v_w1,
+                                                float *__restrict__ g_w1, unsigned char *__restrict__ lds)
+{
+    using S = GradTile;
+    constexpr int FA = S::FA, FB = S::FB;
+    static_assert(FA == 2 && FB == 4 && S::SHARE == 1, "two neighbouring j, one k to a lane");
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l15 = lane & 15, kq = lane >> 4;
+    const int k0 = tile_k * S::COLS, j0 = tile_j * S::ROWS + 32 * wave;
+
+    // d_h and d are multiples of 4: rows and columns that do not exist are others', computed and dropped
+    GradSource src;
+    src.d_h = d_h, src.d = d, src.B = B, src.kq = kq;
+    src.dact = dact + min(j0 + 2 * l15, d_h - 2);
+    src.x = x + min(k0 + 4 * l15 + wave, d - 1);  // a wave stages fragment `wave`
+    src.place0 = (wave * 64 + lane) * 16;
+    split_f32x4 acc[FA][FB];
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int b = 0; b < FB; ++b)
+            acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
+    split_contract<S>(lds, (B + S::STEP - 1) / S::STEP, lane, acc, src);
+
+    const int k = k0 + 4 * l15;
+    if (k >= d)
+        return;
+    float4 w[FA][4], m[FA][4], v[FA][4];
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            // rows that do not exist: a valid place, not used
+            const long at = (long)min(j0 + 2 * (4 * kq + i) + a, d_h - 1) * d + k;
+            w[a][i] = *(const float4 *)(w1 + at);
+            m[a][i] = *(const float4 *)(m_w1 + at);
+            v[a][i] = *(const float4 *)(v_w1 + at);
+        }
+#pragma unroll
+    for (int a = 0; a < FA; ++a)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int j = j0 + 2 * (4 * kq + i) + a;
+            if (j >= d_h)
+                continue;
+            const long at = (long)j * d + k;
+            const float4 grad = make_float4(acc[a][0][i], acc[a][1][i], acc[a][2][i], acc[a][3][i]);
+            adamw(h, grad.x, w[a][i].x, m[a][i].x, v[a][i].x);
+            adamw(h, grad.y, w[a][i].y, m[a][i].y, v[a][i].y);
+            adamw(h, grad.z, w[a][i].z, m[a][i].z, v[a][i].z);
+            adamw(h, grad.w, w[a][i].w, m[a][i].w, v[a][i].w);
+            *(float4 *)(w1 + at) = w[a][i];
+            *(float4 *)(m_w1 + at) = m[a][i];
+            *(float4 *)(v_w1 + at) = v[a][i];
+            if (g_w1)
+                *(float4 *)(g_w1 + at) = grad;
+        }
+}
+
 // ---- 3. + 4. + 5. in one launch: all three need only what the per-sample kernel left behind and touch
 // disjoint parameters, so they share a grid.  The W1 tiles come first in launch order (they carry the
 // memory traffic of the step), then the workgroups of the small parameters, the loss last.
@@ -385,13 +497,22 @@ struct UpdateArgs {
     float *loss;
 };
 
-__global__ __launch_bounds__(256) void train_update_kernel(UpdateArgs a, Adam h)
+template <bool SPLIT>
+__global__ __launch_bounds__(256, SPLIT ? 2 : 1) void train_update_kernel(UpdateArgs a, Adam h)
 {
-    __shared__ __align__(16) float lds[2 * GRAD_STAGE_FLOATS];
-    static_assert(2 * GRAD_STAGE_FLOATS >= 4 * W2_ROWS * 64, "LDS of the small-parameter part");
+    constexpr int LDS_FLOATS = SPLIT ? GradTile::LDS_BYTES / 4 : 2 * GRAD_STAGE_FLOATS;
+    __shared__ __align__(16) float lds[LDS_FLOATS];
+    static_assert(LDS_FLOATS >= 4 * W2_ROWS * 64, "LDS of the small-parameter part");
+    const int small = (int)gridDim.x - a.tiles_w1;  // the other workgroups: behind the tiles, or (split) before them
     int id = blockIdx.x;
+    if (SPLIT)
+        id = id < small ? a.tiles_w1 + id : id - small;
     if (id < a.tiles_w1) {
-        w1_update(id % a.tiles_k, id / a.tiles_k, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, lds);
+        const int tk = id % a.tiles_k, tj = id / a.tiles_k;
+        if constexpr (SPLIT)
+            w1_update_split(tk, tj, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, (unsigned char *)lds);
+        else
+            w1_update(tk, tj, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, lds);
         return;
     }
     id -= a.tiles_w1;
@@ -453,7 +574,12 @@ hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
     u.b2 = {a.b2, a.m_b2, a.v_b2, a.g_b2};
     u.b1 = {a.b1, a.m_b1, a.v_b1, a.g_b1};
     u.loss = a.loss;
-    const long tiles_k = (a.d + GN - 1) / GN, tiles_j = (a.d_h + GM - 1) / GM;
+    // (rows of dact start on 8-byte boundaries)
+    const bool split = a.B >= SPLIT_SAMPLES && a.d_h % 4 == 0 &&
+                       (long)((a.d_h + GradTile::ROWS - 1) / GradTile::ROWS) * ((a.d + GradTile::COLS - 1) / GradTile::COLS) >=
+                           SPLIT_TILES;
+    const int tile_j = split ? GradTile::ROWS : GM, tile_k = split ? GradTile::COLS : GN;
+    const long tiles_k = (a.d + tile_k - 1) / tile_k, tiles_j = (a.d_h + tile_j - 1) / tile_j;
     u.tiles_k = (int)tiles_k;
     u.tiles_w1 = (int)(tiles_k * tiles_j);
     u.cols_h = (a.d_h + 63) / 64;
@@ -462,7 +588,10 @@ hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
     const long wgs = tiles_k * tiles_j + u.blocks_w2 + u.cols_h + u.blocks_b2 + 1;
     if (wgs > 0x7fffffffL)
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(train_update_kernel, dim3((unsigned)wgs), dim3(256), 0, st, u, h);
+    if (split)
+        hipLaunchKernelGGL(train_update_kernel<true>, dim3((unsigned)wgs), dim3(256), 0, st, u, h);
+    else
+        hipLaunchKernelGGL(train_update_kernel<false>, dim3((unsigned)wgs), dim3(256), 0, st, u, h);
     return hipGetLastError();
 }
 

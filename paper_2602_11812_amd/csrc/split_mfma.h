@@ -1,0 +1,167 @@
+// Products of fp32 operands on the bf16 matrix cores: every value is the exact sum of three bf16 pieces, a product of two
+// pieces is exact in fp32, and of the nine piece products of a pair the six of relative size 2^-16 and more are accumulated
+// (the other three are below 2^-24, fp32's own rounding).  Six 16x16x32 MFMAs take the place of eight 16x16x4 ones that
+// cost four times as many cycles.  Device-side header.
+#pragma once
+#include "bf16_split.h"
+
+namespace egtp {
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float split_f32x4;
+
+// Workgroup tile: 4 waves one above the other, each with 16 FA rows of its own, against 16 FB columns.  A wave splits its
+// rows in registers; the columns are shared through the LDS: a K step of 32 lies there as fragments (16 columns x 32 K
+// elements, 1 KiB: lane l holds column l % 16, K elements 8 (l / 16) .. + 8), piece by piece.
+template <int FA_, int FB_>
+struct SplitTile {
+    static constexpr int FA = FA_, FB = FB_, WAVES = 4, THREADS = 64 * WAVES, STEP = 32;
+    static constexpr int ROWS = 16 * FA * WAVES, COLS = 16 * FB;
+    static constexpr int PIECE = FB * 1024, BYTES = 3 * PIECE;
+    static constexpr int LDS_BYTES = 2 * BYTES;  // a step is read while the next is staged
+    static constexpr int SHARE = FB / WAVES;     // column fragments' lanes that a thread stages: 8 K elements each
+};
+
+// acc[a][b] += row fragment a . column fragment b over `steps` K steps of the tile.
+//
+// Everything that a step needs is under way before it: while the products of step i run, the column fragments of step i + 1
+// are read from the LDS and its rows split, the columns of step i + 2 are split into the other buffer, rows of step i + 3
+// and columns of step i + 4 are asked for.  There is one wave per SIMD, so the order inside a step is pinned: a row of FB
+// products at a time with its share of everything else, which hides in the cycles that an MFMA leaves to other
+// instructions.  One barrier per step: behind it step i + 1 is whole and everyone has read step i.  Of a step the smallest
+// products come first.
+//
+// Source: this thread's share of the operands; past the end of the contraction any valid place is loaded, and not used
+//   load_rows(i, l, r), load_cols(i, l, r)    load number l of ROW_LOADS / COL_LOADS of step i
+//   clear_rows(i, r), clear_cols(i, r)        zeros what of step i lies past the end
+//   row_value(r, a, e), col_value(r, p, e)    K element e of row fragment a / of share p
+//   place(p)                                  where share p goes in a buffer
+//   COLS_MAY_BE_INF                           a column may hold infinities: their lower pieces are zeros, not NaN
+template <class T, class Source>
+__device__ __forceinline__ void split_contract(unsigned char *lds, int steps, int lane, split_f32x4 (&acc)[T::FA][T::FB],
+                                               const Source &src)
+{
+    constexpr int FA = T::FA, FB = T::FB, SHARE = T::SHARE;
+    typename Source::Rows ra0, ra1;
+    typename Source::Cols rb0, rb1;
+    struct RowFragments {
+        split_u32x4 p[3][FA];
+    } a0, a1;
+    struct ColFragments {
+        split_bf16x8 p[3][FB];
+    } b0, b1;
+    auto read = [&](ColFragments &f, const unsigned char *buf, int n) {
+        f.p[n / FB][n % FB] = *(const split_bf16x8 *)(buf + n / FB * T::PIECE + (n % FB * 64 + lane) * 16);
+    };
+    auto split_rows = [&](const typename Source::Rows &r, RowFragments &f, int n) {
+        const int a = n / 4, e = n % 4;
+        unsigned h, m, l;
+        split3_pair(false, src.row_value(r, a, 2 * e), src.row_value(r, a, 2 * e + 1), h, m, l);
+        f.p[0][a][e] = h, f.p[1][a][e] = m, f.p[2][a][e] = l;
+    };
+    split_u32x4 part[SHARE][3];
+    auto split_cols = [&](const typename Source::Cols &r, int n) {
+        const int p = n / 4, e = n % 4;
+        unsigned h, m, l;
+        split3_pair(Source::COLS_MAY_BE_INF, src.col_value(r, p, 2 * e), src.col_value(r, p, 2 * e + 1), h, m, l);
+        part[p][0][e] = h, part[p][1][e] = m, part[p][2][e] = l;
+    };
+    auto write = [&](unsigned char *buf, int n) { *(split_u32x4 *)(buf + src.place(n / 3) + n % 3 * T::PIECE) = part[n / 3][n % 3]; };
+
+    constexpr int ROW_PAIRS = 4 * FA, COL_PAIRS = 4 * SHARE, WRITES = 3 * SHARE, READS = 3 * FB;
+    constexpr int ROW_LOADS = Source::ROW_LOADS, COL_LOADS = Source::COL_LOADS;
+    auto fetch_cols = [&](int i, typename Source::Cols &r) {
+#pragma unroll
+        for (int l = 0; l < COL_LOADS; ++l)
+            src.load_cols(i, l, r);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto fetch_rows = [&](int i, typename Source::Rows &r) {
+#pragma unroll
+        for (int l = 0; l < ROW_LOADS; ++l)
+            src.load_rows(i, l, r);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto stage = [&](int i, typename Source::Cols &r, unsigned char *buf) {
+        src.clear_cols(i, r);
+#pragma unroll
+        for (int n = 0; n < COL_PAIRS; ++n)
+            split_cols(r, n);
+#pragma unroll
+        for (int n = 0; n < WRITES; ++n)
+            write(buf, n);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch_cols(0, rb0);
+    fetch_rows(0, ra0);
+    fetch_cols(1, rb1);
+    fetch_rows(1, ra1);
+    stage(0, rb0, lds);
+    fetch_cols(2, rb0);
+    src.clear_rows(0, ra0);
+#pragma unroll
+    for (int n = 0; n < ROW_PAIRS; ++n)
+        split_rows(ra0, a0, n);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_rows(2, ra0);
+    stage(1, rb1, lds + T::BYTES);
+    fetch_cols(3, rb1);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): own reads and writes of the LDS; loads stay in flight
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int n = 0; n < READS; ++n)
+        read(b0, lds, n);
+    // rb: holds the columns of step i + 2; ra: the rows of step i + 1
+    auto step = [&](int i, const RowFragments &a, RowFragments &a_next, const ColFragments &b, ColFragments &b_next,
+                    typename Source::Rows &ra, typename Source::Cols &rb, unsigned char *mine, const unsigned char *other) {
+        constexpr int PA[6] = {2, 1, 0, 1, 0, 0}, PB[6] = {0, 1, 2, 0, 1, 0};
+        constexpr int ROWS = 6 * FA, SPLIT = ROWS * 2 / 3, TAIL = ROWS - SPLIT;
+        src.clear_cols(i + 2, rb);
+        src.clear_rows(i + 1, ra);
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int row = 0; row < ROWS; ++row) {
+            const int t = row / FA, fa = row % FA;
+#pragma unroll
+            for (int fb = 0; fb < FB; ++fb)
+                acc[fa][fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, a.p[PA[t]][fa]),
+                                                                      b.p[PB[t]][fb], acc[fa][fb], 0, 0, 0);
+#pragma unroll
+            for (int n = row * READS / ROWS; n < (row + 1) * READS / ROWS; ++n)
+                read(b_next, other, n);
+            if (row < SPLIT) {
+#pragma unroll
+                for (int n = row * COL_PAIRS / SPLIT; n < (row + 1) * COL_PAIRS / SPLIT; ++n)
+                    split_cols(rb, n);
+#pragma unroll
+                for (int n = row * ROW_PAIRS / SPLIT; n < (row + 1) * ROW_PAIRS / SPLIT; ++n)
+                    split_rows(ra, a_next, n);
+            } else {
+                const int q = row - SPLIT;
+#pragma unroll
+                for (int n = q * WRITES / TAIL; n < (q + 1) * WRITES / TAIL; ++n)
+                    write(mine, n);
+#pragma unroll
+                for (int l = q * COL_LOADS / TAIL; l < (q + 1) * COL_LOADS / TAIL; ++l)
+                    src.load_cols(i + 4, l, rb);
+#pragma unroll
+                for (int l = q * ROW_LOADS / TAIL; l < (q + 1) * ROW_LOADS / TAIL; ++l)
+                    src.load_rows(i + 3, l, ra);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int i = 0;
+    for (; i + 2 <= steps; i += 2) {
+        step(i, a0, a1, b0, b1, ra1, rb0, lds, lds + T::BYTES);
+        step(i + 1, a1, a0, b1, b0, ra0, rb1, lds + T::BYTES, lds);
+    }
+    if (i < steps)
+        step(i, a0, a1, b0, b1, ra1, rb0, lds, lds + T::BYTES);
+}
+
+}  // namespace
+}  // namespace egtp
