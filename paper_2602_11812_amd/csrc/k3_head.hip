@@ -4,9 +4,8 @@
 // Layer 1 is a small [B x d] . [d x d_h] contraction kept entirely in fp32 (the pooled
 // vector is never re-rounded), on the fp32 matrix instructions where the weights are fp32 and the batch is more
 // than a handful, and as products of bf16 pieces where it is more than 64.  The contraction is split along d so that several hundred workgroups exist even for one
-// small batch; the splits leave partial pre-activations that layer 2 adds in split order
-// (fixed order, bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode are one
-// workgroup per sequence.
+// small batch; the splits leave partial pre-activations that layer 2 adds in a fixed order
+// (bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode: head_tail.h.
 //
 // With bf16 weights and d a multiple of 8, layer 1 runs on the bf16 matrix cores without
 // rounding the pooled vector: an fp32 value is the exact sum of three bf16 values (its top 8
@@ -14,8 +13,8 @@
 // fp32, so three MFMAs per weight fragment accumulate the same products an fp32 dot product
 // would, in fp32.  Fragments come straight from global memory: a lane's 8 K-elements are 16
 // contiguous bytes of a weight row and 32 contiguous bytes of a pooled row.
+#include "head_tail.h"
 #include "kernels.h"
-#include "partial_planes.h"
 #include "split_mfma.h"
 #include "wave_reduce.h"
 
@@ -197,18 +196,9 @@ __global__ __launch_bounds__(256) void head_layer1_skinny_kernel(const float *__
             }
         }
     }
-    // halving butterfly over the lanes: after the step with distance o a lane holds n / 2 sums, the upper half
+    // halving butterfly over the lanes: after a step with bit o a lane holds n / 2 sums, the upper half
     // of the indices if its bit o is set
-#pragma unroll
-    for (int o = 32, n = 64; o >= 1; o >>= 1, n >>= 1) {
-        const bool upper = (lane & o) != 0;
-#pragma unroll
-        for (int i = 0; i < n / 2; ++i) {
-            const float keep = upper ? acc[i + n / 2] : acc[i];
-            const float pass = upper ? acc[i] : acc[i + n / 2];
-            acc[i] = keep + __shfl_xor(pass, o);
-        }
-    }
+    halve_over_lanes(acc);
     const int b = lane & 15, j = j0 + (lane >> 4);
     if (b < B && j < d_h)
         act_part[((long)blockIdx.y * B + b) * d_h + j] = acc[0];
@@ -600,98 +590,87 @@ __global__ __launch_bounds__(256) void head_layer1_mfma_kernel(const float *__re
     }
 }
 
-// one workgroup (4 waves) per sequence: out[o] = b2[o] + w2[o,:] . act[b,:]; n_out > 1 => Eq. 6
-// LDS: a[d_h] | z[max(n_out, 4)]
-constexpr int OUTS_AT_ONCE = 5;
-
-template <bool WBF16>
-__global__ __launch_bounds__(256) void head_layer2_kernel(const float *__restrict__ act_part, int nks, int B,
-                                                          const float *__restrict__ b1, int d_h, int n_out,
-                                                          const void *__restrict__ w2,
-                                                          const float *__restrict__ b2,
-                                                          const float *__restrict__ centers,
-                                                          float *__restrict__ pred,
-                                                          float *__restrict__ p_hat)
+// Layer 2 of a scalar head: pred = b2 + w2 . act[b,:].  NS sequences per workgroup (head_tail.h); TINY: d_h < 4.
+// LDS: a[NS][lda] | part[NS][TAIL_WAVES]
+template <bool WBF16, bool TINY, int NS>
+__global__ __launch_bounds__(TAIL_THREADS) void head_scalar_kernel(const float *__restrict__ act_part, int nks, int B,
+                                                                   const float *__restrict__ b1, int d_h,
+                                                                   const void *__restrict__ w2_any,
+                                                                   const float *__restrict__ b2, float *__restrict__ pred)
 {
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    using W = std::conditional_t<WBF16, unsigned short, float>;
+    const W *w2 = (const W *)w2_any;
+    __shared__ float4 join[NS < 4 ? TAIL_JOIN_FLOATS / 4 : 1];
     extern __shared__ __align__(16) float a[];
-    float *z = a + d_h;
-    // hidden activations: partial sums in split order, then bias and ReLU; kept in LDS
-    if ((d_h & 3) == 0) {
-        for (int j = tid * 4; j < d_h; j += 1024) {
-            const float4 pre = sum_planes4(act_part, nks, B, b, d_h, j);
-            const float v[4] = {pre.x, pre.y, pre.z, pre.w};
+    const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *part = a + NS * lda;
+    // thread t takes the chunks t, t + TAIL_THREADS, ... of the dot product (fixed assignment: bit-reproducible)
+    const float bias = b2 ? b2[0] : 0.f;
+    ChunkOf<W> w = load_chunk(w2, RowChunk<TINY>(tid, d_h), d_h);
+    hidden_units<TINY, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, nullptr);
+    float s[NS] = {};
+    for (int c0 = tid; 4 * c0 < lda; c0 += TAIL_THREADS) {
+        const RowChunk<TINY> c(c0, d_h);
+        if (c0 != tid)
+            w = load_chunk(w2, c, d_h);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float p = v[i] + (b1 ? b1[j + i] : 0.f);
-                a[j + i] = p > 0.f ? p : 0.f;
-            }
-        }
-    } else {
-        for (int j = tid; j < d_h; j += 256) {
-            float pre = 0.f;
-#pragma unroll 8
-            for (int z = 0; z < nks; ++z)
-                pre += act_part[((long)z * B + b) * d_h + j];
-            pre += b1 ? b1[j] : 0.f;
-            a[j] = pre > 0.f ? pre : 0.f;
-        }
+        for (int n = 0; n < NS; ++n)
+            s[n] = chunk_dot(w, c, *(const float4 *)(a + n * lda + 4 * c0), s[n]);
     }
-    __syncthreads();
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    auto weight = [&](int o, int j) {
-        return WBF16 ? __uint_as_float((unsigned)((const unsigned short *)w2)[(long)o * d_h + j] << 16)
-                     : ((const float *)w2)[(long)o * d_h + j];
-    };
-    if (n_out == 1) {
-        // every wave takes a quarter of the dot product (fixed assignment: bit-reproducible)
-        float s = 0.f;
-#pragma unroll 4
-        for (int j = tid; j < d_h; j += 256)
-            s = fmaf(weight(0, j), a[j], s);
-        s = wave_sum(s);
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        const float t = wave_sum(s[n]);
         if (lane == 0)
-            z[wave] = s;
-        __syncthreads();
-        if (tid == 0)
-            pred[b] = ((z[0] + z[1]) + (z[2] + z[3])) + (b2 ? b2[0] : 0.f);
-        return;
-    }
-    // A wave takes whole dot products, OUTS_AT_ONCE outputs at a time, so that their weight loads are in flight
-    // together: W2 is small and cache-resident, what costs is each dependent round of loads (one output after the
-    // other, 20 bins at d_h = 1024: 23.6 us for the launch, now 6).
-    for (int o0 = wave_u * OUTS_AT_ONCE; o0 < n_out; o0 += 4 * OUTS_AT_ONCE) {
-        float s[OUTS_AT_ONCE];
-#pragma unroll
-        for (int q = 0; q < OUTS_AT_ONCE; ++q)
-            s[q] = 0.f;
-#pragma unroll 4
-        for (int j = lane; j < d_h; j += 64) {
-            const float aj = a[j];
-#pragma unroll
-            for (int q = 0; q < OUTS_AT_ONCE; ++q)
-                s[q] = fmaf(weight(min(o0 + q, n_out - 1), j), aj, s[q]);  // past the end: a valid row, not used
-        }
-#pragma unroll
-        for (int q = 0; q < OUTS_AT_ONCE; ++q) {
-            const float t = wave_sum(s[q]);
-            if (lane == 0 && o0 + q < n_out)
-                z[o0 + q] = t + (b2 ? b2[o0 + q] : 0.f);
-        }
+            part[n * TAIL_WAVES + wave] = t;
     }
     __syncthreads();
-    if (wave != 0)
+    if (tid < NS && b0 + tid < B) {
+        float t = part[tid * TAIL_WAVES];
+#pragma unroll
+        for (int q = 1; q < TAIL_WAVES; ++q)
+            t += part[tid * TAIL_WAVES + q];
+        pred[b0 + tid] = t + bias;
+    }
+}
+
+// Layer 2 of a K-bin head: out[o] = b2[o] + w2[o,:] . act[b,:], then Eq. 6.  LDS: a[NS][lda] | z[NS][n_out]
+template <bool WBF16, bool TINY, int NS>
+__global__ __launch_bounds__(TAIL_THREADS) void head_bins_kernel(const float *__restrict__ act_part, int nks, int B,
+                                                                 const float *__restrict__ b1, int d_h, int n_out,
+                                                                 const void *__restrict__ w2,
+                                                                 const float *__restrict__ b2,
+                                                                 const float *__restrict__ centers,
+                                                                 float *__restrict__ pred, float *__restrict__ p_hat)
+{
+    using W = std::conditional_t<WBF16, unsigned short, float>;
+    __shared__ float4 join[NS < 4 ? TAIL_JOIN_FLOATS / 4 : 1];
+    extern __shared__ __align__(16) float a[];
+    const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float *z = a + NS * lda;
+    // bin o < 64 belongs to lane o: its bias and centre are asked for now
+    const int o_near = min(lane, n_out - 1);
+    const float b2_near = b2 ? b2[o_near] : 0.f, center_near = centers[o_near];
+    output_layer<TINY, NS>((const W *)w2, n_out, d_h, a, lda, z,
+                           [&] { hidden_units<TINY, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, nullptr); });
+    __syncthreads();
+    const int b = b0 + wave;
+    if (wave >= NS || b >= B)
         return;
+    z += wave * n_out;
     // Eq. 6: softmax over the bins (bin o by lane o % 64) and its expectation
     float m = -__builtin_inff(), den = 0.f, num = 0.f;
-    for (int o = lane; o < n_out; o += 64)
-        m = fmaxf(m, z[o]);
+    for (int o = lane; o < n_out; o += 64) {
+        const float v = z[o] + (o < 64 ? b2_near : (b2 ? b2[o] : 0.f));
+        z[o] = v;
+        m = fmaxf(m, v);
+    }
     m = wave_max(m);
     for (int o = lane; o < n_out; o += 64) {
         const float e = __expf(z[o] - m);
         den += e;
-        num = fmaf(e, centers[o], num);
+        num = fmaf(e, o < 64 ? center_near : centers[o], num);
     }
     den = wave_sum(den);
     num = wave_sum(num);
@@ -811,29 +790,48 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
     return hipGetLastError();
 }
 
+template <bool WBF16, bool TINY, int NS>
+static hipError_t launch_layer2(const HeadArgs &a, int nks, size_t lds, hipStream_t st)
+{
+    static DeviceMask raised_scalar{0}, raised_bins{0};
+    const dim3 grid((a.B - 1) / NS + 1), block(TAIL_THREADS);
+    hipError_t e;
+    if (a.n_out == 1) {
+        e = raise_dynamic_lds_limit((const void *)head_scalar_kernel<WBF16, TINY, NS>, (int)TAIL_LDS_LIMIT, raised_scalar);
+        if (e == hipSuccess)
+            hipLaunchKernelGGL((head_scalar_kernel<WBF16, TINY, NS>), grid, block, NS * lds, st, a.act, nks, a.B, a.b1, a.d_h,
+                               a.w2, a.b2, a.pred);
+    } else {
+        e = raise_dynamic_lds_limit((const void *)head_bins_kernel<WBF16, TINY, NS>, (int)TAIL_LDS_LIMIT, raised_bins);
+        if (e == hipSuccess)
+            hipLaunchKernelGGL((head_bins_kernel<WBF16, TINY, NS>), grid, block, NS * lds, st, a.act, nks, a.B, a.b1, a.d_h,
+                               a.n_out, a.w2, a.b2, a.bin_centers, a.pred, a.p_hat);
+    }
+    return e == hipSuccess ? hipGetLastError() : e;
+}
+
+template <bool WBF16>
+static hipError_t launch_layer2(const HeadArgs &a, int nks, size_t lds, hipStream_t st)
+{
+    if (a.d_h < 4)
+        return launch_layer2<WBF16, true, 1>(a, nks, lds, st);
+    const int ns = tail_sequences(a.B, lds);
+    return ns == 4 ? launch_layer2<WBF16, false, 4>(a, nks, lds, st)
+           : ns == 2 ? launch_layer2<WBF16, false, 2>(a, nks, lds, st) : launch_layer2<WBF16, false, 1>(a, nks, lds, st);
+}
+
 hipError_t head_forward(const HeadArgs &a, hipStream_t st)
 {
     if (a.B <= 0)
         return hipSuccess;
     const int nks = head_k_splits(a.d, a.d_h, a.B, a.wdtype);
-    const size_t lds2 = ((size_t)a.d_h + 4 * (size_t)a.n_out) * sizeof(float);
-    if (lds2 > 96 * 1024)
+    const size_t lds = ((size_t)tail_row(a.d_h) + (size_t)(a.n_out > TAIL_WAVES ? a.n_out : TAIL_WAVES)) * sizeof(float);
+    if (lds > TAIL_LDS_LIMIT)
         return hipErrorInvalidValue;
-    static DeviceMask raised_bf16{0}, raised_f32{0};
-    hipError_t e1 = raise_dynamic_lds_limit((const void *)head_layer2_kernel<true>, 96 * 1024, raised_bf16);
-    hipError_t e2 = raise_dynamic_lds_limit((const void *)head_layer2_kernel<false>, 96 * 1024, raised_f32);
-    if (e1 != hipSuccess || e2 != hipSuccess)
-        return e1 != hipSuccess ? e1 : e2;
     hipError_t e = head_layer1(a.x, a.slot, a.B, a.d, a.d_h, a.w1, a.wdtype, a.act, st);
     if (e != hipSuccess)
         return e;
-    if (a.wdtype == DT_BF16)
-        hipLaunchKernelGGL(head_layer2_kernel<true>, dim3(a.B), dim3(256), lds2, st, a.act, nks, a.B, a.b1, a.d_h,
-                           a.n_out, a.w2, a.b2, a.bin_centers, a.pred, a.p_hat);
-    else
-        hipLaunchKernelGGL(head_layer2_kernel<false>, dim3(a.B), dim3(256), lds2, st, a.act, nks, a.B, a.b1, a.d_h,
-                           a.n_out, a.w2, a.b2, a.bin_centers, a.pred, a.p_hat);
-    return hipGetLastError();
+    return a.wdtype == DT_BF16 ? launch_layer2<true>(a, nks, lds, st) : launch_layer2<false>(a, nks, lds, st);
 }
 
 }  // namespace egtp

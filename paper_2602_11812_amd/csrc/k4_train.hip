@@ -17,8 +17,8 @@
 //                          order and consumed by AdamW on the spot
 //      loss                fixed-order sum of the per-sample terms (the last workgroup)
 // No floating-point atomics anywhere: results are bit-reproducible.
+#include "head_tail.h"
 #include "kernels.h"
-#include "partial_planes.h"
 #include "split_mfma.h"
 #include "wave_reduce.h"
 
@@ -39,117 +39,114 @@ __device__ __forceinline__ void adamw(const Adam &h, float g, float &w, float &m
     w = w - h.lr * h.wd * w - h.lr * mhat / (sqrtf(vhat) + h.eps);
 }
 
-// ---- 2. one workgroup per sample ---------------------------------------------------------
-// LDS: a[d_h] | z[K] | dz[K]
-__global__ __launch_bounds__(256) void train_sample_kernel(
+// ---- 2. the samples, NS per workgroup (head_tail.h) ---------------------------------------
+// TINY: d_h < 4.  LDS: a[NS][lda] | z[NS][K] | dz[NS][K]
+constexpr int DACT_ROWS = 20;  // rows of W2 in flight per thread
+
+template <bool TINY, int NS>
+__global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     const float *__restrict__ act_part, int nks, int B, int d_h, int K, const float *__restrict__ b1,
     const float *__restrict__ w2, const float *__restrict__ b2, const float *__restrict__ centers,
     const int32_t *__restrict__ bin, const float *__restrict__ y, const int32_t *__restrict__ steps, int n_seqs,
     float lambda, float *__restrict__ act, float *__restrict__ dact, float *__restrict__ dz_out,
     float *__restrict__ loss_part)
 {
-    extern __shared__ __align__(16) float sm[];
-    float *a = sm;
-    float *z = a + d_h;
-    float *dz = z + K;
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ float4 join[NS < 4 ? TAIL_JOIN_FLOATS / 4 : 1];
+    extern __shared__ __align__(16) float a[];
+    const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
+    float *z = a + NS * lda;
+    float *dz = z + NS * K;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // pre-activations: the slices' partial sums, added in slice order
-    if ((d_h & 3) == 0) {
-        for (int j = tid * 4; j < d_h; j += 1024) {
-            const float4 pre = sum_planes4(act_part, nks, B, b, d_h, j);
-            float4 r;  // the caller's bias vector need not be 16-byte aligned
-            r.x = fmaxf(pre.x + b1[j], 0.f), r.y = fmaxf(pre.y + b1[j + 1], 0.f);
-            r.z = fmaxf(pre.z + b1[j + 2], 0.f), r.w = fmaxf(pre.w + b1[j + 3], 0.f);
-            *(float4 *)(a + j) = r;
-            *(float4 *)(act + (long)b * d_h + j) = r;
+    // what the softmax of wave w's sample needs is asked for now; bin o < 64 belongs to lane o
+    const int b = min(b0 + min(wave, NS - 1), B - 1);
+    const int o_near = min(lane, K - 1), bin_b = bin[b], steps_b = steps ? steps[b] : 0;
+    const float y_b = y[b], b2_near = b2[o_near], center_near = centers[o_near];
+    output_layer<TINY, NS>(w2, K, d_h, a, lda, z,
+                           [&] { hidden_units<TINY, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, act); });
+    // ... and before the softmax the first rows of this thread's column of W2
+    float w[DACT_ROWS];
+    auto load_rows = [&](int o0, int j) {
+        const float *p = w2 + (long)o0 * d_h;
+#pragma unroll
+        for (int o = 0; o < DACT_ROWS; ++o) {
+            w[o] = p[j];
+            p += o0 + o + 1 < K ? d_h : 0;  // past the end: a valid row, not used
         }
-    } else {
-        for (int j = tid; j < d_h; j += 256) {
-            float pre = 0.f;
-#pragma unroll 8
-            for (int s = 0; s < nks; ++s)
-                pre += act_part[((long)s * B + b) * d_h + j];
-            pre += b1[j];
-            const float r = pre > 0.f ? pre : 0.f;
-            a[j] = r;
-            act[(long)b * d_h + j] = r;
-        }
-    }
+    };
+    load_rows(0, min(tid, d_h - 1));
     __syncthreads();
-    // logits: a wave takes OUTS_AT_ONCE outputs at a time so that their weight loads are all in flight together
-    // (W2 is small and cache-resident; what costs is the latency of each dependent round of loads)
-    constexpr int OUTS_AT_ONCE = 5;
-    for (int o0 = wave * OUTS_AT_ONCE; o0 < K; o0 += 4 * OUTS_AT_ONCE) {
-        float s[OUTS_AT_ONCE];
-#pragma unroll
-        for (int q = 0; q < OUTS_AT_ONCE; ++q)
-            s[q] = 0.f;
-#pragma unroll 4
-        for (int j = lane; j < d_h; j += 64) {
-            const float aj = a[j];
-#pragma unroll
-            for (int q = 0; q < OUTS_AT_ONCE; ++q) {
-                const int o = o0 + q < K ? o0 + q : K - 1;  // past the end: a valid row, not used
-                s[q] = fmaf(w2[(long)o * d_h + j], aj, s[q]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < OUTS_AT_ONCE; ++q) {
-            const float t = wave_sum(s[q]);
-            if (lane == 0 && o0 + q < K)
-                z[o0 + q] = t + b2[o0 + q];
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {
-        int i = bin[b];
-        i = i < 0 ? 0 : (i >= K ? K - 1 : i);
+    if (wave < NS) {
+        const bool kept = b0 + wave < B;
+        float *zs = z + wave * K, *ds = dz + wave * K;
+        const int i = bin_b < 0 ? 0 : (bin_b >= K ? K - 1 : bin_b);
         float m = -__builtin_inff();
-        for (int o = lane; o < K; o += 64)
-            m = fmaxf(m, z[o]);
+#pragma unroll 1
+        for (int o = lane; o < K; o += 64) {
+            const float v = zs[o] + (o < 64 ? b2_near : b2[o]);
+            zs[o] = v;
+            m = fmaxf(m, v);
+        }
         m = wave_max(m);
         float S = 0.f, Zl = 0.f;  // normalisers of the prediction and of the soft label (Eq. 5)
+#pragma unroll 1
         for (int o = lane; o < K; o += 64) {
-            S += expf(z[o] - m);
+            const float e = expf(zs[o] - m);
+            ds[o] = e;
+            S += e;
             Zl += expf(-fabsf((float)(o - i)));
         }
         S = wave_sum(S);
         Zl = wave_sum(Zl);
         const float lnS = logf(S);
         float yhat = 0.f, ce = 0.f;
+#pragma unroll 1
         for (int o = lane; o < K; o += 64) {
-            const float ph = expf(z[o] - m) / S;
+            const float ph = ds[o] / S;
             const float p = expf(-fabsf((float)(o - i))) / Zl;
-            yhat = fmaf(ph, centers[o], yhat);  // Eq. 6
-            ce -= p * ((z[o] - m) - lnS);
+            yhat = fmaf(ph, o < 64 ? center_near : centers[o], yhat);  // Eq. 6
+            ce -= p * ((zs[o] - m) - lnS);
         }
         yhat = wave_sum(yhat);
         ce = wave_sum(ce);
-        const float err = yhat - y[b];
+        const float err = yhat - y_b;
         // Eq. 9: a sequence's steps share its 1/N; without step counts every sample weighs 1/B
-        const float wb = steps ? 1.0f / ((float)n_seqs * (float)steps[b]) : 1.0f / (float)B;
+        const float wb = steps ? 1.0f / ((float)n_seqs * (float)steps_b) : 1.0f / (float)B;
+#pragma unroll 1
         for (int o = lane; o < K; o += 64) {
-            const float ph = expf(z[o] - m) / S;
+            const float ph = ds[o] / S;
             const float p = expf(-fabsf((float)(o - i))) / Zl;
-            const float g = wb * (lambda * (ph - p) + (1.0f - lambda) * 2.0f * err * ph * (centers[o] - yhat));
-            dz[o] = g;
-            dz_out[(long)b * K + o] = g;
+            const float center = o < 64 ? center_near : centers[o];
+            const float g = wb * (lambda * (ph - p) + (1.0f - lambda) * 2.0f * err * ph * (center - yhat));
+            ds[o] = g;
+            if (kept)
+                dz_out[(long)b * K + o] = g;
         }
-        if (lane == 0) {
+        if (lane == 0 && kept) {
             loss_part[2 * b] = wb * ce;
             loss_part[2 * b + 1] = wb * err * err;
         }
     }
     __syncthreads();
-    // d loss / d pre-activation = (W2^T dz) where the unit is active; many rows of W2 in flight per thread
-    for (int j = tid; j < d_h; j += 256) {
-        float s = 0.f;
-#pragma unroll 20
-        for (int o = 0; o < K; ++o)
-            s = fmaf(dz[o], w2[(long)o * d_h + j], s);
-        dact[(long)b * d_h + j] = a[j] > 0.f ? s : 0.f;
+    // d loss / d pre-activation = (W2^T dz) where the unit is active
+#pragma unroll 1
+    for (int j = tid; j < d_h; j += TAIL_THREADS) {
+        float s[NS] = {};
+#pragma unroll 1
+        for (int o0 = 0; o0 < K; o0 += DACT_ROWS) {
+            if (j != tid || o0 > 0)
+                load_rows(o0, j);
+#pragma unroll
+            for (int o = 0; o < DACT_ROWS; ++o)
+                if (o0 + o < K)
+#pragma unroll
+                    for (int n = 0; n < NS; ++n)
+                        s[n] = fmaf(dz[n * K + o0 + o], w[o], s[n]);
+        }
+#pragma unroll
+        for (int n = 0; n < NS; ++n)
+            if (b0 + n < B)
+                dact[(long)(b0 + n) * d_h + j] = a[n * lda + hidden_place(j, d_h)] > 0.f ? s[n] : 0.f;
     }
 }
 
@@ -535,25 +532,43 @@ __global__ __launch_bounds__(256, SPLIT ? 2 : 1) void train_update_kernel(Update
 
 }  // namespace
 
+template <bool TINY, int NS>
+static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStream_t st)
+{
+    static DeviceMask raised{0};
+    hipError_t e = raise_dynamic_lds_limit((const void *)train_sample_kernel<TINY, NS>, (int)TAIL_LDS_LIMIT, raised);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL((train_sample_kernel<TINY, NS>), dim3((a.B - 1) / NS + 1), dim3(TAIL_THREADS), NS * lds, st, a.act_part,
+                       nks, a.B, a.d_h, a.K, a.b1, a.w2, a.b2, a.centers, a.bin, a.y, a.steps, a.n_seqs, a.lambda, a.act,
+                       a.dact, a.dz, a.loss_part);
+    return hipGetLastError();
+}
+
+static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStream_t st)
+{
+    if (a.d_h < 4)
+        return launch_samples<true, 1>(a, nks, lds, st);
+    const int ns = tail_sequences(a.B, lds);
+    return ns == 4 ? launch_samples<false, 4>(a, nks, lds, st)
+           : ns == 2 ? launch_samples<false, 2>(a, nks, lds, st) : launch_samples<false, 1>(a, nks, lds, st);
+}
+
 hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
 {
     if (a.B <= 0)
         return hipSuccess;
     if (a.d % 4 != 0)
         return hipErrorInvalidValue;
-    const size_t lds = ((size_t)a.d_h + 2 * (size_t)a.K) * sizeof(float);
-    if (lds > 96 * 1024)
+    const size_t lds = ((size_t)tail_row(a.d_h) + 2 * (size_t)a.K) * sizeof(float);
+    if (lds > TAIL_LDS_LIMIT)
         return hipErrorInvalidValue;
-    static DeviceMask lds_limit_raised{0};
-    hipError_t ea = raise_dynamic_lds_limit((const void *)train_sample_kernel, 96 * 1024, lds_limit_raised);
-    if (ea != hipSuccess)
-        return ea;
     hipError_t e = head_layer1(a.x, nullptr, a.B, a.d, a.d_h, a.w1, DT_F32, a.act_part, st);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(train_sample_kernel, dim3(a.B), dim3(256), lds, st, a.act_part, head_k_splits(a.d, a.d_h, a.B, DT_F32), a.B,
-                       a.d_h, a.K, a.b1, a.w2, a.b2, a.centers, a.bin, a.y, a.steps, a.n_seqs, a.lambda, a.act,
-                       a.dact, a.dz, a.loss_part);
+    e = launch_samples(a, head_k_splits(a.d, a.d_h, a.B, DT_F32), lds, st);
+    if (e != hipSuccess)
+        return e;
     Adam h;
     h.lr = a.lr;
     h.beta1 = a.beta1;
