@@ -134,9 +134,9 @@ __device__ constexpr int SPLIT_W[K1_SPLIT_TERMS] = {2, 1, 0, 1, 0, 0};
 __device__ constexpr int SPLIT_H[K1_SPLIT_TERMS] = {0, 1, 2, 0, 1, 0};
 
 // Packs rows of a row-major fp32 matrix src[R x d] (d % 4 == 0) into the six segments of one operand
-// side.  Thread layout as in the bf16 kernel, over the `kseg` blocks of ONE segment: every thread reads
+// side, or into the first three, which hold every piece once. Thread layout as in the bf16 kernel, over the `kseg` blocks of ONE segment: every thread reads
 // its 8 values once, splits them, and stores the piece each segment asks for.
-template <bool HIDDEN_SIDE>
+template <bool HIDDEN_SIDE, int SEGMENTS>
 __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *__restrict__ src, long R, int d,
                                                                   int kseg, int tile_rows, int rows_per_wg,
                                                                   unsigned char *__restrict__ dst)
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *_
     if (kk >= kseg)
         return;
     const long k_elem = (long)kk * BK + chunk * 8;
-    const long KT = (long)K1_SPLIT_TERMS * kseg;
+    const long KT = (long)SEGMENTS * kseg;
     const int r0 = blockIdx.z * rows_per_wg;
     for (int r = r0 + rsub; r < r0 + rows_per_wg; r += 8) {
         const long row = tile * tile_rows + r;
@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *_
                               (pc[p][6] >> 16) | pc[p][7]);
         const int in_block = r * ROW_BYTES + ((chunk ^ swizzle_key(r)) << 4);
 #pragma unroll
-        for (int s = 0; s < K1_SPLIT_TERMS; ++s) {
+        for (int s = 0; s < SEGMENTS; ++s) {
             const int piece = HIDDEN_SIDE ? SPLIT_H[s] : SPLIT_W[s];
             *(uint4 *)(dst + (tile * KT + (long)s * kseg + kk) * (long)(tile_rows * ROW_BYTES) + in_block) = q[piece];
         }
@@ -196,8 +196,8 @@ hipError_t k1_clear_pace(int *pace, long count, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, int tile_rows, void *dst,
-                                  hipStream_t st)
+hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, bool pieces, int tile_rows,
+                                  void *dst, hipStream_t st)
 {
     if (rows <= 0)
         return hipSuccess;
@@ -209,12 +209,16 @@ hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hid
         return hipErrorInvalidValue;
     const int rows_per_wg = tiles * ((kseg + 7) / 8) >= 1024 ? tile_rows : 32;
     const dim3 grid((unsigned)tiles, (kseg + 7) / 8, tile_rows / rows_per_wg);
-    if (hidden_side)
-        hipLaunchKernelGGL(pack_rows_f32_split_kernel<true>, grid, dim3(256), 0, st, (const float *)src, (long)rows,
-                           d, kseg, tile_rows, rows_per_wg, (unsigned char *)dst);
+#define EGTP_PACK_SPLIT(SIDE, SEGMENTS)                                                                                     \
+    hipLaunchKernelGGL((pack_rows_f32_split_kernel<SIDE, SEGMENTS>), grid, dim3(256), 0, st, (const float *)src, (long)rows, d, \
+                       kseg, tile_rows, rows_per_wg, (unsigned char *)dst)
+    if (!hidden_side)
+        EGTP_PACK_SPLIT(false, K1_SPLIT_TERMS);
+    else if (pieces)
+        EGTP_PACK_SPLIT(true, 3);
     else
-        hipLaunchKernelGGL(pack_rows_f32_split_kernel<false>, grid, dim3(256), 0, st, (const float *)src, (long)rows,
-                           d, kseg, tile_rows, rows_per_wg, (unsigned char *)dst);
+        EGTP_PACK_SPLIT(true, K1_SPLIT_TERMS);
+#undef EGTP_PACK_SPLIT
     return hipGetLastError();
 }
 

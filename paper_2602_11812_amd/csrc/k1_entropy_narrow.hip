@@ -13,6 +13,15 @@
 // of the current step have returned, so its stage can be loaded again; fragments are read one step ahead of
 // their MFMAs into two register sets that swap roles (the loop is unrolled by two, K is an even number of steps).
 //
+// fp32 operands (PIECES): W_lm and the hidden states as three bf16 pieces each, of whose nine products six matter.  The six
+// segments of the packed W_lm hold pieces 2, 1, 0, 1, 0, 0; a contraction that walks them reads every piece twice on
+// average.  Here a K step brings the pieces (2, 0), (1, 1), (0, 2) of (W_lm, hidden) one after the other, and the fragments
+// of earlier pieces are still in registers for the other three products: half the reads and half the steps.  The leading
+// product (0, 0) has accumulators of its own, one set for each half of K, so that the small ones meet only their like, as in
+// the long contraction, and the large sums are half as long.  Whole decode steps: 24
+// tokens against V = 151936, d = 4096 1170 to 1270 -> 670 (5.7 TB/s of pieces); 2, V = 94086, d = 1160 216 -> 125; 64, V = 32000,
+// d = 2048 156 -> 87; 47, V = 6763, d = 3440 160 -> 105.
+//
 // Measured: 64 tokens against V = 151936, d = 4096: 199 us = 6.3 TB/s of W_lm (the 256 x 256 tile: 286 us on 198 of the
 // 256 compute units); 309 fp32 tokens against V = 4096, d = 256: 15.4 us, 37.1 before.  Two K steps per barrier gain
 // nothing.  (Blocks of 192 tokens, which ran on this kernel as well, are the stream kernel's now.)
@@ -34,7 +43,7 @@ constexpr int STAGES = 144 * 1024 / STAGE_BYTES;    // 12
 constexpr int RING_BYTES = STAGES * STAGE_BYTES;
 static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "ring depth");
 
-template <bool STREAM_W>
+template <bool PIECES, bool STREAM_W>
 __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigned char *__restrict__ Wp,
                                                                    const unsigned char *__restrict__ Hp, long T, int KT,
                                                                    int V, int ntb, int nsplit, int ntiles_v,
@@ -69,22 +78,25 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     const int vt_begin = sp * per_range + min(sp, longer);
     const int vt_end = vt_begin + per_range + (sp < longer ? 1 : 0);
     const long tok0 = (long)tb * (32 * NI);
-    const int total = (vt_end - vt_begin) * KT;
+    // KT blocks of a packed row tile of W_lm, of which a sweep loads KL in turn: all, or with PIECES the first three segments,
+    // segment by segment for every K step
+    const int kseg = PIECES ? KT / K1_SPLIT_TERMS : KT, KL = PIECES ? 3 * kseg : KT;
+    const int total = (vt_end - vt_begin) * KL;
 
     // ---- global -> LDS: a block is copied linearly, 1 KiB per wave-wide load
     const int lane_off = wave * 1024 + lane * 16;
     const int w_tile_bytes = KT * TILE_BYTES;  // (the launcher checks the range)
-    const int h_tile_bytes = KT * H_STEP_BYTES;
+    const int h_tile_bytes = KL * H_STEP_BYTES;
     const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
     unsigned char *lds_wave = smem + wave * 1024;
     // The load stream runs ahead of the MFMAs by the ring.  Past the end it keeps re-reading the last step (into
     // stages nobody reads any more), so every step issues the same number of loads and one wait constant serves.
-    int lvt = vt_begin, lkt = 0, lstep = 0;
+    int lvt = vt_begin, lkt = 0, lseg = 0, lstep = 0;  // (segment lseg: blocks lseg, lseg + kseg, ...)
     auto issue_loads = [&](int stage) {
         lvt = __builtin_amdgcn_readfirstlane(lvt);  // a descriptor must be uniform, and known to be
         const __amdgpu_buffer_rsrc_t rW = raw_buffer(Wp + (long)(lvt >> 1) * w_tile_bytes, w_tile_bytes);
-        const int woff = lkt * TILE_BYTES + (lvt & 1) * W_STEP_BYTES;
-        const int hoff = lkt * H_STEP_BYTES;
+        const int woff = (lseg + lkt) * TILE_BYTES + (lvt & 1) * W_STEP_BYTES;
+        const int hoff = (lseg + lkt) * H_STEP_BYTES;
         unsigned char *dst = lds_wave + stage * STAGE_BYTES;
 #pragma unroll
         for (int p = 0; p < W_STEP_BYTES / 4096; ++p)
@@ -94,8 +106,13 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
             load16_to_lds(rH, lane_off, hoff + p * 4096, dst + W_STEP_BYTES + p * 4096);
         const int adv = lstep + 1 < total ? 1 : 0;
         lstep += adv;
-        const int nk = lkt + adv;
-        const int wrap = nk == KT ? 1 : 0;
+        int next = adv;  // to the next K step
+        if (PIECES) {
+            next = lseg + adv * kseg == 3 * kseg ? 1 : 0;
+            lseg = next ? 0 : lseg + adv * kseg;
+        }
+        const int nk = lkt + next;
+        const int wrap = nk == kseg ? 1 : 0;
         lkt = wrap ? 0 : nk;
         lvt += wrap;
     };
@@ -121,7 +138,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     };
 
     Stats st[NI];
-    f32x4 acc[4][NI];
+    f32x4 acc[4][NI], lead[4][NI], half[4][NI];  // PIECES: the small products, the leading ones of a half of K, of the first half
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
         st[ni].m = NEG_BIG;
@@ -129,8 +146,15 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
         st[ni].U = 0.f;
 #pragma unroll
         for (int mi = 0; mi < 4; ++mi)
-            acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+            acc[mi][ni] = lead[mi][ni] = half[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    auto multiply = [&](f32x4 (&to)[4][NI], const Frags &w, const Frags &h) {
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+                to[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.a[mi], h.b[ni], to[mi][ni], 0, 0, 0);
+    };
 
 #pragma unroll
     for (int s = 0; s < STAGES; ++s)
@@ -138,14 +162,14 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     wait_vmcnt<(STAGES - 1) * LOADS>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    Frags f0, f1;
+    Frags f0, f1, f2;
     read_frags(f0, 0);
     int cstage = 0;  // stage of the step whose MFMAs are next
 
-    // One step: `cur` holds its fragments.  Wait for the next step's loads (the newest STAGES - 2 steps may still be
+    // One step.  Wait for the next step's loads (the newest STAGES - 2 steps may still be
     // in flight) and for this wave's own fragment reads, meet the other waves, refill the stage just freed, read the
     // next fragments, multiply.  A bare barrier: a fence would drain the ring.
-    auto step = [&](const Frags &cur, Frags &next) {
+    auto step = [&](Frags &next, auto products) {
         wait_vmcnt<(STAGES - 2) * LOADS>();
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
         __builtin_amdgcn_s_barrier();
@@ -153,19 +177,42 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
         const int nstage = cstage + 1 == STAGES ? 0 : cstage + 1;
         read_frags(next, nstage);
         issue_loads(cstage);
-#pragma unroll
-        for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a[mi], cur.b[ni], acc[mi][ni], 0, 0, 0);
+        products();
         cstage = nstage;
         __builtin_amdgcn_sched_barrier(0);
     };
 
     for (int vt = vt_begin; vt < vt_end; ++vt) {
-        for (int kt = 0; kt < KT; kt += 2) {
-            step(f0, f1);
-            step(f1, f0);
+        if constexpr (PIECES) {
+            for (int h = 0, kk = 0; h < 2; ++h) {
+                for (const int end = h ? kseg : kseg / 2; kk < end; ++kk) {
+                    step(f1, [&] { multiply(acc, f0, f0); });
+                    step(f2, [&] {
+                        multiply(acc, f1, f1);
+                        multiply(acc, f1, f0);
+                    });
+                    Frags ahead;
+                    step(ahead, [&] {
+                        multiply(acc, f2, f2);
+                        multiply(acc, f2, f1);
+                        multiply(lead, f2, f0);
+                    });
+                    f0 = ahead;
+                }
+                if (h == 0)
+#pragma unroll
+                    for (int mi = 0; mi < 4; ++mi)
+#pragma unroll
+                        for (int ni = 0; ni < NI; ++ni) {
+                            half[mi][ni] = lead[mi][ni];
+                            lead[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        }
+            }
+        } else {
+            for (int kt = 0; kt < KT; kt += 2) {
+                step(f1, [&] { multiply(acc, f0, f0); });
+                step(f0, [&] { multiply(acc, f1, f1); });
+            }
         }
         // a tile of logits is in registers: fold it into the statistics and forget it
         const int row_base = vt * NM + wm * 64 + 4 * kq;
@@ -177,8 +224,8 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
             for (int q = 0; q < 4; ++q)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    z[4 * q + i] = acc[q][ni][i];
-                    acc[q][ni][i] = 0.f;
+                    z[4 * q + i] = PIECES ? (half[q][ni][i] + lead[q][ni][i]) + acc[q][ni][i] : acc[q][ni][i];
+                    acc[q][ni][i] = lead[q][ni][i] = 0.f;
                 }
             if (masked)
                 fold<true>(z, st[ni], row_base, V);
@@ -233,16 +280,16 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     }
 }
 
-template <bool STREAM_W>
+template <bool PIECES, bool STREAM_W>
 hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p,
                   float *part, hipStream_t st)
 {
     static DeviceMask lds_limit_raised{0};
-    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<STREAM_W>, RING_BYTES,
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<PIECES, STREAM_W>, RING_BYTES,
                                                  lds_limit_raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((k1_entropy_narrow_kernel<STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), RING_BYTES,
+    hipLaunchKernelGGL((k1_entropy_narrow_kernel<PIECES, STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), RING_BYTES,
                        st, (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
                        p.nsplit, p.ntiles_v, part);
     return hipGetLastError();
@@ -254,15 +301,21 @@ hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, in
                              const K1Plan &p, float *part, hipStream_t st)
 {
     const int kt = k_steps(K);
+    if (p.pieces && kt % K1_SPLIT_TERMS != 0)
+        return hipErrorInvalidValue;
     if (T <= 0 || p.tb_tokens != K1_NARROW_TOKENS || p.tile_v != NM || p.nsplit < 1 || p.nsplit > p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
         (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + NM - 1) / NM || (long)kt * TILE_BYTES > 0x7fffffffL)
         return hipErrorInvalidValue;
     // One token block reads W_lm once.  If the 256 MiB Infinity Cache cannot hold it until the next call either, its
     // loads carry the non-temporal hint: 64 tokens, d = 4096, V = 151936 (1.24 GB) 225 -> 199 us = 6.3 TB/s; V = 65536
     // and d = 2560 (336 MB) 60.5 -> 55.7; but V = 65536 and d = 2048 (268 MB) 44 -> 46 and V = 32000 (131 MB) 25 -> 26.
-    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * kt * W_STEP_BYTES > ((int64_t)256 << 20);
-    return stream ? launch<true>(hidden_packed, w_packed, T, kt, V, p, part, st)
-                  : launch<false>(hidden_packed, w_packed, T, kt, V, p, part, st);
+    const int read = p.pieces ? kt / 2 : kt;  // blocks that a sweep reads
+    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * read * W_STEP_BYTES > ((int64_t)256 << 20);
+#define EGTP_NARROW(PIECES)                                                              \
+    (stream ? launch<PIECES, true>(hidden_packed, w_packed, T, kt, V, p, part, st)       \
+            : launch<PIECES, false>(hidden_packed, w_packed, T, kt, V, p, part, st))
+    return p.pieces ? EGTP_NARROW(true) : EGTP_NARROW(false);
+#undef EGTP_NARROW
 }
 
 }  // namespace egtp

@@ -54,6 +54,29 @@ static_assert(Shape<12>::TOKENS == K1_STREAM_WIDE_TOKENS && Shape<12>::FPW * 64 
 constexpr int PACE_SWEEPS = K1_STREAM_PACE_TILES / Shape<8>::MAX_MI;  // sweeps between two pacing points
 static_assert(2L * K1_STREAM_MAX_STEPS * TILE_BYTES <= 0x7fffffffL, "two packed tiles under one offset");
 
+// fp32 operands read by their pieces: the blocks that each K step multiplies.  Only the first three segments are read, W_lm's
+// holding pieces 2, 1, 0 and the hidden states' 0, 1, 2; every K step of those is taken through the five small
+// products (2,0) (1,1) (0,2) (1,0) (0,1) in turn, so that a piece is read again while it is in the L2, and the leading
+// products (0,0) follow in a pass of their own: the accumulators meet the small terms first, as in the long contraction.
+struct PieceWalk {
+    static constexpr unsigned W_SEGMENTS = 0 | 1 << 2 | 2 << 4 | 1 << 6 | 2 << 8 | 2 << 10;  // two bits per product
+    static constexpr unsigned H_SEGMENTS = 0 | 1 << 2 | 2 << 4 | 0 << 6 | 1 << 8 | 0 << 10;
+    static constexpr int LEAD = K1_SPLIT_TERMS - 1;
+    int kk = 0, product = 0;
+    // the block of this step; moves on to the next step, from the last one to the first
+    __device__ __forceinline__ int next(unsigned segments, int kseg)
+    {
+        const int block = (int)(segments >> (2 * product) & 3u) * kseg + kk;
+        const bool lead = product == LEAD, next_k = product >= LEAD - 1;
+        product = lead ? LEAD : (next_k ? 0 : product + 1);
+        const int k = kk + (next_k ? 1 : 0);
+        const bool end = k == kseg;
+        kk = end ? 0 : k;
+        product = end ? (lead ? 0 : LEAD) : product;
+        return block;
+    }
+};
+
 template <bool STREAM_W>
 __device__ __forceinline__ bf16x8 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int lane_byte_offset, int scalar_byte_offset)
 {
@@ -61,7 +84,7 @@ __device__ __forceinline__ bf16x8 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int
                                                                            STREAM_W ? 2 : 0));
 }
 
-template <int NI, int D, bool STREAM_W>
+template <int NI, int D, bool PIECES, bool STREAM_W>
 __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigned char *__restrict__ Wp,
                                                                    const unsigned char *__restrict__ Hp, long T, int KT,
                                                                    int V, int ntb, int nsplit, int tps, int ntiles_v, int group, bool whole_cohorts,
@@ -152,17 +175,23 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
         }
     };
     bf16x8 wr[D][MAX_MI];
+    const int kseg = KT / K1_SPLIT_TERMS;  // PIECES: K steps of a segment
+    PieceWalk walk_w, walk_h;
+    auto w_offset = [&](int kt) {  // of the step whose fragments are loaded next
+        return (PIECES ? walk_w.next(PieceWalk::W_SEGMENTS, kseg) : kt) * TILE_BYTES;
+    };
 
     // ---- hidden states: memory -> LDS ring, copied linearly, 1 KiB per wave-wide load; the same block sweep after sweep
     const int lane_h = wave * 1024 + lane * 16;
-    const int h_tile_bytes = KT * H_STEP_BYTES;
+    const int h_tile_bytes = (PIECES ? 3 * kseg : KT) * H_STEP_BYTES;
     const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
     int hkt = 0;
     auto load_h = [&](int stage) {
         unsigned char *dst = smem + stage * H_STEP_BYTES + wave * 1024;
+        const int off = (PIECES ? walk_h.next(PieceWalk::H_SEGMENTS, kseg) : hkt) * H_STEP_BYTES;
 #pragma unroll
         for (int p = 0; p < H_LOADS; ++p)
-            load16_to_lds(rH, lane_h, hkt * H_STEP_BYTES + p * 4096, dst + p * 4096);
+            load16_to_lds(rH, lane_h, off + p * 4096, dst + p * 4096);
         hkt = hkt + 1 == KT ? 0 : hkt + 1;
     };
     const unsigned frag_h = (unsigned)lane_w;
@@ -181,10 +210,12 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     for (int s = 0; s < H_STAGES; ++s)
         load_h(s);
 #pragma unroll
-    for (int s = 0; s < D; ++s)
+    for (int s = 0; s < D; ++s) {
+        const int off = w_offset(s);
 #pragma unroll
         for (int m = 0; m < MAX_MI; ++m)
-            wr[s][m] = load_fragment<STREAM_W>(rW, lane_w, s * TILE_BYTES + frag_off[m]);
+            wr[s][m] = load_fragment<STREAM_W>(rW, lane_w, off + frag_off[m]);
+    }
     wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -214,6 +245,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
             __builtin_amdgcn_sched_barrier(0);
             const int nstage = cstage + 1 == H_STAGES ? 0 : cstage + 1;
             const unsigned char *s = smem + nstage * H_STEP_BYTES + frag_h;
+            const int woff = w_offset(kt_load + P);
             // The order is pinned row by row: the fragment reads behind the first row's MFMAs, then in every row the
             // load of the row before it (whose registers are free by then), the hidden states' loads in rows 0 and 1.
 #pragma unroll
@@ -223,7 +255,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
                     for (int ni = 0; ni < NI; ++ni)
                         fb[Q ^ 1][ni] = *(const bf16x8 *)(s + ni * FRAG_BYTES);
                 } else {
-                    wr[P][mi - 1] = load_fragment<STREAM_W>(rW, lane_w, (kt_load + P) * TILE_BYTES + frag_off[mi - 1]);
+                    wr[P][mi - 1] = load_fragment<STREAM_W>(rW, lane_w, woff + frag_off[mi - 1]);
                 }
                 if (mi == 1)
                     load_h(cstage);
@@ -246,7 +278,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            wr[P][MI - 1] = load_fragment<STREAM_W>(rW, lane_w, (kt_load + P) * TILE_BYTES + frag_off[MI - 1]);
+            wr[P][MI - 1] = load_fragment<STREAM_W>(rW, lane_w, woff + frag_off[MI - 1]);
             cstage = nstage;
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -374,18 +406,18 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     }
 }
 
-template <int NI, int D, bool STREAM_W>
+template <int NI, int D, bool PIECES, bool STREAM_W>
 hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p, int group,
                   long wgs, float *part, int *pace, hipStream_t st)
 {
     using S = Shape<NI>;
     static_assert(4 * S::TOKENS * 3 * sizeof(float) <= S::LDS_BYTES, "LDS");
     static DeviceMask lds_limit_raised{0};
-    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_stream_kernel<NI, D, STREAM_W>, S::LDS_BYTES,
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_stream_kernel<NI, D, PIECES, STREAM_W>, S::LDS_BYTES,
                                                  lds_limit_raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((k1_entropy_stream_kernel<NI, D, STREAM_W>), dim3((unsigned)wgs), dim3(256), S::LDS_BYTES, st,
+    hipLaunchKernelGGL((k1_entropy_stream_kernel<NI, D, PIECES, STREAM_W>), dim3((unsigned)wgs), dim3(256), S::LDS_BYTES, st,
                        (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
                        p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
     return hipGetLastError();
@@ -393,15 +425,16 @@ hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, in
 
 }  // namespace
 
-hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V, const K1Plan &p,
-                             float *part, int *pace, hipStream_t st)
+hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+                             const K1Plan &p, float *part, int *pace, hipStream_t st)
 {
     const int kt = k_steps(K);
     if (T <= 0 || p.nsplit < 1 || p.tiles_per_split < 1 || (long)p.nsplit * p.tiles_per_split < p.ntiles_v ||
         (long)(p.nsplit - 1) * p.tiles_per_split >= p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
-        (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + p.tile_v - 1) / p.tile_v || kt > K1_STREAM_MAX_STEPS)
+        (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + p.tile_v - 1) / p.tile_v || kt > K1_STREAM_MAX_STEPS || (p.pieces && kt % K1_SPLIT_TERMS != 0))
         return hipErrorInvalidValue;
-    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * p.tile_v * kt * ROW_BYTES > ((int64_t)256 << 20);
+    const int read = p.pieces ? kt / 2 : kt;  // blocks of W_lm that a sweep needs
+    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * p.tile_v * read * ROW_BYTES > ((int64_t)256 << 20);
     const int group = p.tile_v == K1_STREAM_TILE_V ? k1_stream_group(p.nsplit) : 8;
     const long units = (long)p.ntb * p.nsplit, cohorts = k1_stream_cohorts(p.ntb, p.nsplit);
     const long wgs = p.whole_cohorts ? 8 * ((cohorts + 7) / 8) * COHORT : units;
@@ -414,14 +447,16 @@ hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, in
         if (e != hipSuccess)
             return e;
     }
-#define EGTP_STREAM(NI, D)                                                                                     \
-    (stream ? launch<NI, D, true>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st)             \
-            : launch<NI, D, false>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st))
+#define EGTP_STREAM_OF(NI, D, PIECES)                                                                           \
+    (stream ? launch<NI, D, PIECES, true>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st)      \
+            : launch<NI, D, PIECES, false>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st))
+#define EGTP_STREAM(NI, D) (p.pieces ? EGTP_STREAM_OF(NI, D, true) : EGTP_STREAM_OF(NI, D, false))
     if (p.tb_tokens == K1_STREAM_TOKENS && p.tile_v == K1_STREAM_TILE_V)
         return EGTP_STREAM(8, 2);
     if (p.tb_tokens == K1_STREAM_WIDE_TOKENS && p.tile_v == K1_NARROW_TILE_V)
         return kt % 4 == 0 ? EGTP_STREAM(12, 4) : EGTP_STREAM(12, 2);
 #undef EGTP_STREAM
+#undef EGTP_STREAM_OF
     return hipErrorInvalidValue;
 }
 

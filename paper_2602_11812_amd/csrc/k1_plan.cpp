@@ -19,7 +19,7 @@ static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number 
 // the load ring, final merge and stores) -- and no plan is faster than one read of W_lm (5.7 TB/s).
 //   wide     256 rows x 256 tokens        625 a step for a W_lm of 48 MB, 18.5 more per doubling up to 712 for 1.2 GB;
 //            5000 a tile
-//   narrow   128 rows x 64 tokens         206 a step, 624 a tile
+//   narrow   128 rows x 64 tokens         206 a step, 624 a tile; fp32 operands, in half the steps, 300 and 1300
 //   stream   512 rows x 128 tokens        642 a step (+ 400 / token blocks: fewer of them share a read of W_lm), 6200
 //            a sweep; remainders of 4 and 2 fragments a wave 406 and 288, 3100 and 1550
 //            256 rows x 192 tokens        700 a step, 4000 a sweep; the remainder of 128 rows 410 and 2000
@@ -33,7 +33,7 @@ static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number 
 // (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964, where WORTH_IT
 // keeps the wide tile -- the 2.5 %; at d = 256 the folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
 static constexpr double WIDE_STEP_NS = 625.0, WIDE_STEP_NS_PER_DOUBLING = 18.5, WIDE_W_BYTES = 48e6, WIDE_FOLD_NS = 5000.0;
-static constexpr double NARROW_STEP_NS = 206.0, NARROW_FOLD_NS = 624.0;
+static constexpr double NARROW_STEP_NS = 206.0, NARROW_PIECES_STEP_NS = 300.0, NARROW_FOLD_NS = 624.0, NARROW_PIECES_FOLD_NS = 1300.0;
 static constexpr double PAIR_STEP_NS = 700.0, SINGLE_STEP_NS = 410.0, PAIR_FOLD_NS = 4000.0;
 static constexpr double STREAM_STEP_NS = 642.0, STREAM_ALONE_NS = 400.0, STREAM_FOLD_NS = 6200.0;
 static constexpr double STREAM_STEP4_NS = 406.0, STREAM_STEP2_NS = 288.0;
@@ -78,7 +78,7 @@ static double stream_range_ns(const K1Plan &p, long steps)
 }
 
 // the plan of another kernel where that is cheaper than the wide plan p
-static K1Plan cheaper(const K1Plan &p, int64_t T, int V, long steps)
+static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int V, long steps)
 {
     if (V <= TV || T <= 0)
         return p;  // a vocabulary inside one tile: there is nothing to divide
@@ -101,9 +101,14 @@ static K1Plan cheaper(const K1Plan &p, int64_t T, int V, long steps)
         q.ntiles_v = (V + tile_v - 1) / tile_v;
         q.tiles_per_split = (int)((q.ntiles_v + ranges - 1) / ranges);
         q.nsplit = (q.ntiles_v + q.tiles_per_split - 1) / q.tiles_per_split;
+        // Worth it where W_lm's read is the bound: narrow plans, and one or two blocks of the stream kernel (d = 2048, V = 32000:
+        // 160 tokens 196 -> 180 us, 256 240 -> 186; of more blocks, 1500 tokens, d = 1024, V = 8000 144 -> 152).
+        q.pieces = dtype == DT_F32 && ((tb_tokens == K1_NARROW_TOKENS && tile_v == K1_NARROW_TILE_V) || q.ntb <= 2);
     };
     K1Plan q;
     const int64_t blocks64 = (T + 63) / 64;
+    const double narrow_step = dtype == DT_F32 ? NARROW_PIECES_STEP_NS : NARROW_STEP_NS;
+    const double narrow_fold = dtype == DT_F32 ? NARROW_PIECES_FOLD_NS : NARROW_FOLD_NS;
     for (int tokens = K1_NARROW_TOKENS; tokens <= K1_STREAM_WIDE_TOKENS && blocks64 <= 32;
          tokens += K1_STREAM_WIDE_TOKENS - K1_NARROW_TOKENS)
         for (int rounds = 1; rounds <= 3 && (tokens == K1_NARROW_TOKENS || steps <= K1_STREAM_MAX_STEPS); ++rounds) {
@@ -111,11 +116,13 @@ static K1Plan cheaper(const K1Plan &p, int64_t T, int V, long steps)
             if (ranges < 1)
                 continue;
             cut(q, tokens, K1_NARROW_TILE_V, ranges);
+            // (of fp32 operands the narrow kernel reads every piece once, three of the six segments)
+            const long read = tokens == K1_NARROW_TOKENS && dtype == DT_F32 ? steps / 2 : steps;
             const double range = tokens == K1_NARROW_TOKENS
-                                     ? q.tiles_per_split * ((double)steps * NARROW_STEP_NS + NARROW_FOLD_NS)
+                                     ? q.tiles_per_split * ((double)read * narrow_step + narrow_fold)
                                      : (q.tiles_per_split / 2) * ((double)steps * PAIR_STEP_NS + PAIR_FOLD_NS) +
                                            (q.tiles_per_split % 2) * ((double)steps * SINGLE_STEP_NS + PAIR_FOLD_NS / 2);
-            const double ns = plan_ns(q, steps, range);
+            const double ns = plan_ns(q, read, range);
             if (ns < best_ns && fits(q)) {
                 best_ns = ns;
                 best = q;
@@ -176,7 +183,7 @@ K1Plan k1_plan(int dtype, int64_t T, int d, int V)
                 p.tiles_per_split = tps;
             }
         }
-        return cheaper(p, T, V, 2 * ((dk + 63) / 64));
+        return cheaper(p, dtype, T, V, 2 * ((dk + 63) / 64));
     }
     // One workgroup per (token block, vocabulary range), one workgroup per compute unit at a
     // time, all of about the same length: among the next few range counts take the one whose
@@ -198,7 +205,7 @@ K1Plan k1_plan(int dtype, int64_t T, int d, int V)
         if (nsc == p.ntiles_v)
             break;
     }
-    return cheaper(p, T, V, 2 * ((dk + 63) / 64));
+    return cheaper(p, dtype, T, V, 2 * ((dk + 63) / 64));
 }
 
 size_t k1_partial_floats(const K1Plan &p, int64_t T) { return (size_t)3 * (size_t)p.nsplit * (size_t)T; }

@@ -53,6 +53,9 @@ struct K1Plan {
     int nsplit;           // vocabulary ranges
     int tiles_per_split;  // tiles per range (last range may hold fewer)
     bool whole_cohorts = false;  // stream kernel, paced: each XCD gets whole cohorts (k1_stream_cohorts)
+    // fp32 operands, narrow and stream kernel: the sweep reads the three segments that hold each piece once, and the
+    // hidden states are packed into those alone
+    bool pieces = false;
 };
 
 K1Plan k1_plan(int dtype, int64_t T, int d, int V);

@@ -51,8 +51,9 @@ constexpr int K1_PACK_BLOCK_BYTES = K1_PACK_ROWS * K1_PACK_K * 2;
 // (`tile_rows`, a multiple of 64 up to 256); everything else is the same.
 size_t k1_packed_bytes(int64_t rows, int K);
 hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, hipStream_t st);
-// fp32 rows (d % 4 == 0) into the six K segments of the W_lm side or of the hidden-state side
-hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, int tile_rows, void *dst,
+// fp32 rows (d % 4 == 0) into the six K segments of the W_lm side or of the hidden-state side; `pieces`: the first three
+// of the latter
+hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, bool pieces, int tile_rows, void *dst,
                                   hipStream_t st);
 
 // Eq. 2, fused: partial (m = max z log2 e, sum e^{z-m}, sum e^{z-m}(z-m) log2 e) per token and vocabulary range.
