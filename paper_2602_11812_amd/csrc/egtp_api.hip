@@ -51,10 +51,11 @@ struct Carver {
 
 struct Workspace {
     float *entropy;      // [T]
-    float *k1_part;      // partial triples of the fused kernel; later, in the same memory, of the pooling:
-    float *pool_part;    //   partial rows of its units ...
-    float *pool_stats;   //   ... and two statistics each
+    float *k1_part;      // partial triples of the fused kernel
+    float *pool_part;    // of the pooling: partial rows of its units ...
+    float *pool_stats;   // ... and two statistics each
     int pool_unit;       // tokens per unit
+    bool pool_merges;    // they leave the triples alone: the pooling can merge them itself
     float *lse_old;      // [B]
     int *k1_pace;        // pacing counters of the fused kernel
     float *act;          // [k splits x B x d_h_max]
@@ -73,18 +74,21 @@ Workspace carve(const egtp_ctx *ctx, void *base, int64_t T, int32_t B)
     const size_t act_len = head_act_floats_bound(c.d, c.head_len.d_h, B, c.head_len.wdtype);
     const size_t act_rem = head_act_floats_bound(c.d, c.head_rem.d_h, B, c.head_rem.wdtype);
     w.entropy = cv.take<float>((size_t)T);
-    // the pooling runs when the partial triples have been merged: its units take their place
     const size_t triples = k1_partial_floats_bound(T), units = pool_unit_floats(c.d, T, B, POOL_UNIT);
     const size_t shared_floats = triples > units ? triples : units;
     w.k1_part = cv.take<float>(shared_floats);
     w.k1_pace = cv.take<int>(k1_pace_ints_bound(T));
     w.pool_unit = pool_unit(c.dtype, c.d, T, B, shared_floats);
-    w.pool_part = w.k1_part;
-    w.pool_stats = w.k1_part ? w.k1_part + (size_t)pool_units_bound(T, B, w.pool_unit) * (size_t)c.d : nullptr;
     w.lse_old = cv.take<float>((size_t)B);
     w.act = cv.take<float>(act_len > act_rem ? act_len : act_rem);
     const int K = (int)k1_contraction_len(c.dtype, c.d);
-    w.hidden_packed = cv.take<unsigned char>(k1_packed_bytes(T, K));
+    const size_t packed_bytes = k1_packed_bytes(T, K);
+    w.hidden_packed = cv.take<unsigned char>(packed_bytes);
+    // The pooling runs when the fused kernel has read the packed hidden states: its units take their place, or, where a
+    // batch of many empty sequences has too few, that of the triples, merged by then.
+    w.pool_merges = pool_unit_floats(c.d, T, B, w.pool_unit) * sizeof(float) <= packed_bytes;
+    w.pool_part = w.pool_merges ? (float *)w.hidden_packed : w.k1_part;
+    w.pool_stats = w.pool_part ? w.pool_part + (size_t)pool_units_bound(T, B, w.pool_unit) * (size_t)c.d : nullptr;
     w.w_packed = ctx->w_packed ? nullptr : cv.take<unsigned char>(k1_packed_bytes(c.vocab, K));
     w.bytes = cv.off;
     return w;
@@ -527,7 +531,8 @@ egtp_status score_impl(egtp_ctx *ctx, const void *hidden, const int32_t *offsets
     const egtp_config &c = ctx->cfg;
     const Workspace w = carve(ctx, workspace, T, B);
     float *entropy = entropy_out ? entropy_out : w.entropy;
-    if (T > 0 && (s = run_entropy(ctx, hidden, T, w, entropy, st)) != EGTP_OK)
+    int nsplit_left = 0;  // the pooling finishes the entropies itself where it can (one launch less)
+    if (T > 0 && (s = run_entropy(ctx, hidden, T, w, entropy, st, w.pool_merges ? &nsplit_left : nullptr)) != EGTP_OK)
         return s;
 
     PoolArgs a;
@@ -535,8 +540,8 @@ egtp_status score_impl(egtp_ctx *ctx, const void *hidden, const int32_t *offsets
     a.dtype = c.dtype;
     a.d = c.d;
     a.entropy = entropy;
-    a.k1_part = nullptr;
-    a.k1_nsplit = 0;
+    a.k1_part = nsplit_left > 0 ? w.k1_part : nullptr;
+    a.k1_nsplit = nsplit_left;
     a.offsets = offsets_dev;
     a.slot = nullptr;
     a.B = B;
@@ -583,10 +588,10 @@ egtp_status step_impl(egtp_ctx *ctx, const void *hidden_new, const int32_t *offs
     const egtp_config &c = ctx->cfg;
     const Workspace w = carve(ctx, workspace, T_new, B);
     float *entropy = entropy_out ? entropy_out : w.entropy;
-    // one token per sequence: the state update finishes the entropy itself (one launch less per decode step)
+    // the state update finishes the entropies itself where it can (one launch less)
     int nsplit_left = 0;
-    if (T_new > 0 &&
-        (s = run_entropy(ctx, hidden_new, T_new, w, entropy, st, offsets_new_dev ? nullptr : &nsplit_left)) != EGTP_OK)
+    if (T_new > 0 && (s = run_entropy(ctx, hidden_new, T_new, w, entropy, st,
+                                      !offsets_new_dev || w.pool_merges ? &nsplit_left : nullptr)) != EGTP_OK)
         return s;
 
     PoolArgs a;

@@ -135,15 +135,57 @@ __device__ int unit_sequence(const int32_t *__restrict__ offsets, int B, long u,
     return *sh;
 }
 
+// Eq. 2 finished for a unit: the nsplit partial triples that the fused kernel left for each of its n tokens from t0 on are
+// merged by a fixed tree -- 256 / unit threads share a token, thread g of them takes ranges g, g + 256 / unit, ... in
+// order, MERGE_AHEAD fetched before any is merged, then halves join halves through LDS.  Thread t < n returns with H of
+// token t0 + t.  The slices of a unit each merge for themselves; against a launch of its own in between (two slices and more
+// included): four short fp32 prompts 43.2 -> 39.7 us a pass, 173 tokens, d = 4096, V = 151936 274.8 -> 268.7 (different boxes), 2500
+// tokens, d = 2048, V = 32000 271 -> 262, 3600 tokens, d = 256 against 151936 rows (many ranges) 429 -> 424.
+constexpr int MERGE_AHEAD = 8;
+__device__ __forceinline__ float unit_entropy(const float *__restrict__ part, int nsplit, long T, long t0, int n, int unit_log2,
+                                              float (&sh)[3][256])
+{
+    const int tid = threadIdx.x, token = tid & ((1 << unit_log2) - 1), g = tid >> unit_log2, groups = 256 >> unit_log2;
+    const long plane = (long)nsplit * T;
+    const float *p = part + t0 + min(token, n - 1);
+    Stats a = {NEG_BIG, 0.f, 0.f};
+    for (int s0 = g; s0 < nsplit; s0 += groups * MERGE_AHEAD) {
+        Stats v[MERGE_AHEAD];
+#pragma unroll
+        for (int i = 0; i < MERGE_AHEAD; ++i) {
+            const float *q = p + (long)min(s0 + i * groups, nsplit - 1) * T;  // past the end: a valid range, not used
+            v[i].m = q[0], v[i].S = q[plane], v[i].U = q[2 * plane];
+        }
+#pragma unroll
+        for (int i = 0; i < MERGE_AHEAD; ++i)
+            if (s0 + i * groups < nsplit)
+                a = merge(a, v[i]);
+    }
+    for (int o = groups >> 1; o > 0; o >>= 1) {
+        if (g >= o && g < 2 * o)
+            sh[0][tid] = a.m, sh[1][tid] = a.S, sh[2][tid] = a.U;
+        __syncthreads();
+        if (g < o) {
+            const int other = tid + (o << unit_log2);
+            a = merge(a, Stats{sh[0][other], sh[1][other], sh[2][other]});
+        }
+    }
+    return logf(a.S) - a.U * 0.6931471805599453f / a.S;
+}
+
+// With part != NULL the weighted mode finishes Eq. 2 for its unit's tokens first and writes H to entropy; tokens that no
+// sequence holds (a table that begins after 0 or ends before T) get theirs from two units that the grid has beyond
+// those of the sequences and from the numbers that these leave unused.
 template <bool BF16, int MODE>
 __global__ __launch_bounds__(256) void pool_partial_kernel(
-    const void *__restrict__ hidden, int d, const float *__restrict__ entropy,
+    const void *__restrict__ hidden, int d, float *entropy, const float *__restrict__ part, int nsplit,
     const int32_t *__restrict__ offsets, int32_t B, long T, float inv_alpha, int unit_log2, int ysplit,
     const int32_t *__restrict__ slot, const float *state_lse, float *__restrict__ lse_old,
     float *__restrict__ partial, float2 *__restrict__ unit_stats)
 {
     __shared__ float w[256];
     __shared__ float red[2][4];
+    __shared__ float triples[MODE == POOL_WEIGHTED ? 3 : 1][256];
     __shared__ int seq;
     // Workgroup = (unit, feature slice), the slice varying fastest so that the slices of a unit -- pieces of
     // the same token rows -- are read at about the same time.  The grid holds pool_units_bound(T, B, unit) units:
@@ -156,14 +198,41 @@ __global__ __launch_bounds__(256) void pool_partial_kernel(
         lse_old[blockIdx.x] = state_lse[slot ? slot[blockIdx.x] : blockIdx.x];
     const int b = unit_sequence(offsets, B, u, unit_log2, &seq);
     const int begin = offsets[b];
-    const long t0 = clamp_token(begin + ((u - unit_base(begin, b, unit_log2)) << unit_log2), T);
-    const int n = (int)max(0L, min(1L << unit_log2, clamp_token(offsets[b + 1], T) - t0));
-    if (n == 0)
-        return;  // an unused number
-    if (MODE == POOL_WEIGHTED) {
+    const long nth = u - unit_base(begin, b, unit_log2);
+    long t0 = clamp_token(begin + (nth << unit_log2), T);
+    int n = (int)max(0L, min(1L << unit_log2, clamp_token(offsets[b + 1], T) - t0));
+    if (n == 0 || nth < 0 || u >= (T >> unit_log2) + B) {  // an unused number, or one of the two beyond
+        if constexpr (MODE == POOL_WEIGHTED)
+            if (part != nullptr && yslice == 0) {
+                const long first = clamp_token(offsets[0], T), last = clamp_token(offsets[B], T);
+                const long behind = u - unit_base((int)last, B, unit_log2);
+                long t1 = t0 = 0;
+                if (u == (T >> unit_log2) + B + 1)  // before the first sequence: less than a unit ...
+                    t0 = (first >> unit_log2) << unit_log2, t1 = first;
+                else if (u < (first >> unit_log2))  // ... and whole ones
+                    t0 = (long)u << unit_log2, t1 = t0 + (1L << unit_log2);
+                else if (behind >= 0)  // behind the last sequence
+                    t0 = last + (behind << unit_log2), t1 = min(t0 + (1L << unit_log2), T);
+                if (t1 > t0) {
+                    const float H = unit_entropy(part, nsplit, T, t0, (int)(t1 - t0), unit_log2, triples);
+                    if ((int)threadIdx.x < t1 - t0)
+                        entropy[t0 + threadIdx.x] = H;
+                }
+            }
+        return;
+    }
+    if constexpr (MODE == POOL_WEIGHTED) {
         const int tid = threadIdx.x, wave = tid >> 6;
         static_assert(POOL_UNIT <= 256, "a token per thread");
-        const float a = tid < n ? entropy[t0 + tid] * inv_alpha : NEG_INF;
+        float H = 0.f;
+        if (part != nullptr) {
+            H = unit_entropy(part, nsplit, T, t0, n, unit_log2, triples);
+            if (tid < n && yslice == 0)
+                entropy[t0 + tid] = H;
+        } else if (tid < n) {
+            H = entropy[t0 + tid];
+        }
+        const float a = tid < n ? H * inv_alpha : NEG_INF;
         const float wm = wave_max(a);
         if ((tid & 63) == 0)
             red[0][wave] = wm;
@@ -557,19 +626,19 @@ hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st)
                                a.k1_part, a.k1_nsplit, (long)a.T, a.slot, a.inv_alpha, a.out_pooled, a.out_lse);
         return hipGetLastError();
     }
-    const long units = pool_units_bound(a.T, a.B, a.unit);
+    const long units = pool_units_bound(a.T, a.B, a.unit), grid = units + (a.k1_part ? 2 : 0);
     const unsigned ysplit = pool_feature_split(a.d, bf16);
-    if (units * ysplit > 0x7fffffffL)
+    if (grid * ysplit > 0x7fffffffL)
         return hipErrorInvalidValue;
     float2 *stats = (float2 *)a.unit_stats;
     const int unit_log2 = __builtin_ctz(a.unit);
     if (bf16)
-        hipLaunchKernelGGL((pool_partial_kernel<true, POOL_WEIGHTED>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, a.hidden,
-                           a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
+        hipLaunchKernelGGL((pool_partial_kernel<true, POOL_WEIGHTED>), dim3((unsigned)(grid * ysplit)), dim3(256), 0, st, a.hidden,
+                           a.d, a.entropy, a.k1_part, a.k1_nsplit, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
                            a.lse_old, a.partial, stats);
     else
-        hipLaunchKernelGGL((pool_partial_kernel<false, POOL_WEIGHTED>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, a.hidden,
-                           a.d, a.entropy, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
+        hipLaunchKernelGGL((pool_partial_kernel<false, POOL_WEIGHTED>), dim3((unsigned)(grid * ysplit)), dim3(256), 0, st, a.hidden,
+                           a.d, a.entropy, a.k1_part, a.k1_nsplit, a.offsets, a.B, (long)a.T, a.inv_alpha, unit_log2, (int)ysplit, a.slot, a.state_lse,
                            a.lse_old, a.partial, stats);
     hipLaunchKernelGGL(pool_finalize_kernel, dim3(a.B, (a.d + JOIN_COLS - 1) / JOIN_COLS), dim3(256), 0, st, a.partial, stats, a.offsets,
                        a.slot, (long)a.T, a.d, unit_log2, units, a.state_pooled, a.state_lse ? a.lse_old : nullptr, a.out_pooled,
@@ -604,7 +673,7 @@ hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offse
 #define EGTP_POOL_PLAIN(BF, MODE)                                                                          \
     do {                                                                                                   \
         hipLaunchKernelGGL((pool_partial_kernel<BF, MODE>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, hidden, \
-                           d, nullptr, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
+                           d, nullptr, nullptr, 0, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
                            partial, nullptr);                                                              \
         hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, offsets, (long)T, d, \
                            unit_log2, units, out_pooled);                                                  \
