@@ -40,20 +40,5 @@ __device__ __forceinline__ void split3_pair(bool may_be_inf, float even, float o
                      __float_as_uint(o1z - __uint_as_float(__float_as_uint(o1z) & 0xffff0000u)));
 }
 
-// 8 fp32 values -> three bf16 fragments whose sum is exactly the input
-__device__ __forceinline__ void split3(const float (&f)[8], split_bf16x8 &hi, split_bf16x8 &mid, split_bf16x8 &lo)
-{
-    split_u32x4 ph, pm, pl;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        unsigned h, m, l;
-        split3_pair(false, f[2 * i], f[2 * i + 1], h, m, l);
-        ph[i] = h, pm[i] = m, pl[i] = l;
-    }
-    hi = __builtin_bit_cast(split_bf16x8, ph);
-    mid = __builtin_bit_cast(split_bf16x8, pm);
-    lo = __builtin_bit_cast(split_bf16x8, pl);
-}
-
 }  // namespace
 }  // namespace egtp

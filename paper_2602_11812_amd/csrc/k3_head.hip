@@ -7,12 +7,9 @@
 // small batch; the splits leave partial pre-activations that layer 2 adds in a fixed order
 // (bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode: head_tail.h.
 //
-// With bf16 weights and d a multiple of 8, layer 1 runs on the bf16 matrix cores without
-// rounding the pooled vector: an fp32 value is the exact sum of three bf16 values (its top 8
-// significant bits, the top 8 of what is left, and the rest), a bf16 x bf16 product is exact in
-// fp32, so three MFMAs per weight fragment accumulate the same products an fp32 dot product
-// would, in fp32.  Fragments come straight from global memory: a lane's 8 K-elements are 16
-// contiguous bytes of a weight row and 32 contiguous bytes of a pooled row.
+// With bf16 weights and d a multiple of 8, layer 1 runs on the bf16 matrix cores without rounding the pooled vector: an
+// fp32 value is the exact sum of three bf16 values, a bf16 x bf16 product is exact in fp32, so three MFMAs per weight fragment
+// accumulate the same products an fp32 dot product would, in fp32 (split_mfma.h).
 #include "head_tail.h"
 #include "kernels.h"
 #include "split_mfma.h"
@@ -328,8 +325,8 @@ __global__ __launch_bounds__(256) void head_layer1_f32_kernel(const float *__res
     }
 }
 
-// Layer 1, fp32 weights, more sequences: fp32 products as bf16 pieces (split_mfma.h), weights as the rows of the tile,
-// sequences as its columns.  Bound: six bf16 MFMAs per 32 K elements, 34 us at the rate that the matrix cores hold for
+// Layer 1, bf16 weights (d % 8 == 0) or fp32 weights and more sequences: products of bf16 pieces (split_mfma.h), weights as the rows,
+// sequences as the columns of the tile.  Bound (fp32): six bf16 MFMAs per 32 K elements, 34 us at the rate that the matrix cores hold for
 // 1024 sequences, d = 4096, d_h = 1024, beside the splitting of both operands (208 vector instructions to 96 MFMAs).  That
 // batch took 86 to 90 us on the fp32 matrix instructions (95 to 100 TFLOP/s), now 50 to 54; the error against fp64
 // is 0.7 of what it was (fewer roundings: one per MFMA, of 32 products).  Tried: both operands split once per workgroup
@@ -337,31 +334,51 @@ __global__ __launch_bounds__(256) void head_layer1_f32_kernel(const float *__res
 // Columns of 64 instead of 128 fill the chip with two workgroups per compute unit (59 us) and hold the pipeline's start
 // down: taken where a slice has fewer than SPLIT_WIDE_STEPS steps (1024 sequences, d = 1024, d_h = 300: training step
 // 69.7 -> 64.1 us; 309, d = 2208, d_h = 700: 66.2 -> 62.8).
+// Loads: in fragment order the lanes of a quad ask for four different rows, four lines each time, and the address unit takes
+// them one by one.  Here a quad loads one line of a row and the operands turn on their way through the LDS: the columns,
+// which pass through it anyway, and in tiles of 64 columns the rows (bf16, 1017 sequences, d = 4096, d_h = 1024 44.6 ->
+// 36.4 us, d = 5120, d_h = 1280 63 -> 50; fp32, 512, d = 2048 20.5 -> 18; in tiles of 128 the LDS is the tighter bound:
+// 50 -> 52).  The kernel of their own that served bf16 weights before staged both operands, two waves a row of tiles: 512
+// sequences, d = 4096, d_h = 1024 27.3 -> 22.9 us, 128 16.9 -> 12.4, 24 9.0 -> 7.5; tiles of 128 columns are slower there
+// (12 -> 16 us for 128 sequences, 32 -> 44 for 512 at d = 5120).
 constexpr int SPLIT_WIDE_STEPS = 8;
+typedef SplitTile<2, 8> WideTile;
+typedef SplitTile<2, 4> NarrowTile;
 
-template <class S>
+template <class S, typename W>
 struct Layer1Source {
-    static constexpr int ROW_LOADS = 2 * S::FA, COL_LOADS = 2 * S::SHARE;
-    static constexpr bool COLS_MAY_BE_INF = true;
+    static constexpr bool BF16 = sizeof(W) == 2;
+    static constexpr int ROW_PIECES = BF16 ? 1 : 3, ROW_LOADS = BF16 ? S::FA : 2 * S::FA, COL_LOADS = 2 * S::SHARE;
+    static constexpr bool COLS_MAY_BE_INF = !BF16, ROWS_TURN = S::FB == 4;
+    static constexpr int TURN_BYTES = 16 * S::STEP * sizeof(W);  // a fragment of rows as it lies in memory
     struct Rows {
-        float4 v[S::FA][2];
+        std::conditional_t<BF16, u32x4, float4> v[S::FA][BF16 ? 1 : 2];
     };
     struct Cols {
         float4 v[S::SHARE][2];
     };
-    const float *w[S::FA], *x[S::SHARE];  // + 8 (lane / 16)
-    int kbeg, kend, kq, wave, lane;
+    const W *w[S::FA];
+    const float *x[S::SHARE];
+    int kbeg, kend, row, chunk, wave, lane;  // this lane loads 8 elements, from 8 chunk on, of row `row` of every fragment ...
+    int wchunk;                              // ... (of w: where its rows do not turn, of the row and chunk that it uses)
+    unsigned char *turn;                     // FA fragments of the wave's own
 
-    // Past the end of the slice its last four elements are loaded again (no branch around a load: the loads in flight stay
-    // countable) and counted as zeros; kend is a multiple of 4, so four elements are inside the slice or outside.
-    __device__ __forceinline__ float4 four(const float *p, int i, int h) const
+    // Past the end of the slice its last elements are loaded again (no branch around a load: the loads in flight stay
+    // countable) and counted as zeros; kend is a multiple of 4 (bf16: 8), so the elements of a load are inside the slice or outside.
+    __device__ __forceinline__ float4 four(const float *p, int c, int i, int h) const
     {
-        return *(const float4 *)(p + min(kbeg + i * S::STEP + 4 * h, kend - 4 - 8 * kq));
+        return *(const float4 *)(p + min(kbeg + i * S::STEP + 8 * c + 4 * h, kend - 4));
     }
-    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const { r.v[l / 2][l % 2] = four(w[l / 2], i, l % 2); }
-    __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const { r.v[l / 2][l % 2] = four(x[l / 2], i, l % 2); }
-    template <int N>
-    __device__ __forceinline__ void clear(int i, float4 (&v)[N][2]) const
+    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const
+    {
+        if constexpr (BF16)
+            r.v[l][0] = *(const u32x4 *)(w[l] + min(kbeg + i * S::STEP + 8 * wchunk, kend - 8));
+        else
+            r.v[l / 2][l % 2] = four(w[l / 2], wchunk, i, l % 2);
+    }
+    __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const { r.v[l / 2][l % 2] = four(x[l / 2], chunk, i, l % 2); }
+    template <class V, int N, int H>
+    __device__ __forceinline__ void clear(int i, int c, V (&v)[N][H]) const
     {
         const int k0 = kbeg + i * S::STEP;
         if (k0 + S::STEP <= kend)
@@ -369,25 +386,46 @@ struct Layer1Source {
 #pragma unroll
         for (int n = 0; n < N; ++n)
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                if (k0 + 8 * kq + 4 * h >= kend)
-                    v[n][h] = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int h = 0; h < H; ++h)
+                if (k0 + 8 * c + 4 * h >= kend)
+                    v[n][h] = V{};
     }
-    __device__ __forceinline__ void clear_rows(int i, Rows &r) const { clear(i, r.v); }
-    __device__ __forceinline__ void clear_cols(int i, Cols &r) const { clear(i, r.v); }
+    __device__ __forceinline__ void clear_rows(int i, Rows &r) const { clear(i, wchunk, r.v); }
+    __device__ __forceinline__ void clear_cols(int i, Cols &r) const { clear(i, chunk, r.v); }
+    // Places of 16 bytes in the LDS, keyed so that the eight lanes that are served at a time meet eight different ones both
+    // ways: a row of 8 (bf16: 4) of them on the way in, a column of rows on the way out.
+    __device__ __forceinline__ unsigned char *turn_place(int r, int c, int l) const
+    {
+        return BF16 ? turn + l * TURN_BYTES + r * 64 + ((c ^ (r >> 1 & 3)) << 4)
+                    : turn + l / 2 * TURN_BYTES + r * 128 + ((2 * c + l % 2) ^ (r & 7)) * 16;
+    }
+    __device__ __forceinline__ void write_row(const Rows &r, int l) const
+    {
+        *(u32x4 *)turn_place(row, chunk, l) = __builtin_bit_cast(u32x4, BF16 ? r.v[l % S::FA][0] : r.v[l / 2][BF16 ? 0 : l % 2]);
+    }
+    __device__ __forceinline__ void read_row(Rows &r, int l) const
+    {
+        auto &v = BF16 ? r.v[l % S::FA][0] : r.v[l / 2][BF16 ? 0 : l % 2];
+        v = __builtin_bit_cast(std::remove_reference_t<decltype(v)>, *(const u32x4 *)turn_place(lane & 15, lane >> 4, l));
+    }
     __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const { return (&r.v[a][e / 4].x)[e % 4]; }
+    __device__ __forceinline__ unsigned row_pair(const Rows &r, int a, int e) const { return r.v[a][0][e]; }
     __device__ __forceinline__ float col_value(const Cols &r, int p, int e) const { return (&r.v[p][e / 4].x)[e % 4]; }
-    __device__ __forceinline__ int place(int p) const { return ((wave + S::WAVES * p) * 64 + lane) * 16; }
+    __device__ __forceinline__ static int fragment_place(int r, int c) { return c * 16 + (r ^ 2 * c); }
+    __device__ __forceinline__ int place(int p) const { return ((wave + S::WAVES * p) * 64 + fragment_place(row, chunk)) * 16; }
+    __device__ __forceinline__ int slot() const { return fragment_place(lane & 15, lane >> 4); }
 };
 
-template <class S>
+template <class S, typename W>
 __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_split_kernel(
-    const float *__restrict__ x, const int32_t *__restrict__ slot, int B, int d, int d_h, const float *__restrict__ w1,
+    const float *__restrict__ x, const int32_t *__restrict__ slot, int B, int d, int d_h, const W *__restrict__ w1,
     int kchunk, int nks, int jtiles, float *__restrict__ act_part)
 {
     static_assert(S::ROWS == FJ, "tile");
     constexpr int FA = S::FA, FB = S::FB;
-    __shared__ __align__(16) unsigned char lds[S::LDS_BYTES];
+    constexpr bool TURNS = Layer1Source<S, W>::ROWS_TURN;
+    constexpr int TURN = TURNS ? FA * Layer1Source<S, W>::TURN_BYTES : 0;
+    __shared__ __align__(16) unsigned char lds[S::LDS_BYTES + S::WAVES * TURN];
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l15 = lane & 15, kq = lane >> 4;
@@ -396,19 +434,21 @@ __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_sp
     const int tile = blockIdx.x / nks;
     const int j0 = (tile % jtiles) * S::ROWS, s0 = (tile / jtiles) * S::COLS;
 
-    Layer1Source<S> src;
+    Layer1Source<S, W> src;
     src.kbeg = kslice * kchunk;
     src.kend = min(d, src.kbeg + kchunk);
-    src.kq = kq, src.wave = wave, src.lane = lane;
+    src.row = lane >> 2, src.chunk = lane & 3, src.wave = wave, src.lane = lane;
+    src.wchunk = TURNS ? src.chunk : kq;
+    src.turn = lds + S::LDS_BYTES + wave * TURN;
 #pragma unroll
     for (int a = 0; a < FA; ++a) {
-        const int j = min(j0 + 16 * (wave * FA + a) + l15, d_h - 1);  // clamped rows are computed and dropped
-        src.w[a] = w1 + (long)j * d + 8 * kq;
+        const int j = min(j0 + 16 * (wave * FA + a) + (TURNS ? src.row : l15), d_h - 1);  // clamped rows are computed and dropped
+        src.w[a] = w1 + (long)j * d;
     }
 #pragma unroll
     for (int p = 0; p < S::SHARE; ++p) {
-        const int sq = min(s0 + 16 * (wave + S::WAVES * p) + l15, B - 1);
-        src.x[p] = x + (long)(slot ? slot[sq] : sq) * d + 8 * kq;
+        const int sq = min(s0 + 16 * (wave + S::WAVES * p) + src.row, B - 1);
+        src.x[p] = x + (long)(slot ? slot[sq] : sq) * d;
     }
     split_f32x4 acc[FA][FB];
 #pragma unroll
@@ -417,7 +457,7 @@ __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_sp
         for (int b = 0; b < FB; ++b)
             acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
     if (src.kbeg < src.kend)
-        split_contract<S>(lds, (src.kend - src.kbeg + S::STEP - 1) / S::STEP, lane, acc, src);
+        split_contract<S>(lds, (src.kend - src.kbeg + S::STEP - 1) / S::STEP, acc, src);
 
     float *act = act_part + (long)kslice * B * d_h;
 #pragma unroll
@@ -430,156 +470,6 @@ __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_sp
             const int jj = j0 + 16 * (wave * FA + a) + 4 * kq;
             if (jj + 3 < d_h && (d_h & 3) == 0) {
                 *(split_f32x4 *)(act + (long)s * d_h + jj) = acc[a][b];
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (jj + i < d_h)
-                        act[(long)s * d_h + jj + i] = acc[a][b][i];
-            }
-        }
-    }
-}
-
-constexpr int MK = 32;  // K elements per MFMA step
-
-// Layer 1 on the matrix cores, bf16 weights, d % 8 == 0.  Workgroup = 4 waves, MJ = 128 head rows x
-// TN = 64 sequences; wave = 64 x 32 = 4 x 2 MFMA 16x16x32 tiles, weights as the row operand (lane l:
-// head row l % 16, K elements 8 * (l / 16) .. + 8), pooled vectors as the column operand; in the
-// accumulator a lane holds head rows 4 * (l / 16) + i of sequence l % 16.  Per K step every thread
-// fetches 8 K-elements of one pooled row (32 bytes) and of two weight rows (16 bytes each), splits
-// the fp32 values once, and leaves all of it in LDS in fragment order -- fragment f, lane l at
-// (f * 64 + l) * 16 bytes -- so that a fragment read is one linear 16-byte read per lane.  Two
-// LDS buffers; global fetches run three steps ahead in registers.
-constexpr int MJ = 128;
-constexpr int MFMA_W_FRAGS = MJ / 16;             // 8 weight fragments per step
-constexpr int MFMA_X_FRAGS = 3 * (TN / 16);       // 3 parts x 4 sequence fragments
-constexpr int MFMA_STAGE_BYTES = (MFMA_W_FRAGS + MFMA_X_FRAGS) * 1024;
-
-__global__ __launch_bounds__(256) void head_layer1_mfma_kernel(const float *__restrict__ x,
-                                                               const int32_t *__restrict__ slot, int B, int d,
-                                                               int d_h, const unsigned short *__restrict__ w1,
-                                                               int kchunk, int nks, int jtiles,
-                                                               float *__restrict__ act_part)
-{
-    __shared__ __align__(16) unsigned char lds[2 * MFMA_STAGE_BYTES];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int l15 = lane & 15, kq = lane >> 4;
-    // Workgroup i runs on XCD i % 8: the slice along d varies fastest, so that an XCD's L2 only
-    // ever pulls its own slices of the weights and of the pooled vectors over the fabric.
-    const int kslice = blockIdx.x % nks;
-    const int tile = blockIdx.x / nks;
-    const int j0 = (tile % jtiles) * MJ, s0 = (tile / jtiles) * TN;
-    const int wj = (wave & 1) * 4;  // first of this wave's 4 weight fragments
-    const int ws = (wave >> 1) * 2; // first of its 2 sequence fragments
-
-    // what this thread stages: row 16 * wave + lane % 16 of the tile (and that row + 64 of the
-    // weights), K elements 8 * (lane / 16) .. + 8 -- which is lane `lane` of fragment `wave`, so a
-    // wave's 16-byte LDS writes are one linear KiB
-    const int srow_l = wave * 16 + l15, kpart = kq;
-    int srow = s0 + srow_l;
-    srow = srow < B ? srow : B - 1;  // clamped rows are computed and dropped
-    const long xrow = slot ? slot[srow] : srow;
-    const float *xp = x + xrow * (long)d + 8 * kpart;
-    const unsigned short *wp[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        int jrow = j0 + 64 * r + srow_l;
-        jrow = jrow < d_h ? jrow : d_h - 1;
-        wp[r] = w1 + (long)jrow * d + 8 * kpart;
-    }
-    const unsigned stage_lane = (unsigned)(lane * 16);
-    const unsigned w_dst0 = (unsigned)(wave * 1024) + stage_lane;                   // rows 0..63
-    const unsigned w_dst1 = (unsigned)((4 + wave) * 1024) + stage_lane;             // rows 64..127
-    const unsigned x_dst = (unsigned)((MFMA_W_FRAGS + wave) * 1024) + stage_lane;   // part p: + p * 4096
-
-    f32x4 acc[4][2];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-            acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    const int kbeg = kslice * kchunk;
-    const int kend = min(d, kbeg + kchunk);
-    // kend and 8 * kpart are multiples of 8: a thread's 8 elements are inside [kbeg, kend) or all outside
-    struct Fetched {
-        u32x4 w[2];
-        float4 x[2];
-    };
-    auto fetch = [&](int k0, Fetched &r) {
-        r.w[0] = r.w[1] = u32x4{0u, 0u, 0u, 0u};
-        r.x[0] = r.x[1] = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (k0 + 8 * kpart < kend) {
-            r.w[0] = *(const u32x4 *)(wp[0] + k0);
-            r.w[1] = *(const u32x4 *)(wp[1] + k0);
-            r.x[0] = *(const float4 *)(xp + k0);
-            r.x[1] = *(const float4 *)(xp + k0 + 4);
-        }
-    };
-    auto stage = [&](const Fetched &r, unsigned char *buf) {
-        const float f[8] = {r.x[0].x, r.x[0].y, r.x[0].z, r.x[0].w, r.x[1].x, r.x[1].y, r.x[1].z, r.x[1].w};
-        bf16x8 hi, mid, lo;
-        split3(f, hi, mid, lo);
-        *(u32x4 *)(buf + w_dst0) = r.w[0];
-        *(u32x4 *)(buf + w_dst1) = r.w[1];
-        *(bf16x8 *)(buf + x_dst) = hi;
-        *(bf16x8 *)(buf + x_dst + 4096) = mid;
-        *(bf16x8 *)(buf + x_dst + 8192) = lo;
-    };
-
-    // Operands are fetched three steps ahead into a ring of three register sets (the loop is
-    // unrolled by three so that the ring is indexed statically) and staged one step ahead.
-    Fetched ring[3];
-    fetch(kbeg, ring[0]);
-    fetch(kbeg + MK, ring[1]);
-    fetch(kbeg + 2 * MK, ring[2]);
-    stage(ring[0], lds);
-    __syncthreads();
-    int cur = 0;
-    for (int base = kbeg; base < kend; base += 3 * MK) {
-#pragma unroll
-        for (int u = 0; u < 3; ++u) {
-            const int k0 = base + u * MK;
-            if (k0 >= kend)
-                break;
-            fetch(k0 + 3 * MK, ring[u]);  // ring[u] held step k0, which is in LDS already
-            const unsigned char *buf = lds + cur * MFMA_STAGE_BYTES;
-            bf16x8 wf[4], xf[3][2];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-                wf[a] = *(const bf16x8 *)(buf + ((wj + a) * 64 + lane) * 16);
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-#pragma unroll
-                for (int b = 0; b < 2; ++b)
-                    xf[p][b] = *(const bf16x8 *)(buf + ((MFMA_W_FRAGS + 4 * p + ws + b) * 64 + lane) * 16);
-#pragma unroll
-            for (int p = 2; p >= 0; --p)  // smallest parts first
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-#pragma unroll
-                    for (int b = 0; b < 2; ++b)
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], xf[p][b], acc[a][b], 0, 0, 0);
-            if (k0 + MK < kend)
-                stage(ring[(u + 1) % 3], lds + (cur ^ 1) * MFMA_STAGE_BYTES);  // nobody reads that buffer now
-            __syncthreads();
-            cur ^= 1;
-        }
-    }
-
-    float *act = act_part + (long)kslice * B * d_h;
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-        const int s = s0 + 16 * (ws + b) + l15;
-        if (s >= B)
-            continue;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int jj = j0 + 16 * (wj + a) + 4 * kq;
-            if (jj + 3 < d_h && (d_h & 3) == 0) {
-                *(f32x4 *)(act + (long)s * d_h + jj) = acc[a][b];
             } else {
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
@@ -696,6 +586,25 @@ static bool skinny_serves(int d, int32_t B, int wdtype)
 // training steps at batch 1024 199.7 us against 199.4, at d = 1024, d_h = 300, batch 256 39.1 against 34.6.)
 static int f32_tile_seqs(int32_t B) { return B > 32 ? 64 : 32; }
 
+// Slices of layer 1 on bf16 pieces, fp32 weights, n of them asked for.  Tiles of 128 columns run one to a compute unit: from n down
+// to half of it, the number whose rounds take the fewest steps (one more for a round's start), the smaller of two (planes).
+// 512 sequences, d = 5120, d_h = 1280: 320 tiles in two rounds 71.6 us, 240 in one 43; 1017 115 -> 77; 300, d = 4096, d_h = 1024 36 -> 25.
+static int split_slices(int n, int d, int d_h, int32_t B)
+{
+    constexpr int STEP = WideTile::STEP, UNITS = 256;
+    const long tiles = (long)((d_h + FJ - 1) / FJ) * ((B + WideTile::COLS - 1) / WideTile::COLS);
+    int best = n;
+    long best_steps = 0;
+    for (int m = n; m >= (n + 1) / 2; --m) {
+        const long steps = ((d + m - 1) / m + STEP - 1) / STEP, cost = (tiles * m + UNITS - 1) / UNITS * (steps + 1);
+        if (m == n && steps < SPLIT_WIDE_STEPS)
+            break;  // tiles of 64 columns
+        if (m == n || cost <= best_steps)
+            best = m, best_steps = cost;
+    }
+    return best;
+}
+
 int head_k_splits(int d, int d_h, int32_t B, int wdtype)
 {
     if (skinny_serves(d, B, wdtype))
@@ -703,7 +612,9 @@ int head_k_splits(int d, int d_h, int32_t B, int wdtype)
     int base = (d + 511) / 512;  // slices of at most 512 along d ...
     base = base < 1 ? 1 : (base > 8 ? 8 : base);
     const long tiles = (long)((d_h + TM - 1) / TM) * ((B + TN - 1) / TN);
-    long want = tiles > 0 ? (1024 + tiles - 1) / tiles : 1;  // ... thinner when the batch has few tiles
+    // (bf16, d = 4096, d_h = 1024, both layers: twice as many slices cost 24 sequences 15.8 us for 12.0, 128 22.2 for 17.0)
+    const int wanted = wdtype == DT_F32 ? 1024 : 512;
+    long want = tiles > 0 ? (wanted + tiles - 1) / tiles : 1;  // ... thinner when the batch has few tiles
     const int cap = (d + TK - 1) / TK < 64 ? (d + TK - 1) / TK : 64;
     long n = want > base ? want : base;
     n = n > cap ? cap : n;
@@ -711,9 +622,8 @@ int head_k_splits(int d, int d_h, int32_t B, int wdtype)
         const long ftiles = (long)((d_h + FJ - 1) / FJ) * ((B + f32_tile_seqs(B) - 1) / f32_tile_seqs(B));
         const long fwant = ftiles > 0 ? (F32_WORKGROUPS + ftiles - 1) / ftiles : 1;
         n = n > fwant ? fwant : n;
-        // a slice of at least two K steps of the kernel on bf16 pieces
-        if (B > F32_MAX_SEQS && n > (d + 63) / 64)
-            n = (d + 63) / 64;
+        if (B > F32_MAX_SEQS)
+            n = split_slices((int)(n > (d + 63) / 64 ? (d + 63) / 64 : n), d, d_h, B);  // a slice of at least two K steps
     }
     return n < 1 ? 1 : (int)n;
 }
@@ -762,9 +672,9 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
     hipLaunchKernelGGL(KERNEL, dim3((unsigned)wgs), dim3(256), 0, st, x, slot, B, d, d_h, (const float *)w1, kchunk_f, \
                        nks, jtiles, act_part)
         if (wide)
-            EGTP_LAYER1_F32((head_layer1_split_kernel<SplitTile<2, 8>>));
+            EGTP_LAYER1_F32((head_layer1_split_kernel<WideTile, float>));
         else if (!small)
-            EGTP_LAYER1_F32((head_layer1_split_kernel<SplitTile<2, 4>>));
+            EGTP_LAYER1_F32((head_layer1_split_kernel<NarrowTile, float>));
         else if (fs == 64)
             EGTP_LAYER1_F32(head_layer1_f32_kernel<2>);
         else
@@ -773,15 +683,14 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
         return hipGetLastError();
     }
     if (wdtype == DT_BF16 && d % 8 == 0) {
-        // matrix-core path: slices are multiples of the MFMA K step (late slices may be empty
-        // and then write zeros)
-        const int kchunk_m = ((d + nks - 1) / nks + MK - 1) / MK * MK;
-        const int jtiles = (d_h + MJ - 1) / MJ;
-        const long wgs = (long)jtiles * ((B + TN - 1) / TN) * nks;
+        constexpr int STEP = NarrowTile::STEP;
+        const int kchunk_b = ((d + nks - 1) / nks + STEP - 1) / STEP * STEP;  // (late slices may be empty and then write zeros)
+        const int jtiles = (d_h + FJ - 1) / FJ;
+        const long wgs = (long)jtiles * ((B + NarrowTile::COLS - 1) / NarrowTile::COLS) * nks;
         if (wgs > 0x7fffffffL)
             return hipErrorInvalidValue;
-        hipLaunchKernelGGL(head_layer1_mfma_kernel, dim3((unsigned)wgs), dim3(256), 0, st, x, slot, B, d, d_h,
-                           (const unsigned short *)w1, kchunk_m, nks, jtiles, act_part);
+        hipLaunchKernelGGL((head_layer1_split_kernel<NarrowTile, unsigned short>), dim3((unsigned)wgs), dim3(256), 0, st, x, slot, B,
+                           d, d_h, (const unsigned short *)w1, kchunk_b, nks, jtiles, act_part);
         return hipGetLastError();
     }
     const int kchunk = ((d + nks - 1) / nks + TK - 1) / TK * TK;  // multiple of the K step

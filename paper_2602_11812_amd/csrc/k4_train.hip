@@ -386,8 +386,8 @@ typedef SplitTile<2, 4> GradTile;
 constexpr int SPLIT_SAMPLES = 192, SPLIT_TILES = 128;
 
 struct GradSource {
-    static constexpr int ROW_LOADS = 8, COL_LOADS = 8;
-    static constexpr bool COLS_MAY_BE_INF = false;
+    static constexpr int ROW_PIECES = 3, ROW_LOADS = 8, COL_LOADS = 8;
+    static constexpr bool COLS_MAY_BE_INF = false, ROWS_TURN = false;
     struct Rows {
         float2 v[8];
     };
@@ -418,6 +418,7 @@ struct GradSource {
     __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const { return a == 0 ? r.v[e].x : r.v[e].y; }
     __device__ __forceinline__ float col_value(const Cols &r, int, int e) const { return r.v[e]; }
     __device__ __forceinline__ int place(int) const { return place0; }
+    __device__ __forceinline__ int slot() const { return threadIdx.x & 63; }
 };
 
 __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const float *__restrict__ x,
@@ -444,7 +445,7 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
 #pragma unroll
         for (int b = 0; b < FB; ++b)
             acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
-    split_contract<S>(lds, (B + S::STEP - 1) / S::STEP, lane, acc, src);
+    split_contract<S>(lds, (B + S::STEP - 1) / S::STEP, acc, src);
 
     const int k = k0 + 4 * l15;
     if (k >= d)

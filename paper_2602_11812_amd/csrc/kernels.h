@@ -131,8 +131,8 @@ struct HeadArgs {
     float *p_hat;             // [B x n_out] softmax over the bins (Eq. 6), or NULL; n_out > 1 only
 };
 // Number of partial pre-activation planes layer 1 leaves: it is split along d so that the chip is filled whatever the
-// batch (a small batch gets many thin slices): into about a thousand 64 x 64 tiles' worth with bf16 weights, 512
-// workgroups of larger tiles (at least two K steps of 32 each for more than 64 sequences) with fp32 weights.  At most sixteen sequences on fp32 weights are served by a kernel of
+// batch (a small batch gets many thin slices): into about 512 64 x 64 tiles' worth with bf16 weights, up to 512
+// workgroups of larger tiles (at least two K steps of 32 each for more than 64 sequences, and as many as fill the compute units) with fp32 weights.  At most sixteen sequences on fp32 weights are served by a kernel of
 // its own that leaves one plane per 512 elements of d.
 int head_k_splits(int d, int d_h, int32_t B, int wdtype);
 // floats of partial planes sufficient for every batch of at most B sequences

@@ -35,3 +35,24 @@ def test_fp32_head_through_slots(B, d, d_h, n_out):
     scale = float(centers.max()) if n_out > 1 else 1.0 + float(np.abs(want).max())
     assert np.abs(got - want).max() <= 2e-5 * scale
     sc.close()
+
+
+# bf16 head weights on the matrix cores: batches around tiles of 64 sequences, rows of W1 around 16 and 128, slices of d that end
+# inside a K step of 32 (a chunk of eight, three, one step and a chunk), slices past the end of d; fp32 weights
+# whose slices fill the compute units' rounds (320 tiles in two rounds became 240 in one)
+@pytest.mark.parametrize("wdtype,B,d,d_h", [("bf16", 1, 8, 1), ("bf16", 64, 24, 130), ("bf16", 65, 40, 127),
+                                            ("bf16", 129, 264, 17), ("bf16", 3, 4104, 9), ("bf16", 200, 1160, 300),
+                                            ("bf16", 513, 544, 129), ("f32", 300, 2564, 1161), ("f32", 513, 1284, 1290)])
+def test_layer1_on_matrix_cores_at_tile_edges(wdtype, B, d, d_h):
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    gen = torch.Generator(device="cuda").manual_seed(8300 + B)
+    rnd = lambda *s, std=1.0: torch.randn(*s, generator=gen, device="cuda") * std
+    store = torch.bfloat16 if wdtype == "bf16" else torch.float32
+    w1, w2 = rnd(d_h, d, std=d ** -0.5).to(store), rnd(1, d_h, std=d_h ** -0.5).to(store)
+    sc = gpu.Scorer(rnd(300, d).bfloat16() if d % 8 == 0 else rnd(300, d), gpu.make_head(w1, w2))
+    hidden, pooled = rnd(B, d).to(sc.storage), rnd(B, d)
+    got = sc.step(hidden, pooled, torch.full((B,), 6.0).cuda()).double()
+    want = torch.relu(pooled.double() @ w1.double().T) @ w2.double()[0]
+    assert (got - want).abs().max() <= 2e-5 * (1.0 + want.abs().max())
+    sc.close()
