@@ -161,7 +161,10 @@ def _host_ptr(a: Optional[np.ndarray]):
 
 
 def _stream(stream) -> Optional[int]:
+    """Handle of a stream, or of the current device's current one (without a Stream object around it: 2.9 -> 0.3 us a call)."""
     if stream is None:
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
 
