@@ -348,7 +348,8 @@ typedef SplitTile<2, 4> NarrowTile;
 template <class S, typename W>
 struct Layer1Source {
     static constexpr bool BF16 = sizeof(W) == 2;
-    static constexpr int ROW_PIECES = BF16 ? 1 : 3, ROW_LOADS = BF16 ? S::FA : 2 * S::FA, COL_LOADS = 2 * S::SHARE;
+    static constexpr int ROW_PIECES = BF16 ? 1 : 3, ROW_LOADS = BF16 ? S::FA : 2 * S::FA, COL_LOADS = 2 * S::SHARE,
+                         COL_WRITES = 3 * S::SHARE;
     static constexpr bool COLS_MAY_BE_INF = !BF16, ROWS_TURN = S::FB == 4;
     static constexpr int TURN_BYTES = 16 * S::STEP * sizeof(W);  // a fragment of rows as it lies in memory
     struct Rows {
@@ -412,7 +413,10 @@ struct Layer1Source {
     __device__ __forceinline__ unsigned row_pair(const Rows &r, int a, int e) const { return r.v[a][0][e]; }
     __device__ __forceinline__ float col_value(const Cols &r, int p, int e) const { return (&r.v[p][e / 4].x)[e % 4]; }
     __device__ __forceinline__ static int fragment_place(int r, int c) { return c * 16 + (r ^ 2 * c); }
-    __device__ __forceinline__ int place(int p) const { return ((wave + S::WAVES * p) * 64 + fragment_place(row, chunk)) * 16; }
+    __device__ __forceinline__ void write_col(unsigned char *buf, const u32x4 (&part)[S::SHARE][3], int n) const
+    {
+        *(u32x4 *)(buf + n % 3 * S::PIECE + ((wave + S::WAVES * (n / 3)) * 64 + fragment_place(row, chunk)) * 16) = part[n / 3][n % 3];
+    }
     __device__ __forceinline__ int slot() const { return fragment_place(lane & 15, lane >> 4); }
 };
 

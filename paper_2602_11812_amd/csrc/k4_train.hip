@@ -373,51 +373,76 @@ __device__ __forceinline__ void w1_update(int tile_k, int tile_j, const float *_
 
 // The same for more samples: fp32 products as bf16 pieces (split_mfma.h).  Workgroup = 128 rows j x 64 columns k, a wave 32
 // rows of its own.  The contraction runs over the samples, the slow index of both operands, of which a fragment wants eight
-// in a lane: a lane loads two neighbouring j (or one k) of eight samples and deals them to two fragments (one), so that row
-// c of a wave's fragment a is j = 2 c + a and column c of fragment b is k = 4 c + b.  A lane ends up with four neighbouring
-// k of a row j, one 16-byte access each to W1 and the moments.
+// in a lane: a lane loads two neighbouring j of eight samples and deals them to two fragments, so that row c of a wave's
+// fragment a is j = 2 c + a; of the columns it loads four neighbouring k of two samples, a pair of K elements for each of four
+// fragments, so that column c of fragment b is k = 4 c + b.  A lane ends up with four neighbouring k of a row j, one 16-byte
+// access each to W1 and the moments.
 // Two workgroups per compute unit; the workgroups of the small parameters, chains of cache latencies, start before the
 // tiles, which puts some tiles' parameter streams beside others' products (512 samples 92.7 -> 89.1 us a step).
 // Bound: the splitting beside the MFMAs, 49 us per 1024 samples at d = 4096, d_h = 1024, and about 30 us for the parameters.
-// 1024 samples: the launch 117 to 120 us on the fp32 matrix instructions, now 75 to 82.  128 x 128 tiles: 85.
+// 1024 samples: the launch 117 to 120 us on the fp32 matrix instructions, then 75 to 82; the way of loaded data back into
+// the compute unit was the busiest part of it (69 %), a quarter of what a load of one k per lane fetched was used.  With
+// four k per lane, a quarter of these loads: whole steps of 1024 samples 135.2 -> 127.4 us, 256 62.3 -> 58.4, 1024 at d = 5120,
+// d_h = 1280 213 -> 195.5.  128 x 128 tiles: 85.  Rows by 16-byte loads as well, turned in the LDS: no faster.
 typedef SplitTile<2, 4> GradTile;
 // From this many samples and tiles on (whole steps, fp32 -> split: 128 samples, d = 4096, d_h = 1024 52.4 -> 56.6 us, 256
 // 67.5 -> 65.2; 309 samples against 210 tiles 62.8 -> 60.8, 1024 against 48 64.1 -> 65.6).
 constexpr int SPLIT_SAMPLES = 192, SPLIT_TILES = 128;
 
 struct GradSource {
-    static constexpr int ROW_PIECES = 3, ROW_LOADS = 8, COL_LOADS = 8;
+    static constexpr int ROW_PIECES = 3, ROW_LOADS = 8, COL_LOADS = 2, COL_WRITES = 12;
     static constexpr bool COLS_MAY_BE_INF = false, ROWS_TURN = false;
     struct Rows {
         float2 v[8];
     };
     struct Cols {
-        float v[8];
+        float4 v[2];
     };
     const float *dact, *x;  // this lane's columns of the two operands
     long d_h, d;
-    int B, kq, place0;
+    int B, kq, wave, l15;
 
     // Past the end of the batch the last sample is loaded again (no branch around a load: the loads in flight stay
     // countable) and counted as zeros.
-    __device__ __forceinline__ int sample(int i, int l) const { return min(i * GradTile::STEP + 8 * kq + l, B - 1); }
-    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const { r.v[l] = *(const float2 *)(dact + sample(i, l) * d_h); }
-    __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const { r.v[l] = x[sample(i, l) * d]; }
-    template <class V>
-    __device__ __forceinline__ void clear(int i, V (&v)[8], V zero) const
+    __device__ __forceinline__ int row_sample(int i, int l) const { return i * GradTile::STEP + 8 * kq + l; }
+    __device__ __forceinline__ int col_sample(int i, int l) const { return i * GradTile::STEP + 8 * wave + kq + 4 * l; }
+    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const
+    {
+        r.v[l] = *(const float2 *)(dact + min(row_sample(i, l), B - 1) * d_h);
+    }
+    __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const
+    {
+        r.v[l] = *(const float4 *)(x + min(col_sample(i, l), B - 1) * d);
+    }
+    __device__ __forceinline__ void clear_rows(int i, Rows &r) const
     {
         if ((i + 1) * GradTile::STEP <= B)
             return;
 #pragma unroll
         for (int l = 0; l < 8; ++l)
-            if (i * GradTile::STEP + 8 * kq + l >= B)
-                v[l] = zero;
+            if (row_sample(i, l) >= B)
+                r.v[l] = make_float2(0.f, 0.f);
     }
-    __device__ __forceinline__ void clear_rows(int i, Rows &r) const { clear(i, r.v, make_float2(0.f, 0.f)); }
-    __device__ __forceinline__ void clear_cols(int i, Cols &r) const { clear(i, r.v, 0.f); }
-    __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const { return a == 0 ? r.v[e].x : r.v[e].y; }
-    __device__ __forceinline__ float col_value(const Cols &r, int, int e) const { return r.v[e]; }
-    __device__ __forceinline__ int place(int) const { return place0; }
+    __device__ __forceinline__ void clear_cols(int i, Cols &r) const
+    {
+        if ((i + 1) * GradTile::STEP <= B)
+            return;
+#pragma unroll
+        for (int l = 0; l < 2; ++l)
+            if (col_sample(i, l) >= B)
+                r.v[l] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    // K elements 2 g and 2 g + 1 of eight are samples g and g + 4: a pair is what a lane loads of a column
+    __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const
+    {
+        const float2 v = r.v[e / 2 + e % 2 * 4];
+        return a == 0 ? v.x : v.y;
+    }
+    __device__ __forceinline__ float col_value(const Cols &r, int, int e) const { return (&r.v[e % 2].x)[e / 2]; }
+    __device__ __forceinline__ void write_col(unsigned char *buf, const split_u32x4 (&part)[1][3], int n) const
+    {
+        *(unsigned *)(buf + n % 3 * GradTile::PIECE + n / 3 * 1024 + (wave * 16 + l15) * 16 + kq * 4) = part[0][n % 3][n / 3];
+    }
     __device__ __forceinline__ int slot() const { return threadIdx.x & 63; }
 };
 
@@ -437,8 +462,8 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
     GradSource src;
     src.d_h = d_h, src.d = d, src.B = B, src.kq = kq;
     src.dact = dact + min(j0 + 2 * l15, d_h - 2);
-    src.x = x + min(k0 + 4 * l15 + wave, d - 1);  // a wave stages fragment `wave`
-    src.place0 = (wave * 64 + lane) * 16;
+    src.x = x + min(k0 + 4 * l15, d - 4);  // a wave stages eight samples
+    src.wave = wave, src.l15 = l15;
     split_f32x4 acc[FA][FB];
 #pragma unroll
     for (int a = 0; a < FA; ++a)

@@ -37,7 +37,8 @@ struct SplitTile {
 //   ROW_PIECES                                3, or 1 for rows that are bf16: three products instead of six
 //   row_value(r, a, e), col_value(r, p, e)    K element e of row fragment a / of share p
 //   row_pair(r, a, e)                         (one piece) K elements 2 e and 2 e + 1 of row fragment a
-//   place(p), slot()                          where share p goes in a buffer; the 16 bytes of a fragment that this lane reads
+//   write_col(buf, part, n), slot()           write number n of COL_WRITES of the pieces of this thread's pairs, part[share]
+//                                             [piece][pair]; the 16 bytes of a fragment that this lane reads
 //   ROWS_TURN                                 rows are loaded by other lanes than use them, and turned in the LDS of the wave:
 //   write_row(r, l), read_row(t, l)           load number l of ROW_LOADS on its way there and back
 //   COLS_MAY_BE_INF                           a column may hold infinities: their lower pieces are zeros, not NaN
@@ -77,9 +78,9 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
         split3_pair(Source::COLS_MAY_BE_INF, src.col_value(r, p, 2 * e), src.col_value(r, p, 2 * e + 1), h, m, l);
         part[p][0][e] = h, part[p][1][e] = m, part[p][2][e] = l;
     };
-    auto write = [&](unsigned char *buf, int n) { *(split_u32x4 *)(buf + src.place(n / 3) + n % 3 * T::PIECE) = part[n / 3][n % 3]; };
+    auto write = [&](unsigned char *buf, int n) { src.write_col(buf, part, n); };
 
-    constexpr int ROW_PAIRS = 4 * FA, COL_PAIRS = 4 * SHARE, WRITES = 3 * SHARE, READS = 3 * FB;
+    constexpr int ROW_PAIRS = 4 * FA, COL_PAIRS = 4 * SHARE, WRITES = Source::COL_WRITES, READS = 3 * FB;
     constexpr int ROW_LOADS = Source::ROW_LOADS, COL_LOADS = Source::COL_LOADS;
     auto fetch_cols = [&](int i, typename Source::Cols &r) {
 #pragma unroll
