@@ -133,11 +133,12 @@ egtp_status hip_fail(egtp_ctx *ctx, hipError_t e)
     } while (0)
 
 // row-major operand -> the packed blocks the fused kernel reads (fp32: split into bf16 pieces on the way)
+// and zeros for pace_ints of the fused kernel's counters
 hipError_t pack_rows(int dtype, const void *src, int64_t rows, int d, bool hidden_side, bool pieces, int tile_rows, void *dst,
-                     hipStream_t st)
+                     int *pace, long pace_ints, hipStream_t st)
 {
-    return dtype == EGTP_BF16 ? k1_pack_rows_bf16(src, rows, d, tile_rows, dst, st)
-                              : k1_pack_rows_f32_split(src, rows, d, hidden_side, pieces, tile_rows, dst, st);
+    return dtype == EGTP_BF16 ? k1_pack_rows_bf16(src, rows, d, tile_rows, dst, pace, pace_ints, st)
+                              : k1_pack_rows_f32_split(src, rows, d, hidden_side, pieces, tile_rows, dst, pace, pace_ints, st);
 }
 
 // Eq. 2 for T tokens: fused partials, then the per-token merge into `entropy` -- unless the caller merges
@@ -150,10 +151,10 @@ egtp_status run_entropy(egtp_ctx *ctx, const void *hidden, int64_t T, const Work
     const bool timed = ctx->prof_events && ctx->prof_count < ctx->prof_cap;
     const void *wp = ctx->w_packed;
     if (!wp) {  // no persistent packed W_lm: pack it for this call
-        EGTP_HIP(pack_rows(c.dtype, c.w_lm, c.vocab, c.d, false, false, K1_PACK_ROWS, w.w_packed, st));
+        EGTP_HIP(pack_rows(c.dtype, c.w_lm, c.vocab, c.d, false, false, K1_PACK_ROWS, w.w_packed, nullptr, 0, st));
         wp = w.w_packed;
     }
-    EGTP_HIP(pack_rows(c.dtype, hidden, T, c.d, true, p.pieces, p.tb_tokens, w.hidden_packed, st));
+    EGTP_HIP(pack_rows(c.dtype, hidden, T, c.d, true, p.pieces, p.tb_tokens, w.hidden_packed, w.k1_pace, k1_pace_ints(p), st));
     if (timed)
         EGTP_HIP(hipEventRecord(ctx->prof_events[2 * ctx->prof_count], st));
     const int K = (int)k1_contraction_len(c.dtype, c.d);
@@ -470,7 +471,7 @@ egtp_status egtp_pack_w_lm(egtp_ctx *ctx, void *packed_dev, size_t bytes, void *
     if (((uintptr_t)packed_dev % ALIGN) != 0 || bytes < egtp_packed_w_lm_bytes(ctx))
         return EGTP_ERR_WORKSPACE;
     EGTP_HIP(pack_rows(ctx->cfg.dtype, ctx->cfg.w_lm, ctx->cfg.vocab, ctx->cfg.d, false, false, K1_PACK_ROWS, packed_dev,
-                       (hipStream_t)stream));
+                       nullptr, 0, (hipStream_t)stream));
     ctx->w_packed = packed_dev;
     return EGTP_OK;
 }

@@ -95,6 +95,15 @@ __global__ __launch_bounds__(256) void k1_merge_wide_kernel(const float *__restr
     }
 }
 
+// The packing kernels' first workgroup also clears the counters that the fused kernel behind it paces with (in a launch of
+// their own 4.7 us of a pass: 10689 tokens, d = 2048, V = 32000; and by a kernel, since a caller may be capturing a graph).
+__device__ __forceinline__ void clear_pace(int *__restrict__ pace, int n)
+{
+    if (blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+        for (int i = threadIdx.x; i < n; i += 256)
+            pace[i] = 0;
+}
+
 // Packs rows of a row-major bf16 matrix src[R x d] into blocks of tile_rows (256, or fewer for the hidden states of the
 // narrow and the stream kernel) rows x 32 K-elements in
 // LDS-image order; rows >= R and K >= d are zero.  One workgroup packs 8 consecutive K steps
@@ -102,8 +111,9 @@ __global__ __launch_bounds__(256) void k1_merge_wide_kernel(const float *__restr
 // reads 512 contiguous bytes of each of two rows at a time.
 __global__ __launch_bounds__(256) void pack_rows_bf16_kernel(const unsigned char *__restrict__ src, long R,
                                                              int d, int KT, int tile_rows, int rows_per_wg,
-                                                             unsigned char *__restrict__ dst)
+                                                             unsigned char *__restrict__ dst, int *__restrict__ pace, int pace_ints)
 {
+    clear_pace(pace, pace_ints);
     const long tile = blockIdx.x;
     const int ks0 = blockIdx.y * 8;
     const int c32 = threadIdx.x & 31;   // 16-byte chunk of the 512-byte span: K step c32/4, chunk c32%4
@@ -139,8 +149,9 @@ __device__ constexpr int SPLIT_H[K1_SPLIT_TERMS] = {0, 1, 2, 0, 1, 0};
 template <bool HIDDEN_SIDE, int SEGMENTS>
 __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *__restrict__ src, long R, int d,
                                                                   int kseg, int tile_rows, int rows_per_wg,
-                                                                  unsigned char *__restrict__ dst)
+                                                                  unsigned char *__restrict__ dst, int *__restrict__ pace, int pace_ints)
 {
+    clear_pace(pace, pace_ints);
     const long tile = blockIdx.x;
     const int c32 = threadIdx.x & 31;
     const int rsub = threadIdx.x >> 5;
@@ -179,25 +190,10 @@ __global__ __launch_bounds__(256) void pack_rows_f32_split_kernel(const float *_
     }
 }
 
-__global__ void k1_pace_zero_kernel(int *__restrict__ pace, int n)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n)
-        pace[i] = 0;
-}
-
 }  // namespace
 
-// pacing counters, cleared by a kernel (a caller may be capturing a graph)
-hipError_t k1_clear_pace(int *pace, long count, hipStream_t st)
-{
-    const int n = (int)count;
-    hipLaunchKernelGGL(k1_pace_zero_kernel, dim3((n + 255) / 256), dim3(256), 0, st, pace, n);
-    return hipGetLastError();
-}
-
 hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, bool pieces, int tile_rows,
-                                  void *dst, hipStream_t st)
+                                  void *dst, int *pace, long pace_ints, hipStream_t st)
 {
     if (rows <= 0)
         return hipSuccess;
@@ -211,7 +207,7 @@ hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hid
     const dim3 grid((unsigned)tiles, (kseg + 7) / 8, tile_rows / rows_per_wg);
 #define EGTP_PACK_SPLIT(SIDE, SEGMENTS)                                                                                     \
     hipLaunchKernelGGL((pack_rows_f32_split_kernel<SIDE, SEGMENTS>), grid, dim3(256), 0, st, (const float *)src, (long)rows, d, \
-                       kseg, tile_rows, rows_per_wg, (unsigned char *)dst)
+                       kseg, tile_rows, rows_per_wg, (unsigned char *)dst, pace, (int)pace_ints)
     if (!hidden_side)
         EGTP_PACK_SPLIT(false, K1_SPLIT_TERMS);
     else if (pieces)
@@ -229,7 +225,8 @@ size_t k1_packed_bytes(int64_t rows, int K)
     return (size_t)(tiles * kt) * TILE_BYTES;
 }
 
-hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, hipStream_t st)
+hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, int *pace, long pace_ints,
+                             hipStream_t st)
 {
     if (rows <= 0)
         return hipSuccess;
@@ -243,7 +240,8 @@ hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows
     // would otherwise leave most of the chip idle
     const int rows_per_wg = tiles * ((kt + 7) / 8) >= 1024 ? tile_rows : 32;
     hipLaunchKernelGGL(pack_rows_bf16_kernel, dim3((unsigned)tiles, (kt + 7) / 8, tile_rows / rows_per_wg), dim3(256), 0,
-                       st, (const unsigned char *)src, (long)rows, d, kt, tile_rows, rows_per_wg, (unsigned char *)dst);
+                       st, (const unsigned char *)src, (long)rows, d, kt, tile_rows, rows_per_wg, (unsigned char *)dst, pace,
+                       (int)pace_ints);
     return hipGetLastError();
 }
 

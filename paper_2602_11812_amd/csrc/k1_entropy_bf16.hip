@@ -386,8 +386,6 @@ hipError_t k1_entropy_bf16(const void *hidden_packed, const void *w_packed, int6
         return hipErrorInvalidValue;  // a row tile over all of K is addressed with 32-bit byte offsets
     if (!k1_plan_paces(p))
         pace = nullptr;  // no pacing point inside a range
-    if (pace != nullptr && (ea = k1_clear_pace(pace, 8 * k1_pace_cohorts(units), st)) != hipSuccess)
-        return ea;
     hipLaunchKernelGGL((k1_entropy_bf16_kernel<NSTAGE>), dim3((unsigned)units), dim3(256), LDS_BYTES, st,
                        (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V,
                        p.ntb, p.nsplit, p.tiles_per_split, p.ntiles_v, part, pace);

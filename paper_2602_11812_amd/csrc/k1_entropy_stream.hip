@@ -442,11 +442,6 @@ hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, in
         return hipErrorInvalidValue;
     if (!k1_plan_paces(p))
         pace = nullptr;
-    if (pace != nullptr) {
-        const hipError_t e = k1_clear_pace(pace, p.whole_cohorts ? cohorts : 8 * k1_pace_cohorts(units), st);
-        if (e != hipSuccess)
-            return e;
-    }
 #define EGTP_STREAM_OF(NI, D, PIECES)                                                                           \
     (stream ? launch<NI, D, PIECES, true>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st)      \
             : launch<NI, D, PIECES, false>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st))

@@ -88,5 +88,12 @@ inline bool k1_plan_paces(const K1Plan &p)
         return p.tiles_per_split > K1_STREAM_PACE_TILES && p.ntb >= 16;
     return p.tile_v != K1_NARROW_TILE_V && p.tiles_per_split > K1_PACE_TILES && p.ntb >= 8;
 }
+// counters that a plan paces with, to be zero when the fused kernel starts
+inline long k1_pace_ints(const K1Plan &p)
+{
+    if (!k1_plan_paces(p))
+        return 0;
+    return p.whole_cohorts ? k1_stream_cohorts(p.ntb, p.nsplit) : 8L * k1_pace_cohorts((long)p.ntb * p.nsplit);
+}
 
 }  // namespace egtp

@@ -50,22 +50,22 @@ constexpr int K1_PACK_BLOCK_BYTES = K1_PACK_ROWS * K1_PACK_K * 2;
 // Hidden states for the narrow and the stream kernel use row tiles of the plan's tb_tokens instead of 256 rows
 // (`tile_rows`, a multiple of 64 up to 256); everything else is the same.
 size_t k1_packed_bytes(int64_t rows, int K);
-hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, hipStream_t st);
+// Both also write zeros to `pace_ints` ints at `pace`.
+hipError_t k1_pack_rows_bf16(const void *src, int64_t rows, int d, int tile_rows, void *dst, int *pace, long pace_ints,
+                             hipStream_t st);
 // fp32 rows (d % 4 == 0) into the six K segments of the W_lm side or of the hidden-state side; `pieces`: the first three
 // of the latter
 hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hidden_side, bool pieces, int tile_rows, void *dst,
-                                  hipStream_t st);
+                                  int *pace, long pace_ints, hipStream_t st);
 
 // Eq. 2, fused: partial (m = max z log2 e, sum e^{z-m}, sum e^{z-m}(z-m) log2 e) per token and vocabulary range.
 // Both operands in the packed layout, contraction length K; `pace`: k1_pace_ints_bound ints of scratch
-// (contents do not matter on entry), or NULL to run without pacing.
+// of which the first k1_pace_ints(p) are zero, or NULL to run without pacing.
 hipError_t k1_entropy_bf16(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
                            const K1Plan &p, float *part, int *pace, hipStream_t st);
 // the same for a narrow plan (p.tile_v == K1_NARROW_TILE_V)
 hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, hipStream_t st);
-// clears `count` pacing counters
-hipError_t k1_clear_pace(int *pace, long count, hipStream_t st);
 // ... and for a plan with p.tile_v == K1_STREAM_TILE_V
 hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, int *pace, hipStream_t st);
