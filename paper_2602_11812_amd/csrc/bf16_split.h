@@ -28,16 +28,14 @@ __device__ __forceinline__ unsigned pack_halves(unsigned even, unsigned odd)
 }
 
 // two neighbours, packed piece by piece
-__device__ __forceinline__ void split3_pair(bool may_be_inf, float even, float odd, unsigned &hi, unsigned &mid, unsigned &lo)
+__device__ __forceinline__ void split3_pair(float even, float odd, unsigned &hi, unsigned &mid, unsigned &lo)
 {
     const float e1 = even - __uint_as_float(__float_as_uint(even) & 0xffff0000u);
     const float o1 = odd - __uint_as_float(__float_as_uint(odd) & 0xffff0000u);
-    // an infinite value: its lower pieces are zero, not NaN
-    const float e1z = may_be_inf && __builtin_isinf(even) ? 0.f : e1, o1z = may_be_inf && __builtin_isinf(odd) ? 0.f : o1;
     hi = pack_halves(__float_as_uint(even), __float_as_uint(odd));
-    mid = pack_halves(__float_as_uint(e1z), __float_as_uint(o1z));
-    lo = pack_halves(__float_as_uint(e1z - __uint_as_float(__float_as_uint(e1z) & 0xffff0000u)),
-                     __float_as_uint(o1z - __uint_as_float(__float_as_uint(o1z) & 0xffff0000u)));
+    mid = pack_halves(__float_as_uint(e1), __float_as_uint(o1));
+    lo = pack_halves(__float_as_uint(e1 - __uint_as_float(__float_as_uint(e1) & 0xffff0000u)),
+                     __float_as_uint(o1 - __uint_as_float(__float_as_uint(o1) & 0xffff0000u)));
 }
 
 }  // namespace

@@ -350,7 +350,7 @@ struct Layer1Source {
     static constexpr bool BF16 = sizeof(W) == 2;
     static constexpr int ROW_PIECES = BF16 ? 1 : 3, ROW_LOADS = BF16 ? S::FA : 2 * S::FA, COL_LOADS = 2 * S::SHARE,
                          COL_WRITES = 3 * S::SHARE;
-    static constexpr bool COLS_MAY_BE_INF = !BF16, ROWS_TURN = S::FB == 4;
+    static constexpr bool ROWS_TURN = S::FB == 4;
     static constexpr int TURN_BYTES = 16 * S::STEP * sizeof(W);  // a fragment of rows as it lies in memory
     struct Rows {
         std::conditional_t<BF16, u32x4, float4> v[S::FA][BF16 ? 1 : 2];
@@ -420,6 +420,15 @@ struct Layer1Source {
     __device__ __forceinline__ int slot() const { return fragment_place(lane & 15, lane >> 4); }
 };
 
+template <typename T>
+__device__ __forceinline__ void four_or_zeros(const T *__restrict__ p, bool in, float (&v)[4])
+{
+    const ChunkOf<T> q = *(const ChunkOf<T> *)p;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        v[e] = in ? widen(q[e]) : 0.f;
+}
+
 template <class S, typename W>
 __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_split_kernel(
     const float *__restrict__ x, const int32_t *__restrict__ slot, int B, int d, int d_h, const W *__restrict__ w1,
@@ -462,6 +471,28 @@ __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_sp
             acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
     if (src.kbeg < src.kend)
         split_contract<S>(lds, (src.kend - src.kbeg + S::STEP - 1) / S::STEP, acc, src);
+    if (!all_finite(acc)) {
+        const W *wp[FA];
+        const float *xp[FB];
+#pragma unroll
+        for (int a = 0; a < FA; ++a)
+            wp[a] = w1 + (long)min(j0 + 16 * (wave * FA + a) + l15, d_h - 1) * d;
+#pragma unroll
+        for (int b = 0; b < FB; ++b) {
+            const int sq = min(s0 + 16 * b + l15, B - 1);
+            xp[b] = x + (long)(slot ? slot[sq] : sq) * d;
+        }
+        redo_not_finite(src.kend - src.kbeg, acc, [&](int i, float (&av)[FA][4], float (&bv)[FB][4]) {
+            // a slice is a multiple of 4 long: the four elements are inside or past the end
+            const int k = src.kbeg + 16 * i + 4 * kq, at = min(k, src.kend - 4);
+#pragma unroll
+            for (int a = 0; a < FA; ++a)
+                four_or_zeros(wp[a] + at, k < src.kend, av[a]);
+#pragma unroll
+            for (int b = 0; b < FB; ++b)
+                four_or_zeros(xp[b] + at, k < src.kend, bv[b]);
+        });
+    }
 
     float *act = act_part + (long)kslice * B * d_h;
 #pragma unroll

@@ -391,7 +391,7 @@ constexpr int SPLIT_SAMPLES = 192, SPLIT_TILES = 128;
 
 struct GradSource {
     static constexpr int ROW_PIECES = 3, ROW_LOADS = 8, COL_LOADS = 2, COL_WRITES = 12;
-    static constexpr bool COLS_MAY_BE_INF = false, ROWS_TURN = false;
+    static constexpr bool ROWS_TURN = false;
     struct Rows {
         float2 v[8];
     };
@@ -471,6 +471,18 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
         for (int b = 0; b < FB; ++b)
             acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
     split_contract<S>(lds, (B + S::STEP - 1) / S::STEP, acc, src);
+    if (!all_finite(acc))
+        redo_not_finite(B, acc, [&](int i, float (&av)[FA][4], float (&bv)[FB][4]) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int b = 16 * i + 4 * kq + e, sample = min(b, B - 1);
+                const float2 dv = *(const float2 *)(src.dact + sample * src.d_h);
+                const float4 xv = *(const float4 *)(src.x + sample * src.d);
+                av[0][e] = b < B ? dv.x : 0.f, av[1][e] = b < B ? dv.y : 0.f;
+                bv[0][e] = b < B ? xv.x : 0.f, bv[1][e] = b < B ? xv.y : 0.f;
+                bv[2][e] = b < B ? xv.z : 0.f, bv[3][e] = b < B ? xv.w : 0.f;
+            }
+        });
 
     const int k = k0 + 4 * l15;
     if (k >= d)

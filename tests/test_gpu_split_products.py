@@ -5,8 +5,10 @@ step of 32, samples that end inside one."""
 import numpy as np
 import pytest
 
+import oracle
+from helpers import rel_l2
 from paper_2602_11812_amd import workloads as wl
-from test_gpu_training import _run_steps, gpu  # noqa: F401  (the fixture)
+from test_gpu_training import _gpu_step, _oracle_head, _run_steps, _trainer, gpu  # noqa: F401  (the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -38,3 +40,72 @@ def test_infinite_feature_stays_in_its_sequence(gpu):  # noqa: F811
         assert not np.isfinite(got[b])
         assert np.array_equal(np.delete(got, b), np.delete(clean, b)), b
     sc.close()
+
+
+# The fp32 matrix instructions (64), pieces in tiles of 64 columns, in tiles of 128, and a slice that ends inside a step of 32;
+# bf16 weights.
+@pytest.mark.parametrize("B,d,d_h,bf16", [(64, 64, 70, False), (65, 64, 70, False), (130, 36, 129, False), (449, 1028, 2044, False),
+                                          (40, 40, 17, True), (129, 264, 130, True)])
+def test_operands_that_are_not_finite(gpu, B, d, d_h, bf16):  # noqa: F811
+    """An infinite weight or feature gives what IEEE arithmetic gives, whatever the batch size and however few bits the other
+    factors have (pieces that are zero); finite values at the end of the range stay finite."""
+    import torch
+    rng = np.random.default_rng(8700 + B)
+    f32 = lambda *s, std=1.0: (std * rng.standard_normal(s)).astype(np.float32)
+    td = gpu.to_device
+    few_bits = lambda a: (a.view(np.uint32) & 0xffff0000).view(np.float32)
+    store = torch.bfloat16 if bf16 else torch.float32
+    w_lm, hidden, w2 = td(f32(300, d, std=d ** -0.5)), td(np.zeros((B, d), np.float32)), td(f32(1, d_h)).to(store)
+    lse = td(np.full(B, 80.0, np.float32))  # the new tokens add nothing: the states stay as they are
+    k, big = d - 3, 3.4e38                  # (past the largest bf16 value)
+    for place, value in (("w1", np.inf), ("w1", -np.inf), ("x", np.inf), ("x", -np.inf), ("w1", big), ("x", big)):
+        if bf16 and (place, value) == ("w1", big):
+            continue  # not a bf16 value
+        w1, x = f32(d_h, d, std=d ** -0.5), f32(B, d)
+        if place == "w1":
+            x[:, k] *= np.float32(2.0 ** -100 if value == big else 1.0)
+            w1[d_h - 2, k] = value
+        else:
+            w1[:, k] *= np.float32(2.0 ** -100 if value == big else 1.0)
+            w1 = few_bits(w1)
+            x[B - 2, k] = value
+        w1 = td(w1).to(store)
+        sc, state = gpu.Scorer(w_lm, gpu.make_head(w1, w2)), td(x)
+        got = sc.step(hidden, state, lse.clone()).cpu().numpy().astype(np.float64)
+        sc.close()
+        assert np.array_equal(state.cpu().numpy(), x)
+        with np.errstate(all="ignore"):
+            want = oracle.predict(x.astype(np.float64), oracle.Head(w1.float().cpu().numpy(), w2.float().cpu().numpy()))
+        ok = np.isfinite(want)
+        assert ok.all() == (value == big)
+        assert np.array_equal(got[~ok], want[~ok], equal_nan=True), (place, value)
+        assert (np.abs(got[ok] - want[ok]) <= 2e-5 * (1.0 + np.abs(want[ok]))).all(), (place, value)
+
+
+@pytest.mark.parametrize("B,d_h", [(66, 260), (257, 516)])
+def test_diverged_head_shows_in_the_loss(gpu, B, d_h):  # noqa: F811
+    ts = wl.make_train(4700 + B, B=B, d=36, d_h=d_h, K=3)
+    ts.w1[5, 7] = np.inf
+    ts.w1[9, 7] = -np.inf
+    tr = _trainer(gpu, ts)
+    assert np.isnan(_gpu_step(gpu, tr, ts)).all()
+
+
+def test_gradient_beyond_the_range_is_infinite(gpu):  # noqa: F811
+    """A unit's pre-activation gradient that overflows makes its row of W1's gradient infinite, not NaN, where the features
+    have few bits, and leaves the other rows alone."""
+    B, d, d_h, j = 195, 2052, 516, 77
+    ts = wl.make_train(4800, B=B, d=d, d_h=d_h, K=3)
+    rng = np.random.default_rng(4801)
+    ts.x[:] = rng.choice(np.float32([0.5, 1.0, 2.0]), ts.x.shape)
+    ts.y[:] = 1e6
+    ts.w1[j] = 0.0
+    ts.b1[j], ts.w2[0, j], ts.w2[1:, j] = 1e-38, 3e38, 0.0
+    _, gs = oracle.head_loss_grad(ts.x, ts.bins, ts.y, _oracle_head(ts), float(np.float32(0.95)), None)
+    assert (gs[0][j] > 1e39).all()
+    tr = _trainer(gpu, ts)
+    _gpu_step(gpu, tr, ts)
+    got = tr.grads["w1"].cpu().numpy().astype(np.float64)
+    assert np.all(got[j] == np.inf)
+    rest = np.arange(d_h) != j
+    assert rel_l2(got[rest], gs[0][rest]) <= 2e-5
