@@ -199,7 +199,8 @@ __device__ __forceinline__ float unit_entropy(const float *__restrict__ part, in
 
 // With part != NULL the weighted mode finishes Eq. 2 for its unit's tokens first and writes H to entropy; tokens that no
 // sequence holds (a table that begins after 0 or ends before T) get theirs from two units that the grid has beyond
-// those of the sequences and from the numbers that these leave unused.
+// those of the sequences and from the numbers that these leave unused.  (What a malformed table
+// leaves out: pool_finalize_kernel.)
 template <bool BF16, int MODE>
 __global__ __launch_bounds__(256) void pool_partial_kernel(
     const void *__restrict__ hidden, int d, float *entropy, const float *__restrict__ part, int nsplit,
@@ -409,11 +410,13 @@ __global__ __launch_bounds__(256) void pool_finalize_plain_kernel(const float *_
 __global__ __launch_bounds__(256) void pool_finalize_kernel(
     const float *__restrict__ partial, const float2 *__restrict__ unit_stats, const int32_t *__restrict__ offsets,
     const int32_t *__restrict__ slot, long T, int d, int unit_log2, long units_cap, const float *state_pooled,
-    const float *__restrict__ lse_old, float *out_pooled, float *out_lse)
+    const float *__restrict__ lse_old, float *out_pooled, float *out_lse, float *__restrict__ entropy,
+    const float *__restrict__ part, int nsplit)
 {
     __shared__ float factor[JOIN_FACTORS];
     __shared__ float4 waves[3][64];
     __shared__ float red[2][4];
+    __shared__ float triples[3][256];
     const int b = blockIdx.x;
     const int k = blockIdx.y * JOIN_COLS + (threadIdx.x & 63) * 4;
     const int tid = threadIdx.x, wave = tid >> 6;
@@ -471,6 +474,24 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
             r.z = fmaf(old.z, sc, r.z), r.w = fmaf(old.w, sc, r.w);
         }
         *(float4 *)(out_pooled + (long)s * d + k) = r;
+    }
+
+    auto wrong = [&](int i) { return offsets[i + 1] < offsets[i] || offsets[i] < 0; };
+    if (part != nullptr && wrong(b)) {
+        // Entropies belong to the tokens, whatever the table holds.  The units reach every token as long as the offsets begin
+        // at 0 or later and do not decrease; the workgroups of the first sequence for which that is not so merge the
+        // whole batch's triples.
+        bool earlier = false;
+        for (int i = threadIdx.x; i < b; i += 256)
+            earlier |= wrong(i);
+        if (__syncthreads_or(earlier) == 0)
+            for (long t0 = (long)blockIdx.y << unit_log2; t0 < T; t0 += (long)gridDim.y << unit_log2) {
+                const int n = (int)min(1L << unit_log2, T - t0);
+                const float H = unit_entropy(part, nsplit, T, t0, n, unit_log2, triples);
+                if ((int)threadIdx.x < n)
+                    entropy[t0 + threadIdx.x] = H;
+                __syncthreads();  // the triples have been read
+            }
     }
 }
 
@@ -668,7 +689,7 @@ hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st)
                            a.lse_old, a.partial, stats);
     hipLaunchKernelGGL(pool_finalize_kernel, dim3(a.B, (a.d + JOIN_COLS - 1) / JOIN_COLS), dim3(256), 0, st, a.partial, stats, a.offsets,
                        a.slot, (long)a.T, a.d, unit_log2, units, a.state_pooled, a.state_lse ? a.lse_old : nullptr, a.out_pooled,
-                       a.out_lse);
+                       a.out_lse, a.entropy, a.k1_part, a.k1_nsplit);
     return hipGetLastError();
 }
 

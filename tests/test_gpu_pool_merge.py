@@ -65,3 +65,23 @@ def gpu_rows(hidden, a, b):
     """Rows of a batch in fp64, whatever it is stored in."""
     from paper_2602_11812_amd import binding as gpu
     return gpu.to_device(hidden[a:b]).double().cpu().numpy()
+
+
+@pytest.mark.parametrize("cuts", [(0, 500, 100, 701), (0, 701, 0, 701), (0, 600, 650, 20, 30), (-1000, 300, 701), (-6, 300, 701),
+                                  (-2000, -900, -30), (900, 0, 650, 701), (0, 701) + (0,) * 2100, (0,) * 2100 + (701, 690)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 2052)])
+def test_entropies_do_not_depend_on_the_table(dtype, d, cuts):
+    """A device table that decreases or begins below 0 gives meaningless sequences (the kernels clamp every index into the batch),
+    but the entropies are those of the tokens."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    w, sc = _batch(dtype, d, 3000, (701,), 8300)
+    hidden = gpu.to_device(w.hidden)
+    good = sc.score(hidden, torch.tensor([0, 701], dtype=torch.int32).cuda())["entropy"].cpu().numpy()
+    B = len(cuts) - 1
+    out = [torch.full(n, float("nan"), device="cuda") for n in ((701,), (B, d), (B,), (B,))]
+    gpu.egtp_score(sc.ctx, hidden, torch.tensor(cuts, dtype=torch.int32).cuda(), None, B, 701, sc.workspace(701, B), *out)
+    H = out[0].cpu().numpy()
+    sc.close()
+    assert np.abs(good - oracle.entropy(w.hidden, w.w_lm)).max() <= 2e-5
+    assert np.abs(H - good).max() <= 1e-6  # (units of another size merge the triples in another order)
