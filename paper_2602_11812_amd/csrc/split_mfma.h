@@ -1,7 +1,16 @@
 // Products of fp32 operands on the bf16 matrix cores: every value is the exact sum of three bf16 pieces, a product of two
-// pieces is exact in fp32, and of the nine piece products of a pair the six of relative size 2^-16 and more are accumulated
-// (the other three are below 2^-24, fp32's own rounding).  Six 16x16x32 MFMAs take the place of eight 16x16x4 ones that
-// cost four times as many cycles.  Device-side header.
+// pieces is exact in fp32, and of the nine piece products of a pair the six largest are accumulated (the pieces are rounded to
+// nearest: the other three come to 2^-24 of the product at most, fp32's own rounding, and have either sign).  Six 16x16x32
+// MFMAs take the place of eight 16x16x4 ones that cost four times as many cycles.
+//
+// The five small products have sums of their own, so that the large sums are rounded once a step: every MFMA may cost a
+// running sum an ulp.  Relative distance of the gradients of W1 and W2 (which shows layer 1) to fp64, 8 seeds, 250 samples, d = 4096,
+// d_h = 500, Gaussian operands / all low mantissa bits set:
+//   as it is                               2.1e-7 7.0e-8 / 2.2e-7 6.9e-8
+//   one sum for all six                    3.2e-7 8.3e-8 / 2.7e-7 7.1e-8
+//   ... and pieces cut off (split3_bits)   3.3e-7 1.1e-7 / 3.9e-7 3.2e-7
+//   fp32 matrix instructions               3.2e-7 8.2e-8 / 3.0e-7 8.7e-8
+// A step of 1024 samples, d = 4096, d_h = 1024: 128.4 us with pieces cut off and one sum, 129.1 as it is.  Device-side header.
 #pragma once
 #include "bf16_split.h"
 
@@ -26,9 +35,9 @@ struct SplitTile {
 //
 // Everything that a step needs is under way before it: while the products of step i run, the column fragments of step i + 1
 // are read from the LDS and its rows split, the columns of step i + 2 are split into the other buffer, rows of step i + 3
-// and columns of step i + 4 are asked for.  There is one wave per SIMD, so the order inside a step is pinned: a row of FB
-// products at a time with its share of everything else, which hides in the cycles that an MFMA leaves to other
-// instructions.  One barrier per step: behind it step i + 1 is whole and everyone has read step i.  Of a step the smallest
+// and columns of step i + 4 are asked for.  There are one (tiles of 128 columns) or two waves per SIMD, so the order inside a
+// step is pinned: a row of FB products at a time with its share of everything else, which hides in the cycles that an
+// MFMA leaves to other instructions.  One barrier per step: behind it step i + 1 is whole and everyone has read step i.  Of a step the smallest
 // products come first.
 //
 // Source: this thread's share of the operands; past the end of the contraction any valid place is loaded, and not used
@@ -66,7 +75,7 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
             f.p[0][a][e] = src.row_pair(r, a, e);
         } else {
             unsigned h, m, l;
-            split3_pair(src.row_value(r, a, 2 * e), src.row_value(r, a, 2 * e + 1), h, m, l);
+            split3_pair_nearest(src.row_value(r, a, 2 * e), src.row_value(r, a, 2 * e + 1), h, m, l);
             f.p[0][a][e] = h, f.p[1][a][e] = m, f.p[2][a][e] = l;
         }
     };
@@ -74,7 +83,10 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
     auto split_cols = [&](const typename Source::Cols &r, int n) {
         const int p = n / 4, e = n % 4;
         unsigned h, m, l;
-        split3_pair(src.col_value(r, p, 2 * e), src.col_value(r, p, 2 * e + 1), h, m, l);
+        if constexpr (Source::ROW_PIECES == 1)  // every product is taken
+            split3_pair(src.col_value(r, p, 2 * e), src.col_value(r, p, 2 * e + 1), h, m, l);
+        else
+            split3_pair_nearest(src.col_value(r, p, 2 * e), src.col_value(r, p, 2 * e + 1), h, m, l);
         part[p][0][e] = h, part[p][1][e] = m, part[p][2][e] = l;
     };
     auto write = [&](unsigned char *buf, int n) { src.write_col(buf, part, n); };
@@ -132,8 +144,7 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
 #pragma unroll
     for (int n = 0; n < READS; ++n)
         read(b0, lds, n);
-    // Rows in one piece: the small products have sums of their own, so that the large ones are rounded once a step, not
-    // three times (prediction, 300 sequences, d = 4096, d_h = 1024: 2.00e-7 from fp64 -> 1.54e-7).
+    // the sums of the small products
     split_f32x4 small[FA][FB];
 #pragma unroll
     for (int fa = 0; fa < FA; ++fa)
@@ -157,11 +168,11 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
             const int t = row / FA, fa = row % FA;
 #pragma unroll
             for (int fb = 0; fb < FB; ++fb)
-                {
-                    split_f32x4 &sum = WHOLE && t < PRODUCTS - 1 ? small[fa][fb] : acc[fa][fb];
-                    sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, a.p[PA[WHOLE][t]][fa]),
-                                                                  b.p[PB[WHOLE][t]][fb], sum, 0, 0, 0);
-                }
+            {
+                split_f32x4 &sum = t < PRODUCTS - 1 ? small[fa][fb] : acc[fa][fb];
+                sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, a.p[PA[WHOLE][t]][fa]),
+                                                              b.p[PB[WHOLE][t]][fb], sum, 0, 0, 0);
+            }
 #pragma unroll
             for (int n = row * READS / ROWS; n < (row + 1) * READS / ROWS; ++n)
                 read(b_next, other, n);
@@ -204,12 +215,11 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
     }
     if (i < steps)
         step(i, a0, a1, b0, b1, ra1, rb0, lds, lds + T::BYTES);
-    if constexpr (Source::ROW_PIECES == 1)
 #pragma unroll
-        for (int fa = 0; fa < FA; ++fa)
+    for (int fa = 0; fa < FA; ++fa)
 #pragma unroll
-            for (int fb = 0; fb < FB; ++fb)
-                acc[fa][fb] += small[fa][fb];
+        for (int fb = 0; fb < FB; ++fb)
+            acc[fa][fb] += small[fa][fb];
 }
 
 // whether every sum of the wave is finite

@@ -109,3 +109,61 @@ def test_gradient_beyond_the_range_is_infinite(gpu):  # noqa: F811
     assert np.all(got[j] == np.inf)
     rest = np.arange(d_h) != j
     assert rel_l2(got[rest], gs[0][rest]) <= 2e-5
+
+
+def _full(rng, *shape):
+    """Values of either sign whose mantissas fill every piece: low bits all set, or any."""
+    bits = rng.integers(0, 1 << 23, shape).astype(np.uint32)
+    bits = np.where(rng.random(shape) < 0.5, bits | np.uint32(0xffff), bits) | np.uint32(0x3f800000)
+    return bits.view(np.float32) * rng.choice(np.float32([-0.5, 1.0, 2.0]), shape)
+
+
+# A sum of one product shows every piece product: the smallest that is kept is of size 2^-16, and what is dropped and rounded
+# may come to 4 x 2^-24 (pieces rounded to nearest drop at most 2^-24 of a product; of six sums few round).
+ONE_PRODUCT = 2.0 ** -22
+
+
+# tiles of 64 columns; of 128; bf16 weights
+@pytest.mark.parametrize("B,d,d_h,bf16", [(65, 64, 260, False), (130, 520, 129, False), (449, 1028, 2044, False),
+                                          (66, 264, 130, True)])
+def test_single_products_of_layer_1(gpu, B, d, d_h, bf16):  # noqa: F811
+    import torch
+    rng = np.random.default_rng(8800 + B)
+    td = gpu.to_device
+    w1 = np.zeros((d_h, d), np.float32)
+    at = rng.integers(0, d, d_h)
+    w1[np.arange(d_h), at] = np.abs(_full(rng, d_h))
+    store = td(w1).to(torch.bfloat16 if bf16 else torch.float32)
+    w1 = store.float().cpu().numpy()
+    x = np.abs(_full(rng, B, d))
+    w_lm, hidden = td(rng.standard_normal((300, d)).astype(np.float32)), td(np.zeros((B, d), np.float32))
+    for j in (0, 17, 35, 63, 64, 101, 127, d_h - 1):
+        w2 = torch.zeros(1, d_h, device="cuda", dtype=store.dtype)
+        w2[0, j] = 1.0
+        sc, state = gpu.Scorer(w_lm, gpu.make_head(store, w2)), td(x)
+        got = sc.step(hidden, state, td(np.full(B, 80.0, np.float32))).cpu().numpy().astype(np.float64)
+        sc.close()
+        assert np.array_equal(state.cpu().numpy(), x)
+        want = x[:, at[j]].astype(np.float64) * w1[j, at[j]].astype(np.float64)
+        assert (np.abs(got - want) <= ONE_PRODUCT * want).all(), (j, np.abs(got / want - 1.0).max())
+
+
+@pytest.mark.parametrize("B,d,d_h", [(193, 2052, 516), (449, 1028, 1020)])
+def test_single_products_of_the_gradient(gpu, B, d, d_h):  # noqa: F811
+    """Every hidden unit is active in one sample (which a column of its own names), so that an element of W1's gradient is one
+    product, of a feature and of the unit's element of b1's gradient."""
+    ts = wl.make_train(4900 + B, B=B, d=d, d_h=d_h, K=5)
+    rng = np.random.default_rng(4950 + B)
+    own = np.arange(d_h) % B
+    rng.shuffle(own)
+    ts.x[:, B:] = _full(rng, B, d - B)
+    ts.x[:, :B] = np.eye(B)
+    ts.w1[:] = 0.0
+    ts.w1[np.arange(d_h), own] = 2.0
+    ts.b1[:] = -1.0
+    tr = _trainer(gpu, ts)
+    _gpu_step(gpu, tr, ts)
+    b1, w1 = (tr.grads[n].cpu().numpy().astype(np.float64) for n in ("b1", "w1"))
+    assert (b1 != 0.0).all()
+    want = b1[:, None] * ts.x[own].astype(np.float64)
+    assert (np.abs(w1 - want) <= ONE_PRODUCT * np.abs(want)).all(), np.abs(w1 / want - 1.0)[want != 0.0].max()
