@@ -55,3 +55,23 @@ def assert_egtp_close(got: dict, want: "oracle.EgtpResult", lens=None):
         assert np.abs(got["lse"][finite].astype(np.float64) - want.lse[finite]).max() <= TOL_LSE_ABS
     assert np.all(got["lse"][~finite] == -np.inf)
     assert_pred_close(got["pred"], want.pred)
+
+
+def piece_operands(rng, T, V, d):
+    """(hidden, w_lm) pairs of fp32 values whose dot products are exact in fp32 in whatever order they are formed (whole numbers
+    below 2^24 of one unit) and that between them need every product of the operands' bf16 pieces: W_lm with all three against
+    hidden states with one, the other way round, and two each."""
+    whole = lambda bits, *shape: rng.integers(1 << (bits - 1), 1 << bits, shape) * rng.choice([-1.0, 1.0], shape)
+
+    def rows(values, per_row):  # at most per_row of a row's elements are not zero
+        w = np.zeros((V, d))
+        for _ in range(per_row):
+            w[np.arange(V), rng.integers(0, d, V)] = values
+        return w
+
+    pairs = []
+    for scale in (2.0, 4.0):  # spreads that leave few and several logits near the largest, whatever V is
+        pairs += [(rng.choice([-1.0, 1.0], (T, d)), rows(whole(21, V) * scale * 2.0 ** -16, 2)),
+                  (whole(21, T, d) * scale * 2.0 ** -18, rows(rng.choice([-2.0, -1.0, 1.0, 2.0], V), 2)),
+                  (whole(12, T, d) * scale * 2.0 ** -9, rows(whole(12, V) * 2.0 ** -9, 1))]
+    return [(h.astype(np.float32), w.astype(np.float32)) for h, w in pairs]

@@ -1,12 +1,13 @@
 """fp32 operands read by their pieces (few tokens): the narrow kernel, whose fragments of a piece serve several products, and
 one or two token blocks of the stream kernel, which walks the products of a K step in turn; three blocks, which do not.
 One K step of pieces, an odd and an even number of them, ranges of one and of several tiles, ragged last blocks.  Entropies
-against the fp64 oracle to the fp32 bar (2e-5 nat), and operands whose products and sums are whole numbers below 2^24, of
-which a dropped or doubled piece product would change every logit."""
+against the fp64 oracle to the fp32 bar (2e-5 nat), of Gaussian operands and of ones whose logits are exact and move the
+entropies well past the bar if any of the six piece products is dropped or doubled (test_piece_operands.py)."""
 import numpy as np
 import pytest
 
 import oracle
+from helpers import piece_operands
 from paper_2602_11812_amd import workloads as wl
 
 pytestmark = pytest.mark.gpu
@@ -26,13 +27,9 @@ def test_against_the_oracle(d, V, T, block, per_range):
     plan = gpu.egtp_launch_plan_query(gpu.EGTP_F32, d, V, T)
     assert (plan.tokens_per_block, plan.tiles_per_range) == (block, per_range)
     w = wl.make(wl.scaled(wl.SPECS["tiny"], seed=9500 + T + d, B=1, d=d, V=V, d_h=16, lengths=(T,)))
-    rng = np.random.default_rng(9600 + T)
-    # whole numbers with bits in all three pieces of one side and in the leading piece of the other, few enough non-zeros
-    exact_w = np.where(rng.random((V, d)) < 3.0 / d, rng.integers(-(1 << 20), 1 << 20, (V, d)) * 2.0 ** -16, 0.0).astype(np.float32)
-    exact_h = rng.integers(-1, 2, (T, d)).astype(np.float32)
     off = torch.tensor([0, T], dtype=torch.int32).cuda()
     td = gpu.to_device
-    for hidden, w_lm in ((w.hidden, w.w_lm), (exact_h, exact_w)):
+    for hidden, w_lm in ((w.hidden, w.w_lm), *piece_operands(np.random.default_rng(9600 + T), T, V, d)):
         sc = gpu.Scorer(td(w_lm), gpu.make_head(td(w.w1), td(w.w2)))
         ws = sc.workspace(T, 1)
         runs = []

@@ -1,7 +1,8 @@
 """fp32 products as bf16 pieces in the head: layer 1 of more than 64 sequences (tiles of 64 and of 128 columns) and W1's
 gradient from 192 samples on.  A step each at the edges of their tiles against the fp64 oracle, to the bars of the fp32
 training tests: batches one past and one short of a tile, rows of W1 off the 128-row tile, slices of d that end inside a K
-step of 32, samples that end inside one."""
+step of 32, samples that end inside one.  Sums of a single product, which show every piece product; operands and results that
+are not finite."""
 import numpy as np
 import pytest
 
