@@ -29,8 +29,9 @@
  *     (bf16: d a multiple of 8; fp32: d a multiple of 4).  The LM-head contraction of Eq. 2 runs
  *     on the bf16 matrix cores for both types: products of bf16 values are exact in the fp32
  *     accumulators; an fp32 value enters as the exact sum of three bf16 pieces, and of the nine
- *     piece products of w*h the six of relative size >= 2^-16 are accumulated (the rest is below
- *     fp32's own rounding), so fp32 inputs give fp32-grade logits at six times the bf16 cost.
+ *     piece products of w*h the six largest are accumulated (the rest comes to at most 2^-21 of a
+ *     product, 2^-24.5 on average, and is always missed towards zero), so fp32 inputs give
+ *     fp32-grade logits at six times the bf16 cost.
  *   - Ragged batches: offsets[B+1] int32, offsets[0] = 0, non-decreasing, offsets[B] = T.
  *     A repeated offset is an empty sequence: pooled = 0, lse = -inf, prediction = head(0).
  *   - Errors are return codes; on any error nothing has been launched.  B == 0 or T == 0 with

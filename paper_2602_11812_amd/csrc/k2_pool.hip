@@ -502,7 +502,7 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
 // is read.
 // The token and its state are asked for before the triples are merged: FOLD_AHEAD chunks per thread (all of them up to d = 4096 in
 // bf16), so that the kernel is two memory latencies long, not three; lanes
-// exchange without the LDS.  24 sequences, d = 4096, V = 151936 6.0 -> 5.4 us, the step 214.2 -> 213.2; another of 176.8 us -> 174.7.
+// exchange without the LDS.  24 sequences, d = 4096, V = 151936 6.0 -> 5.4 us (of a step of 213: no more than two runs of one differ by).
 constexpr int FOLD_AHEAD = 2;
 
 template <bool BF16>

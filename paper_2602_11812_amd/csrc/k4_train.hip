@@ -2,7 +2,9 @@
 // soft labels of Eq. 5, the joint loss of Eq. 7, the per-sequence step average of Eq. 9
 // (as a per-sample weight), the backward pass through the head only, and AdamW.
 //
-// Everything is fp32 (master weights, moments, activations).  Three launches:
+// Master weights, moments, activations and sums are fp32.  For large batches (layer 1 from 65 samples on, W1's gradient from
+// 192 on) fp32 products are formed from bf16 pieces, six of the nine of a pair; what is left out is 2^-24 of a product at most
+// (split_mfma.h).  Three launches:
 //   1. layer 1 forward     partial pre-activations, split along d   (shared with scoring)
 //   2. per-sample kernel   ReLU, logits, softmax, expected value, soft label, the two loss
 //                          terms, d loss / d logits and d loss / d pre-activation
@@ -383,10 +385,16 @@ __device__ __forceinline__ void w1_update(int tile_k, int tile_j, const float *_
 // 1024 samples: the launch 117 to 120 us on the fp32 matrix instructions, then 75 to 82; the way of loaded data back into
 // the compute unit was the busiest part of it (69 %), a quarter of what a load of one k per lane fetched was used.  With
 // four k per lane, a quarter of these loads: whole steps of 1024 samples 135.2 -> 127.4 us, 256 62.3 -> 58.4, 1024 at d = 5120,
-// d_h = 1280 213 -> 195.5.  128 x 128 tiles: 85.  Rows by 16-byte loads as well, turned in the LDS: no faster.
+// d_h = 1280 213 -> 195.5; the launch alone, clocks warm, 65 (75 to 85 in a short run).  128 x 128 tiles: 85.  Rows by
+// 16-byte loads as well, turned in the LDS: no faster.
 typedef SplitTile<2, 4> GradTile;
-// From this many samples and tiles on (whole steps, fp32 -> split: 128 samples, d = 4096, d_h = 1024 52.4 -> 56.6 us, 256
-// 67.5 -> 65.2; 309 samples against 210 tiles 62.8 -> 60.8, 1024 against 48 64.1 -> 65.6).
+// From this many samples and tiles on.  Whole steps, us, fp32 instructions / pieces:
+//   512 tiles (d = 4096, d_h = 1024)   128 samples 55.2 / 56.4   160 66.8 / 64.0   192 70.5 / 67.1   256 72.9 / 67.4
+//   144 tiles (d = 1024, d_h = 1100)   192 samples 39.6 / 38.0   512 63.3 / 54.9   768 83.0 / 68.7
+//   128 tiles (d = 1024, d_h = 1024)   192 samples 32.0 / 34.2   384 44.5 / 44.8   512 46.7 / 45.9   768 64.4 / 61.7
+//    48 tiles (d = 1024, d_h = 384)    192 samples 25.0 / 27.5   512 38.6 / 39.0   1024 62.0 / 58.9
+// At up to 128 tiles, where half the compute units stay without one, the two meet at 400 to 500 samples, elsewhere
+// at about 150: the line is up to 7 % off on its corner, 128 tiles and fewer than 384 samples.
 constexpr int SPLIT_SAMPLES = 192, SPLIT_TILES = 128;
 
 struct GradSource {
@@ -460,7 +468,7 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
 {
     using S = GradTile;
     constexpr int FA = S::FA, FB = S::FB;
-    static_assert(FA == 2 && FB == 4 && S::SHARE == 1, "two neighbouring j, one k to a lane");
+    static_assert(FA == 2 && FB == 4 && S::SHARE == 1, "two neighbouring j, four neighbouring k to a lane");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int k0 = tile_k * S::COLS, j0 = tile_j * S::ROWS + 32 * wave;
 
