@@ -166,6 +166,7 @@ __device__ __forceinline__ Stats wave_merge(Stats a)
 // included): four short fp32 prompts 43.2 -> 39.7 us a pass, 173 tokens, d = 4096, V = 151936 274.8 -> 268.7 (different boxes), 2500
 // tokens, d = 2048, V = 32000 271 -> 262, 3600 tokens, d = 256 against 151936 rows (many ranges) 429 -> 424.
 constexpr int MERGE_AHEAD = 8;
+template <int AHEAD = MERGE_AHEAD>
 __device__ __forceinline__ float unit_entropy(const float *__restrict__ part, int nsplit, long T, long t0, int n, int unit_log2,
                                               float (&sh)[3][256])
 {
@@ -173,15 +174,15 @@ __device__ __forceinline__ float unit_entropy(const float *__restrict__ part, in
     const long plane = (long)nsplit * T;
     const float *p = part + t0 + min(token, n - 1);
     Stats a = {NEG_BIG, 0.f, 0.f};
-    for (int s0 = g; s0 < nsplit; s0 += groups * MERGE_AHEAD) {
-        Stats v[MERGE_AHEAD];
+    for (int s0 = g; s0 < nsplit; s0 += groups * AHEAD) {
+        Stats v[AHEAD];
 #pragma unroll
-        for (int i = 0; i < MERGE_AHEAD; ++i) {
+        for (int i = 0; i < AHEAD; ++i) {
             const float *q = p + (long)min(s0 + i * groups, nsplit - 1) * T;  // past the end: a valid range, not used
             v[i].m = q[0], v[i].S = q[plane], v[i].U = q[2 * plane];
         }
 #pragma unroll
-        for (int i = 0; i < MERGE_AHEAD; ++i)
+        for (int i = 0; i < AHEAD; ++i)
             if (s0 + i * groups < nsplit)
                 a = merge(a, v[i]);
     }
@@ -413,10 +414,13 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
     const float *__restrict__ lse_old, float *out_pooled, float *out_lse, float *__restrict__ entropy,
     const float *__restrict__ part, int nsplit)
 {
-    __shared__ float factor[JOIN_FACTORS];
+    __shared__ union {
+        float factor[JOIN_FACTORS];
+        float triples[3][256];  // of a malformed table's tokens
+    } lds;
     __shared__ float4 waves[3][64];
     __shared__ float red[2][4];
-    __shared__ float triples[3][256];
+    float *const factor = lds.factor;
     const int b = blockIdx.x;
     const int k = blockIdx.y * JOIN_COLS + (threadIdx.x & 63) * 4;
     const int tid = threadIdx.x, wave = tid >> 6;
@@ -424,6 +428,24 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
     const float L_old = lse_old ? lse_old[b] : NEG_INF;
     long u0, u1;
     sequence_units(offsets, b, T, unit_log2, units_cap, u0, u1);
+    auto wrong = [&](int i) { return offsets[i + 1] < offsets[i] || offsets[i] < 0; };
+    if (part != nullptr && wrong(b)) {
+        // Entropies belong to the tokens, whatever the table holds.  The units reach every token as long as the offsets begin
+        // at 0 or later and do not decrease; the workgroups of the first sequence for which that is not so merge the
+        // whole batch's triples.  (Here, two at a time: behind the join the kernel has 66 registers, a wave less per SIMD,
+        // and joins 65088 tokens of 1017 sequences in 39.5 us instead of 35.5.)
+        bool earlier = false;
+        for (int i = threadIdx.x; i < b; i += 256)
+            earlier |= wrong(i);
+        if (__syncthreads_or(earlier) == 0)
+            for (long t0 = (long)blockIdx.y << unit_log2; t0 < T; t0 += (long)gridDim.y << unit_log2) {
+                const int n = (int)min(1L << unit_log2, T - t0);
+                const float H = unit_entropy<2>(part, nsplit, T, t0, n, unit_log2, lds.triples);
+                if ((int)threadIdx.x < n)
+                    entropy[t0 + threadIdx.x] = H;
+                __syncthreads();  // the triples have been read
+            }
+    }
     float mx = NEG_INF;
     for (long u = u0 + tid; u < u1; u += 256)
         mx = fmaxf(mx, unit_stats[u].x);
@@ -474,24 +496,6 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
             r.z = fmaf(old.z, sc, r.z), r.w = fmaf(old.w, sc, r.w);
         }
         *(float4 *)(out_pooled + (long)s * d + k) = r;
-    }
-
-    auto wrong = [&](int i) { return offsets[i + 1] < offsets[i] || offsets[i] < 0; };
-    if (part != nullptr && wrong(b)) {
-        // Entropies belong to the tokens, whatever the table holds.  The units reach every token as long as the offsets begin
-        // at 0 or later and do not decrease; the workgroups of the first sequence for which that is not so merge the
-        // whole batch's triples.
-        bool earlier = false;
-        for (int i = threadIdx.x; i < b; i += 256)
-            earlier |= wrong(i);
-        if (__syncthreads_or(earlier) == 0)
-            for (long t0 = (long)blockIdx.y << unit_log2; t0 < T; t0 += (long)gridDim.y << unit_log2) {
-                const int n = (int)min(1L << unit_log2, T - t0);
-                const float H = unit_entropy(part, nsplit, T, t0, n, unit_log2, triples);
-                if ((int)threadIdx.x < n)
-                    entropy[t0 + threadIdx.x] = H;
-                __syncthreads();  // the triples have been read
-            }
     }
 }
 
