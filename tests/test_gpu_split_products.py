@@ -57,7 +57,7 @@ def test_operands_that_are_not_finite(gpu, B, d, d_h, bf16):  # noqa: F811
     few_bits = lambda a: (a.view(np.uint32) & 0xffff0000).view(np.float32)
     store = torch.bfloat16 if bf16 else torch.float32
     w_lm, hidden, w2 = td(f32(300, d, std=d ** -0.5)), td(np.zeros((B, d), np.float32)), td(f32(1, d_h)).to(store)
-    lse = td(np.full(B, 80.0, np.float32))  # the new tokens add nothing: the states stay as they are
+    lse = td(np.full(B + 5, 80.0, np.float32))  # the new tokens add nothing: the states stay as they are
     k, big = d - 3, 3.4e38                  # (past the largest bf16 value)
     for place, value in (("w1", np.inf), ("w1", -np.inf), ("x", np.inf), ("x", -np.inf), ("w1", big), ("x", big)):
         if bf16 and (place, value) == ("w1", big):
@@ -71,10 +71,13 @@ def test_operands_that_are_not_finite(gpu, B, d, d_h, bf16):  # noqa: F811
             w1 = few_bits(w1)
             x[B - 2, k] = value
         w1 = td(w1).to(store)
-        sc, state = gpu.Scorer(w_lm, gpu.make_head(w1, w2)), td(x)
-        got = sc.step(hidden, state, lse.clone()).cpu().numpy().astype(np.float64)
+        slot = rng.permutation(B + 5)[:B].astype(np.int32)
+        sc, states = gpu.Scorer(w_lm, gpu.make_head(w1, w2)), np.zeros((B + 5, d), np.float32)
+        states[slot] = x
+        states = td(states)
+        got = sc.step(hidden, states, lse.clone(), slot_dev=td(slot)).cpu().numpy().astype(np.float64)
         sc.close()
-        assert np.array_equal(state.cpu().numpy(), x)
+        assert np.array_equal(states.cpu().numpy()[slot], x)
         with np.errstate(all="ignore"):
             want = oracle.predict(x.astype(np.float64), oracle.Head(w1.float().cpu().numpy(), w2.float().cpu().numpy()))
         ok = np.isfinite(want)
