@@ -429,7 +429,7 @@ __global__ __launch_bounds__(256) void pool_finalize_kernel(
     long u0, u1;
     sequence_units(offsets, b, T, unit_log2, units_cap, u0, u1);
     auto wrong = [&](int i) { return offsets[i + 1] < offsets[i] || offsets[i] < 0; };
-    if (part != nullptr && wrong(b)) {
+    if (__builtin_expect(part != nullptr && wrong(b), 0)) {
         // Entropies belong to the tokens, whatever the table holds.  The units reach every token as long as the offsets begin
         // at 0 or later and do not decrease; the workgroups of the first sequence for which that is not so merge the
         // whole batch's triples.  (Here, two at a time: behind the join the kernel has 66 registers, a wave less per SIMD,

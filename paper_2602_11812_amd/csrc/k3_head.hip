@@ -471,7 +471,7 @@ __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_sp
             acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
     if (src.kbeg < src.kend)
         split_contract<S>(lds, (src.kend - src.kbeg + S::STEP - 1) / S::STEP, acc, src);
-    if (!all_finite(acc)) {
+    if (__builtin_expect(!all_finite(acc), 0)) {  // (behind the kernel: in between, its code is a cold fetch for all)
         const W *wp[FA];
         const float *xp[FB];
 #pragma unroll

@@ -491,7 +491,7 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
     asm("" : "+v"(again));
     const int l15 = again & 15, kq = again >> 4 & 3;
     const int j_at = min(j0 + 2 * l15, d_h - 2), k_at = min(k0 + 4 * l15, d - 4);
-    if (!all_finite(acc))
+    if (__builtin_expect(!all_finite(acc), 0))
         redo_not_finite(B, acc, [&](int i, float (&av)[FA][4], float (&bv)[FB][4]) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {

@@ -226,15 +226,15 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
 template <int FA, int FB>
 __device__ __forceinline__ bool all_finite(const split_f32x4 (&acc)[FA][FB])
 {
-    float probe = 0.f;  // NaN as soon as one is not
+    float probe[4] = {0.f, 0.f, 0.f, 0.f};  // NaN as soon as one is not; four chains, not one of all elements
 #pragma unroll
     for (int fa = 0; fa < FA; ++fa)
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                probe = fmaf(acc[fa][fb][e], 0.f, probe);
-    return __builtin_amdgcn_ballot_w64(probe != 0.f) == 0;
+                probe[e] = fmaf(acc[fa][fb][e], 0.f, probe[e]);
+    return __builtin_amdgcn_ballot_w64((probe[0] + probe[1]) + (probe[2] + probe[3]) != 0.f) == 0;
 }
 
 // Sums that split_contract left without a finite value, again on the fp32 matrix instructions.  Pieces have no infinities: the
