@@ -515,17 +515,18 @@ __global__ __launch_bounds__(S::THREADS, S::FB == 4 ? 2 : 1) void head_layer1_sp
     }
 }
 
-// Layer 2 of a scalar head: pred = b2 + w2 . act[b,:].  NS sequences per workgroup (head_tail.h); TINY: d_h < 4.
+// Layer 2 of a scalar head: pred = b2 + w2 . act[b,:].  NS sequences per workgroup (head_tail.h).
 // LDS: a[NS][lda] | part[NS][TAIL_WAVES]
-template <bool WBF16, bool TINY, int NS>
+template <bool WBF16, TailRow ROW, int NS>
 __global__ __launch_bounds__(TAIL_THREADS) void head_scalar_kernel(const float *__restrict__ act_part, int nks, int B,
                                                                    const float *__restrict__ b1, int d_h,
                                                                    const void *__restrict__ w2_any,
                                                                    const float *__restrict__ b2, float *__restrict__ pred)
 {
     using W = std::conditional_t<WBF16, unsigned short, float>;
+    constexpr bool TINY = ROW == TAIL_TINY;
     const W *w2 = (const W *)w2_any;
-    __shared__ float4 join[NS < 4 ? TAIL_JOIN_FLOATS / 4 : 1];
+    __shared__ float4 join[tail_joins<ROW, NS>];
     extern __shared__ __align__(16) float a[];
     const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -533,7 +534,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void head_scalar_kernel(const float *
     // thread t takes the chunks t, t + TAIL_THREADS, ... of the dot product (fixed assignment: bit-reproducible)
     const float bias = b2 ? b2[0] : 0.f;
     ChunkOf<W> w = load_chunk(w2, RowChunk<TINY>(tid, d_h), d_h);
-    hidden_units<TINY, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, nullptr);
+    hidden_units<ROW, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, nullptr);
     float s[NS] = {};
     for (int c0 = tid; 4 * c0 < lda; c0 += TAIL_THREADS) {
         const RowChunk<TINY> c(c0, d_h);
@@ -560,7 +561,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void head_scalar_kernel(const float *
 }
 
 // Layer 2 of a K-bin head: out[o] = b2[o] + w2[o,:] . act[b,:], then Eq. 6.  LDS: a[NS][lda] | z[NS][n_out]
-template <bool WBF16, bool TINY, int NS>
+template <bool WBF16, TailRow ROW, int NS>
 __global__ __launch_bounds__(TAIL_THREADS) void head_bins_kernel(const float *__restrict__ act_part, int nks, int B,
                                                                  const float *__restrict__ b1, int d_h, int n_out,
                                                                  const void *__restrict__ w2,
@@ -569,7 +570,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void head_bins_kernel(const float *__
                                                                  float *__restrict__ pred, float *__restrict__ p_hat)
 {
     using W = std::conditional_t<WBF16, unsigned short, float>;
-    __shared__ float4 join[NS < 4 ? TAIL_JOIN_FLOATS / 4 : 1];
+    __shared__ float4 join[tail_joins<ROW, NS>];
     extern __shared__ __align__(16) float a[];
     const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -577,8 +578,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void head_bins_kernel(const float *__
     // bin o < 64 belongs to lane o: its bias and centre are asked for now
     const int o_near = min(lane, n_out - 1);
     const float b2_near = b2 ? b2[o_near] : 0.f, center_near = centers[o_near];
-    output_layer<TINY, NS>((const W *)w2, n_out, d_h, a, lda, z,
-                           [&] { hidden_units<TINY, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, nullptr); });
+    output_layer<ROW, NS>((const W *)w2, n_out, d_h, a, lda, z,
+                          [&] { hidden_units<ROW, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, nullptr); });
     __syncthreads();
     const int b = b0 + wave;
     if (wave >= NS || b >= B)
@@ -734,21 +735,21 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
     return hipGetLastError();
 }
 
-template <bool WBF16, bool TINY, int NS>
+template <bool WBF16, TailRow ROW, int NS>
 static hipError_t launch_layer2(const HeadArgs &a, int nks, size_t lds, hipStream_t st)
 {
     static DeviceMask raised_scalar{0}, raised_bins{0};
     const dim3 grid((a.B - 1) / NS + 1), block(TAIL_THREADS);
     hipError_t e;
     if (a.n_out == 1) {
-        e = raise_dynamic_lds_limit((const void *)head_scalar_kernel<WBF16, TINY, NS>, (int)TAIL_LDS_LIMIT, raised_scalar);
+        e = raise_dynamic_lds_limit((const void *)head_scalar_kernel<WBF16, ROW, NS>, (int)TAIL_LDS_LIMIT, raised_scalar);
         if (e == hipSuccess)
-            hipLaunchKernelGGL((head_scalar_kernel<WBF16, TINY, NS>), grid, block, NS * lds, st, a.act, nks, a.B, a.b1, a.d_h,
+            hipLaunchKernelGGL((head_scalar_kernel<WBF16, ROW, NS>), grid, block, NS * lds, st, a.act, nks, a.B, a.b1, a.d_h,
                                a.w2, a.b2, a.pred);
     } else {
-        e = raise_dynamic_lds_limit((const void *)head_bins_kernel<WBF16, TINY, NS>, (int)TAIL_LDS_LIMIT, raised_bins);
+        e = raise_dynamic_lds_limit((const void *)head_bins_kernel<WBF16, ROW, NS>, (int)TAIL_LDS_LIMIT, raised_bins);
         if (e == hipSuccess)
-            hipLaunchKernelGGL((head_bins_kernel<WBF16, TINY, NS>), grid, block, NS * lds, st, a.act, nks, a.B, a.b1, a.d_h,
+            hipLaunchKernelGGL((head_bins_kernel<WBF16, ROW, NS>), grid, block, NS * lds, st, a.act, nks, a.B, a.b1, a.d_h,
                                a.n_out, a.w2, a.b2, a.bin_centers, a.pred, a.p_hat);
     }
     return e == hipSuccess ? hipGetLastError() : e;
@@ -757,11 +758,9 @@ static hipError_t launch_layer2(const HeadArgs &a, int nks, size_t lds, hipStrea
 template <bool WBF16>
 static hipError_t launch_layer2(const HeadArgs &a, int nks, size_t lds, hipStream_t st)
 {
-    if (a.d_h < 4)
-        return launch_layer2<WBF16, true, 1>(a, nks, lds, st);
-    const int ns = tail_sequences(a.B, lds);
-    return ns == 4 ? launch_layer2<WBF16, false, 4>(a, nks, lds, st)
-           : ns == 2 ? launch_layer2<WBF16, false, 2>(a, nks, lds, st) : launch_layer2<WBF16, false, 1>(a, nks, lds, st);
+    return tail_launch(a.d_h, tail_sequences(a.B, lds), [&](auto row, auto ns) {
+        return launch_layer2<WBF16, decltype(row)::value, decltype(ns)::value>(a, nks, lds, st);
+    });
 }
 
 hipError_t head_forward(const HeadArgs &a, hipStream_t st)

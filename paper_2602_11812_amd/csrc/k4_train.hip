@@ -42,10 +42,10 @@ __device__ __forceinline__ void adamw(const Adam &h, float g, float &w, float &m
 }
 
 // ---- 2. the samples, NS per workgroup (head_tail.h) ---------------------------------------
-// TINY: d_h < 4.  LDS: a[NS][lda] | z[NS][K] | dz[NS][K]
+// LDS: a[NS][lda] | z[NS][K] | dz[NS][K]
 constexpr int DACT_ROWS = 20;  // rows of W2 in flight per thread
 
-template <bool TINY, int NS>
+template <TailRow ROW, int NS>
 __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     const float *__restrict__ act_part, int nks, int B, int d_h, int K, const float *__restrict__ b1,
     const float *__restrict__ w2, const float *__restrict__ b2, const float *__restrict__ centers,
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     float lambda, float *__restrict__ act, float *__restrict__ dact, float *__restrict__ dz_out,
     float *__restrict__ loss_part)
 {
-    __shared__ float4 join[NS < 4 ? TAIL_JOIN_FLOATS / 4 : 1];
+    __shared__ float4 join[tail_joins<ROW, NS>];
     extern __shared__ __align__(16) float a[];
     const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
     float *z = a + NS * lda;
@@ -64,8 +64,8 @@ __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     const int b = min(b0 + min(wave, NS - 1), B - 1);
     const int o_near = min(lane, K - 1), bin_b = bin[b], steps_b = steps ? steps[b] : 0;
     const float y_b = y[b], b2_near = b2[o_near], center_near = centers[o_near];
-    output_layer<TINY, NS>(w2, K, d_h, a, lda, z,
-                           [&] { hidden_units<TINY, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, act); });
+    output_layer<ROW, NS>(w2, K, d_h, a, lda, z,
+                          [&] { hidden_units<ROW, NS>(act_part, nks, B, b0, d_h, b1, a, lda, join, act); });
     // ... and before the softmax the first rows of this thread's column of W2
     float w[DACT_ROWS];
     auto load_rows = [&](int o0, int j) {
@@ -76,7 +76,12 @@ __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
             p += o0 + o + 1 < K ? d_h : 0;  // past the end: a valid row, not used
         }
     };
-    load_rows(0, min(tid, d_h - 1));
+    // (wide: a thread's columns tid, tid + 1024, ... of all samples; narrow: a group of 256 threads for each sample)
+    constexpr bool NARROW = ROW != TAIL_WIDE;
+    const int j0 = NARROW ? tid % TAIL_NARROW_COLS : tid, n0 = NARROW ? tid / TAIL_NARROW_COLS : 0;
+    const bool busy = !NARROW || n0 < NS;  // the same for a wave
+    if (busy)
+        load_rows(0, min(j0, d_h - 1));
     __syncthreads();
     if (wave < NS) {
         const bool kept = b0 + wave < B;
@@ -131,24 +136,27 @@ __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     }
     __syncthreads();
     // d loss / d pre-activation = (W2^T dz) where the unit is active
+    if (!busy)
+        return;
+    constexpr int PER = NARROW ? 1 : NS;  // samples of a thread
 #pragma unroll 1
-    for (int j = tid; j < d_h; j += TAIL_THREADS) {
-        float s[NS] = {};
+    for (int j = j0; j < d_h; j += TAIL_THREADS) {
+        float s[PER] = {};
 #pragma unroll 1
         for (int o0 = 0; o0 < K; o0 += DACT_ROWS) {
-            if (j != tid || o0 > 0)
+            if (j != j0 || o0 > 0)
                 load_rows(o0, j);
 #pragma unroll
             for (int o = 0; o < DACT_ROWS; ++o)
                 if (o0 + o < K)
 #pragma unroll
-                    for (int n = 0; n < NS; ++n)
-                        s[n] = fmaf(dz[n * K + o0 + o], w[o], s[n]);
+                    for (int n = 0; n < PER; ++n)
+                        s[n] = fmaf(dz[(n0 + n) * K + o0 + o], w[o], s[n]);
         }
 #pragma unroll
-        for (int n = 0; n < NS; ++n)
-            if (b0 + n < B)
-                dact[(long)(b0 + n) * d_h + j] = a[n * lda + hidden_place(j, d_h)] > 0.f ? s[n] : 0.f;
+        for (int n = 0; n < PER; ++n)
+            if (b0 + n0 + n < B)
+                dact[(long)(b0 + n0 + n) * d_h + j] = a[(n0 + n) * lda + hidden_place(j, d_h)] > 0.f ? s[n] : 0.f;
     }
 }
 
@@ -590,14 +598,14 @@ __global__ __launch_bounds__(256, SPLIT ? 2 : 1) void train_update_kernel(Update
 
 }  // namespace
 
-template <bool TINY, int NS>
+template <TailRow ROW, int NS>
 static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStream_t st)
 {
     static DeviceMask raised{0};
-    hipError_t e = raise_dynamic_lds_limit((const void *)train_sample_kernel<TINY, NS>, (int)TAIL_LDS_LIMIT, raised);
+    hipError_t e = raise_dynamic_lds_limit((const void *)train_sample_kernel<ROW, NS>, (int)TAIL_LDS_LIMIT, raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((train_sample_kernel<TINY, NS>), dim3((a.B - 1) / NS + 1), dim3(TAIL_THREADS), NS * lds, st, a.act_part,
+    hipLaunchKernelGGL((train_sample_kernel<ROW, NS>), dim3((a.B - 1) / NS + 1), dim3(TAIL_THREADS), NS * lds, st, a.act_part,
                        nks, a.B, a.d_h, a.K, a.b1, a.w2, a.b2, a.centers, a.bin, a.y, a.steps, a.n_seqs, a.lambda, a.act,
                        a.dact, a.dz, a.loss_part);
     return hipGetLastError();
@@ -605,11 +613,9 @@ static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStr
 
 static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStream_t st)
 {
-    if (a.d_h < 4)
-        return launch_samples<true, 1>(a, nks, lds, st);
-    const int ns = tail_sequences(a.B, lds);
-    return ns == 4 ? launch_samples<false, 4>(a, nks, lds, st)
-           : ns == 2 ? launch_samples<false, 2>(a, nks, lds, st) : launch_samples<false, 1>(a, nks, lds, st);
+    return tail_launch(a.d_h, tail_sequences(a.B, lds), [&](auto row, auto ns) {
+        return launch_samples<decltype(row)::value, decltype(ns)::value>(a, nks, lds, st);
+    });
 }
 
 hipError_t head_train_step(const TrainArgs &a, hipStream_t st)

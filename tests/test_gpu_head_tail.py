@@ -1,5 +1,5 @@
 """The head behind layer 1 at its edges, scoring (layer 2) and training (the samples): rows of hidden units shorter than a
-vector, not a multiple of one, at and past a pass of 1024 columns; outputs at and past the rows that a round of waves takes;
+vector, not a multiple of one, at and past a pass of 256 and of 1024 columns; outputs at and past the rows that a round of waves takes;
 batches where workgroups take one, two or four sequences with some missing from the last; the longest rows.  Bars: the fp32
 bars of the head and training tests (2e-5 of the largest term; fp32 sums of d + d_h products); bf16 weights are exact in
 both."""
@@ -15,7 +15,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("B,d,d_h,n_out", [(3, 16, 1, 1), (2, 16, 3, 2), (5, 16, 4, 1), (257, 16, 5, 33), (515, 16, 1023, 1),
-                                           (514, 24, 1025, 16), (9, 520, 4099, 1), (258, 16, 2050, 65), (2, 16, 16383, 1024)])
+                                           (514, 24, 1025, 16), (9, 520, 4099, 1), (258, 16, 2050, 65), (2, 16, 16383, 1024),
+                                           (515, 16, 2, 1), (259, 16, 3, 33), (65, 2048, 253, 17), (258, 16, 256, 1), (517, 16, 255, 70),
+                                           (3, 520, 257, 1)])
 def test_scoring(gpu, B, d, d_h, n_out, bf16):  # noqa: F811
     import torch
     rng = np.random.default_rng(9000 + B + d_h)
@@ -37,7 +39,8 @@ def test_scoring(gpu, B, d, d_h, n_out, bf16):  # noqa: F811
     sc.close()
 
 
-@pytest.mark.parametrize("B,d,d_h,K", [(2, 12, 1, 3), (3, 12, 3, 33), (258, 12, 1027, 21), (514, 12, 6, 40), (5, 12, 2049, 65)])
+@pytest.mark.parametrize("B,d,d_h,K", [(2, 12, 1, 3), (3, 12, 3, 33), (258, 12, 1027, 21), (514, 12, 6, 40), (5, 12, 2049, 65),
+                                       (515, 12, 2, 9), (259, 12, 255, 33), (70, 1024, 256, 21), (601, 12, 253, 90), (2, 12, 257, 5)])
 def test_training(gpu, B, d, d_h, K):  # noqa: F811
     _run_steps(gpu, wl.make_train(9200 + B, B=B, d=d, d_h=d_h, K=K), 1)
 
