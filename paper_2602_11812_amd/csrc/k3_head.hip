@@ -3,9 +3,9 @@
 //
 // Layer 1 is a small [B x d] . [d x d_h] contraction kept entirely in fp32 (the pooled
 // vector is never re-rounded), on the fp32 matrix instructions where the weights are fp32 and the batch is more
-// than a handful, and as products of bf16 pieces where it is more than 64.  The contraction is split along d so that several hundred workgroups exist even for one
-// small batch; the splits leave partial pre-activations that layer 2 adds in a fixed order
-// (bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode: head_tail.h.
+// than a handful, and as products of bf16 pieces where it is more than 64 and the contraction not small.  It is split
+// along d so that several hundred workgroups exist even for one small batch; the splits leave partial pre-activations that
+// layer 2 adds in a fixed order (bit-reproducible) before bias and ReLU.  Layer 2 and the K-bin decode: head_tail.h.
 //
 // With bf16 weights and d a multiple of 8, layer 1 runs on the bf16 matrix cores without rounding the pooled vector: an
 // fp32 value is the exact sum of three bf16 values, a bf16 x bf16 product is exact in fp32, so three MFMAs per weight fragment
@@ -201,15 +201,15 @@ __global__ __launch_bounds__(256) void head_layer1_skinny_kernel(const float *__
         act_part[((long)blockIdx.y * B + b) * d_h + j] = acc[0];
 }
 
-// Layer 1, fp32 weights, 17 to F32_MAX_SEQS sequences: fp32 matrix instructions (16x16x4, fp32 operands and accumulators: the
+// Layer 1, fp32 weights, 17 to F32_MAX_SEQS sequences and small contractions of more (f32_serves): fp32 matrix instructions (16x16x4, fp32 operands and accumulators: the
 // precision of an FMA chain).  Bound: latency of the few chunks that a slice has.
 // Workgroup = 4 waves (2 x 2), FJ = 128 head rows x 32 NS sequences; wave = 64 x 16 NS = 4 x NS tiles, weights as the
 // row operand.  K is staged 16 elements at a time as 64-byte rows, 16-byte chunks XOR-ed with swizzle key (r >> 1) & 3:
 // lane l reads chunk l / 16 of row l % 16, i.e. four neighbouring K elements that feed four MFMAs (an MFMA then
 // contracts elements s, 4 + s, 8 + s, 12 + s of the sixteen: the order inside a sum, the same for both operands).  The
 // next chunk's global loads are in flight during the current one's MFMAs; two LDS buffers.
-// (On bf16 pieces, below, whose pipeline takes longer to fill: whole training steps with 32 and 64 samples 38.3 -> 41.0 us and
-// 45.8 -> 47.0; 71 samples, d = 4040 52.6 -> 51.1.)
+// (On bf16 pieces, below, whose pipeline takes longer to fill: whole training steps with 32 and 64 samples, d = 4096, d_h = 1024 38.3 ->
+// 41.0 us and 45.8 -> 47.0; 71 samples, d = 4040 52.6 -> 51.1.)
 constexpr int FJ = 128, FK = 16;
 constexpr int F32_WORKGROUPS = 512;  // workgroups asked for by splitting along d
 constexpr int F32_MAX_SEQS = 64;
@@ -622,6 +622,19 @@ static bool skinny_serves(int d, int32_t B, int wdtype)
 // training steps at batch 1024 199.7 us against 199.4, at d = 1024, d_h = 300, batch 256 39.1 against 34.6.)
 static int f32_tile_seqs(int32_t B) { return B > 32 ? 64 : 32; }
 
+// More sequences: from F32_MAX_PRODUCTS on, the pieces.  They take 5.6 us at the least where the fp32 kernel, in thinner slices, takes
+// 4.5.  Both at 121 sizes, 65 to 1024 sequences, d = 256 to 2048, d_h = 64 to 1024, fp32 instructions / pieces (us):
+//   2^21 to 2^23 products   4.5 to 5.2 / 5.6 to 6.3           3 2^23   5.8 to 7.3 / 6.1 to 6.9
+//   2^24                    4.7 to 6.0 / 5.7 to 6.5           2^25     5.6 to 8.1 / 6.2 to 7.4
+//   3 2^24                  7.2 to 10.6 / 6.6 to 7.4          2^26     6.6 to 16.7 / 6.7 to 7.9
+// Counted in whole tiles of 64 x 64, of which the instructions take all, and so that the number of planes follows the number
+// of tiles of sequences alone, on which its bound rests.
+constexpr long F32_MAX_PRODUCTS = 1L << 24;
+static bool f32_serves(int d, int d_h, int32_t B)
+{
+    return B <= F32_MAX_SEQS || (long)((B + TN - 1) / TN) * ((d_h + TM - 1) / TM) <= F32_MAX_PRODUCTS / (TM * TN) / d;
+}
+
 // Slices of layer 1 on bf16 pieces, fp32 weights, n of them asked for.  Tiles of 128 columns run one to a compute unit: from n down
 // to half of it, the number whose rounds take the fewest steps (one more for a round's start), the smaller of two (planes).
 // 512 sequences, d = 5120, d_h = 1280: 320 tiles in two rounds 71.6 us, 240 in one 43; 1017 115 -> 77; 300, d = 4096, d_h = 1024 36 -> 25.
@@ -658,7 +671,7 @@ int head_k_splits(int d, int d_h, int32_t B, int wdtype)
         const long ftiles = (long)((d_h + FJ - 1) / FJ) * ((B + f32_tile_seqs(B) - 1) / f32_tile_seqs(B));
         const long fwant = ftiles > 0 ? (F32_WORKGROUPS + ftiles - 1) / ftiles : 1;
         n = n > fwant ? fwant : n;
-        if (B > F32_MAX_SEQS)
+        if (!f32_serves(d, d_h, B))
             n = split_slices((int)(n > (d + 63) / 64 ? (d + 63) / 64 : n), d, d_h, B);  // a slice of at least two K steps
     }
     return n < 1 ? 1 : (int)n;
@@ -696,7 +709,7 @@ hipError_t head_layer1(const float *x, const int32_t *slot, int32_t B, int d, in
         return hipGetLastError();
     }
     if (wdtype == DT_F32) {
-        const bool small = B <= F32_MAX_SEQS;
+        const bool small = f32_serves(d, d_h, B);
         const int kstep = small ? FK : SplitTile<2, 4>::STEP;
         const int kchunk_f = ((d + nks - 1) / nks + kstep - 1) / kstep * kstep;
         const bool wide = !small && kchunk_f >= SPLIT_WIDE_STEPS * kstep;

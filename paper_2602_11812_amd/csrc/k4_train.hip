@@ -2,8 +2,8 @@
 // soft labels of Eq. 5, the joint loss of Eq. 7, the per-sequence step average of Eq. 9
 // (as a per-sample weight), the backward pass through the head only, and AdamW.
 //
-// Master weights, moments, activations and sums are fp32.  For large batches (layer 1 from 65 samples on, W1's gradient from
-// 192 on) fp32 products are formed from bf16 pieces, six of the nine of a pair; what is left out is 2^-24 of a product at most
+// Master weights, moments, activations and sums are fp32.  For large batches (layer 1 from 65 samples and 2^24 products on, W1's
+// gradient from 192 samples on) fp32 products are formed from bf16 pieces, six of the nine of a pair; what is left out is 2^-24 of a product at most
 // (split_mfma.h).  Three launches:
 //   1. layer 1 forward     partial pre-activations, split along d   (shared with scoring)
 //   2. per-sample kernel   ReLU, logits, softmax, expected value, soft label, the two loss

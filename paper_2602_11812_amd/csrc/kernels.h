@@ -132,8 +132,9 @@ struct HeadArgs {
 };
 // Number of partial pre-activation planes layer 1 leaves: it is split along d so that the chip is filled whatever the
 // batch (a small batch gets many thin slices): into about 512 64 x 64 tiles' worth with bf16 weights, up to 512
-// workgroups of larger tiles (at least two K steps of 32 each for more than 64 sequences, and as many as fill the compute units) with fp32 weights.  At most sixteen sequences on fp32 weights are served by a kernel of
-// its own that leaves one plane per 512 elements of d.
+// workgroups of larger tiles with fp32 weights (where they are read by their pieces, at least two K steps of 32 each and as
+// many as fill the compute units).  At most sixteen sequences on fp32 weights are served by a kernel of its own that leaves one
+// plane per 512 elements of d.
 int head_k_splits(int d, int d_h, int32_t B, int wdtype);
 // floats of partial planes sufficient for every batch of at most B sequences
 size_t head_act_floats_bound(int d, int d_h, int32_t B, int wdtype);

@@ -1,5 +1,5 @@
-"""fp32 products as bf16 pieces in the head: layer 1 of more than 64 sequences (tiles of 64 and of 128 columns) and W1's
-gradient from 192 samples on.  A step each at the edges of their tiles against the fp64 oracle, to the bars of the fp32
+"""fp32 products as bf16 pieces in the head: layer 1 of more than 64 sequences (tiles of 64 and of 128 columns; up to 2^24 products,
+counted in tiles of 64 x 64, the fp32 instructions) and W1's gradient from 192 samples on.  A step each at the edges of their tiles against the fp64 oracle, to the bars of the fp32
 training tests: batches one past and one short of a tile, rows of W1 off the 128-row tile, slices of d that end inside a K
 step of 32, samples that end inside one.  Sums of a single product, which show every piece product; operands and results that
 are not finite."""
@@ -15,18 +15,20 @@ pytestmark = pytest.mark.gpu
 
 
 # layer 1 in tiles of 128 columns (slices of 288) and the gradient; the same with tiles of 64 and one sample past a K step;
-# a single K step, two, and columns of W1 that end off every tile
+# a single K step, two, and columns of W1 that end off every tile; the fp32 instructions with a single slice and at their last size,
+# pieces at the next, with two K steps, with slices that end inside one
 @pytest.mark.parametrize("B,d,d_h,K", [(449, 1028, 2044, 5), (193, 4100, 136, 3), (66, 36, 260, 2), (127, 68, 128, 20),
-                                       (223, 2052, 516, 9)])
+                                       (223, 2052, 516, 9), (128, 512, 256, 20), (128, 512, 257, 3), (70, 36, 4100, 2),
+                                       (65, 520, 516, 4)])
 def test_one_step_at_tile_edges(gpu, B, d, d_h, K):  # noqa: F811
     _run_steps(gpu, wl.make_train(4200 + B, B=B, d=d, d_h=d_h, K=K), 1)
 
 
-def test_infinite_feature_stays_in_its_sequence(gpu):  # noqa: F811
+@pytest.mark.parametrize("B,d,d_h", [(130, 64, 70), (130, 1028, 129)])
+def test_infinite_feature_stays_in_its_sequence(gpu, B, d, d_h):  # noqa: F811
     """An infinite pooled feature makes its own sequence's prediction non-finite and leaves the others' bits alone."""
     import torch
     rng = np.random.default_rng(8200)
-    B, d, d_h = 130, 64, 70
     f32 = lambda *s, std=1.0: (std * rng.standard_normal(s)).astype(np.float32)
     td = gpu.to_device
     sc = gpu.Scorer(td(f32(300, d, std=d ** -0.5)), gpu.make_head(td(f32(d_h, d)), td(f32(1, d_h)), td(f32(d_h)), td(f32(1))))
@@ -43,9 +45,10 @@ def test_infinite_feature_stays_in_its_sequence(gpu):  # noqa: F811
     sc.close()
 
 
-# The fp32 matrix instructions (64), pieces in tiles of 64 columns, in tiles of 128, and a slice that ends inside a step of 32;
-# bf16 weights.
+# The fp32 matrix instructions; pieces in tiles of 128 columns, in tiles of 64, and a slice that ends inside a step of 32; bf16
+# weights.
 @pytest.mark.parametrize("B,d,d_h,bf16", [(64, 64, 70, False), (65, 64, 70, False), (130, 36, 129, False), (449, 1028, 2044, False),
+                                          (129, 512, 192, False), (65, 520, 516, False), (70, 36, 4100, False),
                                           (40, 40, 17, True), (129, 264, 130, True)])
 def test_operands_that_are_not_finite(gpu, B, d, d_h, bf16):  # noqa: F811
     """An infinite weight or feature gives what IEEE arithmetic gives, whatever the batch size and however few bits the other
@@ -86,7 +89,7 @@ def test_operands_that_are_not_finite(gpu, B, d, d_h, bf16):  # noqa: F811
         assert (np.abs(got[ok] - want[ok]) <= 2e-5 * (1.0 + np.abs(want[ok]))).all(), (place, value)
 
 
-@pytest.mark.parametrize("B,d_h", [(66, 260), (257, 516)])
+@pytest.mark.parametrize("B,d_h", [(66, 260), (257, 516), (70, 4100)])
 def test_diverged_head_shows_in_the_loss(gpu, B, d_h):  # noqa: F811
     ts = wl.make_train(4700 + B, B=B, d=36, d_h=d_h, K=3)
     ts.w1[5, 7] = np.inf
@@ -127,8 +130,9 @@ def _full(rng, *shape):
 ONE_PRODUCT = 2.0 ** -22
 
 
-# tiles of 64 columns; of 128; bf16 weights
-@pytest.mark.parametrize("B,d,d_h,bf16", [(65, 64, 260, False), (130, 520, 129, False), (449, 1028, 2044, False),
+# the fp32 instructions; pieces in tiles of 64 columns; of 128; bf16 weights
+@pytest.mark.parametrize("B,d,d_h,bf16", [(65, 64, 260, False), (130, 520, 129, False), (65, 520, 516, False), (70, 36, 4100, False),
+                                          (449, 1028, 2044, False),
                                           (66, 264, 130, True)])
 def test_single_products_of_layer_1(gpu, B, d, d_h, bf16):  # noqa: F811
     import torch
