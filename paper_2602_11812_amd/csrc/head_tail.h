@@ -86,10 +86,12 @@ __device__ __forceinline__ float chunk_dot(const Q &w, const RowChunk<TINY> &c, 
     return fmaf(c.keep[3] ? widen(w[3]) : 0.f, v.w, s);
 }
 
-// hidden units of NS sequences from b0 on: ReLU(sum of the planes + bias) into a[NS][lda] (LDS) and, if `copy` is
-// given, into copy[B][d_h].  `join`: tail_joins<ROW, NS> elements of LDS.  Ends with a barrier.
+// what the groups of a workgroup that share a sequence's planes pass to the first of them (four columns a thread)
 template <TailRow ROW, int NS>
 constexpr int tail_joins = TAIL_THREADS > NS * TailPass<ROW>::GROUP ? TAIL_THREADS - NS * TailPass<ROW>::GROUP : 1;
+
+// hidden units of NS sequences from b0 on: ReLU(sum of the planes + bias) into a[NS][lda] (LDS) and, if `copy` is
+// given, into copy[B][d_h].  `join`: tail_joins<ROW, NS> elements of LDS.  Ends with a barrier.
 template <TailRow ROW, int NS>
 __device__ __forceinline__ void hidden_units(const float *__restrict__ act_part, int nks, int B, int b0, int d_h,
                                              const float *__restrict__ b1, float *a, int lda, float4 *join,
