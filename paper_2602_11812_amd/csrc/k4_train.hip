@@ -29,16 +29,29 @@ namespace {
 
 struct Adam {
     float lr, beta1, beta2, omb1, omb2, eps, wd, corr1, corr2;
+    float step, inv_corr2, decay;  // lr / corr1, 1 / corr2, lr wd
+    bool quick;                    // eps is at least QUICK_EPS
 };
 
-// decoupled weight decay: w <- w - lr wd w - lr mhat / (sqrt(vhat) + eps)
+// Decoupled weight decay: w <- w - lr wd w - lr mhat / (sqrt(vhat) + eps).
+// With the divisions and the square root rounded correctly this is 59 vector instructions, 13 as it is: the quotients by the
+// corrections are products, root and reciprocal the hardware's (within one unit in the last place each, of an update that is
+// lr of the weight).  The root flushes denormals, 1e-19 beside an eps of at least QUICK_EPS.  64 samples, d = 4096, d_h = 1024 42.9 -> 38.8 us a
+// step, 256 60.3 -> 56.9, 1024 127.5 -> 123.8; 16, the stream of W1 and its moments, 31.4 -> 31.0.
+constexpr float QUICK_EPS = 1e-12f;
 __device__ __forceinline__ void adamw(const Adam &h, float g, float &w, float &m, float &v)
 {
     m = h.beta1 * m + h.omb1 * g;
     v = h.beta2 * v + h.omb2 * g * g;
-    const float mhat = m / h.corr1;
-    const float vhat = v / h.corr2;
-    w = w - h.lr * h.wd * w - h.lr * mhat / (sqrtf(vhat) + h.eps);
+    if (__builtin_expect(h.quick, 1)) {
+        const float r = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(v * h.inv_corr2) + h.eps);
+        w = fmaf(-h.decay, w, w);
+        w = fmaf(-(h.step * m), r, w);
+    } else {
+        const float mhat = m / h.corr1;
+        const float vhat = v / h.corr2;
+        w = w - h.lr * h.wd * w - h.lr * mhat / (sqrtf(vhat) + h.eps);
+    }
 }
 
 // ---- 2. the samples, NS per workgroup (head_tail.h) ---------------------------------------
@@ -643,6 +656,10 @@ hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
     h.wd = a.weight_decay;
     h.corr1 = a.corr1;
     h.corr2 = a.corr2;
+    h.step = (float)((double)a.lr / (double)a.corr1);
+    h.inv_corr2 = (float)(1.0 / (double)a.corr2);
+    h.decay = (float)((double)a.lr * (double)a.weight_decay);
+    h.quick = a.eps >= QUICK_EPS;
     // the parameter updates come last: the forward and the backward pass above read the old W1 / W2
     UpdateArgs u;
     u.x = a.x, u.act = a.act, u.dact = a.dact, u.dz = a.dz, u.loss_part = a.loss_part;

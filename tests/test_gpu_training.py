@@ -280,3 +280,29 @@ def test_matrix_kernels_at_tile_edges(gpu, B, d, d_h, K):
 @pytest.mark.parametrize("B,d_h,K", [(127, 65, 4), (128, 64, 5), (129, 63, 7), (300, 128, 3)])
 def test_small_parameters_at_chunk_edges(gpu, B, d_h, K):
     _run_steps(gpu, wl.make_train(6000 + B, B=B, d=64, d_h=d_h, K=K), 1)
+
+
+@pytest.mark.parametrize("eps", [1e-8, 1.1e-12, 1e-12, 9e-13, 1e-20, 1e-38])
+def test_update_on_both_sides_of_the_quick_arithmetic(gpu, eps):
+    """AdamW's update around the smallest eps for which it is formed with the hardware's root and reciprocal; gradients over 24 decades, and
+    none at all (inactive units).  Against fp64 from the moments that the step left: the weight is rounded twice (2^-22 of it covers
+    both), the update ten times within one unit in the last place each (2^-20)."""
+    import torch
+    B, d, d_h, K = 8, 64, 32, 4
+    rng = np.random.default_rng(11)
+    x = (rng.standard_normal((B, d)) * 10.0 ** rng.uniform(-12, 12, (1, d))).astype(np.float32)
+    w1 = (rng.standard_normal((d_h, d)) * 1e-14).astype(np.float32)
+    b1 = np.where(np.arange(d_h) < 16, 5.0, -5.0).astype(np.float32)
+    w2, b2 = (rng.standard_normal((K, d_h)) * 0.1).astype(np.float32), np.zeros(K, np.float32)
+    td = gpu.to_device
+    tr = gpu.HeadTrainer(td(w1), td(b1), td(w2), td(b2), td(np.linspace(1, 4, K, dtype=np.float32)), lr=1e-2, weight_decay=0.1, eps=eps)
+    tr.step(td(x), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.ones(B, device="cuda"))
+    f = lambda t: t.cpu().numpy().astype(np.float64)
+    m, v, got = f(tr.m["w1"]), f(tr.v["w1"]), f(tr.params["w1"])
+    beta1, beta2, lr = (float(np.float32(t)) for t in (0.9, 0.999, 1e-2))
+    update = lr * m / (1 - beta1) / (np.sqrt(v / (1 - beta2)) + float(np.float32(eps)))
+    want = w1 - lr * float(np.float32(0.1)) * w1.astype(np.float64) - update
+    assert np.isfinite(got).all() and (m[16:] == 0).all() and (m[:16] != 0).all()
+    normal = (v == 0) | (v > 2.0 ** -126)  # a denormal second moment is known to its own step only
+    assert normal.mean() > 0.8
+    assert (np.abs(got - want) <= 2.0 ** -22 * np.abs(want) + 2.0 ** -20 * np.abs(update))[normal].all()
