@@ -711,6 +711,7 @@ namespace {
 
 struct TrainWorkspace {
     float *act_part, *act, *dact, *dz, *loss_part;
+    unsigned char *dact_pieces;
     size_t bytes;
 };
 
@@ -723,6 +724,7 @@ TrainWorkspace carve_train(void *base, int32_t B, int32_t d, int32_t d_h, int32_
     w.dact = cv.take<float>((size_t)B * (size_t)d_h);
     w.dz = cv.take<float>((size_t)B * (size_t)K);
     w.loss_part = cv.take<float>((size_t)B * 2);
+    w.dact_pieces = cv.take<unsigned char>(train_pieces_bytes(B, d, d_h));
     w.bytes = cv.off;
     return w;
 }
@@ -810,6 +812,7 @@ egtp_status egtp_head_train_step(const egtp_head_train *h, const float *x, const
     a.dact = w.dact;
     a.dz = w.dz;
     a.loss_part = w.loss_part;
+    a.dact_pieces = w.dact_pieces;
     return head_train_step(a, (hipStream_t)stream) == hipSuccess ? EGTP_OK : EGTP_ERR_HIP;
 }
 

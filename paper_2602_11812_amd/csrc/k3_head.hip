@@ -350,7 +350,7 @@ struct Layer1Source {
     static constexpr bool BF16 = sizeof(W) == 2;
     static constexpr int ROW_PIECES = BF16 ? 1 : 3, ROW_LOADS = BF16 ? S::FA : 2 * S::FA, COL_LOADS = 2 * S::SHARE,
                          COL_WRITES = 3 * S::SHARE;
-    static constexpr bool ROWS_TURN = S::FB == 4;
+    static constexpr bool ROWS_READY = false, ROWS_TURN = S::FB == 4;
     static constexpr int TURN_BYTES = 16 * S::STEP * sizeof(W);  // a fragment of rows as it lies in memory
     struct Rows {
         std::conditional_t<BF16, u32x4, float4> v[S::FA][BF16 ? 1 : 2];

@@ -3,11 +3,11 @@
 // (as a per-sample weight), the backward pass through the head only, and AdamW.
 //
 // Master weights, moments, activations and sums are fp32.  For large batches (layer 1 from 65 samples and 2^24 products on, W1's
-// gradient from 192 samples on) fp32 products are formed from bf16 pieces, six of the nine of a pair; what is left out is 2^-24 of a product at most
+// gradient from 160 or 256 samples on) fp32 products are formed from bf16 pieces, six of the nine of a pair; what is left out is 2^-24 of a product at most
 // (split_mfma.h).  Three launches:
 //   1. layer 1 forward     partial pre-activations, split along d   (shared with scoring)
 //   2. per-sample kernel   ReLU, logits, softmax, expected value, soft label, the two loss
-//                          terms, d loss / d logits and d loss / d pre-activation
+//                          terms, d loss / d logits and d loss / d pre-activation (for large batches in pieces, too)
 //   3. the updates, one grid of three kinds of workgroups that only need what 2. left behind:
 //      W1                  gradient tile [64 x 64] of  dact^T . x  accumulated over the batch in
 //                          registers and consumed by AdamW on the spot (128 x 64 for large
@@ -15,8 +15,8 @@
 //                          caller asks for a copy.  With the
 //                          paper's batch of 16 this part is a pure stream over W1 and its two
 //                          moments (read and written once each).
-//      small parameters    gradient of W2, b2 and b1, 64 columns a workgroup, reduced over the batch in a fixed
-//                          order and consumed by AdamW on the spot
+//      small parameters    gradient of W2, b2 and b1, reduced over the batch in a fixed order and consumed by
+//                          AdamW on the spot
 //      loss                fixed-order sum of the per-sample terms (the last workgroup)
 // No floating-point atomics anywhere: results are bit-reproducible.
 #include "head_tail.h"
@@ -36,8 +36,7 @@ struct Adam {
 // Decoupled weight decay: w <- w - lr wd w - lr mhat / (sqrt(vhat) + eps).
 // With the divisions and the square root rounded correctly this is 59 vector instructions, 13 as it is: the quotients by the
 // corrections are products, root and reciprocal the hardware's (within one unit in the last place each, of an update that is
-// lr of the weight).  The root flushes denormals, 1e-19 beside an eps of at least QUICK_EPS.  64 samples, d = 4096, d_h = 1024 42.9 -> 38.8 us a
-// step, 256 60.3 -> 56.9, 1024 127.5 -> 123.8; 16, the stream of W1 and its moments, 31.4 -> 31.0.
+// lr of the weight).  The root flushes denormals, 1e-19 beside an eps of at least QUICK_EPS.
 constexpr float QUICK_EPS = 1e-12f;
 __device__ __forceinline__ void adamw(const Adam &h, float g, float &w, float &m, float &v)
 {
@@ -54,21 +53,64 @@ __device__ __forceinline__ void adamw(const Adam &h, float g, float &w, float &m
     }
 }
 
+typedef SplitTile<2, 4> GradTile;  // of W1's gradient (part 4 below)
+// dact as it is multiplied: fragments of 16 rows j x 32 samples (1 KiB: lane l of a wave holds row l % 16, samples 8 (l / 16) .. + 8),
+// [step of 32 samples][fragment][piece], zeros past the batch and past d_h.
+constexpr int FRAGMENT_BYTES = 1024, FRAGMENT_ROWS = 16;
+__host__ __device__ __forceinline__ int dact_fragments(int d_h) { return (d_h + GradTile::ROWS - 1) / GradTile::ROWS * (GradTile::ROWS / FRAGMENT_ROWS); }
+__device__ __forceinline__ long fragment_at(long step, int fragments, int fragment, int piece)
+{
+    return ((step * fragments + fragment) * 3 + piece) * FRAGMENT_BYTES;
+}
+
+// row j of N neighbouring samples from b on (b a multiple of N)
+template <int N>
+__device__ __forceinline__ void store_pieces(const float (&v)[N], int b, int j, int fragments, unsigned char *__restrict__ pieces)
+{
+    typedef __attribute__((ext_vector_type(N > 1 ? N / 2 : 1))) unsigned Pairs;
+    Pairs p[3];
+#pragma unroll
+    for (int n = 0; n < N; n += 2) {
+        unsigned h, m, l;
+        split3_pair_nearest(v[n], n + 1 < N ? v[n + 1 < N ? n + 1 : 0] : 0.f, h, m, l);
+        p[0][n / 2] = h, p[1][n / 2] = m, p[2][n / 2] = l;
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        unsigned char *to = pieces + fragment_at(b / GradTile::STEP, fragments, j / FRAGMENT_ROWS, i) +
+                            (b % GradTile::STEP / 8 * FRAGMENT_ROWS + j % FRAGMENT_ROWS) * 16 + b % 8 * 2;
+        if constexpr (N > 1)
+            *(Pairs *)to = p[i];
+        else
+            *(unsigned short *)to = (unsigned short)p[i][0];
+    }
+}
+
 // ---- 2. the samples, NS per workgroup (head_tail.h) ---------------------------------------
 // LDS: a[NS][lda] | z[NS][K] | dz[NS][K]
 constexpr int DACT_ROWS = 20;  // rows of W2 in flight per thread
 
-template <TailRow ROW, int NS>
+template <TailRow ROW, int NS, bool PIECES>
 __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     const float *__restrict__ act_part, int nks, int B, int d_h, int K, const float *__restrict__ b1,
     const float *__restrict__ w2, const float *__restrict__ b2, const float *__restrict__ centers,
     const int32_t *__restrict__ bin, const float *__restrict__ y, const int32_t *__restrict__ steps, int n_seqs,
     float lambda, float *__restrict__ act, float *__restrict__ dact, float *__restrict__ dz_out,
-    float *__restrict__ loss_part)
+    float *__restrict__ loss_part, unsigned char *__restrict__ pieces)
 {
     __shared__ float4 join[tail_joins<ROW, NS>];
     extern __shared__ __align__(16) float a[];
-    const int b0 = blockIdx.x * NS, lda = tail_row(d_h);
+    // (with pieces, the workgroups that share their 16 bytes, eight samples', run on one XCD, i % 8, whose L2 puts the lines together:
+    // 256 samples, d_h = 1024: 12.8 us where each sample of the eight is another XCD's, 10.8; without pieces 9.8)
+    int b0 = blockIdx.x * NS;
+    if (PIECES) {
+        constexpr int SHARE = 8 / NS;
+        const int x = blockIdx.x & 7, i = blockIdx.x >> 3;
+        b0 = (i / SHARE * 8 + x) * 8 + i % SHARE * NS;
+        if (b0 >= (B + GradTile::STEP - 1) / GradTile::STEP * GradTile::STEP)
+            return;
+    }
+    const int lda = tail_row(d_h);
     float *z = a + NS * lda;
     float *dz = z + NS * K;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -152,13 +194,17 @@ __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
     if (!busy)
         return;
     constexpr int PER = NARROW ? 1 : NS;  // samples of a thread
+    // (with pieces: the zeros behind a row as well)
+    const int fragments = dact_fragments(d_h), end = PIECES ? fragments * FRAGMENT_ROWS : d_h;
 #pragma unroll 1
-    for (int j = j0; j < d_h; j += TAIL_THREADS) {
+    for (int j = j0; j < end; j += TAIL_THREADS) {
+        const bool unit = !PIECES || j < d_h;
+        const int at = PIECES ? min(j, d_h - 1) : j;
         float s[PER] = {};
 #pragma unroll 1
         for (int o0 = 0; o0 < K; o0 += DACT_ROWS) {
             if (j != j0 || o0 > 0)
-                load_rows(o0, j);
+                load_rows(o0, at);
 #pragma unroll
             for (int o = 0; o < DACT_ROWS; ++o)
                 if (o0 + o < K)
@@ -167,9 +213,14 @@ __global__ __launch_bounds__(TAIL_THREADS) void train_sample_kernel(
                         s[n] = fmaf(dz[(n0 + n) * K + o0 + o], w[o], s[n]);
         }
 #pragma unroll
-        for (int n = 0; n < PER; ++n)
-            if (b0 + n0 + n < B)
-                dact[(long)(b0 + n0 + n) * d_h + j] = a[(n0 + n) * lda + hidden_place(j, d_h)] > 0.f ? s[n] : 0.f;
+        for (int n = 0; n < PER; ++n) {
+            const bool in = unit && b0 + n0 + n < B;
+            s[n] = in && a[(n0 + n) * lda + hidden_place(at, d_h)] > 0.f ? s[n] : 0.f;
+            if (in)
+                dact[(long)(b0 + n0 + n) * d_h + j] = s[n];
+        }
+        if constexpr (PIECES)
+            store_pieces(s, b0 + n0, j, fragments, pieces);
     }
 }
 
@@ -202,18 +253,31 @@ __device__ void sum_loss(const float *__restrict__ loss_part, int B, float lambd
 }
 
 // ---- 3. W2, b2, b1: sums over the batch of columns of act, dz and dact ----------------------
-// Workgroup = 64 columns; wave q adds the samples b = q, q + 4, ... (each a coalesced load of 64 columns, SAMPLES_AHEAD in
-// flight: one sample after the other is a chain of cache latencies), then the four partial sums are joined in order.
-// These workgroups start when the first W1 tiles end and are the end of a large batch's launch: with eight samples in
-// flight and dz loaded beside each the whole step took 205.5 us at batch 1024, now 202.2; at batch 309, d = 2208, 55.8, 54.6.
+// Chains of cache latencies beside the tiles of W1: a workgroup's four waves share the samples, keep whole batches of loads in
+// flight and join their sums in a fixed order.  Beside W1's gradient on the fp32 instructions they use FMAs and few registers, so that
+// more workgroups of the W1 part, a stream there, stay on a compute unit; beside its gradient of bf16 pieces, which has the registers,
+// the fp32 matrix instructions, behind the tiles: 1024 samples, d = 4096, d_h = 1024, 20 bins, 98 workgroups on FMAs ahead of the tiles
+// took 20 us of a launch of 66, holding back as many tiles; 82 of them 14 us, beside the last tiles.
+struct Params {
+    float *w, *m, *v, *g;
+};
+
+__device__ __forceinline__ void update_one(const Adam &h, const Params &p, long e, float g)
+{
+    float w = p.w[e], m = p.m[e], v = p.v[e];
+    adamw(h, g, w, m, v);
+    p.w[e] = w;
+    p.m[e] = m;
+    p.v[e] = v;
+    if (p.g)
+        p.g[e] = g;
+}
+
+// Workgroup = 64 columns; wave q adds the samples b = q, q + 4, ... (each a coalesced load of 64 columns, SAMPLES_AHEAD in flight).
 // NO > 0: the column is weighted with dz[b][o0 .. o0 + NO - 1] (rows of W2's gradient; a load of act serves all of
 // them); NO = 0: a plain column sum (the biases).  Parameter (o, column) sits at base + o * ld + column.
 constexpr int W2_ROWS = 4;  // rows of W2 per workgroup
 constexpr int SAMPLES_AHEAD = 32;
-
-struct Params {
-    float *w, *m, *v, *g;
-};
 
 template <int NO>
 __device__ __forceinline__ void column_update(const float *__restrict__ mat, long ld, int n, int col0,
@@ -263,15 +327,111 @@ __device__ __forceinline__ void column_update(const float *__restrict__ mat, lon
 #pragma unroll
         for (int k = 1; k < 4; ++k)
             g += red[(k * NR + r) * 64 + lane];
-        const long e = NO > 0 ? (o0 + r) * ld + col : col;
-        float wv = p.w[e], mv = p.m[e], vv = p.v[e];
-        adamw(h, g, wv, mv, vv);
-        p.w[e] = wv;
-        p.m[e] = mv;
-        p.v[e] = vv;
-        if (p.g)
-            p.g[e] = g;
+        update_one(h, p, NO > 0 ? (o0 + r) * ld + col : col, g);
     }
+}
+
+// Beside the gradient of pieces.  W2: gradient[o][j] = sum over samples of dz[b][o] act[b][j], 32 rows o x 16 columns j a workgroup, on the fp32 matrix
+// instructions (16x16x4; a chain of FMAs' precision).  Wave q takes the samples 16 s + 4 q + 0 .. 3 of step s; lane l holds row and
+// column l % 16 of sample l / 16.  Rows past K and columns past d_h are others', computed and dropped.  `red`: 4 x 32 x 16 floats.
+constexpr int W2_TILE_ROWS = 32, W2_TILE_COLS = 16, W2_AHEAD = 16;
+
+__device__ __forceinline__ void w2_update(const float *__restrict__ act, const float *__restrict__ dz, int B, int d_h, int K, int col0,
+                                          int o0, const Adam &h, const Params &p, float *__restrict__ red)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4;
+    const int tid = threadIdx.x, l15 = tid & 15, kq = tid >> 4 & 3, q = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int sample = 4 * q + kq, steps = (B + 15) / 16;
+    const float *pa = act + (long)min(sample, B - 1) * d_h + min(col0 + l15, d_h - 1);
+    const float *pz = dz + (long)min(sample, B - 1) * K;
+    const int row[2] = {min(o0 + l15, K - 1), min(o0 + 16 + l15, K - 1)};
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    struct Batch {
+        float z[W2_AHEAD][2], a[W2_AHEAD];
+    } now, next;
+    auto load = [&](Batch &t, int s0) {
+#pragma unroll
+        for (int s = 0; s < W2_AHEAD; ++s) {
+            t.a[s] = *pa, t.z[s][0] = pz[row[0]], t.z[s][1] = pz[row[1]];
+            const bool more = 16 * (s0 + s + 1) + sample < B;  // past the end: the last sample, zeros of it
+            pa += more ? 16L * d_h : 0, pz += more ? 16L * K : 0;
+        }
+    };
+    load(now, 0);
+#pragma unroll 1
+    for (int s0 = 0; s0 < steps; s0 += W2_AHEAD) {
+        if (s0 + W2_AHEAD < steps)
+            load(next, s0 + W2_AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < W2_AHEAD; ++s) {
+            const bool in = 16 * (s0 + s) + sample < B;
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? now.z[s][i] : 0.f, in ? now.a[s] : 0.f, acc[i], 0, 0, 0);
+        }
+        now = next;
+    }
+    constexpr int TILE = W2_TILE_ROWS * W2_TILE_COLS;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            red[q * TILE + (16 * i + 4 * kq + e) * W2_TILE_COLS + l15] = acc[i][e];
+    __syncthreads();
+#pragma unroll
+    for (int e = tid; e < TILE; e += 256) {
+        const int o = o0 + e / W2_TILE_COLS, j = col0 + e % W2_TILE_COLS;
+        if (o >= K || j >= d_h)
+            continue;
+        const float g = ((red[e] + red[TILE + e]) + red[2 * TILE + e]) + red[3 * TILE + e];
+        update_one(h, p, (long)o * d_h + j, g);
+    }
+}
+
+// b1, b2: sums over the samples of columns of dact, dz: 64 columns (16 chunks of four, head_tail.h) a workgroup, lane l the samples
+// 16 s + l / 16 of every step.  `red`: 16 x 64 floats.
+constexpr int BIAS_COLS = 64, BIAS_AHEAD = 16;
+
+template <bool TINY>
+__device__ __forceinline__ void bias_update_of(const float *__restrict__ mat, int n, int col0, int B, const Adam &h, const Params &p,
+                                            float *__restrict__ red)
+{
+    const int tid = threadIdx.x, l15 = tid & 15, sub = tid >> 4;
+    const RowChunk<TINY> c(min(col0 / 4 + l15, (n - 1) / 4), n);  // chunks past the end are computed and dropped
+    float sum[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int s0 = sub; s0 < B; s0 += 16 * BIAS_AHEAD) {
+        ChunkOf<float> v[BIAS_AHEAD];
+#pragma unroll
+        for (int s = 0; s < BIAS_AHEAD; ++s)  // past the end: the last sample, not used
+            v[s] = load_chunk(mat + (long)min(s0 + 16 * s, B - 1) * n, c, n);
+#pragma unroll
+        for (int s = 0; s < BIAS_AHEAD; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                sum[e] += s0 + 16 * s < B ? v[s][e] : 0.f;
+    }
+    *(float4 *)(red + sub * BIAS_COLS + 4 * l15) = make_float4(sum[0], sum[1], sum[2], sum[3]);
+    __syncthreads();
+    const int j = col0 + tid;
+    if (tid >= BIAS_COLS || j >= n)
+        return;
+    const float *r = red + hidden_place(j, n) - col0;
+    float g = r[0];
+#pragma unroll
+    for (int k = 1; k < 16; ++k)
+        g += r[k * BIAS_COLS];
+    update_one(h, p, j, g);
+}
+
+__device__ __forceinline__ void bias_update(const float *__restrict__ mat, int n, int col0, int B, const Adam &h, const Params &p,
+                                            float *__restrict__ red)
+{
+    if (n < 4)
+        bias_update_of<true>(mat, n, col0, B, h, p, red);
+    else
+        bias_update_of<false>(mat, n, col0, B, h, p, red);
 }
 
 // ---- 4. W1: gradient tile in registers, AdamW in the epilogue -------------------------------
@@ -395,131 +555,111 @@ __device__ __forceinline__ void w1_update(int tile_k, int tile_j, const float *_
 }
 
 // The same for more samples: fp32 products as bf16 pieces (split_mfma.h).  Workgroup = 128 rows j x 64 columns k, a wave 32
-// rows of its own.  The contraction runs over the samples, the slow index of both operands, of which a fragment wants eight
-// in a lane: a lane loads two neighbouring j of eight samples and deals them to two fragments, so that row c of a wave's
-// fragment a is j = 2 c + a; of the columns it loads four neighbouring k of two samples, a pair of K elements for each of four
-// fragments, so that column c of fragment b is k = 4 c + b.  A lane ends up with four neighbouring k of a row j, one 16-byte
-// access each to W1 and the moments.
-// Two workgroups per compute unit; the workgroups of the small parameters, chains of cache latencies, start before the
-// tiles, which puts some tiles' parameter streams beside others' products (512 samples 92.7 -> 89.1 us a step).
-// Bound: the splitting beside the MFMAs, 49 us per 1024 samples at d = 4096, d_h = 1024, and about 30 us for the parameters.
-// 1024 samples: the launch 117 to 120 us on the fp32 matrix instructions, then 75 to 82; the way of loaded data back into
-// the compute unit was the busiest part of it (69 %), a quarter of what a load of one k per lane fetched was used.  With
-// four k per lane, a quarter of these loads: whole steps of 1024 samples 135.2 -> 127.4 us, 256 62.3 -> 58.4, 1024 at d = 5120,
-// d_h = 1280 213 -> 195.5; the launch alone, clocks warm, 65 (75 to 85 in a short run).  128 x 128 tiles: 85.  Rows by
-// 16-byte loads as well, turned in the LDS: no faster.
-typedef SplitTile<2, 4> GradTile;
-// From this many samples and tiles on.  Whole steps, us, fp32 instructions / pieces:
-//   512 tiles (d = 4096, d_h = 1024)   128 samples 55.2 / 56.4   160 66.8 / 64.0   192 70.5 / 67.1   256 72.9 / 67.4
-//   144 tiles (d = 1024, d_h = 1100)   192 samples 39.6 / 38.0   512 63.3 / 54.9   768 83.0 / 68.7
-//   128 tiles (d = 1024, d_h = 1024)   192 samples 32.0 / 34.2   384 44.5 / 44.8   512 46.7 / 45.9   768 64.4 / 61.7
-//    48 tiles (d = 1024, d_h = 384)    192 samples 25.0 / 27.5   512 38.6 / 39.0   1024 62.0 / 58.9
-// At up to 128 tiles, where half the compute units stay without one, the two meet at 400 to 500 samples, elsewhere
-// at about 150: the line is up to 7 % off on its corner, 128 tiles and fewer than 384 samples.
-constexpr int SPLIT_SAMPLES = 192, SPLIT_TILES = 128;
+// rows of its own, two workgroups per compute unit.  The contraction runs over the samples, the slow index of x, of which a fragment
+// wants eight in a lane: a lane loads four neighbouring k of two samples, a pair of K elements for each of four fragments, so that column c
+// of fragment b is k = 4 c + b, and ends up with four neighbouring k of a row j, one 16-byte access each to W1 and the moments.
+// dact comes as fragments of pieces from the samples' kernel: split here, by the 64 workgroups of d = 4096 that share a row, it was
+// 88 of a step's 147 vector instructions a wave, and an MFMA 16x16x32 leaves a SIMD's issue to two others only (8 of its 16 cycles, measured in
+// registers: with two vector instructions behind each MFMA a wave takes 16 cycles, with three 20, with six 32).
+// Bound: loads and the 6 x 2 d d_h products a sample beside each other (33000 cycles of a wave's loop of 48000 with its loads taken out),
+// at 2.0 GHz; then the stream of the parameters, 8 us.
+// Whole steps, us: 1024 samples, d = 4096, d_h = 1024 128.5 -> 121.8; 512 77.6 -> 75.4; d = 1024, d_h = 384, 1024 samples 60.8 -> 53.8.  Tiles of 128 x 128, one
+// workgroup to a compute unit: 116 -> 125.
+// From SPLIT_SAMPLES samples on where the tiles are more than SPLIT_TILES, half a round of the compute units, elsewhere from
+// SPLIT_SAMPLES_FEW_TILES.  Whole steps, us, fp32 instructions / pieces:
+//   512 tiles (d = 4096, d_h = 1024)   128 samples 45.1 / 46.6   160 54.8 / 53.8   192 59.1 / 56.8   384 78.5 / 65.7   1024 162 / 113
+//   144 tiles (d = 1024, d_h = 1100)   128 samples 35.6 / 35.7   160 37.5 / 36.6   256 43.4 / 39.7   512 62.3 / 51.8
+//   128 tiles (d = 1024, d_h = 1024)   192 samples 33.3 / 33.6   256 34.8 / 34.2   384 43.5 / 42.2   1024 67.6 / 58.8
+//   128 tiles (d = 2048, d_h = 512)    192 samples 32.6 / 33.6   256 36.2 / 35.5   384 43.6 / 42.2
+//    48 tiles (d = 1024, d_h = 384)    192 samples 25.4 / 26.1   256 28.2 / 28.4   384 36.0 / 35.9   1024 59.6 / 53.8
+//    16 tiles (d = 512, d_h = 256)     192 samples 22.4 / 22.7   256 24.3 / 24.2   384 30.2 / 28.7   1024 52.3 / 47.9
+constexpr int SPLIT_SAMPLES = 160, SPLIT_SAMPLES_FEW_TILES = 256, SPLIT_TILES = 128;
 
 struct GradSource {
-    static constexpr int ROW_PIECES = 3, ROW_LOADS = 8, COL_LOADS = 2, COL_WRITES = 12;
-    static constexpr bool ROWS_TURN = false;
-    struct Rows {
-        float2 v[8];
-    };
+    static constexpr int ROW_PIECES = 3, ROW_LOADS = 0, COL_LOADS = 2, COL_WRITES = 12;
+    static constexpr bool ROWS_READY = true, ROWS_TURN = false;
+    struct Rows {};
     struct Cols {
         float4 v[2];
     };
-    const float *dact, *x;
-    unsigned row_at, col_at;  // this lane's columns of the two operands and its first sample of a step, in bytes
-    long d_h, d;
-    int B, kq, wave, l15;
+    const unsigned char *pieces;  // this wave's first fragment
+    const float *x;
+    unsigned lane_at, col_at[2];  // this lane's bytes of a fragment; of the columns, its two samples of the wave's eight
+    long x_bytes, step_bytes, d;
+    int steps, wave;
 
-    // The last step (and those that are only asked for) takes the last 32 samples, of which the ones that an earlier step has
-    // count as zeros: no branch around a load, so that the loads in flight stay countable, and addresses are scalar but for
-    // row_at and col_at (a minimum and a 64-bit product per lane and load before: 66.2 -> 64.9 us at 1024 samples, d = 4096, d_h =
-    // 1024, which pays for most of what the small products' sums cost).
-    static_assert(SPLIT_SAMPLES >= GradTile::STEP, "a step's worth of samples");
-    __device__ __forceinline__ int first(int i) const { return min(i * GradTile::STEP, B - GradTile::STEP); }
-    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t from(const float *p)
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t from(const void *p, int bytes)
     {
-        return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, -1, 0x00020000);
+        return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000);
     }
-    __device__ __forceinline__ void load_rows(int i, int l, Rows &r) const
+    // (steps that are only asked for: the last one again)
+    __device__ __forceinline__ split_u32x4 load_rows(int i, int piece, int a) const
     {
-        r.v[l] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(from(dact + first(i) * d_h), row_at, l * (int)d_h * 4, 0));
+        return __builtin_bit_cast(split_u32x4, __builtin_amdgcn_raw_buffer_load_b128(from(pieces + min(i, steps - 1) * step_bytes, 6 * FRAGMENT_BYTES),
+                                                                                     lane_at, (a * 3 + piece) * FRAGMENT_BYTES, 0));
     }
+    // Samples past the batch lie past the end of x: the hardware makes zeros of them.
     __device__ __forceinline__ void load_cols(int i, int l, Cols &r) const
     {
-        r.v[l] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(from(x + (first(i) + 8 * wave) * d), col_at, l * (int)d * 16, 0));
+        const long at = (long)(i * GradTile::STEP + 8 * wave) * d * 4, left = x_bytes - at;
+        const int bytes = left < 0 ? 0 : (int)min(left, 0x7fffffffL);
+        r.v[l] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(from((const unsigned char *)x + at, bytes), col_at[l], 0, 0));
     }
-    __device__ __forceinline__ void clear_rows(int i, Rows &r) const
-    {
-        if ((i + 1) * GradTile::STEP <= B)
-            return;
-#pragma unroll
-        for (int l = 0; l < 8; ++l)
-            if (first(i) + 8 * kq + l < i * GradTile::STEP)
-                r.v[l] = make_float2(0.f, 0.f);
-    }
-    __device__ __forceinline__ void clear_cols(int i, Cols &r) const
-    {
-        if ((i + 1) * GradTile::STEP <= B)
-            return;
-#pragma unroll
-        for (int l = 0; l < 2; ++l)
-            if (first(i) + 8 * wave + 4 * l + kq < i * GradTile::STEP)
-                r.v[l] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    // K elements 2 g and 2 g + 1 of eight are samples g and g + 4: a pair is what a lane loads of a column
-    __device__ __forceinline__ float row_value(const Rows &r, int a, int e) const
-    {
-        const float2 v = r.v[e / 2 + e % 2 * 4];
-        return a == 0 ? v.x : v.y;
-    }
+    __device__ __forceinline__ void clear_rows(int, Rows &) const {}
+    __device__ __forceinline__ void clear_cols(int, Cols &) const {}
+    // a pair is what a lane loads of a column
     __device__ __forceinline__ float col_value(const Cols &r, int, int e) const { return (&r.v[e % 2].x)[e / 2]; }
     __device__ __forceinline__ void write_col(unsigned char *buf, const split_u32x4 (&part)[1][3], int n) const
     {
-        *(unsigned *)(buf + n % 3 * GradTile::PIECE + n / 3 * 1024 + (wave * 16 + l15) * 16 + kq * 4) = part[0][n % 3][n / 3];
+        const int lane = threadIdx.x & 63;
+        *(unsigned *)(buf + n % 3 * GradTile::PIECE + n / 3 * 1024 + (wave * 16 + (lane & 15)) * 16 + (lane >> 4) * 4) = part[0][n % 3][n / 3];
     }
     __device__ __forceinline__ int slot() const { return threadIdx.x & 63; }
 };
 
 __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const float *__restrict__ x,
-                                                const float *__restrict__ dact, int B, int d, int d_h, const Adam &h,
-                                                float *__restrict__ w1, float *__restrict__ m_w1, float *__restrict__ v_w1,
-                                                float *__restrict__ g_w1, unsigned char *__restrict__ lds)
+                                                const float *__restrict__ dact, const unsigned char *__restrict__ pieces, int B, int d,
+                                                int d_h, const Adam &h, float *__restrict__ w1, float *__restrict__ m_w1,
+                                                float *__restrict__ v_w1, float *__restrict__ g_w1, unsigned char *__restrict__ lds)
 {
     using S = GradTile;
     constexpr int FA = S::FA, FB = S::FB;
-    static_assert(FA == 2 && FB == 4 && S::SHARE == 1, "two neighbouring j, four neighbouring k to a lane");
+    static_assert(FB == 4 && S::SHARE == 1, "four neighbouring k to a lane");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int k0 = tile_k * S::COLS, j0 = tile_j * S::ROWS + 32 * wave;
+    const int k0 = tile_k * S::COLS, j0 = tile_j * S::ROWS + 16 * FA * wave;
 
-    // d_h and d are multiples of 4: rows and columns that do not exist are others', computed and dropped
+    // d is a multiple of 4: columns that do not exist are others', computed and dropped
+    const int steps = (B + S::STEP - 1) / S::STEP;
     GradSource src;
-    src.d_h = d_h, src.d = d, src.B = B, src.wave = wave;
-    src.l15 = tid & 15, src.kq = tid >> 4 & 3;
-    src.dact = dact, src.row_at = (unsigned)(8 * src.kq * d_h + min(j0 + 2 * src.l15, d_h - 2)) * 4;
-    src.x = x, src.col_at = (unsigned)(src.kq * d + min(k0 + 4 * src.l15, d - 4)) * 4;  // a wave stages eight samples
+    src.d = d, src.wave = wave, src.steps = steps, src.x = x, src.x_bytes = (long)B * d * 4;
+    src.step_bytes = fragment_at(1, dact_fragments(d_h), 0, 0);
+    src.pieces = pieces + fragment_at(0, 0, j0 / FRAGMENT_ROWS, 0), src.lane_at = (tid & 63) * 16;
+#pragma unroll
+    for (int l = 0; l < 2; ++l)
+        src.col_at[l] = (unsigned)((2 * (tid >> 4 & 3) + l) * d + min(k0 + 4 * (tid & 15), d - 4)) * 4;
     split_f32x4 acc[FA][FB];
 #pragma unroll
     for (int a = 0; a < FA; ++a)
 #pragma unroll
         for (int b = 0; b < FB; ++b)
             acc[a][b] = split_f32x4{0.f, 0.f, 0.f, 0.f};
-    const int steps = (B + S::STEP - 1) / S::STEP;
     __builtin_assume(steps >= SPLIT_SAMPLES / S::STEP);
     split_contract<S>(lds, steps, acc, src);
     int again = tid;  // the lane's place, not held over the contraction (two registers that it does not have)
     asm("" : "+v"(again));
     const int l15 = again & 15, kq = again >> 4 & 3;
-    const int j_at = min(j0 + 2 * l15, d_h - 2), k_at = min(k0 + 4 * l15, d - 4);
+    const int k_at = min(k0 + 4 * l15, d - 4);
     if (__builtin_expect(!all_finite(acc), 0))
         redo_not_finite(B, acc, [&](int i, float (&av)[FA][4], float (&bv)[FB][4]) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int b = 16 * i + 4 * kq + e, sample = min(b, B - 1);
-                const float2 dv = *(const float2 *)(dact + (long)sample * d_h + j_at);
                 const float4 xv = *(const float4 *)(x + (long)sample * d + k_at);
-                av[0][e] = b < B ? dv.x : 0.f, av[1][e] = b < B ? dv.y : 0.f;
+#pragma unroll
+                for (int a = 0; a < FA; ++a) {
+                    const float dv = dact[(long)sample * d_h + min(j0 + 16 * a + l15, d_h - 1)];
+                    av[a][e] = b < B ? dv : 0.f;
+                }
                 bv[0][e] = b < B ? xv.x : 0.f, bv[1][e] = b < B ? xv.y : 0.f;
                 bv[2][e] = b < B ? xv.z : 0.f, bv[3][e] = b < B ? xv.w : 0.f;
             }
@@ -534,7 +674,7 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             // rows that do not exist: a valid place, not used
-            const long at = (long)min(j0 + 2 * (4 * kq + i) + a, d_h - 1) * d + k;
+            const long at = (long)min(j0 + 16 * a + 4 * kq + i, d_h - 1) * d + k;
             w[a][i] = *(const float4 *)(w1 + at);
             m[a][i] = *(const float4 *)(m_w1 + at);
             v[a][i] = *(const float4 *)(v_w1 + at);
@@ -543,7 +683,7 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
     for (int a = 0; a < FA; ++a)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int j = j0 + 2 * (4 * kq + i) + a;
+            const int j = j0 + 16 * a + 4 * kq + i;
             if (j >= d_h)
                 continue;
             const long at = (long)j * d + k;
@@ -565,9 +705,10 @@ __device__ __forceinline__ void w1_update_split(int tile_k, int tile_j, const fl
 // memory traffic of the step), then the workgroups of the small parameters, the loss last.
 struct UpdateArgs {
     const float *x, *act, *dact, *dz, *loss_part;
+    const unsigned char *pieces;  // of dact, for the tiles of bf16 pieces
     int B, d, d_h, K;
     int tiles_k, tiles_w1;
-    int cols_h, blocks_w2, blocks_b2;  // 64-column blocks of d_h; workgroups of W2 and of b2 (b1 has cols_h)
+    int cols_w2, blocks_w2, blocks_b1, blocks_b2;  // tiles of a row of W2; workgroups of W2 and of the biases
     float lambda;
     Params w1, w2, b2, b1;
     float *loss;
@@ -578,57 +719,79 @@ __global__ __launch_bounds__(256, SPLIT ? 2 : 1) void train_update_kernel(Update
 {
     constexpr int LDS_FLOATS = SPLIT ? GradTile::LDS_BYTES / 4 : 2 * GRAD_STAGE_FLOATS;
     __shared__ __align__(16) float lds[LDS_FLOATS];
-    static_assert(LDS_FLOATS >= 4 * W2_ROWS * 64, "LDS of the small-parameter part");
-    const int small = (int)gridDim.x - a.tiles_w1;  // the other workgroups: behind the tiles, or (split) before them
+    static_assert(LDS_FLOATS >= 4 * W2_ROWS * 64 && LDS_FLOATS >= 4 * W2_TILE_ROWS * W2_TILE_COLS && LDS_FLOATS >= 16 * BIAS_COLS,
+                  "LDS of the small-parameter part");
     int id = blockIdx.x;
-    if (SPLIT)
-        id = id < small ? a.tiles_w1 + id : id - small;
     if (id < a.tiles_w1) {
         const int tk = id % a.tiles_k, tj = id / a.tiles_k;
         if constexpr (SPLIT)
-            w1_update_split(tk, tj, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, (unsigned char *)lds);
+            w1_update_split(tk, tj, a.x, a.dact, a.pieces, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, (unsigned char *)lds);
         else
             w1_update(tk, tj, a.x, a.dact, a.B, a.d, a.d_h, h, a.w1.w, a.w1.m, a.w1.v, a.w1.g, lds);
         return;
     }
     id -= a.tiles_w1;
     if (id < a.blocks_w2) {
-        column_update<W2_ROWS>(a.act, a.d_h, a.d_h, (id % a.cols_h) * 64, a.dz, a.K, (id / a.cols_h) * W2_ROWS, a.B, h, a.w2,
-                               lds);
+        if constexpr (SPLIT)
+            w2_update(a.act, a.dz, a.B, a.d_h, a.K, id % a.cols_w2 * W2_TILE_COLS, id / a.cols_w2 * W2_TILE_ROWS, h, a.w2, lds);
+        else
+            column_update<W2_ROWS>(a.act, a.d_h, a.d_h, (id % a.cols_w2) * 64, a.dz, a.K, (id / a.cols_w2) * W2_ROWS, a.B, h, a.w2, lds);
         return;
     }
     id -= a.blocks_w2;
-    if (id < a.cols_h) {
-        column_update<0>(a.dact, a.d_h, a.d_h, id * 64, nullptr, 0, 0, a.B, h, a.b1, lds);
+    if (id < a.blocks_b1) {
+        if constexpr (SPLIT)
+            bias_update(a.dact, a.d_h, id * BIAS_COLS, a.B, h, a.b1, lds);
+        else
+            column_update<0>(a.dact, a.d_h, a.d_h, id * BIAS_COLS, nullptr, 0, 0, a.B, h, a.b1, lds);
         return;
     }
-    id -= a.cols_h;
-    if (id < a.blocks_b2)
-        column_update<0>(a.dz, a.K, a.K, id * 64, nullptr, 0, 0, a.B, h, a.b2, lds);
-    else
+    id -= a.blocks_b1;
+    if (id < a.blocks_b2) {
+        if constexpr (SPLIT)
+            bias_update(a.dz, a.K, id * BIAS_COLS, a.B, h, a.b2, lds);
+        else
+            column_update<0>(a.dz, a.K, a.K, id * BIAS_COLS, nullptr, 0, 0, a.B, h, a.b2, lds);
+    } else
         sum_loss(a.loss_part, a.B, a.lambda, a.loss);
 }
 
 }  // namespace
 
-template <TailRow ROW, int NS>
+template <TailRow ROW, int NS, bool PIECES>
 static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStream_t st)
 {
     static DeviceMask raised{0};
-    hipError_t e = raise_dynamic_lds_limit((const void *)train_sample_kernel<ROW, NS>, (int)TAIL_LDS_LIMIT, raised);
+    hipError_t e = raise_dynamic_lds_limit((const void *)train_sample_kernel<ROW, NS, PIECES>, (int)TAIL_LDS_LIMIT, raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((train_sample_kernel<ROW, NS>), dim3((a.B - 1) / NS + 1), dim3(TAIL_THREADS), NS * lds, st, a.act_part,
+    // (with pieces: whole steps of samples, dealt to the XCDs in eights)
+    constexpr int EIGHTS = 8 * 8;
+    const int wgs = PIECES ? (a.B + EIGHTS - 1) / EIGHTS * (EIGHTS / NS) : (a.B - 1) / NS + 1;
+    hipLaunchKernelGGL((train_sample_kernel<ROW, NS, PIECES>), dim3(wgs), dim3(TAIL_THREADS), NS * lds, st, a.act_part,
                        nks, a.B, a.d_h, a.K, a.b1, a.w2, a.b2, a.centers, a.bin, a.y, a.steps, a.n_seqs, a.lambda, a.act,
-                       a.dact, a.dz, a.loss_part);
+                       a.dact, a.dz, a.loss_part, a.dact_pieces);
     return hipGetLastError();
 }
 
-static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, hipStream_t st)
+static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, bool split, hipStream_t st)
 {
     return tail_launch(a.d_h, tail_sequences(a.B, lds), [&](auto row, auto ns) {
-        return launch_samples<decltype(row)::value, decltype(ns)::value>(a, nks, lds, st);
+        return split ? launch_samples<decltype(row)::value, decltype(ns)::value, true>(a, nks, lds, st)
+                     : launch_samples<decltype(row)::value, decltype(ns)::value, false>(a, nks, lds, st);
     });
+}
+
+// (the offsets of a step's samples in x are 32-bit)
+static bool gradient_splits(int32_t B, int d, int d_h)
+{
+    const long tiles = (long)((d_h + GradTile::ROWS - 1) / GradTile::ROWS) * ((d + GradTile::COLS - 1) / GradTile::COLS);
+    return B >= (tiles > SPLIT_TILES ? SPLIT_SAMPLES : SPLIT_SAMPLES_FEW_TILES) && d <= (1 << 26);
+}
+
+size_t train_pieces_bytes(int32_t B, int d, int d_h)
+{
+    return gradient_splits(B, d, d_h) ? (size_t)((B + GradTile::STEP - 1) / GradTile::STEP) * dact_fragments(d_h) * 3 * FRAGMENT_BYTES : 0;
 }
 
 hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
@@ -643,7 +806,8 @@ hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
     hipError_t e = head_layer1(a.x, nullptr, a.B, a.d, a.d_h, a.w1, DT_F32, a.act_part, st);
     if (e != hipSuccess)
         return e;
-    e = launch_samples(a, head_k_splits(a.d, a.d_h, a.B, DT_F32), lds, st);
+    const bool split = gradient_splits(a.B, a.d, a.d_h);
+    e = launch_samples(a, head_k_splits(a.d, a.d_h, a.B, DT_F32), lds, split, st);
     if (e != hipSuccess)
         return e;
     Adam h;
@@ -670,18 +834,17 @@ hipError_t head_train_step(const TrainArgs &a, hipStream_t st)
     u.b2 = {a.b2, a.m_b2, a.v_b2, a.g_b2};
     u.b1 = {a.b1, a.m_b1, a.v_b1, a.g_b1};
     u.loss = a.loss;
-    // (rows of dact start on 8-byte boundaries; the gradient's offsets from a step's first sample are 32-bit)
-    const bool split = a.B >= SPLIT_SAMPLES && a.d_h % 4 == 0 && a.d <= (1 << 26) &&
-                       (long)((a.d_h + GradTile::ROWS - 1) / GradTile::ROWS) * ((a.d + GradTile::COLS - 1) / GradTile::COLS) >=
-                           SPLIT_TILES;
+    u.pieces = a.dact_pieces;
     const int tile_j = split ? GradTile::ROWS : GM, tile_k = split ? GradTile::COLS : GN;
     const long tiles_k = (a.d + tile_k - 1) / tile_k, tiles_j = (a.d_h + tile_j - 1) / tile_j;
     u.tiles_k = (int)tiles_k;
     u.tiles_w1 = (int)(tiles_k * tiles_j);
-    u.cols_h = (a.d_h + 63) / 64;
-    u.blocks_w2 = u.cols_h * ((a.K + W2_ROWS - 1) / W2_ROWS);
-    u.blocks_b2 = (a.K + 63) / 64;
-    const long wgs = tiles_k * tiles_j + u.blocks_w2 + u.cols_h + u.blocks_b2 + 1;
+    const int w2_cols = split ? W2_TILE_COLS : 64, w2_rows = split ? W2_TILE_ROWS : W2_ROWS;
+    u.cols_w2 = (a.d_h + w2_cols - 1) / w2_cols;
+    u.blocks_w2 = u.cols_w2 * ((a.K + w2_rows - 1) / w2_rows);
+    u.blocks_b1 = (a.d_h + BIAS_COLS - 1) / BIAS_COLS;
+    u.blocks_b2 = (a.K + BIAS_COLS - 1) / BIAS_COLS;
+    const long wgs = tiles_k * tiles_j + u.blocks_w2 + u.blocks_b1 + u.blocks_b2 + 1;
     if (wgs > 0x7fffffffL)
         return hipErrorInvalidValue;
     if (split)

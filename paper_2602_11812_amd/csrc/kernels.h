@@ -166,7 +166,10 @@ struct TrainArgs {
     float *dact;               // [B x d_h]
     float *dz;                 // [B x K]
     float *loss_part;          // [B x 2]
+    unsigned char *dact_pieces;  // train_pieces_bytes(B, d, d_h)
 };
+// bytes of dact as fragments of bf16 pieces, 0 where W1's gradient is on the fp32 instructions; grows with B
+size_t train_pieces_bytes(int32_t B, int d, int d_h);
 hipError_t head_train_step(const TrainArgs &a, hipStream_t st);
 
 // Register-only MFMA loop (measurement aid): MFMA_PROBE_WORKGROUPS workgroups of 4 waves, each

@@ -48,6 +48,8 @@ struct SplitTile {
 //   row_pair(r, a, e)                         (one piece) K elements 2 e and 2 e + 1 of row fragment a
 //   write_col(buf, part, n), slot()           write number n of COL_WRITES of the pieces of this thread's pairs, part[share]
 //                                             [piece][pair]; the 16 bytes of a fragment that this lane reads
+//   ROWS_READY                                rows lie in memory as fragments of their pieces: load_rows(i, piece, a, r) loads one, and
+//                                             only the columns are split
 //   ROWS_TURN                                 rows are loaded by other lanes than use them, and turned in the LDS of the wave:
 //   write_row(r, l), read_row(t, l)           load number l of ROW_LOADS on its way there and back
 template <class T, class Source>
@@ -55,7 +57,7 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
                                                const Source &src)
 {
     constexpr int FA = T::FA, FB = T::FB, SHARE = T::SHARE;
-    constexpr bool TURN = Source::ROWS_TURN;
+    constexpr bool TURN = Source::ROWS_TURN, READY = Source::ROWS_READY, SPREAD = READY;
     const int slot = src.slot();
     typename Source::Rows ra0, ra1;
     typename Source::Cols rb0, rb1;
@@ -73,7 +75,7 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
         const int a = n / 4, e = n % 4;
         if constexpr (Source::ROW_PIECES == 1) {
             f.p[0][a][e] = src.row_pair(r, a, e);
-        } else {
+        } else if constexpr (!READY) {
             unsigned h, m, l;
             split3_pair_nearest(src.row_value(r, a, 2 * e), src.row_value(r, a, 2 * e + 1), h, m, l);
             f.p[0][a][e] = h, f.p[1][a][e] = m, f.p[2][a][e] = l;
@@ -100,9 +102,17 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
         __builtin_amdgcn_sched_barrier(0);
     };
     auto fetch_rows = [&](int i, typename Source::Rows &r) {
+        if constexpr (!READY)
 #pragma unroll
-        for (int l = 0; l < ROW_LOADS; ++l)
-            src.load_rows(i, l, r);
+            for (int l = 0; l < ROW_LOADS; ++l)
+                src.load_rows(i, l, r);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto fetch_fragments = [&](int i, RowFragments &f) {
+        if constexpr (READY)
+#pragma unroll
+            for (int l = 0; l < 3 * FA; ++l)
+                f.p[2 - l / FA][l % FA] = src.load_rows(i, 2 - l / FA, l % FA);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto stage = [&](int i, typename Source::Cols &r, unsigned char *buf) {
@@ -117,8 +127,10 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
     };
     fetch_cols(0, rb0);
     fetch_rows(0, ra0);
+    fetch_fragments(0, a0);
     fetch_cols(1, rb1);
     fetch_rows(1, ra1);
+    fetch_fragments(1, a1);
     stage(0, rb0, lds);
     fetch_cols(2, rb0);
     src.clear_rows(0, ra0);
@@ -131,9 +143,10 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
         for (int l = 0; l < ROW_LOADS; ++l)
             src.read_row(turned, l);
     }
+    if constexpr (!READY)
 #pragma unroll
-    for (int n = 0; n < ROW_PAIRS; ++n)
-        split_rows(TURN ? turned : ra0, a0, n);
+        for (int n = 0; n < ROW_PAIRS; ++n)
+            split_rows(TURN ? turned : ra0, a0, n);
     __builtin_amdgcn_sched_barrier(0);
     fetch_rows(2, ra0);
     stage(1, rb1, lds + T::BYTES);
@@ -151,13 +164,23 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
 #pragma unroll
         for (int fb = 0; fb < FB; ++fb)
             small[fa][fb] = split_f32x4{0.f, 0.f, 0.f, 0.f};
-    // rb: holds the columns of step i + 2; ra: the rows of step i + 1
-    auto step = [&](int i, const RowFragments &a, RowFragments &a_next, const ColFragments &b, ColFragments &b_next,
+    // rb: holds the columns of step i + 2; ra: the rows of step i + 1 (READY: a_next does, a is loaded again when its pieces have been used)
+    auto step = [&](int i, RowFragments &a, RowFragments &a_next, const ColFragments &b, ColFragments &b_next,
                     typename Source::Rows &ra, typename Source::Cols &rb, unsigned char *mine, const unsigned char *other) {
         constexpr int PA[2][6] = {{2, 1, 0, 1, 0, 0}, {0, 0, 0}}, PB[2][6] = {{0, 1, 2, 0, 1, 0}, {2, 1, 0}};
         constexpr int WHOLE = Source::ROW_PIECES == 1 ? 1 : 0;  // rows in one piece
-        constexpr int ROWS = PRODUCTS * FA, SPLIT = ROWS * 2 / 3, TAIL = ROWS - SPLIT;
-        constexpr int TURNED = TURN ? 3 : 0;  // the row of products from which on the rows have been turned
+        // Where what goes beside the products stands, in rows of products.  Ready rows: spread over the step, what the next step waits
+        // for early; where rows are split: the splitting first.
+        constexpr int ROWS = PRODUCTS * FA, SPLIT = SPREAD ? ROWS / 3 : ROWS * 2 / 3;
+        constexpr int READS_TO = SPREAD ? ROWS - 2 : ROWS, ROWS_FROM = SPREAD ? SPLIT : (TURN ? 3 : 0), ROWS_TO = SPREAD ? ROWS - 1 : SPLIT;
+        constexpr int WRITES_TO = SPREAD ? ROWS - 2 : ROWS, COLS_TO = SPREAD ? ROWS - 1 : ROWS, ROW_LOADS_FROM = SPREAD ? ROWS - 1 : SPLIT;
+        // the part of n pieces of work, dealt to rows [from, to) of products, that is row's
+        auto share = [](int row, int from, int to, int n, auto work) {
+#pragma unroll
+            for (int k = 0; k < n; ++k)
+                if (row >= from && row < to && k >= (row - from) * n / (to - from) && k < (row - from + 1) * n / (to - from))
+                    work(k);
+        };
         src.clear_cols(i + 2, rb);
         src.clear_rows(i + 1, ra);
         __builtin_amdgcn_s_waitcnt(0xC07F);
@@ -173,9 +196,7 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
                 sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(split_bf16x8, a.p[PA[WHOLE][t]][fa]),
                                                               b.p[PB[WHOLE][t]][fb], sum, 0, 0, 0);
             }
-#pragma unroll
-            for (int n = row * READS / ROWS; n < (row + 1) * READS / ROWS; ++n)
-                read(b_next, other, n);
+            share(row, 0, READS_TO, READS, [&](int n) { read(b_next, other, n); });
             if constexpr (TURN) {  // (the LDS serves a wave in order)
 #pragma unroll
                 for (int l = 0; l < ROW_LOADS; ++l) {
@@ -185,26 +206,15 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
                         src.read_row(turned, l);
                 }
             }
-            if (row < SPLIT) {
-#pragma unroll
-                for (int n = row * COL_PAIRS / SPLIT; n < (row + 1) * COL_PAIRS / SPLIT; ++n)
-                    split_cols(rb, n);
-                if (row >= TURNED)
-#pragma unroll
-                    for (int n = (row - TURNED) * ROW_PAIRS / (SPLIT - TURNED); n < (row - TURNED + 1) * ROW_PAIRS / (SPLIT - TURNED); ++n)
-                        split_rows(TURN ? turned : ra, a_next, n);
-            } else {
-                const int q = row - SPLIT;
-#pragma unroll
-                for (int n = q * WRITES / TAIL; n < (q + 1) * WRITES / TAIL; ++n)
-                    write(mine, n);
-#pragma unroll
-                for (int l = q * COL_LOADS / TAIL; l < (q + 1) * COL_LOADS / TAIL; ++l)
-                    src.load_cols(i + 4, l, rb);
-#pragma unroll
-                for (int l = q * ROW_LOADS / TAIL; l < (q + 1) * ROW_LOADS / TAIL; ++l)
-                    src.load_rows(i + 3, l, ra);
-            }
+            share(row, 0, SPLIT, COL_PAIRS, [&](int n) { split_cols(rb, n); });
+            if constexpr (!READY)
+                share(row, ROWS_FROM, ROWS_TO, ROW_PAIRS, [&](int n) { split_rows(TURN ? turned : ra, a_next, n); });
+            share(row, SPLIT, WRITES_TO, WRITES, [&](int n) { write(mine, n); });
+            share(row, SPLIT, COLS_TO, COL_LOADS, [&](int l) { src.load_cols(i + 4, l, rb); });
+            if constexpr (!READY)
+                share(row, ROW_LOADS_FROM, ROWS, ROW_LOADS, [&](int l) { src.load_rows(i + 3, l, ra); });
+            else if (t == 0 || t == 3 || t == 5)  // the last of this piece's products
+                a.p[PA[WHOLE][t]][fa] = src.load_rows(i + 2, PA[WHOLE][t], fa);
             __builtin_amdgcn_sched_barrier(0);
         }
     };

@@ -1,5 +1,5 @@
 """fp32 products as bf16 pieces in the head: layer 1 of more than 64 sequences (tiles of 64 and of 128 columns; up to 2^24 products,
-counted in tiles of 64 x 64, the fp32 instructions) and W1's gradient from 192 samples on.  A step each at the edges of their tiles against the fp64 oracle, to the bars of the fp32
+counted in tiles of 64 x 64, the fp32 instructions) and W1's gradient from 160 samples on (256 where it has at most 128 tiles).  A step each at the edges of their tiles against the fp64 oracle, to the bars of the fp32
 training tests: batches one past and one short of a tile, rows of W1 off the 128-row tile, slices of d that end inside a K
 step of 32, samples that end inside one.  Sums of a single product, which show every piece product; operands and results that
 are not finite."""
@@ -9,7 +9,8 @@ import pytest
 import oracle
 from helpers import rel_l2
 from paper_2602_11812_amd import workloads as wl
-from test_gpu_training import _gpu_step, _oracle_head, _run_steps, _trainer, gpu  # noqa: F401  (the fixture)
+from test_gpu_training import (HYPER, NAMES, _Bar, _gpu_step, _oracle_head, _run_steps, _trainer, _weights,  # noqa: F401
+                               gpu)  # (the fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -22,6 +23,30 @@ pytestmark = pytest.mark.gpu
                                        (65, 520, 516, 4)])
 def test_one_step_at_tile_edges(gpu, B, d, d_h, K):  # noqa: F811
     _run_steps(gpu, wl.make_train(4200 + B, B=B, d=d, d_h=d_h, K=K), 1)
+
+
+# The samples' kernel leaves d loss / d pre-activation as fragments of pieces: the first batches of the two rules and the last before them;
+# samples that end one past and one short of a K step, of the eight of a lane and of the groups of one, two and four of a workgroup; rows off
+# the 16 of a fragment and the 128 of a tile, fewer than four; bins off the 32 x 16 tiles of W2's gradient and fewer than four
+@pytest.mark.parametrize("B,d,d_h,K", [(160, 4100, 257, 33), (159, 4100, 257, 33), (161, 1044, 1025, 3), (256, 36, 5, 2), (255, 36, 5, 2),
+                                       (257, 64, 130, 20), (287, 260, 3, 17), (511, 68, 2, 32), (513, 132, 1, 65), (519, 32, 127, 31),
+                                       (1023, 4, 129, 16), (300, 128, 16384, 2)])
+def test_one_step_on_ready_pieces(gpu, B, d, d_h, K):  # noqa: F811
+    # (the bars of _run_steps, without its share of elements for which they are tight: of a W1 of 20 to 516 elements it
+    # counts the two or three whose gradient happens to be near zero)
+    ts = wl.make_train(5200 + B, B=B, d=d, d_h=d_h, K=K)
+    hp = {k: float(np.float32(v)) for k, v in HYPER.items()}
+    tr, oh, bar = _trainer(gpu, ts), _oracle_head(ts), _Bar(_oracle_head(ts).params())
+    wgt = _weights(ts)
+    loss, gs = oracle.head_loss_grad(ts.x, ts.bins, ts.y, oh, hp["lam"], wgt)
+    oracle.train_step(ts.x, ts.bins, ts.y, oh, hp["lam"], hp["lr"], hp["beta1"], hp["beta2"], hp["eps"], hp["weight_decay"], wgt)
+    bar.add_step(oh, gs, hp, 1)
+    assert np.all(np.abs(_gpu_step(gpu, tr, ts) - loss) <= 2e-5 * np.abs(loss) + 1e-12)
+    for i, n in enumerate(NAMES):
+        got = tr.grads[n].cpu().numpy()
+        assert rel_l2(got, gs[i]) <= 2e-5, n
+        assert np.all(got[gs[i] == 0.0] == 0.0), n
+        assert (np.abs(tr.params[n].cpu().numpy() - oh.params()[i]) <= bar.tol[i]).all(), n
 
 
 @pytest.mark.parametrize("B,d,d_h", [(130, 64, 70), (130, 1028, 129)])
