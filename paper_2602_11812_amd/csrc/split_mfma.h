@@ -31,6 +31,22 @@ struct SplitTile {
     static constexpr int SHARE = FB / WAVES;     // column fragments' lanes that a thread stages: 8 K elements each
 };
 
+// The order of a row of N products and of what goes beside it, where one wave has a SIMD to itself: behind each MFMA an LDS read and up to three
+// vector instructions.  Left to itself the compiler puts all of them ahead of the row's MFMAs and half of the splitting behind the step:
+// layer 1 of 1024 sequences, d = 4096, d_h = 1024 3100 cycles a step for 96 MFMAs of 16, now 2500; the launch 61 -> 56 us, a training step
+// 117.2 -> 115.6 (the clock falls to 2.1 GHz).  Tiles of 64 columns, two waves to a SIMD and a few steps, lose by it: 12.3 -> 13.0 us for 160
+// sequences, d = d_h = 1024.
+template <int N>
+__device__ __forceinline__ void interleave()
+{
+#pragma unroll
+    for (int n = 0; n < N; ++n) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // LDS read
+        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);  // other vector instructions
+    }
+}
+
 // acc[a][b] += row fragment a . column fragment b over `steps` K steps of the tile.
 //
 // Everything that a step needs is under way before it: while the products of step i run, the column fragments of step i + 1
@@ -57,7 +73,7 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
                                                const Source &src)
 {
     constexpr int FA = T::FA, FB = T::FB, SHARE = T::SHARE;
-    constexpr bool TURN = Source::ROWS_TURN, READY = Source::ROWS_READY, SPREAD = READY;
+    constexpr bool TURN = Source::ROWS_TURN, READY = Source::ROWS_READY, SPREAD = READY || FB > 4;
     const int slot = src.slot();
     typename Source::Rows ra0, ra1;
     typename Source::Cols rb0, rb1;
@@ -78,6 +94,8 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
         } else if constexpr (!READY) {
             unsigned h, m, l;
             split3_pair_nearest(src.row_value(r, a, 2 * e), src.row_value(r, a, 2 * e + 1), h, m, l);
+            if constexpr (SPREAD)
+                asm volatile("" : "+v"(h), "+v"(m), "+v"(l));  // here, not where they are used (in front of the next step's products)
             f.p[0][a][e] = h, f.p[1][a][e] = m, f.p[2][a][e] = l;
         }
     };
@@ -169,8 +187,8 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
                     typename Source::Rows &ra, typename Source::Cols &rb, unsigned char *mine, const unsigned char *other) {
         constexpr int PA[2][6] = {{2, 1, 0, 1, 0, 0}, {0, 0, 0}}, PB[2][6] = {{0, 1, 2, 0, 1, 0}, {2, 1, 0}};
         constexpr int WHOLE = Source::ROW_PIECES == 1 ? 1 : 0;  // rows in one piece
-        // Where what goes beside the products stands, in rows of products.  Ready rows: spread over the step, what the next step waits
-        // for early; where rows are split: the splitting first.
+        // Where what goes beside the products stands, in rows of products.  Wide tiles and ready rows: spread over the step, what
+        // the next step waits for early; short rows of products that split rows beside them: the splitting first.
         constexpr int ROWS = PRODUCTS * FA, SPLIT = SPREAD ? ROWS / 3 : ROWS * 2 / 3;
         constexpr int READS_TO = SPREAD ? ROWS - 2 : ROWS, ROWS_FROM = SPREAD ? SPLIT : (TURN ? 3 : 0), ROWS_TO = SPREAD ? ROWS - 1 : SPLIT;
         constexpr int WRITES_TO = SPREAD ? ROWS - 2 : ROWS, COLS_TO = SPREAD ? ROWS - 1 : ROWS, ROW_LOADS_FROM = SPREAD ? ROWS - 1 : SPLIT;
@@ -215,6 +233,8 @@ __device__ __forceinline__ void split_contract(unsigned char *lds, int steps, sp
                 share(row, ROW_LOADS_FROM, ROWS, ROW_LOADS, [&](int l) { src.load_rows(i + 3, l, ra); });
             else if (t == 0 || t == 3 || t == 5)  // the last of this piece's products
                 a.p[PA[WHOLE][t]][fa] = src.load_rows(i + 2, PA[WHOLE][t], fa);
+            if constexpr (SPREAD && !READY)
+                interleave<FB>();
             __builtin_amdgcn_sched_barrier(0);
         }
     };
