@@ -154,16 +154,18 @@ egtp_status run_entropy(egtp_ctx *ctx, const void *hidden, int64_t T, const Work
         EGTP_HIP(pack_rows(c.dtype, c.w_lm, c.vocab, c.d, false, false, K1_PACK_ROWS, w.w_packed, nullptr, 0, st));
         wp = w.w_packed;
     }
-    EGTP_HIP(pack_rows(c.dtype, hidden, T, c.d, true, p.pieces, p.tb_tokens, w.hidden_packed, w.k1_pace, k1_pace_ints(p), st));
+    if (!p.direct)
+        EGTP_HIP(pack_rows(c.dtype, hidden, T, c.d, true, p.pieces, p.tb_tokens, w.hidden_packed, w.k1_pace, k1_pace_ints(p), st));
+    const void *h = p.direct ? hidden : w.hidden_packed;
     if (timed)
         EGTP_HIP(hipEventRecord(ctx->prof_events[2 * ctx->prof_count], st));
     const int K = (int)k1_contraction_len(c.dtype, c.d);
     if (p.tile_v == K1_NARROW_TILE_V && p.tb_tokens == K1_NARROW_TOKENS)
-        EGTP_HIP(k1_entropy_narrow(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, st));
+        EGTP_HIP(k1_entropy_narrow(h, wp, T, K, c.vocab, p, w.k1_part, st));
     else if (p.tile_v != K1_WIDE_TILE_V)
-        EGTP_HIP(k1_entropy_stream(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
+        EGTP_HIP(k1_entropy_stream(h, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
     else
-        EGTP_HIP(k1_entropy_bf16(w.hidden_packed, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
+        EGTP_HIP(k1_entropy_bf16(h, wp, T, K, c.vocab, p, w.k1_part, w.k1_pace, st));
     if (timed) {
         EGTP_HIP(hipEventRecord(ctx->prof_events[2 * ctx->prof_count + 1], st));
         ++ctx->prof_count;

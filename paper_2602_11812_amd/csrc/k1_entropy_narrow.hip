@@ -22,9 +22,14 @@
 // tokens against V = 151936, d = 4096 1170 to 1270 -> 670 (5.7 TB/s of pieces); 2, V = 94086, d = 1160 216 -> 125; 64, V = 32000,
 // d = 2048 156 -> 87; 47, V = 6763, d = 3440 160 -> 105.
 //
+// bf16 hidden states are read where they are, two K steps at a time (k1_stream.h), which spares the launch that packs them and the reads of rows past the
+// batch: whole decode steps, d = 4096, V = 151936, 24 tokens 220 -> 209 us, 64 227 -> 210; d = 5120, V = 100000, 24 189 -> 169.
+//
 // Measured: 64 tokens against V = 151936, d = 4096: 199 us = 6.3 TB/s of W_lm (the 256 x 256 tile: 286 us on 198 of the
 // 256 compute units); 309 fp32 tokens against V = 4096, d = 256: 15.4 us, 37.1 before.  Two K steps per barrier gain
 // nothing.  (Blocks of 192 tokens, which ran on this kernel as well, are the stream kernel's now.)
+#include <type_traits>
+
 #include "k1_stream.h"
 
 namespace egtp {
@@ -41,15 +46,17 @@ constexpr int STAGE_BYTES = W_STEP_BYTES + H_STEP_BYTES;
 constexpr int LOADS = STAGE_BYTES / 4096;           // 16-byte loads per lane and step
 constexpr int STAGES = 144 * 1024 / STAGE_BYTES;    // 12
 constexpr int RING_BYTES = STAGES * STAGE_BYTES;
-static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64, "ring depth");
+static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64 && STAGES % 2 == 0, "ring depth");
+constexpr int H_RING = STAGES * W_STEP_BYTES;  // direct: the hidden states' stages, of two steps each, lie behind W_lm's
 
 template <bool PIECES, bool STREAM_W>
 __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigned char *__restrict__ Wp,
-                                                                   const unsigned char *__restrict__ Hp, long T, int KT,
+                                                                   const unsigned char *__restrict__ Hp, long T, int d, int KT,
                                                                    int V, int ntb, int nsplit, int ntiles_v,
                                                                    float *__restrict__ part)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    constexpr bool DIRECT = !PIECES;  // the hidden states where they are (k1_stream.h); Hp: row-major
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -87,23 +94,31 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     const int lane_off = wave * 1024 + lane * 16;
     const int w_tile_bytes = KT * TILE_BYTES;  // (the launcher checks the range)
     const int h_tile_bytes = KL * H_STEP_BYTES;
-    const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
+    const __amdgpu_buffer_rsrc_t rH = DIRECT ? DirectRows::block(Hp, tok0, 32 * NI, T, d) : raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
+    const DirectRows rows(wave, lane, d);
     unsigned char *lds_wave = smem + wave * 1024;
     // The load stream runs ahead of the MFMAs by the ring.  Past the end it keeps re-reading the last step (into
     // stages nobody reads any more), so every step issues the same number of loads and one wait constant serves.
-    int lvt = vt_begin, lkt = 0, lseg = 0, lstep = 0;  // (segment lseg: blocks lseg, lseg + kseg, ...)
-    auto issue_loads = [&](int stage) {
+    const int first = DIRECT ? DirectRows::first_step(sp, KT) : 0;
+    int lvt = vt_begin, lkt = first, lseg = 0, lstep = 0;  // (segment lseg: blocks lseg, lseg + kseg, ...)
+    auto issue_loads = [&](int stage, bool odd) {
         lvt = __builtin_amdgcn_readfirstlane(lvt);  // a descriptor must be uniform, and known to be
         const __amdgpu_buffer_rsrc_t rW = raw_buffer(Wp + (long)(lvt >> 1) * w_tile_bytes, w_tile_bytes);
         const int woff = (lseg + lkt) * TILE_BYTES + (lvt & 1) * W_STEP_BYTES;
         const int hoff = (lseg + lkt) * H_STEP_BYTES;
-        unsigned char *dst = lds_wave + stage * STAGE_BYTES;
+        unsigned char *dst = lds_wave + stage * (DIRECT ? W_STEP_BYTES : STAGE_BYTES);
 #pragma unroll
         for (int p = 0; p < W_STEP_BYTES / 4096; ++p)
             load16_to_lds<STREAM_W>(rW, lane_off, woff + p * 4096, dst + p * 4096);
+        if constexpr (!DIRECT) {
 #pragma unroll
-        for (int p = 0; p < H_STEP_BYTES / 4096; ++p)
-            load16_to_lds(rH, lane_off, hoff + p * 4096, dst + W_STEP_BYTES + p * 4096);
+            for (int p = 0; p < H_STEP_BYTES / 4096; ++p)
+                load16_to_lds(rH, lane_off, hoff + p * 4096, dst + W_STEP_BYTES + p * 4096);
+        } else if (odd) {  // (a pair of steps comes and goes with its second one)
+#pragma unroll
+            for (int q = 0; q < 2 * H_STEP_BYTES / 4096; ++q)
+                load16_to_lds(rH, rows.offset(q, lkt - 1, d), (lkt - 1) * ROW_BYTES, lds_wave + H_RING + (stage >> 1) * 2 * H_STEP_BYTES + q * 4096);
+        }
         const int adv = lstep + 1 < total ? 1 : 0;
         lstep += adv;
         int next = adv;  // to the next K step
@@ -114,7 +129,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
         const int nk = lkt + next;
         const int wrap = nk == kseg ? 1 : 0;
         lkt = wrap ? 0 : nk;
-        lvt += wrap;
+        lvt += DIRECT ? (next && lkt == first ? 1 : 0) : wrap;
     };
 
     // ---- fragment reads: row r, chunk c of a block sits at r * 64 + ((c ^ swizzle_key(r)) * 16)
@@ -124,17 +139,23 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     const unsigned fragA = (unsigned)(wm * 64 + l15) * ROW_BYTES + swz;
     const unsigned fragB = (unsigned)W_STEP_BYTES + (unsigned)(wn * 16 * NI + l15) * ROW_BYTES + swz;
     constexpr int FRAG_STRIDE = 16 * ROW_BYTES;
+    // Loads in flight behind those that a step waits for: steps k + 2 to k + 11 of even k, half of them with a pair's loads; of odd k, k + 3 to k + 11
+    constexpr int W_LOADS = W_STEP_BYTES / 4096, PAIR_LOADS = 2 * H_STEP_BYTES / 4096;
+    constexpr int WAIT_EVEN = (STAGES - 2) * W_LOADS + (STAGES - 2) / 2 * PAIR_LOADS;
+    constexpr int WAIT_ODD = (STAGES - 3) * W_LOADS + (STAGES - 4) / 2 * PAIR_LOADS;
     struct Frags {
         bf16x8 a[4], b[NI];
     };
-    auto read_frags = [&](Frags &f, int stage) {
-        const unsigned char *s = smem + stage * STAGE_BYTES;
+    const unsigned frag_direct = (unsigned)H_RING + (unsigned)(wn * 16 * NI) * 2 * ROW_BYTES + DirectRows::fragment(lane);
+    auto read_frags = [&](Frags &f, int stage, bool odd) {
+        const unsigned char *s = smem + stage * (DIRECT ? W_STEP_BYTES : STAGE_BYTES);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             f.a[i] = *(const bf16x8 *)(s + fragA + i * FRAG_STRIDE);
+        const unsigned char *b = DIRECT ? smem + (stage >> 1) * 2 * H_STEP_BYTES + (frag_direct ^ (odd ? DirectRows::ODD : 0u)) : s + fragB;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            f.b[i] = *(const bf16x8 *)(s + fragB + i * FRAG_STRIDE);
+            f.b[i] = *(const bf16x8 *)(b + i * FRAG_STRIDE * (DIRECT ? 2 : 1));
     };
 
     Stats st[NI];
@@ -158,41 +179,44 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
 
 #pragma unroll
     for (int s = 0; s < STAGES; ++s)
-        issue_loads(s);
-    wait_vmcnt<(STAGES - 1) * LOADS>();
+        issue_loads(s, s & 1);
+    wait_vmcnt<DIRECT ? WAIT_EVEN : (STAGES - 1) * LOADS>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     Frags f0, f1, f2;
-    read_frags(f0, 0);
+    read_frags(f0, 0, false);
     int cstage = 0;  // stage of the step whose MFMAs are next
 
     // One step.  Wait for the next step's loads (the newest STAGES - 2 steps may still be
     // in flight) and for this wave's own fragment reads, meet the other waves, refill the stage just freed, read the
     // next fragments, multiply.  A bare barrier: a fence would drain the ring.
-    auto step = [&](Frags &next, auto products) {
-        wait_vmcnt<(STAGES - 2) * LOADS>();
+    // Direct: an even step waits for the step behind it with its pair's hidden states, an odd one for the next pair's.
+    auto step = [&](auto odd_const, Frags &next, auto products) {
+        constexpr bool ODD = decltype(odd_const)::value;
+        wait_vmcnt<DIRECT ? (ODD ? WAIT_ODD : WAIT_EVEN) : (STAGES - 2) * LOADS>();
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         const int nstage = cstage + 1 == STAGES ? 0 : cstage + 1;
-        read_frags(next, nstage);
-        issue_loads(cstage);
+        read_frags(next, nstage, !ODD);
+        issue_loads(cstage, ODD);
         products();
         cstage = nstage;
         __builtin_amdgcn_sched_barrier(0);
     };
 
+    constexpr std::false_type EVEN{};  // (of the pieces' three steps none is odd)
     for (int vt = vt_begin; vt < vt_end; ++vt) {
         if constexpr (PIECES) {
             for (int h = 0, kk = 0; h < 2; ++h) {
                 for (const int end = h ? kseg : kseg / 2; kk < end; ++kk) {
-                    step(f1, [&] { multiply(acc, f0, f0); });
-                    step(f2, [&] {
+                    step(EVEN, f1, [&] { multiply(acc, f0, f0); });
+                    step(EVEN, f2, [&] {
                         multiply(acc, f1, f1);
                         multiply(acc, f1, f0);
                     });
                     Frags ahead;
-                    step(ahead, [&] {
+                    step(EVEN, ahead, [&] {
                         multiply(acc, f2, f2);
                         multiply(acc, f2, f1);
                         multiply(lead, f2, f0);
@@ -210,8 +234,8 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
             }
         } else {
             for (int kt = 0; kt < KT; kt += 2) {
-                step(f1, [&] { multiply(acc, f0, f0); });
-                step(f0, [&] { multiply(acc, f1, f1); });
+                step(EVEN, f1, [&] { multiply(acc, f0, f0); });
+                step(std::true_type{}, f0, [&] { multiply(acc, f1, f1); });
             }
         }
         // a tile of logits is in registers: fold it into the statistics and forget it
@@ -281,7 +305,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
 }
 
 template <bool PIECES, bool STREAM_W>
-hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p,
+hipError_t launch(const void *hidden, const void *w_packed, int64_t T, int d, int kt, int V, const K1Plan &p,
                   float *part, hipStream_t st)
 {
     static DeviceMask lds_limit_raised{0};
@@ -290,30 +314,29 @@ hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, in
     if (e != hipSuccess)
         return e;
     hipLaunchKernelGGL((k1_entropy_narrow_kernel<PIECES, STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), RING_BYTES,
-                       st, (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
+                       st, (const unsigned char *)w_packed, (const unsigned char *)hidden, (long)T, d, kt, V, p.ntb,
                        p.nsplit, p.ntiles_v, part);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+hipError_t k1_entropy_narrow(const void *hidden, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, hipStream_t st)
 {
     const int kt = k_steps(K);
-    if (p.pieces && kt % K1_SPLIT_TERMS != 0)
+    if (p.pieces == p.direct || (p.pieces && kt % K1_SPLIT_TERMS != 0))
         return hipErrorInvalidValue;
     if (T <= 0 || p.tb_tokens != K1_NARROW_TOKENS || p.tile_v != NM || p.nsplit < 1 || p.nsplit > p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
         (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + NM - 1) / NM || (long)kt * TILE_BYTES > 0x7fffffffL)
         return hipErrorInvalidValue;
-    // One token block reads W_lm once.  If the 256 MiB Infinity Cache cannot hold it until the next call either, its
-    // loads carry the non-temporal hint: 64 tokens, d = 4096, V = 151936 (1.24 GB) 225 -> 199 us = 6.3 TB/s; V = 65536
-    // and d = 2560 (336 MB) 60.5 -> 55.7; but V = 65536 and d = 2048 (268 MB) 44 -> 46 and V = 32000 (131 MB) 25 -> 26.
+    // W_lm with the non-temporal hint where the Infinity Cache cannot hold it: 64 tokens, d = 4096, V = 151936 (1.24 GB) 225 -> 199 us = 6.3 TB/s;
+    // V = 65536 and d = 2560 (336 MB) 60.5 -> 55.7; but V = 65536 and d = 2048 (268 MB) 44 -> 46 and V = 32000 (131 MB) 25 -> 26.
     const int read = p.pieces ? kt / 2 : kt;  // blocks that a sweep reads
-    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * read * W_STEP_BYTES > ((int64_t)256 << 20);
-#define EGTP_NARROW(PIECES)                                                              \
-    (stream ? launch<PIECES, true>(hidden_packed, w_packed, T, kt, V, p, part, st)       \
-            : launch<PIECES, false>(hidden_packed, w_packed, T, kt, V, p, part, st))
+    const bool stream = k1_plan_streams_w(p, read);
+#define EGTP_NARROW(PIECES)                                                          \
+    (stream ? launch<PIECES, true>(hidden, w_packed, T, K, kt, V, p, part, st)       \
+            : launch<PIECES, false>(hidden, w_packed, T, K, kt, V, p, part, st))
     return p.pieces ? EGTP_NARROW(true) : EGTP_NARROW(false);
 #undef EGTP_NARROW
 }

@@ -25,6 +25,9 @@
 // fragment of W_lm loaded twice: 316 us), five fragments at a time (registers spill: 315).  For 256 tokens the pair of
 // waves gives the 256 x 256 tile's times within 2 %, and a wave of its own on 64 rows x 256 tokens spills: not built.
 //
+// bf16 hidden states are read where they are, two K steps at a time (k1_stream.h), unless the plan says otherwise (k1_plan.cpp): 173 tokens, d = 4096,
+// V = 151936 272 -> 260 us a pass.
+//
 // Pacing is that of the 256 x 256 kernel: cohorts of 32 workgroups that share blocks in an XCD's L2 count themselves in
 // every second sweep and wait, bounded, for the rest; a hint that no result depends on.
 #include <type_traits>
@@ -44,10 +47,11 @@ struct Shape {
     static constexpr int MAX_MI = NI == 8 ? 8 : 4;
     static constexpr int FPW = NI == 8 ? 1 : 2;
     static constexpr int STAGES = NI == 8 ? 6 : 8;
+    static constexpr int DIRECT_STAGES = 8;  // four pairs of steps
     static constexpr int H_STEP_BYTES = TOKENS * ROW_BYTES;
     static constexpr int H_LOADS = H_STEP_BYTES / 4096;  // 16-byte loads per lane and step
-    static constexpr int LDS_BYTES = STAGES * H_STEP_BYTES;
-    static_assert((STAGES - 2) * (H_LOADS + MAX_MI) < 64, "one wait covers the ring");
+    static constexpr int LDS_BYTES = STAGES * H_STEP_BYTES, DIRECT_LDS_BYTES = DIRECT_STAGES * H_STEP_BYTES;
+    static_assert((STAGES - 2) * (H_LOADS + MAX_MI) < 64 && (DIRECT_STAGES - 2) * (H_LOADS + MAX_MI) < 64, "one wait covers the ring");
 };
 static_assert(Shape<8>::TOKENS == K1_STREAM_TOKENS && Shape<8>::FPW * 64 == K1_STREAM_TILE_V, "plan");
 static_assert(Shape<12>::TOKENS == K1_STREAM_WIDE_TOKENS && Shape<12>::FPW * 64 == K1_NARROW_TILE_V, "plan");
@@ -84,14 +88,14 @@ __device__ __forceinline__ bf16x8 load_fragment(__amdgpu_buffer_rsrc_t rsrc, int
                                                                            STREAM_W ? 2 : 0));
 }
 
-template <int NI, int D, bool PIECES, bool STREAM_W>
+template <int NI, int D, bool PIECES, bool STREAM_W, bool DIRECT>
 __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigned char *__restrict__ Wp,
-                                                                   const unsigned char *__restrict__ Hp, long T, int KT,
+                                                                   const unsigned char *__restrict__ Hp, long T, int d, int KT,
                                                                    int V, int ntb, int nsplit, int tps, int ntiles_v, int group, bool whole_cohorts,
                                                                    float *__restrict__ part, int *__restrict__ pace)
 {
     using S = Shape<NI>;
-    constexpr int MAX_MI = S::MAX_MI, FPW = S::FPW, H_STAGES = S::STAGES;
+    constexpr int MAX_MI = S::MAX_MI, FPW = S::FPW, H_STAGES = DIRECT ? S::DIRECT_STAGES : S::STAGES;
     constexpr int H_STEP_BYTES = S::H_STEP_BYTES, H_LOADS = S::H_LOADS;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x;
@@ -177,15 +181,19 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     bf16x8 wr[D][MAX_MI];
     const int kseg = KT / K1_SPLIT_TERMS;  // PIECES: K steps of a segment
     PieceWalk walk_w, walk_h;
+    const int first = DIRECT ? DirectRows::first_step(sp, KT) : 0;
     auto w_offset = [&](int kt) {  // of the step whose fragments are loaded next
+        if (DIRECT)
+            kt = kt + first < KT ? kt + first : kt + first - KT;
         return (PIECES ? walk_w.next(PieceWalk::W_SEGMENTS, kseg) : kt) * TILE_BYTES;
     };
 
     // ---- hidden states: memory -> LDS ring, copied linearly, 1 KiB per wave-wide load; the same block sweep after sweep
     const int lane_h = wave * 1024 + lane * 16;
     const int h_tile_bytes = (PIECES ? 3 * kseg : KT) * H_STEP_BYTES;
-    const __amdgpu_buffer_rsrc_t rH = raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
-    int hkt = 0;
+    const __amdgpu_buffer_rsrc_t rH = DIRECT ? DirectRows::block(Hp, tok0, S::TOKENS, T, d) : raw_buffer(Hp + (long)tb * h_tile_bytes, h_tile_bytes);
+    const DirectRows rows(wave, lane, d);
+    int hkt = first;
     auto load_h = [&](int stage) {
         unsigned char *dst = smem + stage * H_STEP_BYTES + wave * 1024;
         const int off = (PIECES ? walk_h.next(PieceWalk::H_SEGMENTS, kseg) : hkt) * H_STEP_BYTES;
@@ -194,7 +202,17 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
             load16_to_lds(rH, lane_h, off + p * 4096, dst + p * 4096);
         hkt = hkt + 1 == KT ? 0 : hkt + 1;
     };
-    const unsigned frag_h = (unsigned)lane_w;
+    // direct: half `part` of the loads of the pair of steps that ends with `stage`
+    auto load_pair = [&](int stage, int part) {
+        unsigned char *dst = smem + (stage >> 1) * 2 * H_STEP_BYTES + wave * 1024;
+#pragma unroll
+        for (int q = part * H_LOADS; q < (part + 1) * H_LOADS; ++q)
+            load16_to_lds(rH, rows.offset(q, hkt, d), hkt * ROW_BYTES, dst + q * 4096);
+        if (part == 1)
+            hkt = hkt + 2 == KT ? 0 : hkt + 2;
+    };
+    const unsigned frag_h = DIRECT ? DirectRows::fragment(lane) : (unsigned)lane_w;
+    constexpr int FRAG_STRIDE = DIRECT ? 2 * FRAG_BYTES : FRAG_BYTES;
     bf16x8 fb[2][NI];
 
     Stats st[NI];
@@ -207,8 +225,12 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
 
     set_rows(f_begin);
 #pragma unroll
-    for (int s = 0; s < H_STAGES; ++s)
-        load_h(s);
+    for (int s = 0; s < H_STAGES; ++s) {
+        if (!DIRECT)
+            load_h(s);
+        else if (s & 1)
+            load_pair(s, 0), load_pair(s, 1);
+    }
 #pragma unroll
     for (int s = 0; s < D; ++s) {
         const int off = w_offset(s);
@@ -221,7 +243,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
-        fb[0][ni] = *(const bf16x8 *)(smem + frag_h + ni * FRAG_BYTES);
+        fb[0][ni] = *(const bf16x8 *)(smem + frag_h + ni * FRAG_STRIDE);
     int cstage = 0;  // stage of the step whose MFMAs are next
 
     // All K steps of MI fragments from f0 on, then the fold of their logits.  Before its last D steps the loads
@@ -239,12 +261,14 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
         // fragment reads of the current step have returned, so its stage can be loaded again.
         auto step = [&](auto p_const, int kt_load) {
             constexpr int P = decltype(p_const)::value, Q = P & 1;
-            wait_vmcnt<(H_STAGES - 2) * (H_LOADS + MI)>();
+            // (direct: pairs come with their odd steps, and an odd step waits for the pair behind it)
+            wait_vmcnt<DIRECT && Q ? (H_STAGES - 3) * MI + (H_STAGES - 4) * H_LOADS : (H_STAGES - 2) * (H_LOADS + MI)>();
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0), the other counters unconstrained
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
             const int nstage = cstage + 1 == H_STAGES ? 0 : cstage + 1;
-            const unsigned char *s = smem + nstage * H_STEP_BYTES + frag_h;
+            const unsigned char *s = DIRECT ? smem + (nstage >> 1) * 2 * H_STEP_BYTES + (frag_h ^ (Q ? 0u : DirectRows::ODD))
+                                            : smem + nstage * H_STEP_BYTES + frag_h;
             const int woff = w_offset(kt_load + P);
             // The order is pinned row by row: the fragment reads behind the first row's MFMAs, then in every row the
             // load of the row before it (whose registers are free by then), the hidden states' loads in rows 0 and 1.
@@ -253,12 +277,18 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
                 if (mi == 0) {
 #pragma unroll
                     for (int ni = 0; ni < NI; ++ni)
-                        fb[Q ^ 1][ni] = *(const bf16x8 *)(s + ni * FRAG_BYTES);
+                        fb[Q ^ 1][ni] = *(const bf16x8 *)(s + ni * FRAG_STRIDE);
                 } else {
                     wr[P][mi - 1] = load_fragment<STREAM_W>(rW, lane_w, woff + frag_off[mi - 1]);
                 }
-                if (mi == 1)
-                    load_h(cstage);
+                constexpr int SECOND = MI > 2 ? 2 : 1;  // (direct: the row of the second half of a pair's loads)
+                int h_loads = 0;
+                if (!DIRECT && mi == 1)
+                    load_h(cstage), h_loads = H_LOADS;
+                if (DIRECT && Q && mi == 1)
+                    load_pair(cstage, 0), h_loads += H_LOADS;
+                if (DIRECT && Q && mi == SECOND)
+                    load_pair(cstage, 1), h_loads += H_LOADS;
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
                     acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[P][mi], fb[Q][ni], acc[mi][ni], 0, 0, 0);
@@ -270,7 +300,7 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
                     }
                 } else {
 #pragma unroll
-                    for (int j = 0; j < (mi == 1 ? 1 + H_LOADS : 1); ++j) {
+                    for (int j = 0; j < 1 + h_loads; ++j) {
                         __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
                         __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
                     }
@@ -406,35 +436,36 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_stream_kernel(const unsigne
     }
 }
 
-template <int NI, int D, bool PIECES, bool STREAM_W>
-hipError_t launch(const void *hidden_packed, const void *w_packed, int64_t T, int kt, int V, const K1Plan &p, int group,
+template <int NI, int D, bool PIECES, bool STREAM_W, bool DIRECT>
+hipError_t launch(const void *hidden, const void *w_packed, int64_t T, int d, int kt, int V, const K1Plan &p, int group,
                   long wgs, float *part, int *pace, hipStream_t st)
 {
     using S = Shape<NI>;
-    static_assert(4 * S::TOKENS * 3 * sizeof(float) <= S::LDS_BYTES, "LDS");
+    constexpr int LDS_BYTES = DIRECT ? S::DIRECT_LDS_BYTES : S::LDS_BYTES;
+    static_assert(4 * S::TOKENS * 3 * sizeof(float) <= LDS_BYTES, "LDS");
     static DeviceMask lds_limit_raised{0};
-    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_stream_kernel<NI, D, PIECES, STREAM_W>, S::LDS_BYTES,
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_stream_kernel<NI, D, PIECES, STREAM_W, DIRECT>, LDS_BYTES,
                                                  lds_limit_raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((k1_entropy_stream_kernel<NI, D, PIECES, STREAM_W>), dim3((unsigned)wgs), dim3(256), S::LDS_BYTES, st,
-                       (const unsigned char *)w_packed, (const unsigned char *)hidden_packed, (long)T, kt, V, p.ntb,
+    hipLaunchKernelGGL((k1_entropy_stream_kernel<NI, D, PIECES, STREAM_W, DIRECT>), dim3((unsigned)wgs), dim3(256), LDS_BYTES, st,
+                       (const unsigned char *)w_packed, (const unsigned char *)hidden, (long)T, d, kt, V, p.ntb,
                        p.nsplit, p.tiles_per_split, p.ntiles_v, group, p.whole_cohorts, part, pace);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+hipError_t k1_entropy_stream(const void *hidden, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, int *pace, hipStream_t st)
 {
     const int kt = k_steps(K);
     if (T <= 0 || p.nsplit < 1 || p.tiles_per_split < 1 || (long)p.nsplit * p.tiles_per_split < p.ntiles_v ||
         (long)(p.nsplit - 1) * p.tiles_per_split >= p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
-        (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + p.tile_v - 1) / p.tile_v || kt > K1_STREAM_MAX_STEPS || (p.pieces && kt % K1_SPLIT_TERMS != 0))
+        (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + p.tile_v - 1) / p.tile_v || kt > K1_STREAM_MAX_STEPS || (p.pieces && (kt % K1_SPLIT_TERMS != 0 || p.direct)))
         return hipErrorInvalidValue;
     const int read = p.pieces ? kt / 2 : kt;  // blocks of W_lm that a sweep needs
-    const bool stream = p.ntb == 1 && (int64_t)p.ntiles_v * p.tile_v * read * ROW_BYTES > ((int64_t)256 << 20);
+    const bool stream = k1_plan_streams_w(p, read);
     const int group = p.tile_v == K1_STREAM_TILE_V ? k1_stream_group(p.nsplit) : 8;
     const long units = (long)p.ntb * p.nsplit, cohorts = k1_stream_cohorts(p.ntb, p.nsplit);
     const long wgs = p.whole_cohorts ? 8 * ((cohorts + 7) / 8) * COHORT : units;
@@ -442,10 +473,11 @@ hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, in
         return hipErrorInvalidValue;
     if (!k1_plan_paces(p))
         pace = nullptr;
-#define EGTP_STREAM_OF(NI, D, PIECES)                                                                           \
-    (stream ? launch<NI, D, PIECES, true>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st)      \
-            : launch<NI, D, PIECES, false>(hidden_packed, w_packed, T, kt, V, p, group, wgs, part, pace, st))
-#define EGTP_STREAM(NI, D) (p.pieces ? EGTP_STREAM_OF(NI, D, true) : EGTP_STREAM_OF(NI, D, false))
+#define EGTP_STREAM_OF(NI, D, PIECES, DIRECT)                                                                      \
+    (stream ? launch<NI, D, PIECES, true, DIRECT>(hidden, w_packed, T, K, kt, V, p, group, wgs, part, pace, st)      \
+            : launch<NI, D, PIECES, false, DIRECT>(hidden, w_packed, T, K, kt, V, p, group, wgs, part, pace, st))
+#define EGTP_STREAM(NI, D) \
+    (p.pieces ? EGTP_STREAM_OF(NI, D, true, false) : (p.direct ? EGTP_STREAM_OF(NI, D, false, true) : EGTP_STREAM_OF(NI, D, false, false)))
     if (p.tb_tokens == K1_STREAM_TOKENS && p.tile_v == K1_STREAM_TILE_V)
         return EGTP_STREAM(8, 2);
     if (p.tb_tokens == K1_STREAM_WIDE_TOKENS && p.tile_v == K1_NARROW_TILE_V)

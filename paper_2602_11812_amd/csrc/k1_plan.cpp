@@ -149,7 +149,31 @@ static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int V, long steps)
     return best;
 }
 
-K1Plan k1_plan(int dtype, int64_t T, int d, int V)
+// Whether a plan without the 256 x 256 tile reads bf16 hidden states where they are (the packing launch is 4 to 7 us, and packed rows past the
+// batch are read like others).  Whole passes, us, packed / direct:
+//   narrow   always: 24 tokens, d = 4096, V = 151936 220 / 209, 64 227 / 210, 12 tokens, d = 968, V = 20409 25.6 / 22.9, 571 tokens, d = 2528,
+//            V = 6951 62.1 / 58.0
+//   stream, 128 and 192 tokens, rows in whole lines of 128 bytes: 173, d = 4096, V = 151936 272 / 260, 100, d = 5120, V = 120000 223 / 212, 786,
+//            d = 3520, V = 119754 571 / 555
+//   rows that begin inside a line ask for two lines of each pair of steps: not for one block that streams W_lm past the Infinity Cache (173,
+//            d = 3000, V = 151936 204 / 226), nor where that outgrows the packing: 376, d = 4344, V = 115887, 3 sweeps of 136 steps 361 / 378; 249,
+//            d = 2136, V = 139839, 3 of 67 186 / 189, but 264, d = 1736, V = 104018, 3 of 55 153 / 138, 705, d = 1056, V = 68703, 4 of 33 124.5 /
+//            118.8; sweeps of two fragments a wave, of which the hidden states are half, count for one and a half: 412, d = 4184, V = 5774, 131 steps
+//            62.4 / 64.2, but 375, d = 3608, V = 9865, 113 steps 59.0 / 58.8
+static constexpr double DIRECT_STEPS = 180.0;
+
+static bool reads_directly(const K1Plan &p, int d, long steps)
+{
+    if (p.tile_v == K1_WIDE_TILE_V || k1_plan_paces(p))
+        return false;
+    if (p.tb_tokens == K1_NARROW_TOKENS || d % 64 == 0)
+        return true;
+    const int per_sweep = p.tile_v == K1_STREAM_TILE_V ? 8 : 2, shortest = per_sweep / 4 > 0 ? per_sweep / 4 : 1;
+    const int sweeps = (p.tiles_per_split + per_sweep - 1) / per_sweep;
+    return !k1_plan_streams_w(p, steps) && (double)sweeps * (double)steps * (p.tiles_per_split <= shortest ? 1.5 : 1.0) <= DIRECT_STEPS;
+}
+
+static K1Plan plan(int dtype, int64_t T, int d, int V)
 {
     K1Plan p;
     p.tb_tokens = TB;
@@ -206,6 +230,13 @@ K1Plan k1_plan(int dtype, int64_t T, int d, int V)
             break;
     }
     return cheaper(p, dtype, T, V, 2 * ((dk + 63) / 64));
+}
+
+K1Plan k1_plan(int dtype, int64_t T, int d, int V)
+{
+    K1Plan p = plan(dtype, T, d, V);
+    p.direct = dtype == DT_BF16 && reads_directly(p, d, 2 * ((d + 63) / 64));
+    return p;
 }
 
 size_t k1_partial_floats(const K1Plan &p, int64_t T) { return (size_t)3 * (size_t)p.nsplit * (size_t)T; }

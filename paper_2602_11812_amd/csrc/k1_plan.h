@@ -56,6 +56,8 @@ struct K1Plan {
     // fp32 operands, narrow and stream kernel: the sweep reads the three segments that hold each piece once, and the
     // hidden states are packed into those alone
     bool pieces = false;
+    // narrow (always) and stream kernel, bf16: hidden states are read where they are instead of from a packed copy
+    bool direct = false;
 };
 
 K1Plan k1_plan(int dtype, int64_t T, int d, int V);
@@ -87,6 +89,12 @@ inline bool k1_plan_paces(const K1Plan &p)
     if (p.tile_v == K1_STREAM_TILE_V)
         return p.tiles_per_split > K1_STREAM_PACE_TILES && p.ntb >= 16;
     return p.tile_v != K1_NARROW_TILE_V && p.tiles_per_split > K1_PACE_TILES && p.ntb >= 8;
+}
+// One token block reads W_lm once, `steps` packed blocks of every tile: whether the 256 MiB Infinity Cache cannot hold it until the next call either, so
+// that its loads carry the non-temporal hint.
+inline bool k1_plan_streams_w(const K1Plan &p, long steps)
+{
+    return p.ntb == 1 && (int64_t)p.ntiles_v * p.tile_v * steps * 64 > ((int64_t)256 << 20);
 }
 // counters that a plan paces with, to be zero when the fused kernel starts
 inline long k1_pace_ints(const K1Plan &p)

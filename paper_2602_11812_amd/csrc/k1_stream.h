@@ -41,6 +41,30 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t raw_buffer(const unsigned char
     return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, bytes, 0x00020000);
 }
 
+// Hidden states read where they are (row-major bf16, rows of 2 d bytes), two K steps at a time: 128 bytes of a row, a whole line, where the
+// 64 of one step would ask for every line twice.  In the LDS a row of two steps has eight places of 16 bytes, keyed by the row so
+// that the fragment reads meet all banks; a wave-wide load fills eight rows.  Rows past the batch lie past the descriptor, and K elements past d are
+// given an offset that does: the hardware makes zeros of both, and asks no memory for them.
+struct DirectRows {
+    int at, chunk;  // this lane's bytes of the first eight rows of its wave: from the block's begin, and inside a row
+    __device__ __forceinline__ DirectRows(int wave, int lane, int d) : chunk(((lane & 7) ^ (lane >> 3)) << 4) { at = (wave * 8 + (lane >> 3)) * 2 * d + chunk; }
+    // load number q (32 rows each) of the pair of steps that begins with kt
+    __device__ __forceinline__ int offset(int q, int kt, int d) const
+    {
+        return chunk < 2 * d - kt * ROW_BYTES ? at + q * 64 * d : (int)0x80000000;
+    }
+    // K step that the workgroups of vocabulary range `range` begin at (in turn to the last one, then from 0 on): where rows are a multiple
+    // of 4 KiB apart, a step's lines lie in one channel of the L2 or a few, and all workgroups would be at the same step.
+    static __device__ __forceinline__ int first_step(int range, int KT) { return (int)((unsigned)range * 4u % (unsigned)KT); }
+    static __device__ __forceinline__ __amdgpu_buffer_rsrc_t block(const unsigned char *hidden, long tok0, int tokens, long T, int d)
+    {
+        return raw_buffer(hidden + tok0 * 2 * d, (int)min((long)tokens, T - tok0) * 2 * d);
+    }
+    // this lane's 16 bytes of a fragment of 16 rows, even step; odd: ^ ODD
+    static __device__ __forceinline__ unsigned fragment(int lane) { return (lane & 15) * 2 * ROW_BYTES + (((lane >> 4) ^ (lane & 7)) << 4); }
+    static constexpr unsigned ODD = 64;
+};
+
 // Fold N logits of one token: zin[4*q+i] is vocabulary row row0 + 16*q + i.  MASK: rows from V on do not exist.
 // Whether a lane has any row at all follows from the row numbers: its maximum cannot tell, fmaxf passes over NaN.
 template <bool MASK, int N>

@@ -63,11 +63,11 @@ hipError_t k1_pack_rows_f32_split(const void *src, int64_t rows, int d, bool hid
 // of which the first k1_pace_ints(p) are zero, or NULL to run without pacing.
 hipError_t k1_entropy_bf16(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
                            const K1Plan &p, float *part, int *pace, hipStream_t st);
-// the same for a narrow plan (p.tile_v == K1_NARROW_TILE_V)
-hipError_t k1_entropy_narrow(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+// the same for a narrow plan (p.tile_v == K1_NARROW_TILE_V); p.direct: hidden states row-major, K their length
+hipError_t k1_entropy_narrow(const void *hidden, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, hipStream_t st);
 // ... and for a plan with p.tile_v == K1_STREAM_TILE_V
-hipError_t k1_entropy_stream(const void *hidden_packed, const void *w_packed, int64_t T, int K, int V,
+hipError_t k1_entropy_stream(const void *hidden, const void *w_packed, int64_t T, int K, int V,
                              const K1Plan &p, float *part, int *pace, hipStream_t st);
 // merges the nsplit partial triples of each token in a fixed order; entropy[t] = ln S - U/S
 hipError_t k1_merge(const float *part, int nsplit, int64_t T, float *entropy, hipStream_t st);
