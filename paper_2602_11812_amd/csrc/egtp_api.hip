@@ -54,6 +54,7 @@ struct Workspace {
     float *k1_part;      // partial triples of the fused kernel
     float *pool_part;    // of the pooling: partial rows of its units ...
     float *pool_stats;   // ... and two statistics each
+    size_t pool_floats;  // room for both
     int pool_unit;       // tokens per unit
     bool pool_merges;    // they leave the triples alone: the pooling can merge them itself
     float *lse_old;      // [B]
@@ -88,6 +89,7 @@ Workspace carve(const egtp_ctx *ctx, void *base, int64_t T, int32_t B)
     // batch of many empty sequences has too few, that of the triples, merged by then.
     w.pool_merges = pool_unit_floats(c.d, T, B, w.pool_unit) * sizeof(float) <= packed_bytes;
     w.pool_part = w.pool_merges ? (float *)w.hidden_packed : w.k1_part;
+    w.pool_floats = w.pool_merges ? packed_bytes / sizeof(float) : shared_floats;
     w.pool_stats = w.pool_part ? w.pool_part + (size_t)pool_units_bound(T, B, w.pool_unit) * (size_t)c.d : nullptr;
     w.w_packed = ctx->w_packed ? nullptr : cv.take<unsigned char>(k1_packed_bytes(c.vocab, K));
     w.bytes = cv.off;
@@ -701,8 +703,8 @@ egtp_status egtp_pool_ablation(egtp_ctx *ctx, const void *hidden, const int32_t 
     hipStream_t st = (hipStream_t)stream;
     const egtp_config &c = ctx->cfg;
     const Workspace w = carve(ctx, workspace, T, B);
-    EGTP_HIP(pool_plain(hidden, c.dtype, c.d, offsets_dev, B, T, (int)kind, w.pool_unit, w.pool_part, pooled_out,
-                        st));
+    EGTP_HIP(pool_plain(hidden, c.dtype, c.d, offsets_dev, B, T, (int)kind, w.pool_unit, w.pool_part, w.pool_floats,
+                        pooled_out, st));
     if (pred_out)
         return run_head(ctx, c.head_len, pooled_out, nullptr, B, w, pred_out, nullptr, st);
     return EGTP_OK;

@@ -314,6 +314,96 @@ __global__ __launch_bounds__(256) void pool_partial_kernel(
     }
 }
 
+// ---- average and maximum of long sequences: the batch dealt out evenly ------------------------
+// Bound: HBM, and how many streams it is read in.  Workgroup = (rows_per_wg rows of the batch, feature slice), whatever sequences they belong to;
+// two workgroups to a compute unit (three with slices of at most 128 chunks), which start together, read the same number of rows and end
+// together.  Units of a sequence's own 256 tokens were five or six workgroups to a compute unit, and the launch ended with the sixth: the
+// serving batch, 137720 tokens of d = 4096 in bf16, 207.6 us a pass; dealt evenly in five workgroups each 193, four 189, three 191, two 181
+// = 6.6 TB/s beside the head (sixteen rows in flight instead of eight 186).  Narrow slices have fewer bytes in flight: 108703 tokens, d = 344 38.4
+// us in units, in two, three, four workgroups 35.6, 33.1, 31.8; 60000, d = 512 29.6; 28.8, 25.8, 25.2; but 137720 of d = 264 in fp32 43.1; 42.2, 42.2, 45.9.
+// What workgroup w adds up of sequence b is unit w + b: no two meet, since w or b grows from one to the next.  A slice is an even share of the
+// 16-byte chunks of a row, at most one per thread (d = 2208 in bf16, 276 chunks, as 256 and 20: 59 us for 37008 tokens, as 138 and 138 42).  The number of
+// rows is odd: rows of 8 KiB dealt in 254 or 128 took 190 to 200 us instead of 173.
+template <bool BF16, int MODE>
+__global__ __launch_bounds__(256) void pool_rows_kernel(const void *__restrict__ hidden, int d, const int32_t *__restrict__ offsets, int32_t B,
+                                                        long T, int rows_per_wg, int ysplit, int slice, float *__restrict__ partial)
+{
+    constexpr int VEC = BF16 ? 8 : 4;  // elements per 16-byte load
+    __shared__ int first_sh;
+    const int w = blockIdx.x / ysplit, yslice = blockIdx.x - w * ysplit;
+    const int lo = w * rows_per_wg, hi = (int)min((long)lo + rows_per_wg, T);
+    // the first sequence that ends behind lo
+    int b;
+    if (B > UNIT_SCAN) {
+        int l = 0, h = B;
+        while (l < h) {
+            const int mid = (l + h) >> 1;
+            if (offsets[mid + 1] > lo)
+                h = mid;
+            else
+                l = mid + 1;
+        }
+        b = l;
+    } else {
+        if (threadIdx.x == 0)
+            first_sh = B;
+        __syncthreads();
+        for (int i = threadIdx.x; i < B; i += 256)
+            if (offsets[i + 1] > lo && (i == 0 || offsets[i] <= lo))
+                first_sh = i;
+        __syncthreads();
+        b = first_sh;
+    }
+    b = __builtin_amdgcn_readfirstlane(b);
+    const int nchunk = d / VEC, c = yslice * slice + threadIdx.x;
+    if ((int)threadIdx.x >= slice || c >= nchunk)
+        return;
+    const long stride = (long)d * (BF16 ? 2 : 4);
+    for (; b < B; ++b) {
+        const int begin = offsets[b];
+        if (begin >= hi)
+            break;
+        const int t0 = max(lo, begin), n = min(hi, offsets[b + 1]) - t0;
+        if (n <= 0)
+            continue;
+        float acc[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+            acc[e] = MODE == POOL_MAXIMUM ? NEG_INF : 0.f;
+        const unsigned char *p = (const unsigned char *)hidden + t0 * stride + (long)c * 16;
+        auto fold = [&](const u32x4 &q) {
+            float h[VEC];
+            widen16<BF16>(q, h);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+                acc[e] = MODE == POOL_MAXIMUM ? fmaxf(acc[e], h[e]) : acc[e] + h[e];
+        };
+        u32x4 q[8];  // eight rows in flight per thread
+        int i = 0;
+        for (; i + 8 <= n; i += 8) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                q[r] = stream_load16(p + (long)(i + r) * stride);
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                fold(q[r]);
+        }
+        if (i < n) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r)  // past the end: the last row, not used
+                q[r] = stream_load16(p + (long)min(i + r, n - 1) * stride);
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+                if (i + r < n)
+                    fold(q[r]);
+        }
+        float *out = partial + (long)(w + b) * d + (long)c * VEC;
+#pragma unroll
+        for (int e = 0; e < VEC; e += 4)
+            *(float4 *)(out + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+    }
+}
+
 // ---- joining a sequence's units ----------------------------------------------------------------
 // Workgroup = JOIN_COLS features of one sequence, four consecutive ones per thread; wave q combines the units
 // q, q + 4, ... of the sequence in order, JOIN_AHEAD of them fetched before any is used (one load at a time
@@ -379,18 +469,29 @@ __device__ __forceinline__ void sequence_units(const int32_t *__restrict__ offse
     u1 = min(u0 + (len > 0 ? (len + (1 << unit_log2) - 1) >> unit_log2 : 0), units_cap);
 }
 
-// Table 3 alternatives: sum / length, or maximum
+// the same for the units of pool_rows_kernel
+__device__ __forceinline__ void sequence_row_units(const int32_t *__restrict__ offsets, int b, long T, int rows_per_wg, long &u0, long &u1)
+{
+    const int t0 = (int)clamp_token(offsets[b], T), t1 = (int)clamp_token(offsets[b + 1], T);
+    u0 = t0 / rows_per_wg + b;
+    u1 = t1 > t0 ? (t1 - 1) / rows_per_wg + b + 1 : u0;
+}
+
+// Table 3 alternatives: sum / length, or maximum.  rows_per_wg > 0: the units are those of pool_rows_kernel
 template <int MODE>
 __global__ __launch_bounds__(256) void pool_finalize_plain_kernel(const float *__restrict__ partial,
                                                                   const int32_t *__restrict__ offsets, long T,
-                                                                  int d, int unit_log2, long units_cap,
+                                                                  int d, int unit_log2, int rows_per_wg, long units_cap,
                                                                   float *__restrict__ out_pooled)
 {
     __shared__ float4 waves[3][64];
     const int b = blockIdx.x;
     const int k = blockIdx.y * JOIN_COLS + (threadIdx.x & 63) * 4;
     long u0, u1;
-    sequence_units(offsets, b, T, unit_log2, units_cap, u0, u1);
+    if (rows_per_wg > 0)
+        sequence_row_units(offsets, b, T, rows_per_wg, u0, u1);
+    else
+        sequence_units(offsets, b, T, unit_log2, units_cap, u0, u1);
     const int len = offsets[b + 1] - offsets[b];
     const float init = (MODE == POOL_MAXIMUM && u1 > u0) ? NEG_INF : 0.f;  // an empty sequence pools to zero
     float4 r = make_float4(init, init, init, init);
@@ -629,6 +730,9 @@ __global__ __launch_bounds__(256) void pool_last_kernel(const void *__restrict__
 // leave fewer partials to write and join: average pooling of 137720 tokens takes 219 us with 256, 222 with 128, 233
 // with 64; of 10689 tokens, d = 2048, 30.3 us where 256 workgroups are asked for, 32.6 with 512 or 1024.
 constexpr int POOL_UNIT_MIN = 16, POOL_WORKGROUPS = 256;
+// Of pool_rows_kernel: mean length from which on.  A workgroup adds up its sequences one after the other: 1024 of them, d = 4096 in bf16, 20000 tokens 70.5 us
+// in units, 66.8 dealt; 3000, d = 2048, 40000 82.3, 86.7, in fp32 121, 112; 1024, d = 2048, 10000 38.2, 40.3.
+constexpr int POOL_ROWS_MEAN = 16;
 
 // workgroups a unit's features are spread over: one 16-byte chunk per thread
 static unsigned pool_feature_split(int d, bool bf16)
@@ -698,7 +802,7 @@ hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st)
 }
 
 hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offsets, int32_t B, int64_t T,
-                      int kind, int unit, float *partial, float *out_pooled, hipStream_t st)
+                      int kind, int unit, float *partial, size_t cap_floats, float *out_pooled, hipStream_t st)
 {
     if (B <= 0)
         return hipSuccess;
@@ -714,20 +818,34 @@ hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offse
                                out_pooled);
         return hipGetLastError();
     }
-    // average and maximum stream every token once: same units as Eq. 4
-    const long units = pool_units_bound(T, B, unit);
-    const int unit_log2 = __builtin_ctz(unit);
+    // average and maximum stream every token once
     const dim3 fgrid(B, (d + JOIN_COLS - 1) / JOIN_COLS);
     const unsigned ysplit = pool_feature_split(d, bf16);
+    const int nchunk = d / (bf16 ? 8 : 4), slice = (nchunk + (int)ysplit - 1) / (int)ysplit;
+    // The even deal for sequences of POOL_ROWS_MEAN tokens and more on average, rows of at most 64 slices, where its units fit.
+    int64_t deal = (int64_t)(slice > 128 ? 2 : 3) * 256 / ysplit;
+    deal = deal < 1 ? 1 : deal;
+    int64_t rows = (T + deal - 1) / deal;
+    rows = rows < POOL_UNIT_MIN ? POOL_UNIT_MIN : rows;
+    rows |= 1;  // (see pool_rows_kernel)
+    deal = (T + rows - 1) / rows;
+    const bool even = T >= (int64_t)POOL_ROWS_MEAN * B && slice <= 256 && (size_t)(deal + B) * (size_t)d <= cap_floats && deal * ysplit <= 0x7fffffffL;
+    // otherwise the same units as Eq. 4
+    const long units = even ? (long)(deal + B) : pool_units_bound(T, B, unit);
+    const int unit_log2 = __builtin_ctz(unit);
     if (units * ysplit > 0x7fffffffL)
         return hipErrorInvalidValue;
 #define EGTP_POOL_PLAIN(BF, MODE)                                                                          \
     do {                                                                                                   \
-        hipLaunchKernelGGL((pool_partial_kernel<BF, MODE>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, hidden, \
-                           d, nullptr, nullptr, 0, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
-                           partial, nullptr);                                                              \
+        if (even)                                                                                          \
+            hipLaunchKernelGGL((pool_rows_kernel<BF, MODE>), dim3((unsigned)(deal * ysplit)), dim3(256), 0, st, hidden, d, offsets, B, \
+                               (long)T, (int)rows, (int)ysplit, slice, partial);                           \
+        else                                                                                               \
+            hipLaunchKernelGGL((pool_partial_kernel<BF, MODE>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, hidden, \
+                               d, nullptr, nullptr, 0, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
+                               partial, nullptr);                                                          \
         hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, offsets, (long)T, d, \
-                           unit_log2, units, out_pooled);                                                  \
+                           unit_log2, even ? (int)rows : 0, units, out_pooled);                            \
     } while (0)
     if (kind == 0) {
         if (bf16)

@@ -113,9 +113,9 @@ struct PoolArgs {
 hipError_t pool_entropy_weighted(const PoolArgs &a, hipStream_t st);
 
 // Table 3 alternatives: kind 0 average, 1 max, 2 last token.  Average and max use units and partials
-// ([pool_units_bound(T, B, unit) x d]) like the weighted pooling.
+// ([pool_units_bound(T, B, unit) x d]) like the weighted pooling, or units of their own if these fit cap_floats.
 hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offsets, int32_t B, int64_t T,
-                      int kind, int unit, float *partial, float *out_pooled, hipStream_t st);
+                      int kind, int unit, float *partial, size_t cap_floats, float *out_pooled, hipStream_t st);
 
 // Prediction head.
 struct HeadArgs {

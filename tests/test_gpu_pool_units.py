@@ -170,3 +170,42 @@ def test_offsets_past_the_batch_pool_the_tokens_there_are(dtype, d):
         for a, b in zip(results(i32(*past)), results(i32(*cut))):
             assert np.array_equal(a, b), past
     sc.close()
+
+
+# (lengths, d): averages and maxima whose rows are dealt out evenly (16 tokens a sequence and more on average).  Deals of 17 rows, of more, the
+# last of one row; sequences that begin and end with a deal, beside it, and hold several; empty ones at both ends and between; more sequences than one
+# workgroup looks through at once; slices of uneven chunks, of one chunk, and more slices than one
+EVEN = [((17,), 8), ((18,), 136), ((1, 33, 0, 0, 17, 16, 18, 0, 51, 1, 300), 264), ((0, 0, 5000, 0), 2056), ((34, 17, 51, 68, 1, 16), 4104),
+        ((40000,), 64), ((16,) * 2100, 40), ((0,) * 900 + (33, 95, 1) * 500, 24), ((70000, 3, 61000), 8)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("lens,d", EVEN)
+def test_rows_dealt_out_evenly(lens, d, dtype):
+    """Against fp64: maxima exactly, averages to 1e-5 of a feature's root mean square (fp32 sums); the same for tables that leave out the first
+    and the last tokens, and for one that runs past the batch."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    B, T = len(lens), sum(lens)
+    rng = np.random.default_rng(B + d)
+    td = gpu.to_device
+    store = torch.bfloat16 if dtype == "bf16" else torch.float32
+    hidden = td(rng.standard_normal((T, d)).astype(np.float32)).to(store)
+    h = hidden.cpu().double().numpy()
+    sc = gpu.Scorer(torch.zeros(40, d, dtype=store, device="cuda"), gpu.make_head(torch.zeros(8, d, dtype=store, device="cuda"),
+                                                                                   torch.zeros(1, 8, dtype=store, device="cuda")))
+    full = np.concatenate([[0], np.cumsum(lens)])
+    for off in (full, np.clip(full, 3, T - 2), full + min(5, T)):
+        ws = sc.workspace(T, B)
+        for kind in (gpu.EGTP_POOL_AVERAGE, gpu.EGTP_POOL_MAX):
+            ws.fill_(255)
+            got = sc.pool_ablation(hidden, td(off.astype(np.int32)), kind, want_pred=False)[0].cpu().numpy().astype(np.float64)
+            for b in range(B):
+                x = h[min(off[b], T):min(off[b + 1], T)]
+                if len(x) == 0:
+                    assert not got[b].any()
+                elif kind == gpu.EGTP_POOL_MAX:
+                    assert np.array_equal(got[b], x.max(axis=0)), b
+                else:
+                    assert np.abs(got[b] - x.sum(axis=0) / (off[b + 1] - off[b])).max() <= 1e-5 * np.sqrt(np.mean(x * x)), b
+    sc.close()
