@@ -30,8 +30,8 @@ static constexpr int NSPLIT_SLACK = 8;  // how far above the minimum the number 
 //   narrow         199
 //   stream, 128    198   199   289   367   495   793  1123  3320  17450   38900
 //   stream, 192                236
-// (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964, where WORTH_IT
-// keeps the wide tile -- the 2.5 %; at d = 256 the folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
+// (d = 5120, 65088 tokens: wide 72.1 ms, stream 66.6; V = 32000, d = 2048, 10689 tokens: 986 us and 964, where
+// WORTH_IT_OTHERS keeps the wide tile -- the 2.5 %; at d = 256 the folds decide for the wide tile, 106 against 114 us for 5000 tokens.)
 static constexpr double WIDE_STEP_NS = 625.0, WIDE_STEP_NS_PER_DOUBLING = 18.5, WIDE_W_BYTES = 48e6, WIDE_FOLD_NS = 5000.0;
 static constexpr double NARROW_STEP_NS = 206.0, NARROW_PIECES_STEP_NS = 300.0, NARROW_FOLD_NS = 624.0, NARROW_PIECES_FOLD_NS = 1300.0;
 static constexpr double PAIR_STEP_NS = 700.0, SINGLE_STEP_NS = 410.0, PAIR_FOLD_NS = 4000.0;
@@ -39,12 +39,36 @@ static constexpr double STREAM_STEP_NS = 642.0, STREAM_ALONE_NS = 400.0, STREAM_
 static constexpr double STREAM_STEP4_NS = 406.0, STREAM_STEP2_NS = 288.0;
 static constexpr double WORKGROUP_NS = 3000.0, W_STREAM_BYTES_PER_NS = 5700.0;
 static constexpr long STREAM_MIN_STEPS = 8;  // below, folds are most of the work and the wide tile folds faster
-static constexpr double WORTH_IT = 0.955;  // another kernel than the wide one is worth this much of its price
+// Another kernel than the wide one is taken at this much of its price: of up to WORTH_IT_TOKENS, in whole cohorts, or else.  Whole passes, us, wide / stream: 187
+// tokens, d = 3152, V = 108446 216 / 178, 300, d = 3400, V = 31345 123 / 108, in fp32 160, d = 3048, V = 64460 499 / 433; whole cohorts: 46211, d = 2280, V = 123447
+// 19354 / 18497, 105153, d = 3344, V = 65385 35283 / 32145, in fp32 35094, d = 600, V = 73501 13643 / 12808, but, all priced 0.98 to 1.01 of the wide tile,
+// 16814, d = 1368, V = 87862 3096 / 3263, 37719, d = 4896, V = 19398 5300 / 5441, in fp32 19818, d = 4352, V = 15161 12672 / 13862; others: 6338, d = 2608,
+// V = 78554 1855 / 1896, 1217, d = 4096, V = 151936 1214 / 1232.
+static constexpr double WORTH_IT_FEW = 1.01, WORTH_IT_FEW_PIECES = 0.985, WORTH_IT_COHORTS = 0.97, WORTH_IT_OTHERS = 0.955;  // (pieces: fp32 operands)
+static constexpr int64_t WORTH_IT_TOKENS = 2 * K1_STREAM_WIDE_TOKENS;
+// What the packing launch of bf16 hidden states takes at the least, which plans that read them directly leave out; less where they then wait for the pieces of
+// unaligned rows.  Whole passes, us, wide / stream with this counted in: 595 tokens, d = 872, V = 15403 64 / 52, 1091, d = 616, V = 8145 56 / 46, 168, d = 600,
+// V = 113504 76 / 66, 3189, d = 1232, V = 9789 114 / 99; in full for 284, d = 4432, V = 14734, it would give 82 / 89.
+// Not counted up to STREAM_MIN_STEPS: 414, d = 256, V = 49778 53.5 / 54.4.
+static constexpr double PACK_NS = 3500.0;
 // Several rounds of the stream kernel, relative to one round or to whole cohorts of 16 token blocks x 2 ranges: cohorts
 // cut anywhere (65088 tokens, d = 5120, in 4 ranges 70.3 ms against 66.1; 137720, d = 4096, 122.7 against 116); whole
 // ones, per doubling of the ranges (64.6, 66.1, 67.1 ms in 2, 4, 8 ranges); all in one range (131072 tokens, d = 4096:
 // 119.0 ms against 109.3 in two).  The three factors rest on these eight launches of three batches, all against V = 151936.
 static constexpr double CUT_COHORTS = 1.05, MORE_RANGES = 0.017, ONE_RANGE = 1.09;
+
+// Ranges of the wide kernel (see plan): what a workgroup pays to start and finish, in steps; of the longer ones the longest sweep and
+// range, in steps, and what they have to gain
+static constexpr double START_STEPS = 8.0;
+static constexpr long SHORT_SWEEP = 24, RANGE_STEPS = 600;
+static constexpr double WORTH_LONGER = 0.98;
+
+static double wide_step_ns(const K1Plan &p, long steps)
+{
+    const double w_bytes = (double)p.ntiles_v * TV * (double)steps * 64.0;
+    const double doublings = w_bytes > WIDE_W_BYTES ? log2(w_bytes / WIDE_W_BYTES) : 0.0;
+    return WIDE_STEP_NS + WIDE_STEP_NS_PER_DOUBLING * (doublings < 5.0 ? doublings : 5.0);
+}
 
 // what a plan takes if a range of its takes range_ns
 static double plan_ns(const K1Plan &p, long steps, double range_ns)
@@ -77,16 +101,41 @@ static double stream_range_ns(const K1Plan &p, long steps)
     return ns;
 }
 
+// Whether a plan without the 256 x 256 tile reads bf16 hidden states where they are (the packing launch is 4 to 7 us, and packed rows past the
+// batch are read like others).  Whole passes, us, packed / direct:
+//   narrow   always: 24 tokens, d = 4096, V = 151936 220 / 209, 64 227 / 210, 12 tokens, d = 968, V = 20409 25.6 / 22.9, 571 tokens, d = 2528,
+//            V = 6951 62.1 / 58.0
+//   stream, 128 and 192 tokens, rows in whole lines of 128 bytes: 173, d = 4096, V = 151936 272 / 260, 100, d = 5120, V = 120000 223 / 212, 786,
+//            d = 3520, V = 119754 571 / 555
+//   rows that begin inside a line ask for two lines of each pair of steps: not for one block that streams W_lm past the Infinity Cache (173,
+//            d = 3000, V = 151936 204 / 226), nor where that outgrows the packing: 376, d = 4344, V = 115887, 3 sweeps of 136 steps 361 / 378; 249,
+//            d = 2136, V = 139839, 3 of 67 186 / 189, but 264, d = 1736, V = 104018, 3 of 55 153 / 138, 705, d = 1056, V = 68703, 4 of 33 124.5 /
+//            118.8; sweeps of two fragments a wave, of which the hidden states are half, count for one and a half: 412, d = 4184, V = 5774, 131 steps
+//            62.4 / 64.2, but 375, d = 3608, V = 9865, 113 steps 59.0 / 58.8
+static constexpr double DIRECT_STEPS = 180.0;
+
+// ns that a bf16 plan gains by reading the hidden states where they are; none: it does not
+static double direct_gain(const K1Plan &p, int d, long steps)
+{
+    if (p.tile_v == K1_WIDE_TILE_V || k1_plan_paces(p))
+        return 0.0;
+    if (p.tb_tokens == K1_NARROW_TOKENS || d % 64 == 0)
+        return PACK_NS;
+    const int per_sweep = p.tile_v == K1_STREAM_TILE_V ? 8 : 2, shortest = per_sweep / 4 > 0 ? per_sweep / 4 : 1;
+    const int sweeps = (p.tiles_per_split + per_sweep - 1) / per_sweep;
+    const double left = DIRECT_STEPS - (double)sweeps * (double)steps * (p.tiles_per_split <= shortest ? 1.5 : 1.0);
+    // (of 113 steps 59.0 / 58.8 above; 316 tokens, d = 5016, V = 15128, 158 steps, in plans without / with 88 / 98)
+    const double even = 1.0 - (DIRECT_STEPS - left) / 113.0;
+    return k1_plan_streams_w(p, steps) || left < 0.0 ? 0.0 : PACK_NS * (even > 1e-3 ? even : 1e-3);
+}
+
 // the plan of another kernel where that is cheaper than the wide plan p
-static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int V, long steps)
+static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int d, int V, long steps)
 {
     if (V <= TV || T <= 0)
         return p;  // a vocabulary inside one tile: there is nothing to divide
-    K1Plan best = p;
-    const double w_bytes = (double)p.ntiles_v * TV * (double)steps * 64.0;
-    const double doublings = w_bytes > WIDE_W_BYTES ? log2(w_bytes / WIDE_W_BYTES) : 0.0;
-    const double wide_step = WIDE_STEP_NS + WIDE_STEP_NS_PER_DOUBLING * (doublings < 5.0 ? doublings : 5.0);
-    double best_ns = WORTH_IT * plan_ns(p, steps, p.tiles_per_split * ((double)steps * wide_step + WIDE_FOLD_NS));
+    K1Plan best = p;  // of the others' plans the cheapest
+    double best_ns = -1.0;
     // Workspace is sized for what wide plans need at most: packed hidden states, partial triples, pacing counters.
     auto fits = [&](const K1Plan &q) {
         return (int64_t)q.ntb * q.tb_tokens <= (int64_t)p.ntb * TB &&
@@ -105,6 +154,18 @@ static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int V, long steps)
         // 160 tokens 196 -> 180 us, 256 240 -> 186; of more blocks, 1500 tokens, d = 1024, V = 8000 144 -> 152).
         q.pieces = dtype == DT_F32 && ((tb_tokens == K1_NARROW_TOKENS && tile_v == K1_NARROW_TILE_V) || q.ntb <= 2);
     };
+    // price of a plan of another kernel, `range_ns` a range
+    auto price = [&](const K1Plan &q, long read, double range_ns) {
+        const double worth = T <= WORTH_IT_TOKENS ? (dtype == DT_BF16 ? WORTH_IT_FEW : WORTH_IT_FEW_PIECES)
+                                                  : (q.whole_cohorts ? WORTH_IT_COHORTS : WORTH_IT_OTHERS);
+        return plan_ns(q, read, range_ns) / worth;
+    };
+    auto take = [&](const K1Plan &q, double ns, double at_least) {
+        if ((best_ns < 0.0 || ns < at_least * best_ns) && fits(q)) {
+            best_ns = ns;
+            best = q;
+        }
+    };
     K1Plan q;
     const int64_t blocks64 = (T + 63) / 64;
     const double narrow_step = dtype == DT_F32 ? NARROW_PIECES_STEP_NS : NARROW_STEP_NS;
@@ -122,11 +183,7 @@ static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int V, long steps)
                                      ? q.tiles_per_split * ((double)read * narrow_step + narrow_fold)
                                      : (q.tiles_per_split / 2) * ((double)steps * PAIR_STEP_NS + PAIR_FOLD_NS) +
                                            (q.tiles_per_split % 2) * ((double)steps * SINGLE_STEP_NS + PAIR_FOLD_NS / 2);
-            const double ns = plan_ns(q, read, range);
-            if (ns < best_ns && fits(q)) {
-                best_ns = ns;
-                best = q;
-            }
+            take(q, price(q, read, range), 1.0);
         }
     // 1, 2, 3, ... long ranges and as many as make one to four rounds of workgroups; paced plans in whole cohorts, too
     for (int i = 1; i <= 20 && steps >= STREAM_MIN_STEPS && steps <= K1_STREAM_MAX_STEPS; ++i) {
@@ -137,40 +194,14 @@ static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int V, long steps)
         cut(q, K1_STREAM_TOKENS, K1_STREAM_TILE_V, ranges);
         for (int whole = 0; whole <= (k1_plan_paces(q) ? 1 : 0); ++whole) {
             q.whole_cohorts = whole != 0;
-            const double ns = plan_ns(q, steps, stream_range_ns(q, steps));
             // (among plans of this kernel, fewer rounds of workgroups unless more are clearly cheaper)
-            if (ns < (best.tile_v == K1_STREAM_TILE_V ? 0.99 : 1.0) * best_ns && fits(q)) {
-                best_ns = ns;
-                best = q;
-            }
+            take(q, price(q, steps, stream_range_ns(q, steps)), best.tile_v == K1_STREAM_TILE_V ? 0.99 : 1.0);
         }
         q.whole_cohorts = false;
     }
-    return best;
-}
-
-// Whether a plan without the 256 x 256 tile reads bf16 hidden states where they are (the packing launch is 4 to 7 us, and packed rows past the
-// batch are read like others).  Whole passes, us, packed / direct:
-//   narrow   always: 24 tokens, d = 4096, V = 151936 220 / 209, 64 227 / 210, 12 tokens, d = 968, V = 20409 25.6 / 22.9, 571 tokens, d = 2528,
-//            V = 6951 62.1 / 58.0
-//   stream, 128 and 192 tokens, rows in whole lines of 128 bytes: 173, d = 4096, V = 151936 272 / 260, 100, d = 5120, V = 120000 223 / 212, 786,
-//            d = 3520, V = 119754 571 / 555
-//   rows that begin inside a line ask for two lines of each pair of steps: not for one block that streams W_lm past the Infinity Cache (173,
-//            d = 3000, V = 151936 204 / 226), nor where that outgrows the packing: 376, d = 4344, V = 115887, 3 sweeps of 136 steps 361 / 378; 249,
-//            d = 2136, V = 139839, 3 of 67 186 / 189, but 264, d = 1736, V = 104018, 3 of 55 153 / 138, 705, d = 1056, V = 68703, 4 of 33 124.5 /
-//            118.8; sweeps of two fragments a wave, of which the hidden states are half, count for one and a half: 412, d = 4184, V = 5774, 131 steps
-//            62.4 / 64.2, but 375, d = 3608, V = 9865, 113 steps 59.0 / 58.8
-static constexpr double DIRECT_STEPS = 180.0;
-
-static bool reads_directly(const K1Plan &p, int d, long steps)
-{
-    if (p.tile_v == K1_WIDE_TILE_V || k1_plan_paces(p))
-        return false;
-    if (p.tb_tokens == K1_NARROW_TOKENS || d % 64 == 0)
-        return true;
-    const int per_sweep = p.tile_v == K1_STREAM_TILE_V ? 8 : 2, shortest = per_sweep / 4 > 0 ? per_sweep / 4 : 1;
-    const int sweeps = (p.tiles_per_split + per_sweep - 1) / per_sweep;
-    return !k1_plan_streams_w(p, steps) && (double)sweeps * (double)steps * (p.tiles_per_split <= shortest ? 1.5 : 1.0) <= DIRECT_STEPS;
+    const double wide_ns = plan_ns(p, steps, p.tiles_per_split * ((double)steps * wide_step_ns(p, steps) + WIDE_FOLD_NS));
+    const double gain_ns = dtype == DT_BF16 && steps > STREAM_MIN_STEPS ? direct_gain(best, d, steps) : 0.0;
+    return best_ns >= 0.0 && best_ns - gain_ns < wide_ns ? best : p;
 }
 
 static K1Plan plan(int dtype, int64_t T, int d, int V)
@@ -178,64 +209,48 @@ static K1Plan plan(int dtype, int64_t T, int d, int V)
     K1Plan p;
     p.tb_tokens = TB;
     p.tile_v = TV;
-    const int target = TARGET_UNITS;
-    const long dk = k1_contraction_len(dtype, d);  // what a K sweep runs over
+    const long steps = 2 * ((k1_contraction_len(dtype, d) + 63) / 64);  // of a sweep over K
     p.ntb = (int)((T + p.tb_tokens - 1) / p.tb_tokens);
     p.ntiles_v = (V + p.tile_v - 1) / p.tile_v;
-    int ns0 = p.ntb > 0 ? (target + p.ntb - 1) / p.ntb : 1;
-    if (ns0 < 1)
-        ns0 = 1;
     p.nsplit = 1;
     p.tiles_per_split = p.ntiles_v;
-    if (ns0 >= p.ntiles_v) {
-        // A small batch: even one range per vocabulary tile gives fewer workgroups than asked for.  What
-        // counts then is the number of rounds the compute units need and what every workgroup pays to
-        // start and finish (filling the load ring, the final merge and stores: about START_STEPS K steps
-        // of a sweep of 2 ceil(K / 64) steps per tile).  512 tokens against 594 tiles are 1188 single-tile
-        // workgroups = 5 rounds of starts, or 238 workgroups of 5 tiles each = one round of the same length.
-        constexpr double START_STEPS = 6.0;
-        const double start_tiles = START_STEPS / (2.0 * (double)((dk + 63) / 64));
-        double best_cost = 0.0;
-        for (int tps = 1; tps <= p.ntiles_v && tps <= 64; ++tps) {
-            const int nsplit = (p.ntiles_v + tps - 1) / tps;
-            const long units = (long)p.ntb * nsplit;
-            const long rounds = (units + NUM_CUS - 1) / NUM_CUS;
-            const double cost = (double)rounds * ((double)tps + start_tiles);
-            if (tps == 1 || cost < best_cost - 1e-9) {
-                best_cost = cost;
-                p.nsplit = nsplit;
-                p.tiles_per_split = tps;
-            }
-        }
-        return cheaper(p, dtype, T, V, 2 * ((dk + 63) / 64));
-    }
-    // One workgroup per (token block, vocabulary range), one workgroup per compute unit at a
-    // time, all of about the same length: among the next few range counts take the one whose
-    // last round of workgroups is fullest.
-    double best = -1.0;
-    for (int ns = ns0; ns <= ns0 + NSPLIT_SLACK; ++ns) {
-        const int nsc = ns > p.ntiles_v ? p.ntiles_v : ns;
-        const int tps = (p.ntiles_v + nsc - 1) / nsc;
+    if (p.ntb <= 0)
+        return p;
+    // One workgroup per (token block, vocabulary range), one workgroup per compute unit at a time, all of about the same length: the
+    // number of tiles per range that is cheapest in rounds of workgroups, each of which also fills its ring and finishes.  512 tokens
+    // against 594 tiles are 1188 single-tile workgroups = 5 rounds of starts, or 238 workgroups of 5 tiles each = one round of the
+    // same length.
+    // Batches of more than TARGET_UNITS tiles take about as many workgroups: ranges of a few tiles.  Where a sweep is no more than SHORT_SWEEP steps their starts
+    // count, and longer ranges may be cheaper: kernel, us, tiles per range then / now: 7680 tokens, d = 256, V = 118784 2 657 / 14 571; 9520, d = 640,
+    // V = 60646 2 720 / 12 690; whole passes 8344, d = 328, V = 118344 2 827 / 15 718, 28500, d = 432, V = 28607 2 768 / 7 697.  Not for longer sweeps, whose
+    // ranges drift apart: 38353, d = 1160, V = 43820 3 3203, 6 3299; 96402, d = 4816, V = 6113 2 4601, 12 4950; nor where it is not WORTH_LONGER.
+    const int64_t most = ((int64_t)TARGET_UNITS + (1 + NSPLIT_SLACK) * (int64_t)p.ntb) / p.ntb;  // ranges that the workspace has room for
+    const int fewest = (int)((p.ntiles_v + most - 1) / most);
+    const int64_t target = ((int64_t)TARGET_UNITS + p.ntb - 1) / p.ntb;
+    const int ordinary = (int)((p.ntiles_v + target - 1) / target);  // for about TARGET_UNITS workgroups
+    const bool large = target < p.ntiles_v;
+    const double step_ns = wide_step_ns(p, steps), tile_ns = (double)steps * step_ns + WIDE_FOLD_NS;
+    double best = 0.0;
+    for (int tps = fewest; tps <= p.ntiles_v && tps < fewest + 64; ++tps) {
         const int nsplit = (p.ntiles_v + tps - 1) / tps;
-        const long units = (long)p.ntb * nsplit;
-        const long rounds = (units + NUM_CUS - 1) / NUM_CUS;
-        // time ~ rounds * tiles per range; work = ntb * ntiles_v tile sweeps on NUM_CUS units
-        const double fill = rounds > 0 ? (double)p.ntb * p.ntiles_v / ((double)rounds * tps * NUM_CUS) : 0.0;
-        if (fill > best + 1e-9) {
-            best = fill;
+        const bool longer = large && tps > ordinary;
+        if (longer && (steps > SHORT_SWEEP || tps * steps > RANGE_STEPS))
+            break;
+        const long rounds = ((long)p.ntb * nsplit + NUM_CUS - 1) / NUM_CUS;
+        const double cost = (double)rounds * ((double)tps * tile_ns + START_STEPS * step_ns);
+        if (tps == fewest || cost < (longer ? WORTH_LONGER : 1.0) * best) {
+            best = cost;
             p.nsplit = nsplit;
             p.tiles_per_split = tps;
         }
-        if (nsc == p.ntiles_v)
-            break;
     }
-    return cheaper(p, dtype, T, V, 2 * ((dk + 63) / 64));
+    return cheaper(p, dtype, T, d, V, steps);
 }
 
 K1Plan k1_plan(int dtype, int64_t T, int d, int V)
 {
     K1Plan p = plan(dtype, T, d, V);
-    p.direct = dtype == DT_BF16 && reads_directly(p, d, 2 * ((d + 63) / 64));
+    p.direct = dtype == DT_BF16 && direct_gain(p, d, 2 * ((d + 63) / 64)) > 0.0;
     return p;
 }
 

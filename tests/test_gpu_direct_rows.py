@@ -30,7 +30,7 @@ CASES = [
     (216, 5422, 338, 128, 64, True), (264, 16511, 65, 128, 64, True), (320, 33136, 128, 128, 64, True), (248, 33136, 66, 128, 64, True),
     (512, 17000, 100, 128, 64, True), (4184, 5774, 412, 128, 64, False), (3000, 50000, 127, 128, 64, False),
     (1000, 32000, 191, 192, 128, True), (1024, 32000, 192, 192, 128, True), (40, 52583, 565, 192, 128, True), (904, 70000, 130, 192, 128, True),
-    (4856, 5110, 816, 192, 128, False),
+    (5216, 5414, 713, 192, 128, False),
 ]
 
 
