@@ -15,6 +15,7 @@
 #include <type_traits>
 
 #include "k1_common.h"
+#include "pool_deal.h"
 #include "stream_load.h"
 #include "wave_reduce.h"
 
@@ -363,7 +364,8 @@ __global__ __launch_bounds__(256) void pool_rows_kernel(const void *__restrict__
         const int begin = offsets[b];
         if (begin >= hi)
             break;
-        const int t0 = max(lo, begin), n = min(hi, offsets[b + 1]) - t0;
+        const RowRun run = dealt_rows(lo, hi, begin, offsets[b + 1], T);
+        const int t0 = run.begin, n = run.end - run.begin;
         if (n <= 0)
             continue;
         float acc[VEC];

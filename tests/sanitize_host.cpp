@@ -7,6 +7,7 @@
 // array, a signed overflow or a misaligned access ends the program; the results are checked
 // against hand-derived values (Eq. 2-4 on a d = 2, V = 4 example; closed forms) and invariants.
 // Exit status 0 = everything passed and no sanitizer report.  No GPU, no HIP runtime.
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdio>
@@ -18,6 +19,7 @@
 
 #include "../include/egtp_sched.h"
 #include "../paper_2602_11812_amd/csrc/k1_plan.h"
+#include "../paper_2602_11812_amd/csrc/pool_deal.h"
 
 extern "C" {
 int oracle_offsets(const int32_t *lengths, int32_t B, int32_t *offsets);
@@ -345,6 +347,28 @@ void plan_checks()
     CHECK(one_tile.nsplit == 1 && one_tile.tiles_per_split == 1 && !k1_plan_paces(one_tile));
 }
 
+// Rows that a dealt workgroup reads, for offsets of any value: inside its own rows, and as many as 64-bit arithmetic finds.
+void pool_deal_checks()
+{
+    constexpr int32_t LOW = std::numeric_limits<int32_t>::min(), HIGH = std::numeric_limits<int32_t>::max();
+    Rng rng(77);
+    auto any = [&](int64_t T) -> int32_t {
+        const int32_t edges[] = {LOW, LOW + 1, LOW + 40, -1, 0, 1, (int32_t)T, (int32_t)(T - 1), HIGH, HIGH - 1};
+        const int pick = rng.below(16);
+        return pick < 10 ? edges[pick] : (int32_t)rng.next();
+    };
+    for (int i = 0; i < 200000; ++i) {
+        const int64_t T = i % 5 == 0 ? HIGH : 1 + rng.below(i % 3 == 0 ? 40 : 1 << 20);
+        const int lo = rng.below((int)T), hi = lo + 1 + rng.below((int)(T - lo));
+        const int32_t first = any(T), last = any(T);
+        const egtp::RowRun r = egtp::dealt_rows(lo, hi, first, last, T);
+        const int n = r.end - r.begin;
+        const int64_t begin = std::max<int64_t>(lo, first), end = std::min<int64_t>(hi, last);
+        CHECK(n <= 0 || (lo <= r.begin && r.end <= hi));
+        CHECK(n > 0 ? (r.begin == begin && r.end == end) : end <= begin);
+    }
+}
+
 }  // namespace
 
 int main()
@@ -354,6 +378,7 @@ int main()
     oracle_ragged_sweep();
     sched_checks();
     plan_checks();
+    pool_deal_checks();
     if (failures) {
         std::fprintf(stderr, "%d check(s) failed\n", failures);
         return 1;
