@@ -315,7 +315,7 @@ __global__ __launch_bounds__(256) void pool_partial_kernel(
     }
 }
 
-// ---- average and maximum of long sequences: the batch dealt out evenly ------------------------
+// ---- average and maximum of large batches: the batch dealt out evenly ------------------------
 // Bound: HBM, and how many streams it is read in.  Workgroup = (rows_per_wg rows of the batch, feature slice), whatever sequences they belong to;
 // two workgroups to a compute unit (three with slices of at most 128 chunks), which start together, read the same number of rows and end
 // together.  Units of a sequence's own 256 tokens were five or six workgroups to a compute unit, and the launch ended with the sixth: the
@@ -325,85 +325,94 @@ __global__ __launch_bounds__(256) void pool_partial_kernel(
 // What workgroup w adds up of sequence b is unit w + b: no two meet, since w or b grows from one to the next.  A slice is an even share of the
 // 16-byte chunks of a row, at most one per thread (d = 2208 in bf16, 276 chunks, as 256 and 20: 59 us for 37008 tokens, as 138 and 138 42).  The number of
 // rows is odd: rows of 8 KiB dealt in 254 or 128 took 190 to 200 us instead of 173.
+// Rows are asked for ahead of the sequences' ends (pool_deal.h), which lie in the LDS; a wave holds 64 of them in its lanes and looks through
+// these at once for the next sequence that is not empty.
 template <bool BF16, int MODE>
 __global__ __launch_bounds__(256) void pool_rows_kernel(const void *__restrict__ hidden, int d, const int32_t *__restrict__ offsets, int32_t B,
                                                         long T, int rows_per_wg, int ysplit, int slice, float *__restrict__ partial)
 {
     constexpr int VEC = BF16 ? 8 : 4;  // elements per 16-byte load
+    constexpr int AHEAD = 8;           // rows in flight per thread
+    __shared__ int ends[POOL_DEAL_SEQUENCES];
     __shared__ int first_sh;
-    const int w = blockIdx.x / ysplit, yslice = blockIdx.x - w * ysplit;
+    const int w = blockIdx.x / ysplit, yslice = blockIdx.x - w * ysplit, lane = threadIdx.x & 63;
     const int lo = w * rows_per_wg, hi = (int)min((long)lo + rows_per_wg, T);
-    // the first sequence that ends behind lo
-    int b;
-    if (B > UNIT_SCAN) {
-        int l = 0, h = B;
-        while (l < h) {
-            const int mid = (l + h) >> 1;
-            if (offsets[mid + 1] > lo)
-                h = mid;
-            else
-                l = mid + 1;
-        }
-        b = l;
-    } else {
-        if (threadIdx.x == 0)
-            first_sh = B;
-        __syncthreads();
-        for (int i = threadIdx.x; i < B; i += 256)
-            if (offsets[i + 1] > lo && (i == 0 || offsets[i] <= lo))
-                first_sh = i;
-        __syncthreads();
-        b = first_sh;
+    // the first row that belongs to a sequence, and the sequence
+    const int begin = max(lo, inside_batch(offsets[0], T)), n = hi - begin;
+    if (threadIdx.x == 0)
+        first_sh = B;
+    __syncthreads();
+    int first = B;
+    for (int i = threadIdx.x; i < B; i += 256) {
+        ends[i] = inside_batch(offsets[i + 1], T);
+        if (ends[i] > begin)
+            first = min(first, i);
     }
-    b = __builtin_amdgcn_readfirstlane(b);
-    const int nchunk = d / VEC, c = yslice * slice + threadIdx.x;
-    if ((int)threadIdx.x >= slice || c >= nchunk)
+    if (first < B)
+        atomicMin(&first_sh, first);
+    __syncthreads();
+    const int b = __builtin_amdgcn_readfirstlane(first_sh);
+    // (lanes behind the slice read and write its last chunk as well: no lane is idle where the wave looks through its ends)
+    const int first_chunk = yslice * slice, last_chunk = min(first_chunk + slice, d / VEC) - 1;
+    if (b == B || n <= 0 || first_chunk + ((int)threadIdx.x & ~63) > last_chunk)
         return;
+    const int c = min(first_chunk + (int)threadIdx.x, last_chunk);
     const long stride = (long)d * (BF16 ? 2 : 4);
-    for (; b < B; ++b) {
-        const int begin = offsets[b];
-        if (begin >= hi)
-            break;
-        const RowRun run = dealt_rows(lo, hi, begin, offsets[b + 1], T);
-        const int t0 = run.begin, n = run.end - run.begin;
-        if (n <= 0)
-            continue;
-        float acc[VEC];
+    const unsigned char *p = (const unsigned char *)hidden + begin * stride + (long)c * 16;
+    float acc[VEC];
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+        acc[e] = MODE == POOL_MAXIMUM ? NEG_INF : 0.f;
+    auto add = [&](const u32x4 &q) {
+        float h[VEC];
+        widen16<BF16>(q, h);
 #pragma unroll
         for (int e = 0; e < VEC; ++e)
-            acc[e] = MODE == POOL_MAXIMUM ? NEG_INF : 0.f;
-        const unsigned char *p = (const unsigned char *)hidden + t0 * stride + (long)c * 16;
-        auto fold = [&](const u32x4 &q) {
-            float h[VEC];
-            widen16<BF16>(q, h);
+            acc[e] = MODE == POOL_MAXIMUM ? fmaxf(acc[e], h[e]) : acc[e] + h[e];
+    };
+    // where 64 sequences from `base` on end, one to a lane
+    auto window_at = [&](int base) { return base + lane < B ? ends[base + lane] - begin : INT32_MIN; };
+    int base = b, window = window_at(b);
+    u32x4 some[AHEAD];
+    walk_rows<AHEAD>(
+        n, b, B,
+        [&](int i) {
+            const unsigned char *at = p + i * stride;
+            u32x4 q[AHEAD];
 #pragma unroll
-            for (int e = 0; e < VEC; ++e)
-                acc[e] = MODE == POOL_MAXIMUM ? fmaxf(acc[e], h[e]) : acc[e] + h[e];
-        };
-        u32x4 q[8];  // eight rows in flight per thread
-        int i = 0;
-        for (; i + 8 <= n; i += 8) {
+            for (int r = 0; r < AHEAD; ++r)
+                q[r] = stream_load16(at + r * stride);
 #pragma unroll
-            for (int r = 0; r < 8; ++r)
-                q[r] = stream_load16(p + (long)(i + r) * stride);
+            for (int r = 0; r < AHEAD; ++r)
+                add(q[r]);
+        },
+        [&](int i) {
 #pragma unroll
-            for (int r = 0; r < 8; ++r)
-                fold(q[r]);
-        }
-        if (i < n) {
+            for (int r = 0; r < AHEAD; ++r)  // past the end: the last row, not used
+                some[r] = stream_load16(p + min(i + r, n - 1) * stride);
 #pragma unroll
-            for (int r = 0; r < 8; ++r)  // past the end: the last row, not used
-                q[r] = stream_load16(p + (long)min(i + r, n - 1) * stride);
+            for (int r = 0; r < AHEAD; ++r)
+                asm volatile("" : "+v"(some[r]));
+        },
+        [&](int r) { widen16<BF16>(some[r], acc); }, [&](int r) { add(some[r]); },
+        [&](int at) { return __builtin_amdgcn_readlane(window, at - base); },
+        [&](int at, int row) {
+            unsigned long long more = __ballot(window > row) & ~1ull << (at - base);
+            while (more == 0) {
+                base += 64;
+                if (base >= B)
+                    return B;
+                window = window_at(base);
+                more = __ballot(window > row);
+            }
+            return base + __builtin_ctzll(more);
+        },
+        [&](int at) {
+            float *out = partial + (long)(w + at) * d + (long)c * VEC;
 #pragma unroll
-            for (int r = 0; r < 8; ++r)
-                if (i + r < n)
-                    fold(q[r]);
-        }
-        float *out = partial + (long)(w + b) * d + (long)c * VEC;
-#pragma unroll
-        for (int e = 0; e < VEC; e += 4)
-            *(float4 *)(out + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
-    }
+            for (int e = 0; e < VEC; e += 4)
+                *(float4 *)(out + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+        });
 }
 
 // ---- joining a sequence's units ----------------------------------------------------------------
@@ -732,9 +741,6 @@ __global__ __launch_bounds__(256) void pool_last_kernel(const void *__restrict__
 // leave fewer partials to write and join: average pooling of 137720 tokens takes 219 us with 256, 222 with 128, 233
 // with 64; of 10689 tokens, d = 2048, 30.3 us where 256 workgroups are asked for, 32.6 with 512 or 1024.
 constexpr int POOL_UNIT_MIN = 16, POOL_WORKGROUPS = 256;
-// Of pool_rows_kernel: mean length from which on.  A workgroup adds up its sequences one after the other: 1024 of them, d = 4096 in bf16, 20000 tokens 70.5 us
-// in units, 66.8 dealt; 3000, d = 2048, 40000 82.3, 86.7, in fp32 121, 112; 1024, d = 2048, 10000 38.2, 40.3.
-constexpr int POOL_ROWS_MEAN = 16;
 
 // workgroups a unit's features are spread over: one 16-byte chunk per thread
 static unsigned pool_feature_split(int d, bool bf16)
@@ -824,30 +830,25 @@ hipError_t pool_plain(const void *hidden, int dtype, int d, const int32_t *offse
     const dim3 fgrid(B, (d + JOIN_COLS - 1) / JOIN_COLS);
     const unsigned ysplit = pool_feature_split(d, bf16);
     const int nchunk = d / (bf16 ? 8 : 4), slice = (nchunk + (int)ysplit - 1) / (int)ysplit;
-    // The even deal for sequences of POOL_ROWS_MEAN tokens and more on average, rows of at most 64 slices, where its units fit.
-    int64_t deal = (int64_t)(slice > 128 ? 2 : 3) * 256 / ysplit;
-    deal = deal < 1 ? 1 : deal;
-    int64_t rows = (T + deal - 1) / deal;
-    rows = rows < POOL_UNIT_MIN ? POOL_UNIT_MIN : rows;
-    rows |= 1;  // (see pool_rows_kernel)
-    deal = (T + rows - 1) / rows;
-    const bool even = T >= (int64_t)POOL_ROWS_MEAN * B && slice <= 256 && (size_t)(deal + B) * (size_t)d <= cap_floats && deal * ysplit <= 0x7fffffffL;
-    // otherwise the same units as Eq. 4
-    const long units = even ? (long)(deal + B) : pool_units_bound(T, B, unit);
+    // The even deal (rows of at most 64 slices) where the rule is for it and its units fit ...
+    const Deal deal = pool_deal(T, B, slice, ysplit, bf16);
+    const bool even = deal.even && slice <= 256 && (size_t)(deal.deals + B) * (size_t)d <= cap_floats && deal.deals * ysplit <= 0x7fffffffL;
+    // ... otherwise the same units as Eq. 4
+    const long units = even ? (long)(deal.deals + B) : pool_units_bound(T, B, unit);
     const int unit_log2 = __builtin_ctz(unit);
     if (units * ysplit > 0x7fffffffL)
         return hipErrorInvalidValue;
 #define EGTP_POOL_PLAIN(BF, MODE)                                                                          \
     do {                                                                                                   \
         if (even)                                                                                          \
-            hipLaunchKernelGGL((pool_rows_kernel<BF, MODE>), dim3((unsigned)(deal * ysplit)), dim3(256), 0, st, hidden, d, offsets, B, \
-                               (long)T, (int)rows, (int)ysplit, slice, partial);                           \
+            hipLaunchKernelGGL((pool_rows_kernel<BF, MODE>), dim3((unsigned)(deal.deals * ysplit)), dim3(256), 0, st, hidden, d, offsets, B, \
+                               (long)T, (int)deal.rows, (int)ysplit, slice, partial);                           \
         else                                                                                               \
             hipLaunchKernelGGL((pool_partial_kernel<BF, MODE>), dim3((unsigned)(units * ysplit)), dim3(256), 0, st, hidden, \
                                d, nullptr, nullptr, 0, offsets, B, (long)T, 0.f, unit_log2, (int)ysplit, nullptr, nullptr, nullptr,    \
                                partial, nullptr);                                                          \
         hipLaunchKernelGGL(pool_finalize_plain_kernel<MODE>, fgrid, dim3(256), 0, st, partial, offsets, (long)T, d, \
-                           unit_log2, even ? (int)rows : 0, units, out_pooled);                            \
+                           unit_log2, even ? (int)deal.rows : 0, units, out_pooled);                            \
     } while (0)
     if (kind == 0) {
         if (bf16)

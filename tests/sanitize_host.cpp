@@ -347,7 +347,7 @@ void plan_checks()
     CHECK(one_tile.nsplit == 1 && one_tile.tiles_per_split == 1 && !k1_plan_paces(one_tile));
 }
 
-// Rows that a dealt workgroup reads, for offsets of any value: inside its own rows, and as many as 64-bit arithmetic finds.
+// Offsets of any value become rows of the batch, whose differences fit 32 bits.
 void pool_deal_checks()
 {
     constexpr int32_t LOW = std::numeric_limits<int32_t>::min(), HIGH = std::numeric_limits<int32_t>::max();
@@ -359,13 +359,98 @@ void pool_deal_checks()
     };
     for (int i = 0; i < 200000; ++i) {
         const int64_t T = i % 5 == 0 ? HIGH : 1 + rng.below(i % 3 == 0 ? 40 : 1 << 20);
-        const int lo = rng.below((int)T), hi = lo + 1 + rng.below((int)(T - lo));
         const int32_t first = any(T), last = any(T);
-        const egtp::RowRun r = egtp::dealt_rows(lo, hi, first, last, T);
-        const int n = r.end - r.begin;
-        const int64_t begin = std::max<int64_t>(lo, first), end = std::min<int64_t>(hi, last);
-        CHECK(n <= 0 || (lo <= r.begin && r.end <= hi));
-        CHECK(n > 0 ? (r.begin == begin && r.end == end) : end <= begin);
+        const int begin = egtp::inside_batch(first, T), end = egtp::inside_batch(last, T);
+        CHECK(begin == std::min<int64_t>(std::max<int64_t>(first, 0), T) && end - begin == (int64_t)end - begin);
+    }
+}
+
+// Dealt out are batches whose sequences, however they fall, are few beside the rows of a workgroup.
+void pool_rule_checks()
+{
+    auto even = [](int64_t T, int32_t B, int d, bool bf16) {
+        const int chunks = d / (bf16 ? 8 : 4), ysplit = std::min((chunks + 255) / 256, 64);
+        const egtp::Deal deal = egtp::pool_deal(T, B, (chunks + ysplit - 1) / ysplit, ysplit, bf16);
+        CHECK(deal.rows % 2 == 1 && deal.rows >= 17 && (deal.deals - 1) * deal.rows < T && deal.deals * deal.rows >= T);
+        return deal.even;
+    };
+    CHECK(even(137720, 134, 4096, true) && !even(137720, 135, 4096, true) && !even(137720, 8000, 4096, true));
+    CHECK(even(137720, 134, 1024, false) && !even(137720, 135, 1024, false) && !even(137720, 67, 512, false));
+    CHECK(even(137720, 45, 344, true) && !even(137720, 46, 344, true) && even(69120, 1, 344, true) && !even(68352, 1, 344, true));
+    CHECK(even(46080, 22, 2048, true) && !even(45568, 1, 2048, true) && !even(17, 1, 8, true) && !even(1, 1, 8, true));
+    CHECK(even(2147483647, 2048, 1 << 20, true) && !even(2147483647, 2049, 1 << 20, true));
+}
+
+// Every row of a batch goes to its sequence once, and what a workgroup leaves of a sequence is the unit that the join looks for; whatever the
+// offsets hold, only the workgroup's own rows are loaded and only its own units written.
+void pool_walk_checks()
+{
+    constexpr int AHEAD = 8;
+    Rng rng(78);
+    for (int round = 0; round < 4000; ++round) {
+        const bool sound = round % 4 != 0;
+        const int B = 1 + rng.below(round % 2 ? 12 : 200);
+        std::vector<int32_t> offsets(1, rng.below(5));
+        for (int b = 0; b < B; ++b) {
+            const int kind = rng.below(10);
+            offsets.push_back(offsets.back() + (kind < 4 ? 0 : kind < 7 ? 1 : kind < 9 ? rng.below(20) : rng.below(300)));
+        }
+        const int T = std::max(1, offsets.back() + rng.below(4) - (round % 8 == 1 ? 3 : 0));  // (or a table that runs past the batch)
+        if (!sound)
+            for (int i = 0; i < 3; ++i)
+                offsets[(size_t)rng.below(B + 1)] = rng.below(2) ? (int32_t)rng.next() : rng.below(2 * T);
+        const int rows = 1 + 2 * rng.below(40), deals = (T + rows - 1) / rows;
+        auto inside = [&](int i) { return egtp::inside_batch(offsets[(size_t)i], T); };
+        std::vector<int> owner((size_t)T, -1), units((size_t)(deals + B), 0);
+        for (int w = 0; w < deals; ++w) {
+            const int lo = w * rows, hi = std::min(lo + rows, T);
+            const int begin = std::max(lo, inside(0)), n = hi - begin;
+            int b = 0;
+            while (b < B && inside(b + 1) <= begin)
+                ++b;
+            if (b == B || n <= 0)
+                continue;
+            int at = 0, current = b, folded = 0;
+            auto add = [&](int row) {
+                CHECK(row < n && owner[(size_t)(begin + row)] == -1);
+                owner[(size_t)(begin + row)] = current;
+                ++folded;
+            };
+            egtp::walk_rows<AHEAD>(
+                n, b, B,
+                [&](int i) {
+                    for (int r = 0; r < AHEAD; ++r)
+                        add(i + r);
+                },
+                [&](int i) { at = i; },
+                [&](int r) {
+                    CHECK(folded == 0);
+                    add(at + r);
+                },
+                [&](int r) { add(at + r); }, [&](int i) { return inside(i + 1) - begin; },
+                [&](int i, int row) {
+                    do
+                        ++i;
+                    while (i < B && inside(i + 1) - begin <= row);
+                    return current = i;
+                },
+                [&](int i) {
+                    CHECK(i == current && (folded > 0 || !sound));
+                    ++units[(size_t)(w + i)];
+                    folded = 0;
+                });
+        }
+        for (int n : units)
+            CHECK(n <= 1);
+        if (!sound)
+            continue;
+        for (int t = 0; t < T; ++t) {
+            const int b = owner[(size_t)t];
+            CHECK(b < 0 ? t < offsets[0] || t >= offsets[(size_t)B] : offsets[(size_t)b] <= t && t < offsets[(size_t)b + 1]);
+        }
+        for (int b = 0; b < B; ++b)
+            for (int u = inside(b) / rows + b; inside(b + 1) > inside(b) && u <= (inside(b + 1) - 1) / rows + b; ++u)
+                CHECK(units[(size_t)u] == 1);
     }
 }
 
@@ -379,6 +464,8 @@ int main()
     sched_checks();
     plan_checks();
     pool_deal_checks();
+    pool_rule_checks();
+    pool_walk_checks();
     if (failures) {
         std::fprintf(stderr, "%d check(s) failed\n", failures);
         return 1;

@@ -172,9 +172,9 @@ def test_offsets_past_the_batch_pool_the_tokens_there_are(dtype, d):
     sc.close()
 
 
-# (lengths, d): averages and maxima whose rows are dealt out evenly (16 tokens a sequence and more on average).  Deals of 17 rows, of more, the
-# last of one row; sequences that begin and end with a deal, beside it, and hold several; empty ones at both ends and between; more sequences than one
-# workgroup looks through at once; slices of uneven chunks, of one chunk, and more slices than one
+# (lengths, d): averages and maxima in units of the sequences' own, the last batch dealt out evenly.  Sequences of a unit's tokens, one more, several units;
+# empty ones at both ends and between; more sequences than one workgroup looks through at once; slices of uneven chunks, of one chunk,
+# and more slices than one
 EVEN = [((17,), 8), ((18,), 136), ((1, 33, 0, 0, 17, 16, 18, 0, 51, 1, 300), 264), ((0, 0, 5000, 0), 2056), ((34, 17, 51, 68, 1, 16), 4104),
         ((40000,), 64), ((16,) * 2100, 40), ((0,) * 900 + (33, 95, 1) * 500, 24), ((70000, 3, 61000), 8)]
 
@@ -208,4 +208,41 @@ def test_rows_dealt_out_evenly(lens, d, dtype):
                     assert np.array_equal(got[b], x.max(axis=0)), b
                 else:
                     assert np.abs(got[b] - x.sum(axis=0) / (off[b + 1] - off[b])).max() <= 1e-5 * np.sqrt(np.mean(x * x)), b
+    sc.close()
+
+
+# Batches that are dealt out: few sequences beside the rows of a workgroup, at least 90 of these.  Short and empty ones side by side, whose ends are closer together than
+# the eight rows that are loaded at a time, runs of more than the 64 ends that a wave holds, at both ends of a batch; ends on and beside those
+# of a deal; the most sequences of the rule and one more
+SKEWED = [((1,) * 20 + (0,) * 8 + (3,) * 4 + (150000,) + (2,) * 3, 8), ((0, 1, 1, 0, 0, 5, 1, 46980, 1, 0, 7, 0, 3), 1032),
+          ((0,) * 66 + (1,) * 4 + (249900,) + (0,) * 5 + (30, 8), 8), ((0,) * 130 + (1,) * 70 + (999000,) + (0,) * 50 + (5,), 8),
+          ((93, 92, 94, 0, 93, 186, 1, 45000, 1441), 1032), ((1000,) * 22 + (48000,), 24), ((1000,) * 23 + (47000,), 24)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("lens,d", SKEWED)
+def test_short_sequences_among_dealt_rows(lens, d, dtype):
+    test_rows_dealt_out_evenly(lens, d, dtype)
+
+
+def test_dealt_rows_of_malformed_tables():
+    """Offsets of any value read and write inside the batch and the workspace: what lies behind both, and the next call with a sound table, are unharmed."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    T, B, d, low, high = 70000, 3, 8, -2 ** 31, 2 ** 31 - 1
+    hidden = torch.randn(T, d, device="cuda")
+    sc = gpu.Scorer(torch.zeros(40, d, device="cuda"), gpu.make_head(torch.zeros(8, d, device="cuda"), torch.zeros(1, 8, device="cuda")))
+    table = lambda *o: torch.tensor(o, dtype=torch.int32, device="cuda")
+    need, guard = sc.workspace(T, B).numel(), 1 << 16
+    ws = torch.full((need + guard,), 255, dtype=torch.uint8, device="cuda")
+    sc.workspace = lambda *_: ws[:need]
+    for kind in (gpu.EGTP_POOL_AVERAGE, gpu.EGTP_POOL_MAX):
+        for o in ((0, low, high, T), (high, low, 5, T), (low,) * 4, (high,) * 4, (-5, T + 5, low + 3, high), (0, low + 299, low + 1, T), (250, 20, high - 1, 3)):
+            sc.pool_ablation(hidden, table(*o), kind, want_pred=False)
+            torch.cuda.synchronize()
+            assert (ws[need:] == 255).all(), o
+        got = sc.pool_ablation(hidden, table(0, 100, 101, T), kind, want_pred=False)[0].double()
+        parts = hidden.double().split([100, 1, T - 101])
+        want = torch.stack([p.mean(0) if kind == gpu.EGTP_POOL_AVERAGE else p.amax(0) for p in parts])
+        assert (got - want).abs().max() <= 1e-5
     sc.close()
