@@ -246,3 +246,19 @@ def test_dealt_rows_of_malformed_tables():
         want = torch.stack([p.mean(0) if kind == gpu.EGTP_POOL_AVERAGE else p.amax(0) for p in parts])
         assert (got - want).abs().max() <= 1e-5
     sc.close()
+
+
+@pytest.mark.parametrize("lens", [(6_300_000,), (100, 6_299_900), (4_000_000, 2_300_000)])
+def test_averages_of_long_batches_do_not_drift(lens):
+    """Every token the same value, one that a running sum of a few thousand of them rounds down each time.  A sum has at most 264 terms in a row, 33 of these
+    make up what a workgroup adds up, of the 768 of them a wave joins 192, then the four waves and the division: 494 roundings of 2^-24."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    T, d, value = sum(lens), 8, 1.0 + 0.49 * 2.0 ** -11
+    hidden = torch.full((T, d), value, dtype=torch.float32, device="cuda")
+    sc = gpu.Scorer(torch.zeros(40, d, device="cuda"), gpu.make_head(torch.zeros(8, d, device="cuda"), torch.zeros(1, 8, device="cuda")))
+    off = torch.tensor([0, *np.cumsum(lens)], dtype=torch.int32, device="cuda")
+    got = sc.pool_ablation(hidden, off, gpu.EGTP_POOL_AVERAGE, want_pred=False)[0].cpu().numpy().astype(np.float64)
+    value = float(np.float32(value))
+    assert np.abs(got - value).max() <= 494 * 2.0 ** -24 * value
+    sc.close()
