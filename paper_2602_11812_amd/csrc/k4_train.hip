@@ -782,11 +782,12 @@ static hipError_t launch_samples(const TrainArgs &a, int nks, size_t lds, bool s
     });
 }
 
-// (the offsets of a step's samples in x are 32-bit)
+// (a lane's offset among the eight samples of a wave, up to 32 d bytes, and its 16 bytes lie inside a descriptor of 2^31 - 1 bytes:
+// GradSource::load_cols)
 static bool gradient_splits(int32_t B, int d, int d_h)
 {
     const long tiles = (long)((d_h + GradTile::ROWS - 1) / GradTile::ROWS) * ((d + GradTile::COLS - 1) / GradTile::COLS);
-    return B >= (tiles > SPLIT_TILES ? SPLIT_SAMPLES : SPLIT_SAMPLES_FEW_TILES) && d <= (1 << 26);
+    return B >= (tiles > SPLIT_TILES ? SPLIT_SAMPLES : SPLIT_SAMPLES_FEW_TILES) && d < (1 << 26);
 }
 
 size_t train_pieces_bytes(int32_t B, int d, int d_h)

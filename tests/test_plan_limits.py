@@ -40,3 +40,13 @@ def test_ranges_fit_the_workspace_and_follow_the_price():
     for T, d, V, rows in ((595, 872, 15403, 128), (1091, 616, 8145, 128), (168, 600, 113504, 128), (389, 232, 31206, 256), (1217, 4096, 151936, 256),
                           (105153, 3344, 65385, 64), (6338, 2608, 78554, 256)):
         assert gpu.egtp_launch_plan_query(gpu.EGTP_BF16, d, V, T).rows_per_tile == rows, (T, d, V)
+
+
+def test_split_gradient_only_where_its_rows_fit_a_descriptor():
+    """W1's gradient of large batches addresses eight samples of 4 d bytes by an offset that has to stay 16 bytes below 2^31: with d = 2^26 the last column of the
+    last sample would not.  The workspace shows which kernel a batch takes: one of pieces holds 8 fragments of 3 KiB for each step of 32 samples, 120 KiB from 160 on."""
+    def grows(d):
+        small, large = (gpu.egtp_head_train_workspace_bytes(B, d, 1, 4) for B in (159, 160))
+        return large - small >= 120 * 1024
+
+    assert grows(1 << 20) and grows((1 << 26) - 4) and not grows(1 << 26)
