@@ -284,7 +284,7 @@ def test_small_parameters_at_chunk_edges(gpu, B, d_h, K):
 
 @pytest.mark.parametrize("eps", [1e-8, 1.1e-12, 1e-12, 9e-13, 1e-20, 1e-38])
 def test_update_on_both_sides_of_the_quick_arithmetic(gpu, eps):
-    """AdamW's update around the smallest eps for which it is formed with the hardware's root and reciprocal; gradients over 24 decades, and
+    """AdamW's update with the hardware's root and reciprocal (eps of 1e-10 and more) and without; gradients over 24 decades, and
     none at all (inactive units).  Against fp64 from the moments that the step left: the weight is rounded twice (2^-22 of it covers
     both), the update ten times within one unit in the last place each (2^-20)."""
     import torch
@@ -306,3 +306,46 @@ def test_update_on_both_sides_of_the_quick_arithmetic(gpu, eps):
     normal = (v == 0) | (v > 2.0 ** -126)  # a denormal second moment is known to its own step only
     assert normal.mean() > 0.8
     assert (np.abs(got - want) <= 2.0 ** -22 * np.abs(want) + 2.0 ** -20 * np.abs(update))[normal].all()
+
+
+def _first_update(gpu, x, lr, eps, d_h=64):
+    """One step from weights of zero without decay: W1, m, v as fp64, W1 being the negative update alone."""
+    import torch
+    B, d = x.shape
+    K = 4
+    rng = np.random.default_rng(12)
+    td = gpu.to_device
+    tr = gpu.HeadTrainer(td(np.zeros((d_h, d), np.float32)), td(np.full(d_h, 5.0, np.float32)), td((rng.standard_normal((K, d_h)) * 0.1).astype(np.float32)),
+                         td(np.zeros(K, np.float32)), td(np.linspace(1, 4, K, dtype=np.float32)), lr=lr, weight_decay=0.0, eps=eps)
+    tr.step(td(x), torch.zeros(B, dtype=torch.int32, device="cuda"), torch.ones(B, device="cuda"))
+    return [t["w1"].cpu().numpy().astype(np.float64) for t in (tr.params, tr.m, tr.v)]
+
+
+@pytest.mark.parametrize("lr,eps,decades", [(1e-2, 1e-8, 0), (3e-4, 1e-8, 0), (1e-2, 1e-8, 3), (2e-5, 1e-6, 2), (1e-3, 1.1e-10, 0), (1e-3, 0.9e-10, 0), (1e-3, 0.9e10, 0), (1e-3, 1.1e10, 0)])
+def test_update_is_no_less_exact_than_rounded_divisions(gpu, lr, eps, decades):
+    """The update alone against fp64, beside lr mhat / (sqrt(vhat) + eps) with every operation of it rounded correctly, which numpy's fp32 is: never further off than the
+    roundings of that form allow (5.5 of 2^-24), and no further by the root of the mean square (1 % for the sample of 260000)."""
+    rng = np.random.default_rng(31)
+    x = (rng.standard_normal((8, 4096)) * 10.0 ** rng.uniform(-decades, decades, (1, 4096))).astype(np.float32)
+    got, m, v = _first_update(gpu, x, lr, eps)
+    f32 = np.float32
+    corr = [1.0 - float(f32(b)) for b in (0.9, 0.999)]
+    exact = float(f32(lr)) * m / corr[0] / (np.sqrt(v / corr[1]) + float(f32(eps)))
+    mhat, vhat = m.astype(f32) / f32(corr[0]), v.astype(f32) / f32(corr[1])
+    rounded = (f32(lr) * mhat / (np.sqrt(vhat) + f32(eps))).astype(np.float64)
+    kept = (v > 2.0 ** -126) & (np.abs(exact) > 2.0 ** -100)
+    assert kept.mean() > 0.9
+    off, off_rounded = ((t - exact)[kept] / exact[kept] * 2.0 ** 24 for t in (-got, rounded))
+    assert np.abs(off).max() <= 5.5
+    assert np.sqrt(np.mean(off ** 2)) <= 1.01 * np.sqrt(np.mean(off_rounded ** 2))
+
+
+@pytest.mark.parametrize("eps", [1e-8, 1e-12])
+def test_infinite_second_moments_leave_no_update(gpu, eps):
+    """Gradients whose square is past fp32's range: the update is divided by infinity, in the quick arithmetic as in the other."""
+    x = np.random.default_rng(3).standard_normal((8, 64)).astype(np.float32)
+    x[:, 1::4] *= 1e26
+    got, m, v = _first_update(gpu, x, 1e-2, eps)
+    big = np.isinf(v)
+    assert big[:, 1::4].mean() > 0.9 and not big[:, ::4].any() and np.isfinite(m).all()
+    assert not got[big].any() and (got[:, ::4] != 0).all()
