@@ -22,8 +22,8 @@
 // tokens against V = 151936, d = 4096 1170 to 1270 -> 670 (5.7 TB/s of pieces); 2, V = 94086, d = 1160 216 -> 125; 64, V = 32000,
 // d = 2048 156 -> 87; 47, V = 6763, d = 3440 160 -> 105.
 //
-// bf16 hidden states are read where they are, two K steps at a time (k1_stream.h), which spares the launch that packs them and the reads of rows past the
-// batch: whole decode steps, d = 4096, V = 151936, 24 tokens 220 -> 209 us, 64 227 -> 210; d = 5120, V = 100000, 24 189 -> 169.
+// bf16 hidden states are read where they are, two K steps at a time (k1_stream.h), unless the plan says otherwise (k1_plan.cpp), which spares the launch
+// that packs them and the reads of rows past the batch: whole passes, d = 4096, V = 151936, 24 tokens 214 -> 207 us, 64 216 -> 208.
 //
 // Measured: 64 tokens against V = 151936, d = 4096: 199 us = 6.3 TB/s of W_lm (the 256 x 256 tile: 286 us on 198 of the
 // 256 compute units); 309 fp32 tokens against V = 4096, d = 256: 15.4 us, 37.1 before.  Two K steps per barrier gain
@@ -49,14 +49,15 @@ constexpr int RING_BYTES = STAGES * STAGE_BYTES;
 static_assert(STAGES >= 3 && (STAGES - 1) * LOADS < 64 && STAGES % 2 == 0, "ring depth");
 constexpr int H_RING = STAGES * W_STEP_BYTES;  // direct: the hidden states' stages, of two steps each, lie behind W_lm's
 
-template <bool PIECES, bool STREAM_W>
+// DIRECT: the hidden states where they are (k1_stream.h); Hp is row-major, of rows of d
+template <bool PIECES, bool STREAM_W, bool DIRECT>
 __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigned char *__restrict__ Wp,
                                                                    const unsigned char *__restrict__ Hp, long T, int d, int KT,
                                                                    int V, int ntb, int nsplit, int ntiles_v,
                                                                    float *__restrict__ part)
 {
+    static_assert(!(PIECES && DIRECT), "pieces are packed");
     extern __shared__ __align__(16) unsigned char smem[];
-    constexpr bool DIRECT = !PIECES;  // the hidden states where they are (k1_stream.h); Hp: row-major
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -304,16 +305,16 @@ __global__ __launch_bounds__(256, 1) void k1_entropy_narrow_kernel(const unsigne
     }
 }
 
-template <bool PIECES, bool STREAM_W>
+template <bool PIECES, bool STREAM_W, bool DIRECT>
 hipError_t launch(const void *hidden, const void *w_packed, int64_t T, int d, int kt, int V, const K1Plan &p,
                   float *part, hipStream_t st)
 {
     static DeviceMask lds_limit_raised{0};
-    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<PIECES, STREAM_W>, RING_BYTES,
+    const hipError_t e = raise_dynamic_lds_limit((const void *)k1_entropy_narrow_kernel<PIECES, STREAM_W, DIRECT>, RING_BYTES,
                                                  lds_limit_raised);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL((k1_entropy_narrow_kernel<PIECES, STREAM_W>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), RING_BYTES,
+    hipLaunchKernelGGL((k1_entropy_narrow_kernel<PIECES, STREAM_W, DIRECT>), dim3((unsigned)(p.ntb * p.nsplit)), dim3(256), RING_BYTES,
                        st, (const unsigned char *)w_packed, (const unsigned char *)hidden, (long)T, d, kt, V, p.ntb,
                        p.nsplit, p.ntiles_v, part);
     return hipGetLastError();
@@ -325,7 +326,7 @@ hipError_t k1_entropy_narrow(const void *hidden, const void *w_packed, int64_t T
                              const K1Plan &p, float *part, hipStream_t st)
 {
     const int kt = k_steps(K);
-    if (p.pieces == p.direct || (p.pieces && kt % K1_SPLIT_TERMS != 0))
+    if (p.pieces && (p.direct || kt % K1_SPLIT_TERMS != 0))
         return hipErrorInvalidValue;
     if (T <= 0 || p.tb_tokens != K1_NARROW_TOKENS || p.tile_v != NM || p.nsplit < 1 || p.nsplit > p.ntiles_v || (long)p.ntb * p.nsplit > 0x7fffffffL ||
         (int64_t)p.ntb * p.tb_tokens < T || p.ntiles_v != (V + NM - 1) / NM || (long)kt * TILE_BYTES > 0x7fffffffL)
@@ -334,10 +335,10 @@ hipError_t k1_entropy_narrow(const void *hidden, const void *w_packed, int64_t T
     // V = 65536 and d = 2560 (336 MB) 60.5 -> 55.7; but V = 65536 and d = 2048 (268 MB) 44 -> 46 and V = 32000 (131 MB) 25 -> 26.
     const int read = p.pieces ? kt / 2 : kt;  // blocks that a sweep reads
     const bool stream = k1_plan_streams_w(p, read);
-#define EGTP_NARROW(PIECES)                                                          \
-    (stream ? launch<PIECES, true>(hidden, w_packed, T, K, kt, V, p, part, st)       \
-            : launch<PIECES, false>(hidden, w_packed, T, K, kt, V, p, part, st))
-    return p.pieces ? EGTP_NARROW(true) : EGTP_NARROW(false);
+#define EGTP_NARROW(PIECES, DIRECT)                                                          \
+    (stream ? launch<PIECES, true, DIRECT>(hidden, w_packed, T, K, kt, V, p, part, st)       \
+            : launch<PIECES, false, DIRECT>(hidden, w_packed, T, K, kt, V, p, part, st))
+    return p.pieces ? EGTP_NARROW(true, false) : (p.direct ? EGTP_NARROW(false, true) : EGTP_NARROW(false, false));
 #undef EGTP_NARROW
 }
 

@@ -101,32 +101,59 @@ static double stream_range_ns(const K1Plan &p, long steps)
     return ns;
 }
 
-// Whether a plan without the 256 x 256 tile reads bf16 hidden states where they are (the packing launch is 4 to 7 us, and packed rows past the
-// batch are read like others).  Whole passes, us, packed / direct:
-//   narrow   always: 24 tokens, d = 4096, V = 151936 220 / 209, 64 227 / 210, 12 tokens, d = 968, V = 20409 25.6 / 22.9, 571 tokens, d = 2528,
-//            V = 6951 62.1 / 58.0
-//   stream, 128 and 192 tokens, rows in whole lines of 128 bytes: 173, d = 4096, V = 151936 272 / 260, 100, d = 5120, V = 120000 223 / 212, 786,
-//            d = 3520, V = 119754 571 / 555
-//   rows that begin inside a line ask for two lines of each pair of steps: not for one block that streams W_lm past the Infinity Cache (173,
-//            d = 3000, V = 151936 204 / 226), nor where that outgrows the packing: 376, d = 4344, V = 115887, 3 sweeps of 136 steps 361 / 378; 249,
-//            d = 2136, V = 139839, 3 of 67 186 / 189, but 264, d = 1736, V = 104018, 3 of 55 153 / 138, 705, d = 1056, V = 68703, 4 of 33 124.5 /
-//            118.8; sweeps of two fragments a wave, of which the hidden states are half, count for one and a half: 412, d = 4184, V = 5774, 131 steps
-//            62.4 / 64.2, but 375, d = 3608, V = 9865, 113 steps 59.0 / 58.8
+// Plans without the 256 x 256 tile, bf16: whether hidden states are read where they are, which spares the launch that packs them (4 to 7 us) and the
+// reads of rows past the batch.  Rows that begin on lines of 128 bytes: always.  Others ask for two lines of each pair of steps; where that is more than
+// the packing they keep the copy.  Whole passes, us, packed / direct, d off the multiples of 64:
+//   W_lm inside the Infinity Cache, or read by several blocks
+//     narrow      12 tokens, d = 968, V = 20409 25.6 / 22.9; 571, 2528, 6951 62.1 / 58.0; 64, 4104, 16000 50.0 / 47.4
+//     stream      264 tokens, d = 1736, V = 104018, 3 sweeps of 55 steps 153 / 138; 705, 1056, 68703, 4 of 33 124.5 / 118.8; but 249, 2136, 139839,
+//                 3 of 67 186 / 189; 376, 4344, 115887, 3 of 136 361 / 378.  Sweeps of two fragments a wave, of which the hidden states are half, count
+//                 for one and a half: 375, 3608, 9865, 113 steps 59.0 / 58.8; 412, 4184, 5774, 131 steps 62.4 / 64.2
+//   one block that streams W_lm past it
+//     stream      173 tokens, d = 3000, V = 151936 204 / 226
+//     narrow      tokens                                  1            8            16           36           44           64
+//                   d = 2568, V = 151936, 238 workgroups  138 / 144    140 / 143    140 / 140    141 / 139    142 / 143    141 / 154
+//                   d = 4104                              209 / 214    211 / 212    211 / 209    212 / 207    213 / 210    212 / 229
+//                   d = 5016                              252 / 260    253 / 259    254 / 256    255 / 249    256 / 255    254 / 277
+//                   d = 2568, V = 100000, 196 workgroups  106 / 97     107 / 97     108 / 99     109 / 108    110 / 112
+//                   d = 5016                              182 / 168    183 / 169    184 / 170    184 / 184    185 / 192
+//                 Few rows are a few lines that all workgroups want at once, which counts where their loads fill the memory's rate.
 static constexpr double DIRECT_STEPS = 180.0;
+static constexpr int64_t NARROW_DIRECT_MIN = 12, NARROW_DIRECT_MAX = 36;  // tokens of a narrow plan that streams W_lm
+static constexpr long FULL_CHIP = NUM_CUS - NUM_CUS / 8;                  // workgroups that do
 
-// ns that a bf16 plan gains by reading the hidden states where they are; none: it does not
-static double direct_gain(const K1Plan &p, int d, long steps)
+// K steps of the sweeps of a range
+static double swept_steps(const K1Plan &p, long steps)
 {
-    if (p.tile_v == K1_WIDE_TILE_V || k1_plan_paces(p))
-        return 0.0;
-    if (p.tb_tokens == K1_NARROW_TOKENS || d % 64 == 0)
-        return PACK_NS;
     const int per_sweep = p.tile_v == K1_STREAM_TILE_V ? 8 : 2, shortest = per_sweep / 4 > 0 ? per_sweep / 4 : 1;
     const int sweeps = (p.tiles_per_split + per_sweep - 1) / per_sweep;
-    const double left = DIRECT_STEPS - (double)sweeps * (double)steps * (p.tiles_per_split <= shortest ? 1.5 : 1.0);
-    // (of 113 steps 59.0 / 58.8 above; 316 tokens, d = 5016, V = 15128, 158 steps, in plans without / with 88 / 98)
-    const double even = 1.0 - (DIRECT_STEPS - left) / 113.0;
-    return k1_plan_streams_w(p, steps) || left < 0.0 ? 0.0 : PACK_NS * (even > 1e-3 ? even : 1e-3);
+    return (double)sweeps * (double)steps * (p.tiles_per_split <= shortest ? 1.5 : 1.0);
+}
+
+bool k1_reads_directly(const K1Plan &p, int dtype, int64_t T, int d, bool on_lines)
+{
+    if (dtype != DT_BF16 || p.tile_v == K1_WIDE_TILE_V || k1_plan_paces(p))
+        return false;
+    if (on_lines)
+        return true;
+    const long steps = 2 * ((d + 63) / 64);
+    if (p.tb_tokens == K1_NARROW_TOKENS)
+        return !k1_plan_streams_w(p, steps) ||
+               (T <= NARROW_DIRECT_MAX && (T >= NARROW_DIRECT_MIN || (long)p.ntb * p.nsplit <= FULL_CHIP));
+    return !k1_plan_streams_w(p, steps) && swept_steps(p, steps) <= DIRECT_STEPS;
+}
+
+// ns that a plan saves by it: the packing launch, less what unaligned rows cost (113 steps 59.0 / 58.8 above; 316 tokens, d = 5016, V = 15128, 158 steps, in
+// plans without / with 88 / 98)
+static double direct_gain(const K1Plan &p, int dtype, int64_t T, int d, long steps)
+{
+    const bool on_lines = d % 64 == 0;
+    if (!k1_reads_directly(p, dtype, T, d, on_lines))
+        return 0.0;
+    if (on_lines || p.tb_tokens == K1_NARROW_TOKENS)
+        return PACK_NS;
+    const double left = 1.0 - swept_steps(p, steps) / 113.0;
+    return left > 0.0 ? PACK_NS * left : 0.0;
 }
 
 // the plan of another kernel where that is cheaper than the wide plan p
@@ -200,7 +227,7 @@ static K1Plan cheaper(const K1Plan &p, int dtype, int64_t T, int d, int V, long 
         q.whole_cohorts = false;
     }
     const double wide_ns = plan_ns(p, steps, p.tiles_per_split * ((double)steps * wide_step_ns(p, steps) + WIDE_FOLD_NS));
-    const double gain_ns = dtype == DT_BF16 && steps > STREAM_MIN_STEPS ? direct_gain(best, d, steps) : 0.0;
+    const double gain_ns = steps > STREAM_MIN_STEPS ? direct_gain(best, dtype, T, d, steps) : 0.0;
     return best_ns >= 0.0 && best_ns - gain_ns < wide_ns ? best : p;
 }
 
@@ -250,7 +277,7 @@ static K1Plan plan(int dtype, int64_t T, int d, int V)
 K1Plan k1_plan(int dtype, int64_t T, int d, int V)
 {
     K1Plan p = plan(dtype, T, d, V);
-    p.direct = dtype == DT_BF16 && direct_gain(p, d, 2 * ((d + 63) / 64)) > 0.0;
+    p.direct = k1_reads_directly(p, dtype, T, d, d % 64 == 0);
     return p;
 }
 

@@ -56,11 +56,13 @@ struct K1Plan {
     // fp32 operands, narrow and stream kernel: the sweep reads the three segments that hold each piece once, and the
     // hidden states are packed into those alone
     bool pieces = false;
-    // narrow (always) and stream kernel, bf16: hidden states are read where they are instead of from a packed copy
+    // narrow and stream kernel, bf16: hidden states are read where they are instead of from a packed copy
     bool direct = false;
 };
 
 K1Plan k1_plan(int dtype, int64_t T, int d, int V);
+// p.direct for T tokens whose rows begin on lines of 128 bytes, or do not
+bool k1_reads_directly(const K1Plan &p, int dtype, int64_t T, int d, bool on_lines);
 // floats needed for the partial triples of a plan (3 * nsplit * T)
 size_t k1_partial_floats(const K1Plan &p, int64_t T);
 // upper bound of k1_partial_floats over every T' <= T, whatever the shapes

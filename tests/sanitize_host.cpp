@@ -347,6 +347,47 @@ void plan_checks()
     CHECK(one_tile.nsplit == 1 && one_tile.tiles_per_split == 1 && !k1_plan_paces(one_tile));
 }
 
+// Which plans read bf16 hidden states where they are, on both sides of the rule's lines (the cases of tests/test_gpu_direct_rows.py among them); never
+// fp32 operands, the 256 x 256 tile or paced plans, and with rows on lines all others.
+void direct_checks()
+{
+    using namespace egtp;
+    struct {
+        int d, V, T, block, rows;
+        bool direct;
+    } cases[] = {
+        {8, 4096, 1, 64, 128, true},        {8, 4096, 65, 64, 128, true},       {24, 5000, 63, 64, 128, true},      {56, 4100, 64, 64, 128, true},
+        {64, 33000, 33, 64, 128, true},     {72, 4223, 129, 64, 128, true},     {1032, 9000, 64, 64, 128, true},    {2048, 4096, 40, 64, 128, true},
+        {216, 5422, 338, 128, 64, true},    {264, 16511, 65, 128, 64, true},    {320, 33136, 128, 128, 64, true},   {248, 33136, 66, 128, 64, true},
+        {512, 17000, 100, 128, 64, true},   {4184, 5774, 412, 128, 64, false},  {3000, 50000, 127, 128, 64, false}, {1000, 32000, 191, 192, 128, true},
+        {1024, 32000, 192, 192, 128, true}, {40, 52583, 565, 192, 128, true},   {904, 70000, 130, 192, 128, true},  {5216, 5414, 713, 192, 128, false},
+        {4968, 28800, 11, 64, 128, false},  {4968, 28800, 12, 64, 128, true},   {4104, 33000, 36, 64, 128, true},   {4104, 33000, 37, 64, 128, false},
+        {4968, 28800, 64, 64, 128, false},  {4968, 28600, 1, 64, 128, true},    {4992, 28800, 64, 64, 128, true},   {4096, 151936, 24, 64, 128, true},
+        {2568, 151936, 64, 64, 128, false}, {2568, 151936, 36, 64, 128, true},  {2568, 151936, 8, 64, 128, false},  {2568, 100000, 8, 64, 128, true},
+        {4096, 151936, 173, 192, 128, true}, {3000, 151936, 173, 192, 128, false}, {4096, 151936, 128, 128, 64, true}, {1192, 34235, 100, 128, 64, true},
+        {4344, 115887, 376, 128, 64, false}, {1736, 104018, 264, 128, 64, true}, {3608, 9865, 375, 128, 64, true},   {4096, 151936, 512, 256, 256, false},
+        {4096, 151936, 137720, 128, 64, false}, {5120, 151936, 65088, 128, 64, false},
+    };
+    for (const auto &c : cases) {
+        const K1Plan p = k1_plan(DT_BF16, c.T, c.d, c.V);
+        if (p.tb_tokens != c.block || p.tile_v != c.rows || p.direct != c.direct) {
+            std::fprintf(stderr, "d %d V %d T %d: plan %d %d %d\n", c.d, c.V, c.T, p.tb_tokens, p.tile_v, p.direct);
+            ++failures;
+        }
+    }
+    Rng rng(79);
+    for (int i = 0; i < 20000; ++i) {
+        const int d = 8 * (1 + rng.below(640)), V = (int)std::exp2(17.3 * rng.uniform()), T = (int)std::exp2(17.1 * rng.uniform());
+        const K1Plan p = k1_plan(DT_BF16, T, d, V);
+        const bool packed = p.tile_v == K1_WIDE_TILE_V || k1_plan_paces(p);
+        CHECK(!(p.direct && packed) && p.direct == k1_reads_directly(p, DT_BF16, T, d, d % 64 == 0));
+        CHECK(k1_reads_directly(p, DT_BF16, T, d, true) == !packed);
+        CHECK(p.direct || packed || d % 64 != 0);
+        const K1Plan f = k1_plan(DT_F32, T, d, V);
+        CHECK(!f.direct && !k1_reads_directly(f, DT_F32, T, d, true));
+    }
+}
+
 // Offsets of any value become rows of the batch, whose differences fit 32 bits.
 void pool_deal_checks()
 {
@@ -463,6 +504,7 @@ int main()
     oracle_ragged_sweep();
     sched_checks();
     plan_checks();
+    direct_checks();
     pool_deal_checks();
     pool_rule_checks();
     pool_walk_checks();
