@@ -149,7 +149,11 @@ egtp_status run_entropy(egtp_ctx *ctx, const void *hidden, int64_t T, const Work
                         hipStream_t st, int *nsplit_left = nullptr)
 {
     const egtp_config &c = ctx->cfg;
-    const K1Plan p = k1_plan(c.dtype, T, c.d, c.vocab);
+    K1Plan p = k1_plan(c.dtype, T, c.d, c.vocab);
+    // a view may begin inside a line (the plan takes the first row for one that does not): 173 tokens, d = 4096, V = 151936, 64 bytes off 275 us read
+    // where they are, 260 packed
+    if (p.direct && (uintptr_t)hidden % 128 != 0)
+        p.direct = k1_reads_directly(p, c.dtype, T, c.d, false);
     const bool timed = ctx->prof_events && ctx->prof_count < ctx->prof_cap;
     const void *wp = ctx->w_packed;
     if (!wp) {  // no persistent packed W_lm: pack it for this call

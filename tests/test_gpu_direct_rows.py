@@ -52,3 +52,24 @@ def test_rows_of_every_length_against_the_oracle(d, V, T, block, rows, direct):
         assert not np.isfinite(got[bad]).any()
         assert np.array_equal(np.delete(got, bad), np.delete(runs[0], bad))
     sc.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,V,T", [(4096, 33000, 64), (4096, 33000, 40), (4096, 33000, 24), (4096, 33000, 5), (2048, 66000, 128), (2048, 66000, 173), (256, 5422, 338), (1024, 32000, 100)])
+@pytest.mark.parametrize("shift", [8, 32, 56])
+def test_views_that_begin_inside_a_line(d, V, T, shift):
+    """Hidden states of whole lines whose first row is 16, 64 or 112 bytes into one, read where they are or packed: the bits of the aligned copy up to the order of the
+    fp32 sums (2e-5 nat, the bar against the oracle), rows of NaN before and behind the view notwithstanding."""
+    import torch
+    from paper_2602_11812_amd import binding as gpu
+    torch.manual_seed(T)
+    w_lm = (torch.randn(V, d, device="cuda") / d ** 0.5).bfloat16()
+    sc = gpu.Scorer(w_lm, gpu.make_head(*(torch.zeros(s, d if s == 8 else 8, dtype=torch.bfloat16, device="cuda") for s in (8, 1))))
+    around = torch.full((T * d + 128,), float("nan"), dtype=torch.bfloat16, device="cuda")
+    view = around[shift:shift + T * d].view(T, d)
+    hidden = torch.randn(T, d, device="cuda").bfloat16()
+    view.copy_(hidden)
+    off = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    want, got = (sc.score(h, off)["entropy"] for h in (hidden, view))
+    assert torch.isfinite(want).all() and (got - want).abs().max() <= 2e-5
+    sc.close()
