@@ -205,7 +205,7 @@ def bench_pool(args, gpu, wl, np, torch) -> int:
         "config": {"workload": f"pool: the serving batch ({B} ragged sequences, {T} tokens, d={spec.d}), poolers only",
                    "B": B, "T": T},
         "ms_per_step_by_pooler": {k: v * 1e3 for k, v in times.items()},
-        "roofline": {"kernel": "pool_partial_kernel (sum mode) + join", "bound": "hbm", "achieved": gbps,
+        "roofline": {"kernel": "pool_rows_kernel (sum mode) + join", "bound": "hbm", "achieved": gbps,
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS, "traffic": None},
         "hbm_read_probe": {"what": "plain 16-byte-per-lane streaming read of the same hidden states, mean of the "
                                    "last 8 of 12 launches", "gbps": read_gbps, "achieved_over_probe": gbps / read_gbps},

@@ -39,16 +39,19 @@ static constexpr double STREAM_STEP_NS = 642.0, STREAM_ALONE_NS = 400.0, STREAM_
 static constexpr double STREAM_STEP4_NS = 406.0, STREAM_STEP2_NS = 288.0;
 static constexpr double WORKGROUP_NS = 3000.0, W_STREAM_BYTES_PER_NS = 5700.0;
 static constexpr long STREAM_MIN_STEPS = 8;  // below, folds are most of the work and the wide tile folds faster
-// Another kernel than the wide one is taken at this much of its price: of up to WORTH_IT_TOKENS, in whole cohorts, or else.  Whole passes, us, wide / stream: 187
-// tokens, d = 3152, V = 108446 216 / 178, 300, d = 3400, V = 31345 123 / 108, in fp32 160, d = 3048, V = 64460 499 / 433; whole cohorts: 46211, d = 2280, V = 123447
-// 19354 / 18497, 105153, d = 3344, V = 65385 35283 / 32145, in fp32 35094, d = 600, V = 73501 13643 / 12808, but, all priced 0.98 to 1.01 of the wide tile,
-// 16814, d = 1368, V = 87862 3096 / 3263, 37719, d = 4896, V = 19398 5300 / 5441, in fp32 19818, d = 4352, V = 15161 12672 / 13862; others: 6338, d = 2608,
-// V = 78554 1855 / 1896, 1217, d = 4096, V = 151936 1214 / 1232.
+// Another kernel than the wide one is taken at this much of its price: of up to WORTH_IT_TOKENS, in whole cohorts, or else.
+// Whole passes, us, wide / stream kernel:
+//   few             187 tokens, d = 3152, V = 108446  216 / 178      300, d = 3400, V = 31345  123 / 108      fp32: 160, d = 3048, V = 64460  499 / 433
+//   whole cohorts   46211, d = 2280, V = 123447  19354 / 18497       105153, d = 3344, V = 65385  35283 / 32145
+//                   fp32: 35094, d = 600, V = 73501  13643 / 12808
+//     all priced 0.98 to 1.01 of the wide tile, but:  16814, d = 1368, V = 87862  3096 / 3263      37719, d = 4896, V = 19398  5300 / 5441
+//                   fp32: 19818, d = 4352, V = 15161  12672 / 13862
+//   others          6338, d = 2608, V = 78554  1855 / 1896           1217, d = 4096, V = 151936  1214 / 1232
 static constexpr double WORTH_IT_FEW = 1.01, WORTH_IT_FEW_PIECES = 0.985, WORTH_IT_COHORTS = 0.97, WORTH_IT_OTHERS = 0.955;  // (pieces: fp32 operands)
 static constexpr int64_t WORTH_IT_TOKENS = 2 * K1_STREAM_WIDE_TOKENS;
-// What the packing launch of bf16 hidden states takes at the least, which plans that read them directly leave out; less where they then wait for the pieces of
-// unaligned rows.  Whole passes, us, wide / stream with this counted in: 595 tokens, d = 872, V = 15403 64 / 52, 1091, d = 616, V = 8145 56 / 46, 168, d = 600,
-// V = 113504 76 / 66, 3189, d = 1232, V = 9789 114 / 99; in full for 284, d = 4432, V = 14734, it would give 82 / 89.
+// What the packing launch of bf16 hidden states takes at the least, which plans that read them directly leave out (direct_gain).  Whole passes, us,
+// wide / stream kernel with this counted in: 595 tokens, d = 872, V = 15403 64 / 52, 1091, d = 616, V = 8145 56 / 46, 168, d = 600,
+// V = 113504 76 / 66, 3189, d = 1232, V = 9789 114 / 99; in full also where unaligned rows cost more, 284, d = 4432, V = 14734 would take 89 for 82.
 // Not counted up to STREAM_MIN_STEPS: 414, d = 256, V = 49778 53.5 / 54.4.
 static constexpr double PACK_NS = 3500.0;
 // Several rounds of the stream kernel, relative to one round or to whole cohorts of 16 token blocks x 2 ranges: cohorts

@@ -12,6 +12,9 @@
 // never meet, because ceil((y - x) / unit) <= floor(y / unit) - floor(x / unit) + 1; of the
 // floor(T / unit) + B numbers some stay unused.  (A scan kernel made a table, and another one the
 // log-sum-exps, before: two launches more.)
+//
+// Averages and maxima of large batches of few sequences have the rows of the batch dealt out evenly instead, whatever sequences they
+// belong to (pool_rows_kernel; the rule is in pool_deal.h); what workgroup w adds up of sequence b is unit w + b.
 #include <type_traits>
 
 #include "k1_common.h"
@@ -756,8 +759,8 @@ __global__ __launch_bounds__(256) void pool_last_kernel(const void *__restrict__
 // Tokens per unit: 256, halved while a batch makes fewer than POOL_WORKGROUPS workgroups and the smaller units'
 // partials fit `cap_floats`.  A workgroup walks its unit's rows eight at a time, one memory latency each: 173 tokens,
 // d = 4096 in units of 128 are 6 workgroups of 16 latencies (14 us), in units of 16 25 of two (7 us).  Large units
-// leave fewer partials to write and join: average pooling of 137720 tokens takes 219 us with 256, 222 with 128, 233
-// with 64; of 10689 tokens, d = 2048, 30.3 us where 256 workgroups are asked for, 32.6 with 512 or 1024.
+// leave fewer partials to write and join: weighted pooling and join of 137720 tokens, d = 4096, 128 sequences take 207 us with 256, 208 with 128, 221
+// with 64; average pooling of 10689 tokens, d = 2048, 30.3 us where 256 workgroups are asked for, 32.6 with 512 or 1024.
 constexpr int POOL_UNIT_MIN = 16, POOL_WORKGROUPS = 256;
 
 // workgroups a unit's features are spread over: one 16-byte chunk per thread
